@@ -90,31 +90,41 @@ template <typename T, int VEC> __device__ __forceinline__ void store_f_nt(T* p, 
 }
 
 // ---- reductions -------------------------------------------------------------------------------------------------------
-// Across the 64 lanes with DPP moves (a prefix scan: shifts by 1, 2, 4, 8 inside a row of 16 lanes, then the rows' totals are
-// broadcast upwards): plain vector instructions of a few cycles each, where a lane exchange through the LDS crossbar
-// (__shfl_xor) takes a round trip of some 60 cycles per level.  All 64 lanes must be active; every lane receives the result.
+// Across the 64 lanes: partners 32, 16, 8, 4, 2 and 1 lanes apart, in this order, which is part of the result: a sum taken in
+// another order flips the rounding of a 2-byte value now and then, and the difference travels through the network.  The moves
+// are plain vector instructions of a few cycles each, where a lane exchange through the LDS crossbar (__shfl_xor) takes a round
+// trip of some 60 cycles per level.  Rows of 16 lanes are rotated: once lanes 8 apart hold the same value, the lane 4 further on
+// (modulo 16) holds that of the lane whose bit 2 differs, and so on down.  All 64 lanes must be active; every lane receives the
+// result.
 template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_move(int old, int x) {
   return __builtin_amdgcn_update_dpp(old, x, CTRL, ROWS, 0xf, false);
 }
-template <typename Op> __device__ __forceinline__ int wave_reduce_bits(int v, int identity, Op op) {
-  v = op(v, dpp_move<0x111, 0xf>(identity, v));          // row_shr:1
-  v = op(v, dpp_move<0x112, 0xf>(identity, v));
-  v = op(v, dpp_move<0x114, 0xf>(identity, v));
-  v = op(v, dpp_move<0x118, 0xf>(identity, v));
-  v = op(v, dpp_move<0x142, 0xa>(identity, v));          // row_bcast:15 into rows 1 and 3
-  v = op(v, dpp_move<0x143, 0xc>(identity, v));          // row_bcast:31 into rows 2 and 3
-  return __builtin_amdgcn_readlane(v, 63);
+// op of a lane's value and of its partner's, 8, 16 and 32 lanes apart: for commutative operations
+template <typename Op> __device__ __forceinline__ uint32_t with_lane_8(uint32_t v, Op op) { return op(v, (uint32_t)dpp_move<0x128, 0xf>(0, (int)v)); }
+template <typename Op> __device__ __forceinline__ uint32_t with_lane_16(uint32_t v, Op op) {
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return op(r[0], r[1]);
+}
+template <typename Op> __device__ __forceinline__ uint32_t with_lane_32(uint32_t v, Op op) {
+  const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return op(r[0], r[1]);
+}
+template <typename Op> __device__ __forceinline__ uint32_t wave_reduce_bits(uint32_t v, Op op) {
+  v = with_lane_8(with_lane_16(with_lane_32(v, op), op), op);
+  v = op(v, (uint32_t)dpp_move<0x124, 0xf>(0, (int)v));  // row_ror:4
+  v = op(v, (uint32_t)dpp_move<0x122, 0xf>(0, (int)v));  // row_ror:2
+  return op(v, (uint32_t)dpp_move<0x121, 0xf>(0, (int)v));                     // row_ror:1
 }
 __device__ __forceinline__ float wave_sum(float v) {
-  return __int_as_float(wave_reduce_bits(__float_as_int(v), 0, [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); }));
+  return __uint_as_float(wave_reduce_bits(__float_as_uint(v), [](uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); }));
 }
 __device__ __forceinline__ float wave_max(float v) {
-  return __int_as_float(wave_reduce_bits(__float_as_int(v), (int)0xff800000, [](int a, int b) {
-    return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b)));
+  return __uint_as_float(wave_reduce_bits(__float_as_uint(v), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
   }));
 }
 __device__ __forceinline__ int wave_min_i32(int v) {
-  return wave_reduce_bits(v, 0x7fffffff, [](int a, int b) { return a < b ? a : b; });
+  return (int)wave_reduce_bits((uint32_t)v, [](uint32_t a, uint32_t b) { return (uint32_t)min((int)a, (int)b); });
 }
 // Block-wide reductions for blockDim.x a multiple of 64, up to 1024 threads.  `sh` holds >= 16 floats.  Every
 // thread receives the result.  The summation order is fixed, so results are reproducible.

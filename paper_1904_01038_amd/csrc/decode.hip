@@ -159,11 +159,8 @@ template <typename Op> __device__ __forceinline__ float over_lanes(float v, Op o
   return op(v, __int_as_float(dpp_move<0x141, 0xf>(0, __float_as_int(v))));    // row_half_mirror
 }
 template <typename Op> __device__ __forceinline__ float over_groups(float v, Op op) {
-  v = op(v, __int_as_float(dpp_move<0x128, 0xf>(0, __float_as_int(v))));       // row_ror:8
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  auto bits = [&](uint32_t a, uint32_t b) { return __float_as_uint(op(__uint_as_float(a), __uint_as_float(b))); };
+  return __uint_as_float(with_lane_32(with_lane_16(with_lane_8(__float_as_uint(v), bits), bits), bits));
 }
 
 constexpr int DEC_ATT_WAVES = 8;                         // rows per block at most

@@ -69,6 +69,25 @@ def test_gemm_forms_and_epilogues(prec, form, shape):
             assert not out[:, N:].any()
 
 
+@pytest.mark.parametrize("d", [64, 264, 512, 1024, 2048])
+def test_sums_over_a_wavefront_keep_their_order(d):
+    """To the bit: a lane adds its own 8-element pieces in order, then lanes 32, 16, 8, 4, 2 and 1 apart are added."""
+    import torch
+    import paper_1904_01038_amd as T
+    rows = 37
+    x = np.random.default_rng(d).standard_normal((rows, d)).astype(np.float32)
+    v = np.zeros((rows, 64), np.float32)
+    for col in range(d):                                       # (a lane's columns ascend)
+        v[:, col // 8 % 64] += x[:, col]
+    for apart in (32, 16, 8, 4, 2, 1):
+        v = v + v[:, np.arange(64) ^ apart]
+    tx = _t(x, torch.float32)
+    g, b, n = torch.ones(d, device="cuda"), torch.zeros(d, device="cuda"), torch.empty_like(tx)
+    mean, rstd = torch.empty(rows, device="cuda"), torch.empty(rows, device="cuda")
+    T.ops.residual_layernorm_fwd(tx, None, g, b, None, n, mean, rstd)
+    assert np.array_equal(mean.cpu().numpy(), v[:, 0] / np.float32(d))
+
+
 @pytest.mark.parametrize("prec", ["fp16", "bf16"])
 @pytest.mark.parametrize("M", [1, 15, 16, 17, 32, 33, 64])
 @pytest.mark.parametrize("N,K", [(8, 8), (24, 520), (1000, 1024), (8200, 72), (40, 2048), (48, 2056), (136, 6152)])
