@@ -294,20 +294,23 @@ void launch_gemm_thin(hipStream_t s, const GemmArgs& a) {
   if (ln) p.ln = *a.norm;
   const bool wide = a.N >= 8192;                         // enough columns for a block to own several tiles of them
   const int nb = (a.N + 15) / 16, least = 64 * THIN_WAVES;
-  // A narrow output has few blocks: slices of K of at least one unit per wavefront fill the chip, where the kernel that
-  // follows adds the slices up anyway (deferred); else only a contraction of more than 4 units per wavefront is cut.
+  // Deferred (the next kernel adds the slices up, with the residual): the result stays in fp32 even as a single slice, so that no
+  // contraction is too short for the sum to be taken in 32 bits.  A narrow output has few blocks, and slices of K of at least one
+  // unit per wavefront then fill the chip.  Otherwise only a contraction of more than 4 units per wavefront is cut.  (No ReLU in a
+  // deferred reduction; and with LN the workspace may hold the slices that the rows are made from.)
   const int need = thin_least_splits(a.K);
+  const size_t slice = (size_t)a.M * a.N * 4;
+  const bool defer = a.deferred_splits && !a.relu && !ln && a.splitk_ws && need * slice <= a.splitk_ws_bytes;
   int splits = need;
-  if (!ln && a.splitk_ws && a.deferred_splits && !a.relu) {
+  if (defer) {
     splits = std::max(splits, std::min(std::min(256 / nb, a.K / least), 4));
-    while (splits > need && (size_t)splits * a.M * a.N * 4 > a.splitk_ws_bytes) --splits;
+    while (splits > need && splits * slice > a.splitk_ws_bytes) --splits;
   }
   p.kblock = ((a.K + splits - 1) / splits + least - 1) / least * least;
   splits = (a.K + p.kblock - 1) / p.kblock;
-  p.partial = splits > 1 ? (float*)a.splitk_ws : nullptr;
+  p.partial = splits > 1 || defer ? (float*)a.splitk_ws : nullptr;
   if (a.dt == F16) thin_dispatch<half_t>(s, p, splits, wide, ln); else thin_dispatch<bf16_t>(s, p, splits, wide, ln);
-  const bool defer = a.deferred_splits && !a.relu;       // (a deferred reduction has no ReLU)
-  if (a.deferred_splits) *a.deferred_splits = defer && splits > 1 ? splits : 0;
+  if (a.deferred_splits) *a.deferred_splits = defer ? splits : 0;
   if (splits > 1 && !defer) launch_splitk_reduce(s, a.dt, p.partial, splits, a.M, a.N, a.C, a.ldc, a.bias, a.relu);
 }
 

@@ -52,9 +52,10 @@ struct GemmArgs {
   uint64_t drop_key = 0;
   float drop_p = 0.f;
   float mask_scale = 1.f;    // with mask: the kept elements are also multiplied by this (the dropout scale of the masked layer)
-  // Deferred split-K reduction (host pointer or null).  If given and the launch splits the contraction, the fp32 partial
-  // results [splits][M][N] stay in splitk_ws, nothing is written to C, bias is NOT applied, and *deferred_splits = splits:
-  // the caller's next kernel adds them up (see launch_splitk_layernorm_fwd).  Otherwise *deferred_splits = 0 and C is complete.
+  // Deferred split-K reduction (host pointer or null).  If given and the launch splits the contraction (or has few rows: a single
+  // slice then), the fp32 partial results [splits][M][N] stay in splitk_ws, nothing is written to C, bias is NOT applied, and
+  // *deferred_splits = splits >= 1: the caller's next kernel adds them up (see launch_splitk_layernorm_fwd).  Otherwise
+  // *deferred_splits = 0 and C is complete.
   int* deferred_splits = nullptr;
   // The rows are made by the product (A is not read): see ThinNorm.  Only where gemm_thin_norm_supported() says so.
   const ThinNorm* norm = nullptr;

@@ -1579,9 +1579,9 @@ void decode_attention(tfm_decoder* D, const void* q, int ldq, const void* k, con
 }
 
 // y = f_k(fin) for the single new position of every row; norm: how fin is made (null: it is there).  The sub-layer's last
-// product has few tiles and usually runs split along K: its fp32 slices are then left in the split-K workspace, without the
-// bias, and their count is returned for the kernel that fuses their sum with the residual connection and LayerNorm (0: D->y is
-// complete).
+// product has few tiles and usually runs split along K: its fp32 slices (one, at least, for few rows) are then left in the split-K
+// workspace, without the bias, and their count is returned for the kernel that fuses their sum with the residual connection and
+// LayerNorm (0: D->y is complete).
 int decode_sublayer(tfm_decoder* D, const Block& b, int layer, const void* fin, double src_positions, const ThinNorm* norm) {
   tfm_ctx* c = D->c;
   const int d = c->cfg.d_model, F = c->cfg.d_ffn, R = D->rows;

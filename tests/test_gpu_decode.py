@@ -305,3 +305,35 @@ def test_candidates_are_the_top_of_the_distribution(vocab, k, distinct, prec):
         assert top_id[r].tolist() == order.tolist()
         assert np.array_equal(top_lp[r], lp[r, order])
     assert np.allclose(np.exp(lp.astype(np.float64)).sum(axis=1), 1.0, atol=1e-4)
+
+
+@pytest.mark.parametrize("prec,tol", [("fp16", 0.006), ("bf16", 0.03)])
+@pytest.mark.parametrize("d,heads,rows", [(d, h, r) for d, h in ((256, 4), (576, 9), (784, 7), (1024, 16)) for r in (1, 8, 9, 64)]
+                         + [(576, 9, 80), (1024, 16, 80)])
+def test_a_sub_layers_result_is_added_to_the_residual_in_32_bits(d, heads, rows, prec, tol):
+    """The attention's output projection cancels the residual down to 2e-4 of it; rounded to 2 bytes before the sum, nothing of the
+    difference is left.  sqrt(d) is whole and the fed token's embedding has small whole numbers, so that the residual itself, the
+    values (the bias alone) and everything but the sum are exact.  Tolerance: two logits of at most 4 rounded to 2 bytes, plus six
+    standard deviations of the rounding of the two normalised states."""
+    import paper_1904_01038_amd as T
+    shape = ModelShape(0, 1, d, heads, 64, 96)
+    rng = np.random.default_rng(d + rows)
+    params = {k: np.zeros_like(v) if k.startswith("dec") else v for k, v in init_params(shape, 1).items()}
+    root = int(round(d ** 0.5))
+    params["embed"][shape.eos_id] = rng.integers(1, 5, d) * rng.choice([-1, 1], d)
+    x = root * params["embed"][shape.eos_id] + np.arange(d) % 2                  # position 0: sin 0, cos 0
+    params["dec.0.self.bqkv"][2 * d:] = rng.standard_normal(d)
+    params["dec.0.self.wo"] = rng.standard_normal((d, d)) * 0.02 / root
+    params["dec.0.self.bo"] = -x
+    params["dec.0.ln_self.g"][:] = params["dec.0.ln_ffn.g"][:] = 1.0
+    p = {"fp16": T.FP16, "bf16": T.BF16}[prec]
+    params = rounded(params, p)
+    assert np.array_equal(params["dec.0.self.bo"], -x)
+    ctx = T.Tfm(T.make_config(shape, precision=p, max_sentences=rows, max_len=4, max_tokens=64))
+    ctx.set_params(params)
+    dec = T.Decoder(ctx, rows, 2, 1, 4)
+    dec.begin(None, None, 1, rows)
+    dec.step(np.full(rows, shape.eos_id, np.int32))
+    got, ref = dec.logprobs().astype(np.float64), DecodingOracle(shape, params).next_logprobs(None, [shape.eos_id])
+    assert np.max(np.abs((got[:, 5:] - got[:, 4:5]) - (ref[5:] - ref[4]))) <= tol
+    ctx.close()
