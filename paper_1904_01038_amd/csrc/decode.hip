@@ -135,21 +135,13 @@ __global__ __launch_bounds__(64) void decode_attention_kernel(DecodeAttnArgs p) 
 // would need a second round then, take chunks of 32 (9.9 -> 8.5 us; small launches keep the single trip: 4.2 us for 4 rows).  Lane exchanges only, no LDS but for a query that arrives in slices.
 // The beams of a sentence are the wavefronts of one block: they read the same source positions (and mostly the same history),
 // which then come into one L1 and one L2 once, where blocks of one row each were dealt out to different XCDs.
-template <typename T> __device__ __forceinline__ float dot8_acc(uint4 a, uint4 b, float c);
-template <> __device__ __forceinline__ float dot8_acc<half_t>(uint4 a, uint4 b, float c) {
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-  c = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, a.x), __builtin_bit_cast(h2, b.x), c, false);
-  c = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, a.y), __builtin_bit_cast(h2, b.y), c, false);
-  c = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, a.z), __builtin_bit_cast(h2, b.z), c, false);
-  return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, a.w), __builtin_bit_cast(h2, b.w), c, false);
-}
-template <> __device__ __forceinline__ float dot8_acc<bf16_t>(uint4 a, uint4 b, float c) {
-  const uint32_t x[4] = {a.x, a.y, a.z, a.w}, y[4] = {b.x, b.y, b.z, b.w};
+// 8 elements of a key against 8 of the query, in 32-bit FMAs.  (v_dot2_f32_f16 truncates what lies far below the larger term and
+// below a fixed floor: 1.6e-5 of the result with subnormal keys, where FMAs are off by 6e-8.)
+template <typename T> __device__ __forceinline__ float dot8_acc(const float (&q)[8], uint4 k, float c) {
+  Pack<T, 8> x;
+  __builtin_memcpy(&x, &k, 16);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    c = fmaf(__uint_as_float(x[i] << 16), __uint_as_float(y[i] << 16), c);
-    c = fmaf(__uint_as_float(x[i] & 0xffff0000u), __uint_as_float(y[i] & 0xffff0000u), c);
-  }
+  for (int i = 0; i < 8; ++i) c = fmaf(q[i], to_f<T>(x.v[i]), c);
   return c;
 }
 // op over the lanes that differ in bits 0, 1 and 2 of their number (a group of 8), and in bits 3, 4 and 5 (across the groups)
@@ -191,7 +183,7 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
   int off[U];                                            // positions g, g + 8, ... of the chunk; past the end: the last one, with weight 0
 #pragma unroll
   for (int u = 0; u < U; ++u) off[u] = row_of(min(8 * u + g, n - 1));
-  uint4 q;                                               // this lane's piece of the query
+  Pack<T, 8> qh;                                         // this lane's piece of the query
   if (p.q_partial) {                                     // the query arrives as the slices of a split-K product (at most 8)
     const size_t at = (size_t)r * p.H * dh + h * dh + lane, slice = (size_t)p.rows * p.H * dh;
     float part[8];
@@ -203,9 +195,15 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
     if (p.q_bias) qv += to_f<T>(reinterpret_cast<const T*>(p.q_bias)[h * dh + lane]);
     qs[lane] = from_f<T>(qv);                            // rounded as the stored projection would be
     __syncthreads();                                     // (every row of the launch comes this way, or none does)
-    q = reinterpret_cast<const uint4*>(qs)[f];
+    qh = reinterpret_cast<const Pack<T, 8>*>(qs)[f];
   } else {
-    q = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(p.q) + (size_t)r * p.ldq + h * dh)[f];
+    qh = reinterpret_cast<const Pack<T, 8>*>(reinterpret_cast<const T*>(p.q) + (size_t)r * p.ldq + h * dh)[f];
+  }
+  float q[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    q[i] = to_f<T>(qh.v[i]);
+    asm("" : "+v"(q[i]));                                // (seen as halves, the compiler would pair the FMAs into v_dot2_f32_f16)
   }
   auto add = [](float x, float y) { return x + y; };
   auto larger = [](float x, float y) { return fmaxf(x, y); };

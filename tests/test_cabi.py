@@ -3,6 +3,8 @@ logic (configuration checks, workspace sizing, dropout keys) behaves.  No kernel
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -77,3 +79,14 @@ def test_parameter_list_matches_the_shared_shape_module(T):
         specs = param_specs(PRESETS[name])
         assert len({n for n, _ in specs}) == len(specs)
         assert specs[0][0] == "embed"
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_decoding_scores_are_formed_by_32_bit_multiply_adds():
+    """v_dot2_f32_f16 truncates small terms against a fixed floor (1.6e-5 of a result with subnormal keys, where 32-bit FMAs are
+    off by 6e-8), and the compiler forms it by itself from FMAs whose factors it sees as halves."""
+    from paper_1904_01038_amd import build
+    r = subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, "decode.hip"), "-o", "-"],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert "decode_attention64_kernel" in r.stdout and "v_dot2" not in r.stdout
