@@ -337,3 +337,54 @@ def test_a_sub_layers_result_is_added_to_the_residual_in_32_bits(d, heads, rows,
     got, ref = dec.logprobs().astype(np.float64), DecodingOracle(shape, params).next_logprobs(None, [shape.eos_id])
     assert np.max(np.abs((got[:, 5:] - got[:, 4:5]) - (ref[5:] - ref[4]))) <= tol
     ctx.close()
+
+
+EDGES = (31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 130)   # where a chunk of 32 or 64 positions ends
+
+
+def peaked(shape, prec, seed):
+    """Parameters whose attention scores spread over several units, so that single positions matter."""
+    params = init_params(shape, seed, generic=True)
+    d = shape.d_model
+    for k in params:
+        if k.endswith("self.wqkv") and k.startswith("dec"):
+            params[k][:2 * d] *= 2.5
+        if k.endswith("cross.wq") or k.endswith("cross.wkv"):
+            params[k][:d] *= 2.5
+    return rounded(params, prec)
+
+
+@pytest.mark.parametrize("prec,tol", [("fp16", 3e-2), ("bf16", 2e-1)])
+@pytest.mark.parametrize("d,heads,beam,copies", [
+    (128, 2, 1, 1), (128, 2, 5, 1), (128, 2, 9, 1),        # a row, the beams of a sentence (odd), or, above 8, again a row per block
+    (256, 4, 5, 15), (256, 4, 9, 9)])                      # more than 2048 wavefronts: chunks of 32 positions
+def test_attention_over_several_chunks_of_positions(d, heads, beam, copies, prec, tol):
+    """Head width 64: histories and sources around the ends of the chunks, with re-ordered beams.  copies: how often each source
+    length occurs; of many rows a sample is compared."""
+    import paper_1904_01038_amd as T
+    shape = ModelShape(1, 1, d, heads, 2 * d, 96)
+    p = {"fp16": T.FP16, "bf16": T.BF16}[prec]
+    params = peaked(shape, p, 4)
+    lens = np.array([1, 31, 32, 33, 64, 65, 130] * copies, np.int32)
+    B, R, steps = len(lens), len(lens) * beam, EDGES[-1]
+    assert (R * heads > 2048) == (copies > 1)
+    rng = np.random.default_rng(beam)
+    src = rng.integers(4, shape.vocab, (B, lens.max())).astype(np.int32)
+    src[np.arange(lens.max())[None, :] >= lens[:, None]] = shape.pad_id
+    ctx = T.Tfm(T.make_config(shape, precision=p, max_sentences=B, max_len=steps, max_tokens=(int(lens.sum()) + 63) // 64 * 64))
+    ctx.set_params(params)
+    dec, oracle = T.Decoder(ctx, R, steps, int(lens.sum()), 4), DecodingOracle(shape, params)
+    dec.begin(src, lens, beam)
+    sample = np.arange(R) if R <= 64 else np.sort(rng.choice(R, 24, replace=False))
+    mems = {b: oracle.encode(src[b, :lens[b]]) for b in set(sample // beam)}
+    base = np.arange(R) // beam * beam
+    hist = np.zeros((R, 0), np.int32)
+    for t in range(steps):
+        prev = np.full(R, shape.eos_id, np.int32) if t == 0 else rng.integers(4, shape.vocab, R).astype(np.int32)
+        parent = None if t == 0 else (base + rng.integers(0, beam, R)).astype(np.int32)
+        hist = np.concatenate([hist if parent is None else hist[parent], prev[:, None]], axis=1)
+        dec.step(prev, parent)
+        if t + 1 in EDGES:
+            ref = np.stack([oracle.next_logprobs(mems[r // beam], hist[r]) for r in sample])
+            assert np.max(np.abs(dec.logprobs()[sample] - ref)) <= tol, t + 1
+    ctx.close()
