@@ -1625,8 +1625,10 @@ int tfm_decoder_create(tfm_ctx* c, void* ws, size_t bytes, int32_t max_rows, int
   if (bytes < need) { delete D; return fail(c, TFM_ENOMEM, "decoder workspace has %zu bytes, %zu needed", bytes, need); }
   decoder_carve(D, (char*)ws);
   hipError_t e = hipHostMalloc((void**)&D->h_src, (2 * (size_t)c->cfg.max_tokens + c->cfg.max_sentences + 1) * 4, hipHostMallocDefault);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_in, 3 * (size_t)max_rows * 4, hipHostMallocDefault);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_out, (size_t)max_rows * topk * 8, hipHostMallocDefault);
+  // Kernels read and write these two in place, step after step: coherence is asked for, the default follows HIP_HOST_COHERENT.
+  const unsigned in_place = hipHostMallocCoherent | hipHostMallocMapped;
+  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_in, 3 * (size_t)max_rows * 4, in_place);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_out, (size_t)max_rows * topk * 8, in_place);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&D->d_in, D->h_in, 0);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&D->d_out, D->h_out, 0);
   if (e != hipSuccess) {

@@ -388,3 +388,34 @@ def test_attention_over_several_chunks_of_positions(d, heads, beam, copies, prec
             ref = np.stack([oracle.next_logprobs(mems[r // beam], hist[r]) for r in sample])
             assert np.max(np.abs(dec.logprobs()[sample] - ref)) <= tol, t + 1
     ctx.close()
+
+
+def _thirty_steps():
+    """The candidates of 30 steps of a small fp16 model, as (values, ids); the tokens fed depend on the step before."""
+    import paper_1904_01038_amd as T
+    shape = SHAPES["half"]
+    ctx = T.Tfm(T.make_config(shape, precision=T.FP16, max_sentences=4, max_len=32, max_tokens=64))
+    ctx.set_params(init_params(shape, 0, generic=True))
+    dec = T.Decoder(ctx, 12, 30, 64, 4)
+    rng = np.random.default_rng(1)
+    src, lens = sources(shape, rng, 4, 3, 9)
+    dec.begin(src, lens, 3)
+    prev, out = np.full(12, shape.eos_id, np.int32), []
+    for t in range(30):
+        out.append(dec.step(prev, None if t == 0 else (np.arange(12) // 3 * 3 + rng.integers(0, 3, 12)).astype(np.int32)))
+        prev = out[-1][1][:, t % 4].copy()
+    ctx.close()
+    return np.stack([v for v, _ in out]), np.stack([i for _, i in out])
+
+
+def test_steps_do_not_depend_on_the_default_coherence_of_pinned_memory(tmp_path):
+    """A step's kernels read tokens from, and write candidates to, pinned host memory that is used again at the next step."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = str(tmp_path / "steps.npz")
+    code = "import sys, numpy as np; sys.path.insert(0, %r); from tests.test_gpu_decode import _thirty_steps; v, i = _thirty_steps(); np.savez(%r, v=v, i=i)" % (root, out)
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=100, env=dict(os.environ, HIP_HOST_COHERENT="0"))
+    got, (v, i) = np.load(out), _thirty_steps()
+    assert np.array_equal(got["v"], v) and np.array_equal(got["i"], i)
