@@ -298,8 +298,9 @@ __device__ __forceinline__ bool better(float v, int i, float w, int j) { return 
 // Selection costs little because almost no value takes part in it.  Every wavefront splits its lanes into at least k groups;
 // the smallest of the groups' maxima is a value that at least k others reach, so no value among the block's k best lies below
 // it.  The largest such bound of the block filters the registers, and every survivor counts how many others are better than
-// itself: that is its place.  Should more than TOPK_LIST survive (many equal values), the block falls back to k rounds over
-// all of its values.
+// itself: that is its place.  Should more than TOPK_LIST survive (many equal values), or too few (values of -infinity, or NaN),
+// the block falls back to k rounds over all of its values.  -infinity is a value like any other, after the finite ones; NaN is
+// never a candidate and makes the row's log-sum-exp NaN.
 constexpr int TOPK_THREADS = 256, TOPK_PER = 16, TOPK_TILE = TOPK_THREADS * TOPK_PER, TOPK_LIST = 256;
 
 struct TopkList { float* v; int* id; float *m, *s; };    // per row: n * k candidates, n (maximum, sum of exp(value - maximum)) pairs
@@ -346,9 +347,9 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
     }
   }
   auto id_of = [&](int e) { return VEC > 0 ? id0 + (e / (VEC > 0 ? VEC : 1)) * 64 * VEC + e % (VEC > 0 ? VEC : 1) : ids[VEC > 0 ? 0 : e]; };
-  float lmax = c[0];
+  float lmax = -INFINITY;
 #pragma unroll
-  for (int e = 1; e < PER; ++e) lmax = fmaxf(lmax, c[e]);
+  for (int e = 0; e < PER; ++e) lmax = fmaxf(lmax, c[e]);
   {
     auto with = [](float v, int moved) { return fmaxf(v, __int_as_float(moved)); };
     float x = lmax;                                      // groups of 4 lanes, of 8 for k <= 8, of 16 for k <= 4
@@ -367,6 +368,9 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
     if (gm > -INFINITY) {
 #pragma unroll
       for (int e = 0; e < PER; ++e) se += __expf(c[e] - gm);
+    } else {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) se += c[e] != c[e] ? c[e] : 0.f;
     }
     gs = block_sum(se, sh);
   } else {
@@ -376,7 +380,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
     float se = 0.f;
     for (int l = l0 + tid; l < l1; l += NT) {
       const float lm = in.m[(size_t)row * n_in + l];
-      if (lm > -INFINITY) se += in.s[(size_t)row * n_in + l] * __expf(lm - gm);
+      se += in.s[(size_t)row * n_in + l] * (lm > -INFINITY ? __expf(lm - gm) : 1.f);       // (0 or NaN times 1)
     }
     gs = block_sum(se, sh);
   }
@@ -412,8 +416,8 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
       out.id[((size_t)row * gridDim.x + blk) * k + r] = id;
     }
   };
-  const int n = list_n;
-  if (n <= TOPK_LIST) {
+  const int n = list_n, least = VEC > 0 ? min(k, V - blk * NT * PER) : k;
+  if (n <= TOPK_LIST && n >= least) {
     if (tid < 16 && n + tid < TOPK_LIST) { list_v[n + tid] = -INFINITY; list_i[n + tid] = 0x7fffffff; }     // whole groups of 16 below
     __syncthreads();
     if (tid < n) {
@@ -434,26 +438,27 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
                   (int)better(o[q].w, oi[q].w, v, id);
       }
       if (rank < k) emit(rank, v, id);
-    } else if (tid < k) emit(tid, -INFINITY, 0x7fffffff);                       // fewer than k finite values
+    } else if (tid < k) emit(tid, -INFINITY, 0x7fffffff);                       // fewer than k columns
     return;
   }
-  for (int r = 0; r < k; ++r) {
-    float v = c[0];
+  unsigned left = 0;                                     // the values that have not been taken yet
 #pragma unroll
-    for (int e = 1; e < PER; ++e) v = fmaxf(v, c[e]);
-    v = block_max(v, sh);
+  for (int e = 0; e < PER; ++e) left |= c[e] == c[e] && id_of(e) < (VEC > 0 ? V : 0x7fffffff) ? 1u << e : 0u;
+  for (int r = 0; r < k; ++r) {
+    float v = -INFINITY;
     int id = 0x7fffffff;
 #pragma unroll
-    for (int e = 0; e < PER; ++e) id = (c[e] == v && v > -INFINITY && id_of(e) < id) ? id_of(e) : id;
-    id = wave_min_i32(id);
+    for (int e = 0; e < PER; ++e)
+      if ((left >> e & 1) && better(c[e], id_of(e), v, id)) { v = c[e]; id = id_of(e); }
+    const float top = block_max(v, sh);
+    id = wave_min_i32(v == top ? id : 0x7fffffff);
     if (lane == 0) list_i[wave] = id;
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < NW; ++w) id = min(id, list_i[w]);
-    if (tid == 0) emit(r, v, id);
+    if (tid == 0) emit(r, top, id);
 #pragma unroll
-    for (int e = 0; e < PER; ++e)
-      if (id_of(e) == id) c[e] = -INFINITY;
+    for (int e = 0; e < PER; ++e) left &= id_of(e) == id ? ~(1u << e) : ~0u;
     __syncthreads();
   }
 }

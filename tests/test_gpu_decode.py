@@ -419,3 +419,42 @@ def test_steps_do_not_depend_on_the_default_coherence_of_pinned_memory(tmp_path)
     subprocess.run([sys.executable, "-c", code], check=True, timeout=100, env=dict(os.environ, HIP_HOST_COHERENT="0"))
     got, (v, i) = np.load(out), _thirty_steps()
     assert np.array_equal(got["v"], v) and np.array_equal(got["i"], i)
+
+
+@pytest.mark.parametrize("prec", ["fp16", "fp32"])
+@pytest.mark.parametrize("vocab", [300, 4099, 32768, 40001, 65536])
+@pytest.mark.parametrize("finite,nans,k", [(1, 0, 1), (1, 0, 8), (5, 0, 16), (2000, 0, 8), (20, 200, 16), (3, 200, 8), (1, -3, 8)])
+def test_candidates_among_infinite_and_undefined_logits(vocab, finite, nans, k, prec):
+    """`finite` tokens have finite logits, the others overflow to -infinity: those follow in ascending id order.  nans > 0: that many
+    tokens side by side are NaN, nans < 0: all but that many; they are never returned, and the row's log-probabilities are NaN."""
+    import paper_1904_01038_amd as T
+    finite = min(finite, vocab // 2)
+    shape = ModelShape(0, 1, 8, 1, 8, vocab, pre_norm=1)
+    rng = np.random.default_rng(vocab + finite)
+    params = {n: np.zeros_like(v) for n, v in init_params(shape, 3).items()}
+    params["dec.ln_final.b"][:] = 1.0                      # the final state is all ones: a logit is the sum of its token's row
+    z = np.full(vocab, -np.inf)
+    ids = np.append(rng.choice(np.setdiff1d(np.arange(vocab), [shape.eos_id]), finite - 1, replace=False), shape.eos_id)
+    z[ids] = 8 * rng.integers(-64, 64, finite) / 64.0      # (several equal ones among many)
+    if nans:
+        kept = np.concatenate([[shape.eos_id], np.arange(vocab - 2, vocab)])
+        gone = np.setdiff1d(np.arange(vocab // 3, min(vocab, vocab // 3 + nans)) if nans > 0 else np.arange(vocab), kept)
+        z[gone] = np.nan
+    params["embed"][:] = np.where(np.isneginf(z), {"fp16": -60000.0, "fp32": -3e38}[prec], z / 8)[:, None]
+    ctx = T.Tfm(T.make_config(shape, precision={"fp16": T.FP16, "fp32": T.FP32}[prec], max_sentences=4, max_len=4, max_tokens=16))
+    ctx.set_params(params)
+    dec = T.Decoder(ctx, 3, 2, 1, k)
+    dec.begin(None, None, 1, 3)
+    top_lp, top_id = dec.step(np.full(3, shape.eos_id, np.int32))
+    there = np.flatnonzero(~np.isnan(z))
+    want = there[np.lexsort((there, -z[there]))][:k]
+    want_id = np.concatenate([want, np.full(k - len(want), 0x7fffffff)])
+    lse = np.nan if nans else np.log(np.exp(z[np.isfinite(z)]).sum())
+    for r in range(3):
+        assert top_id[r].tolist() == want_id.tolist()
+        if nans:
+            assert np.isnan(top_lp[r]).all()
+        else:
+            assert np.array_equal(np.isneginf(top_lp[r]), np.isneginf(z[want]))
+            assert np.allclose(top_lp[r][np.isfinite(z[want])], (z[want] - lse)[np.isfinite(z[want])], atol=1e-5)
+    ctx.close()
