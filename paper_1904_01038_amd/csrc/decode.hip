@@ -315,7 +315,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
   __shared__ __attribute__((aligned(16))) float list_v[TOPK_LIST];
   __shared__ __attribute__((aligned(16))) int list_i[TOPK_LIST];
   __shared__ int list_n;
-  const int row = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = blockIdx.x, blk = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float c[PER];
   int id0 = 0;                                           // VEC > 0: id of this thread's first value (the others follow from it)
   int ids[VEC == 0 ? PER : 1];
@@ -401,19 +401,20 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
       }
   }
   __syncthreads();
-  const bool last = gridDim.x == 1;
+  const int lists = gridDim.y;
+  const bool last = lists == 1;
   const float lse = gm + logf(gs);
   if (tid == 0) {
     if (last) { if (lse_out) lse_out[row] = lse; }
-    else { out.m[(size_t)row * gridDim.x + blk] = gm; out.s[(size_t)row * gridDim.x + blk] = gs; }
+    else { out.m[(size_t)row * lists + blk] = gm; out.s[(size_t)row * lists + blk] = gs; }
   }
   auto emit = [&](int r, float v, int id) {
     if (last) {
       top_logp[(size_t)row * k + r] = v - lse;
       top_id[(size_t)row * k + r] = id;
     } else {
-      out.v[((size_t)row * gridDim.x + blk) * k + r] = v;
-      out.id[((size_t)row * gridDim.x + blk) * k + r] = id;
+      out.v[((size_t)row * lists + blk) * k + r] = v;
+      out.id[((size_t)row * lists + blk) * k + r] = id;
     }
   };
   const int n = list_n, least = VEC > 0 ? min(k, V - blk * NT * PER) : k;
@@ -483,8 +484,9 @@ static void row_topk_typed(hipStream_t s, const void* z, int ldz, int rows, int 
   char* bufs[2] = {(char*)scratch, (char*)scratch + (n > 1 ? topk_list_bytes(rows, n, k) : 0)};
   TopkList out = list_at(bufs[0], n), in{};
   const uintptr_t al = (uintptr_t)z | (uintptr_t)ldz * sizeof(T) | (uintptr_t)V * sizeof(T);       // what every load's address is a multiple of
+  // (rows along x: y and z of a grid end at 65536)
 #define TK(VEC) \
-  hipLaunchKernelGGL((row_topk_kernel<T, VEC>), dim3(n, rows), dim3(TOPK_THREADS), 0, s, (const T*)z, ldz, V, in, n_in, k, out, top_logp, top_id, lse)
+  hipLaunchKernelGGL((row_topk_kernel<T, VEC>), dim3(rows, n), dim3(TOPK_THREADS), 0, s, (const T*)z, ldz, V, in, n_in, k, out, top_logp, top_id, lse)
   if (al % (8 * sizeof(T)) == 0) TK(8); else if (al % (2 * sizeof(T)) == 0) TK(2); else TK(1);
   for (int which = 1; n > 1; which ^= 1) {
     n_in = n;

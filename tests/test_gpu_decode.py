@@ -458,3 +458,21 @@ def test_candidates_among_infinite_and_undefined_logits(vocab, finite, nans, k, 
             assert np.array_equal(np.isneginf(top_lp[r]), np.isneginf(z[want]))
             assert np.allclose(top_lp[r][np.isfinite(z[want])], (z[want] - lse)[np.isfinite(z[want])], atol=1e-5)
     ctx.close()
+
+
+@pytest.mark.parametrize("vocab", [40, 4104])
+def test_more_rows_than_the_second_axis_of_a_grid_holds(vocab):
+    """70000 rows: every row's candidates are those of the same row decoded in a batch of few."""
+    import paper_1904_01038_amd as T
+    shape = ModelShape(0, 1, 8, 1, 8, vocab, pre_norm=1)
+    ctx = T.Tfm(T.make_config(shape, precision=T.FP32, max_sentences=35000, max_len=4, max_tokens=64))
+    ctx.set_params(init_params(shape, 3, generic=True))
+    prev = np.random.default_rng(0).integers(4, shape.vocab, 70000).astype(np.int32)
+    many, few = T.Decoder(ctx, 70000, 2, 1, 3), T.Decoder(ctx, 64, 2, 1, 3)
+    many.begin(None, None, 2, 35000)
+    lp, ids = many.step(prev)
+    for r in (0, 32768, 65472, 69936):
+        few.begin(None, None, 2, 32)
+        want_lp, want_id = few.step(prev[r:r + 64])
+        assert np.array_equal(ids[r:r + 64], want_id) and np.array_equal(lp[r:r + 64], want_lp)
+    ctx.close()
