@@ -33,7 +33,8 @@ static __device__ __forceinline__ f32x4 mfma16(bf16_t, u32x4 a, u32x4 b, f32x4 c
 
 constexpr int THIN_WAVES = 8, THIN_UNIT = 64;            // wavefronts per block; K elements of a unit
 constexpr int THIN_NORM_SPLITS = 4;                      // LN: slices a row's y may come in
-constexpr int THIN_NORM_UNITS = 3;                       // LN: units a wavefront holds beside the row it makes
+constexpr int THIN_UNITS = 4;                            // units a wavefront holds, and beside a row that it makes (LN):
+constexpr int THIN_NORM_UNITS = 3, THIN_NORM_WIDE_UNITS = 2;                   // with one and with four column tiles
 
 struct ThinParams {
   int R, N, K, kblock;                                   // kblock: K elements per blockIdx.y slice
@@ -247,29 +248,36 @@ __global__ __launch_bounds__(64 * THIN_WAVES) void gemm_thin_kernel(ThinParams p
   }
 }
 
-template <typename T, int RT, int NT, bool LN>
+// U: the most units a wavefront may hold, which the callers' limits on K keep to
+template <typename T, int RT, int NT, bool LN, int U>
 static void thin_launch(hipStream_t s, const ThinParams& p, int splits) {
+  if constexpr (U > 1) {
+    if (p.kblock <= (U - 1) * THIN_WAVES * THIN_UNIT) { thin_launch<T, RT, NT, LN, U - 1>(s, p, splits); return; }
+  }
   const dim3 grid((p.N + 16 * NT - 1) / (16 * NT), splits), block(64 * THIN_WAVES);
   size_t sh = (size_t)THIN_WAVES * RT * NT * 1024;
   if (LN) sh = std::max(sh, (size_t)p.R * (p.K + 8) * 2);
-  const int u = (p.kblock + THIN_WAVES * THIN_UNIT - 1) / (THIN_WAVES * THIN_UNIT);
-#define THIN(U) hipLaunchKernelGGL((gemm_thin_kernel<T, RT, NT, U, LN>), grid, block, sh, s, p)
-  if (u <= 1) THIN(1); else if (u == 2) THIN(2); else if (u == 3) THIN(3); else if constexpr (!LN) THIN(4);
-#undef THIN
+  hipLaunchKernelGGL((gemm_thin_kernel<T, RT, NT, U, LN>), grid, block, sh, s, p);
 }
 template <typename T>
-static void thin_dispatch(hipStream_t s, const ThinParams& p, int splits, bool wide, bool ln) {
+static void thin_dispatch(hipStream_t s, const ThinParams& p, int splits, bool wide) {
+  constexpr int U = THIN_UNITS;
   const int rt = (p.R + 15) / 16;
-  // LN with 4 column tiles: up to 2 units a wavefront (K = 1024); beyond, the row in the making and the weights no longer fit
-  // 256 registers (100-430 spilled).  A decoder-only model of 6 blocks, width 1536, inner size 8192, 32 steps: 1 row 10.7 -> 10.1 ms, 8 rows
-  // 12.5 -> 11.7 with a column tile each; inner size 6144, where only the vocabulary is that wide: equal within the spread.
-  if (ln) { if (wide && p.K <= 2 * THIN_WAVES * THIN_UNIT) thin_launch<T, 1, 4, true>(s, p, splits); else thin_launch<T, 1, 1, true>(s, p, splits); }
-  else if (rt == 1) { if (wide) thin_launch<T, 1, 4, false>(s, p, splits); else thin_launch<T, 1, 1, false>(s, p, splits); }
-  else if (rt == 2) { if (wide) thin_launch<T, 2, 4, false>(s, p, splits); else thin_launch<T, 2, 1, false>(s, p, splits); }
-  else { if (wide) thin_launch<T, 4, 2, false>(s, p, splits); else thin_launch<T, 4, 1, false>(s, p, splits); }
+  if (rt == 1) { if (wide) thin_launch<T, 1, 4, false, U>(s, p, splits); else thin_launch<T, 1, 1, false, U>(s, p, splits); }
+  else if (rt == 2) { if (wide) thin_launch<T, 2, 4, false, U>(s, p, splits); else thin_launch<T, 2, 1, false, U>(s, p, splits); }
+  else { if (wide) thin_launch<T, 4, 2, false, U>(s, p, splits); else thin_launch<T, 4, 1, false, U>(s, p, splits); }
+}
+// LN with 4 column tiles: up to 2 units a wavefront (K = 1024); beyond, the row in the making and the weights no longer fit
+// 256 registers (100-430 spilled).  A decoder-only model of 6 blocks, width 1536, inner size 8192, 32 steps: 1 row 10.7 -> 10.1 ms,
+// 8 rows 12.5 -> 11.7 with a column tile each; inner size 6144, where only the vocabulary is that wide: equal within the spread.
+template <typename T>
+static void thin_norm_dispatch(hipStream_t s, const ThinParams& p, bool wide) {
+  if (wide && p.K <= THIN_NORM_WIDE_UNITS * THIN_WAVES * THIN_UNIT) thin_launch<T, 1, 4, true, THIN_NORM_WIDE_UNITS>(s, p, 1);
+  else thin_launch<T, 1, 1, true, THIN_NORM_UNITS>(s, p, 1);
 }
 
-static int thin_least_splits(int K) { return (K + 4 * THIN_WAVES * THIN_UNIT - 1) / (4 * THIN_WAVES * THIN_UNIT); }
+static int thin_least_splits(int K) { return (K + THIN_UNITS * THIN_WAVES * THIN_UNIT - 1) / (THIN_UNITS * THIN_WAVES * THIN_UNIT); }
+static bool thin_wide(int N) { return N >= 8192; }       // enough columns for a block to own several tiles of them
 
 // What the kernel takes: X W^T, at most THIN_ROWS rows, no epilogue but bias and ReLU.  Slices are at most 4 units per
 // wavefront, so a longer contraction needs the split-K workspace.  (Alignment and strides as gemm_mfma_supported.)
@@ -281,26 +289,37 @@ bool gemm_thin_supported(const GemmArgs& a) {
 // ... and with the rows made by the product itself: a wavefront each (8 rows of at most 1536 values: 25 KB of LDS), the contraction
 // in one slice.  Width 2048, 4 units a wavefront, spilled 60-100 registers: 15.2 ms for 32 steps of a 6-block model and 1 row, 18.9 for 8
 // rows; with a LayerNorm kernel before the product 12.7 and 13.6
-bool gemm_thin_norm_supported(const GemmArgs& a) {
-  return gemm_mfma_supported(a) && gemm_thin_supported(a) && a.M <= THIN_WAVES && a.K <= THIN_NORM_UNITS * THIN_WAVES * THIN_UNIT && a.norm->splits <= THIN_NORM_SPLITS;
+bool gemm_thin_norm_supported(const GemmArgs& a, const ThinNorm& q) {
+  return gemm_mfma_supported(a) && gemm_thin_supported(a) && a.M <= THIN_WAVES && a.K <= THIN_NORM_UNITS * THIN_WAVES * THIN_UNIT &&
+         q.splits <= THIN_NORM_SPLITS;
 }
 
-void launch_gemm_thin(hipStream_t s, const GemmArgs& a) {
+static ThinParams thin_params(const GemmArgs& a) {
   ThinParams p{};
   p.R = a.M; p.N = a.N; p.K = a.K;
   p.X = (const uint16_t*)a.A; p.ldx = a.lda; p.W = (const uint16_t*)a.B; p.ldw = a.ldb; p.C = (uint16_t*)a.C; p.ldc = a.ldc;
   p.bias = (const uint16_t*)a.bias; p.relu = a.relu;
-  const bool ln = a.norm != nullptr;
-  if (ln) p.ln = *a.norm;
-  const bool wide = a.N >= 8192;                         // enough columns for a block to own several tiles of them
+  return p;
+}
+
+// (C complete, one slice: the split-K workspace may hold the slices that the rows are made from)
+void launch_gemm_thin_norm(hipStream_t s, const GemmArgs& a, const ThinNorm& q) {
+  ThinParams p = thin_params(a);
+  p.ln = q;
+  p.kblock = (a.K + 64 * THIN_WAVES - 1) / (64 * THIN_WAVES) * (64 * THIN_WAVES);
+  if (a.dt == F16) thin_norm_dispatch<half_t>(s, p, thin_wide(a.N)); else thin_norm_dispatch<bf16_t>(s, p, thin_wide(a.N));
+}
+
+void launch_gemm_thin(hipStream_t s, const GemmArgs& a) {
+  ThinParams p = thin_params(a);
   const int nb = (a.N + 15) / 16, least = 64 * THIN_WAVES;
   // Deferred (the next kernel adds the slices up, with the residual): the result stays in fp32 even as a single slice, so that no
   // contraction is too short for the sum to be taken in 32 bits.  A narrow output has few blocks, and slices of K of at least one
   // unit per wavefront then fill the chip.  Otherwise only a contraction of more than 4 units per wavefront is cut.  (No ReLU in a
-  // deferred reduction; and with LN the workspace may hold the slices that the rows are made from.)
+  // deferred reduction.)
   const int need = thin_least_splits(a.K);
   const size_t slice = (size_t)a.M * a.N * 4;
-  const bool defer = a.deferred_splits && !a.relu && !ln && a.splitk_ws && need * slice <= a.splitk_ws_bytes;
+  const bool defer = a.deferred_splits && !a.relu && a.splitk_ws && need * slice <= a.splitk_ws_bytes;
   int splits = need;
   if (defer) {
     splits = std::max(splits, std::min(std::min(256 / nb, a.K / least), 4));
@@ -309,7 +328,7 @@ void launch_gemm_thin(hipStream_t s, const GemmArgs& a) {
   p.kblock = ((a.K + splits - 1) / splits + least - 1) / least * least;
   splits = (a.K + p.kblock - 1) / p.kblock;
   p.partial = splits > 1 || defer ? (float*)a.splitk_ws : nullptr;
-  if (a.dt == F16) thin_dispatch<half_t>(s, p, splits, wide, ln); else thin_dispatch<bf16_t>(s, p, splits, wide, ln);
+  if (a.dt == F16) thin_dispatch<half_t>(s, p, splits, thin_wide(a.N)); else thin_dispatch<bf16_t>(s, p, splits, thin_wide(a.N));
   if (a.deferred_splits) *a.deferred_splits = defer ? splits : 0;
   if (splits > 1 && !defer) launch_splitk_reduce(s, a.dt, p.partial, splits, a.M, a.N, a.C, a.ldc, a.bias, a.relu);
 }

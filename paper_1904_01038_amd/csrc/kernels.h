@@ -57,15 +57,15 @@ struct GemmArgs {
   // *deferred_splits = splits >= 1: the caller's next kernel adds them up (see launch_splitk_layernorm_fwd).  Otherwise
   // *deferred_splits = 0 and C is complete.
   int* deferred_splits = nullptr;
-  // The rows are made by the product (A is not read): see ThinNorm.  Only where gemm_thin_norm_supported() says so.
-  const ThinNorm* norm = nullptr;
 };
 void launch_gemm(hipStream_t s, const GemmArgs& a);
 // X W^T for at most THIN_ROWS rows (gemm_thin.hip)
 constexpr int THIN_ROWS = 64;
 bool gemm_thin_supported(const GemmArgs& a);                  // on top of gemm_mfma_supported(a)
-bool gemm_thin_norm_supported(const GemmArgs& a);
 void launch_gemm_thin(hipStream_t s, const GemmArgs& a);
+// the same with the rows made by the product (a.A is not read, C is complete, a.deferred_splits is not used): see ThinNorm
+bool gemm_thin_norm_supported(const GemmArgs& a, const ThinNorm& q);
+void launch_gemm_thin_norm(hipStream_t s, const GemmArgs& a, const ThinNorm& q);   // requires gemm_thin_norm_supported(a, q)
 bool gemm_mfma_supported(const GemmArgs& a);
 void launch_gemm_naive(hipStream_t s, const GemmArgs& a);
 void launch_gemm_mfma(hipStream_t s, const GemmArgs& a);      // requires gemm_mfma_supported(a)

@@ -521,11 +521,11 @@ inline void* gr(tfm_ctx* c, int i) { return (char*)c->g + c->params[i].off * c->
 
 void gemm(tfm_ctx* c, int form, int M, int N, int K, const void* A, int lda, const void* B, int ldb, void* C, int ldc,
           const void* bias = nullptr, int relu = 0, const void* mask = nullptr, const void* residual = nullptr, bool side = false,
-          uint64_t drop_key = 0, float drop_p = 0.f, float mask_scale = 1.f, int* deferred_splits = nullptr, const ThinNorm* norm = nullptr) {
+          uint64_t drop_key = 0, float drop_p = 0.f, float mask_scale = 1.f, int* deferred_splits = nullptr) {
   if (deferred_splits) *deferred_splits = 0;
   if (M <= 0 || N <= 0) return;
   GemmArgs a{c->dt, form, M, N, K, A, lda, B, ldb, C, ldc, bias, relu, mask, residual};
-  a.drop_key = drop_key; a.drop_p = drop_p; a.mask_scale = mask_scale; a.deferred_splits = deferred_splits; a.norm = norm;
+  a.drop_key = drop_key; a.drop_p = drop_p; a.mask_scale = mask_scale; a.deferred_splits = deferred_splits;
   side = side && c->overlap;
   hipStream_t stream = side ? c->side : c->stream;
   a.splitk_ws = side ? c->splitk_ws_side : c->splitk_ws;
@@ -1546,11 +1546,16 @@ void decode_gemm(tfm_decoder* D, int N, int K, const void* fin, int w, const voi
   tfm_ctx* c = D->c;
   const void* W = wh(c, w);
   if (norm) {
-    GemmArgs a{c->dt, 0, D->rows, N, K, fin, K, W, K, C, N, bias, relu, nullptr, nullptr};
-    a.norm = norm;
-    if (!gemm_thin_norm_supported(a)) { decode_norm(D, *norm); norm = nullptr; }
+    const GemmArgs a{c->dt, 0, D->rows, N, K, fin, K, W, K, C, N, bias, relu, nullptr, nullptr};
+    if (gemm_thin_norm_supported(a, *norm)) {
+      if (deferred) *deferred = 0;
+      run(c, TFM_PROF_GEMM, 2.0 * D->rows * N * K, (double)c->esz * ((double)D->rows * K + (double)K * N + (double)D->rows * N),
+          [&] { launch_gemm_thin_norm(c->stream, a, *norm); });
+      return;
+    }
+    decode_norm(D, *norm);
   }
-  gemm(c, 0, D->rows, N, K, fin, K, W, K, C, N, bias, relu, nullptr, nullptr, false, 0, 0.f, 1.f, deferred, norm);
+  gemm(c, 0, D->rows, N, K, fin, K, W, K, C, N, bias, relu, nullptr, nullptr, false, 0, 0.f, 1.f, deferred);
 }
 
 // qkv_new (self-attention): the step's fused [rows, 3d] projection, whose keys and values are to be appended to the caches k

@@ -81,12 +81,24 @@ def test_parameter_list_matches_the_shared_shape_module(T):
         assert specs[0][0] == "embed"
 
 
+def assembly(source):
+    from paper_1904_01038_amd import build
+    r = subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", "-"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return r.stdout
+
+
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
 def test_decoding_scores_are_formed_by_32_bit_multiply_adds():
     """v_dot2_f32_f16 truncates small terms against a fixed floor (1.6e-5 of a result with subnormal keys, where 32-bit FMAs are
     off by 6e-8), and the compiler forms it by itself from FMAs whose factors it sees as halves."""
-    from paper_1904_01038_amd import build
-    r = subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, "decode.hip"), "-o", "-"],
-                       capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-2000:]
-    assert "decode_attention64_kernel" in r.stdout and "v_dot2" not in r.stdout
+    text = assembly("decode.hip")
+    assert "decode_attention64_kernel" in text and "v_dot2" not in text
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_no_instance_of_the_few_row_product_spills_registers():
+    """An instance that no call reaches is not built: those are the ones that would not fit."""
+    spills = re.findall(r"\.name: +(\S*gemm_thin_kernel\S*).*?\.vgpr_spill_count: +(\d+)", assembly("gemm_thin.hip"), flags=re.S)
+    assert len(spills) >= 50
+    assert [name for name, n in spills if int(n)] == []
