@@ -476,3 +476,42 @@ def test_more_rows_than_the_second_axis_of_a_grid_holds(vocab):
         want_lp, want_id = few.step(prev[r:r + 64])
         assert np.array_equal(ids[r:r + 64], want_id) and np.array_equal(lp[r:r + 64], want_lp)
     ctx.close()
+
+
+def _normed(d, heads, pre, enc, vocab=96, cutoffs=()):
+    return ModelShape(enc, 2, d, heads, 2 * d, vocab, pre_norm=pre, cutoffs=cutoffs)
+
+
+@pytest.mark.parametrize("prec,tol", [("fp16", 3e-2), ("bf16", 2e-1)])
+@pytest.mark.parametrize("rows", [1, 3, 7, 8])
+@pytest.mark.parametrize("shape", [
+    _normed(72, 9, 0, 1), _normed(72, 9, 1, 0), _normed(520, 5, 1, 1), _normed(520, 5, 0, 0, 8200), _normed(1024, 16, 1, 1),
+    _normed(1024, 16, 1, 0, 8200), _normed(1536, 24, 0, 1), _normed(1536, 24, 1, 0, 8200), SHAPES["adaptive_half"]],
+    ids=lambda s: "d%d_%s%s_v%d" % (s.d_model, "pre" if s.pre_norm else "post", "_enc" if s.enc_layers else "", s.vocab))
+def test_layernorm_inside_the_product_of_a_few_rows(shape, rows, prec, tol):
+    """At most 8 rows are normalised by the product that reads them: against the oracle, and, where the other products are the same
+    ones (no cross-attention, whose query is cut into slices), against a batch of 16 rows, which has a LayerNorm kernel: to the bit
+    in bf16.  In fp16 the compiler fuses some of the last multiply-adds with the conversion, not the same ones in both kernels, so
+    that now and then one is rounded once and not twice; that moves a logit below 8 by at most two steps of 2^-8."""
+    import paper_1904_01038_amd as T
+    p = {"fp16": T.FP16, "bf16": T.BF16}[prec]
+    params = rounded(init_params(shape, 7, generic=True), p)
+    ctx = T.Tfm(T.make_config(shape, precision=p, max_sentences=16, max_len=32, max_tokens=256, label_smoothing=0.0 if shape.cutoffs else 0.1))
+    ctx.set_params(params)
+    few, many, oracle = T.Decoder(ctx, rows, 3, 64, 8), T.Decoder(ctx, 16, 3, 64, 8), DecodingOracle(shape, params)
+    rng = np.random.default_rng(rows)
+    src, lens = sources(shape, rng, rows, 1, 8)
+    few.begin(src, lens, 1, rows)
+    mems = [oracle.encode(src[r, :lens[r]]) if src is not None else None for r in range(rows)]
+    fed = np.concatenate([np.full((1, 16), shape.eos_id), rng.integers(4, shape.vocab, (2, 16))]).astype(np.int32)
+    same = src is None
+    if same:
+        many.begin(None, None, 1, 16)
+    for t in range(3):
+        top_lp, top_id = few.step(fed[t, :rows])
+        lp = few.logprobs()
+        check_step(lp, top_lp, top_id, np.stack([oracle.next_logprobs(mems[r], list(fed[:t + 1, r])) for r in range(rows)]), tol)
+        if same:
+            many.step(fed[t])
+            assert np.max(np.abs(many.logprobs()[:rows] - lp)) <= (0.0 if p == T.BF16 else 2 * 2.0 ** -8)
+    ctx.close()
