@@ -13,11 +13,13 @@ SHAPES = {
     "pre": ModelShape(1, 2, 32, 4, 48, 80, pre_norm=1),
     "lm": ModelShape(0, 2, 32, 2, 64, 96, pre_norm=1),
     "half": ModelShape(2, 2, 128, 2, 256, 512),         # head width 64: the MFMA GEMMs serve rows that are a multiple of 8
-    # contractions long enough for the few-row products to be split along K: the slices of a sub-layer's last product are summed
-    # by the LayerNorm kernel, those of the cross-attention query projection by the attention kernel (head width 64) or, where
-    # the general attention kernel runs (head width 32), by a reduction in front of it
+    # the fp32 slices of a sub-layer's last product are summed by the LayerNorm kernel, those of the cross-attention query projection
+    # by the attention kernel (head width 64) or, where the general attention kernel runs (head width 32), by a reduction in front
+    # of it: a single slice with 9 to 64 rows at width 512, two with more rows or at width 1024
     "wide": ModelShape(1, 1, 512, 8, 1024, 96),
     "wide_dh32": ModelShape(1, 1, 512, 16, 1024, 96),
+    "wider": ModelShape(1, 1, 1024, 16, 2048, 96),
+    "wider_dh32": ModelShape(1, 1, 1024, 32, 2048, 96),
     # adaptive inputs + adaptive softmax: clusters of 24 / 32 / 40 tokens (generic kernels) and of 126 (+2 entries) / 128 / 256
     # tokens, every table a multiple of 8 rows (matrix-core GEMMs)
     "adaptive": ModelShape(0, 2, 32, 2, 64, 96, pre_norm=1, cutoffs=(24, 56), factor=2),
@@ -71,13 +73,14 @@ def check_step(lp_gpu, top_lp, top_id, lp_ref, tol):
 @pytest.mark.parametrize("name,prec,tol", [("post", "fp32", 2e-4), ("pre", "fp32", 2e-4), ("lm", "fp32", 2e-4),
                                            ("half", "fp16", 3e-2), ("half", "bf16", 2e-1),
                                            ("wide", "fp16", 3e-2), ("wide", "bf16", 2e-1), ("wide_dh32", "fp16", 3e-2),
+                                           ("wider", "fp16", 3e-2), ("wider", "bf16", 2e-1), ("wider_dh32", "fp16", 3e-2),
                                            ("adaptive", "fp32", 2e-4), ("adaptive_half", "fp16", 3e-2), ("adaptive_half", "bf16", 2e-1)])
-def test_steps_with_reordered_beams_match_the_full_decoder(name, prec, tol):
+def test_steps_with_reordered_beams_match_the_full_decoder(name, prec, tol, B=4, beam=4):
     import paper_1904_01038_amd as T
     shape = SHAPES[name]
     p = {"fp32": T.FP32, "fp16": T.FP16, "bf16": T.BF16}[prec]
-    B, beam, steps, topk = 4, 4, 7, 8
-    ctx, dec, oracle = make(shape, p, B * beam, steps, 64, topk)
+    steps, topk = 7, 8
+    ctx, dec, oracle = make(shape, p, B * beam, steps, 16 * B, topk)
     rng = np.random.default_rng(5)
     src, lens = sources(shape, rng, B, 1, 11)
     for attempt in range(2):                               # a second batch re-uses the decoder: caches start over
@@ -100,6 +103,11 @@ def test_steps_with_reordered_beams_match_the_full_decoder(name, prec, tol):
             check_step(dec.logprobs(), top_lp, top_id, ref, tol)
         src, lens = sources(shape, rng, B, 2, 9)
     ctx.close()
+
+
+@pytest.mark.parametrize("name,prec,tol", [("wide", "fp16", 3e-2), ("wide", "bf16", 2e-1), ("wide_dh32", "fp16", 3e-2), ("wide_dh32", "bf16", 2e-1)])
+def test_steps_of_more_than_64_rows_match_the_full_decoder(name, prec, tol):
+    test_steps_with_reordered_beams_match_the_full_decoder(name, prec, tol, B=16, beam=5)
 
 
 def test_beam_search_on_both_sides_finds_the_same_hypotheses():
