@@ -13,6 +13,7 @@
 // 3072 x 1024 layer and 4 rows, against 4.7 + 4.4 us for a LayerNorm kernel and the product after it.  (16 rows a block, for
 // products of more rows, cost 13.4 us against 5.0 + 5.9: a block then reads 130-260 KB of slices.)
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "kernels.h"
@@ -259,13 +260,39 @@ static void thin_launch(hipStream_t s, const ThinParams& p, int splits) {
   if (LN) sh = std::max(sh, (size_t)p.R * (p.K + 8) * 2);
   hipLaunchKernelGGL((gemm_thin_kernel<T, RT, NT, U, LN>), grid, block, sh, s, p);
 }
+// How a product is cut: 16-row tiles rt and 16-column tiles nt of a block, blocks along N, slices of K and their length.
+struct ThinPlan { int rt, nt, blocks, splits, kblock; bool defer; };
+static int thin_least_splits(int K) { return (K + THIN_UNITS * THIN_WAVES * THIN_UNIT - 1) / (THIN_UNITS * THIN_WAVES * THIN_UNIT); }
+static bool thin_wide(int N) { return N >= 8192; }       // enough columns for a block to own several tiles of them
+static ThinPlan thin_plan(const GemmArgs& a) {
+  ThinPlan q;
+  const bool wide = thin_wide(a.N);
+  q.rt = a.M <= 16 ? 1 : a.M <= 32 ? 2 : 4;
+  q.nt = !wide ? 1 : q.rt < 4 ? 4 : 2;
+  q.blocks = (a.N + 16 * q.nt - 1) / (16 * q.nt);
+  // Deferred (the next kernel adds the slices up, with the residual): the result stays in fp32 even as a single slice, so that no
+  // contraction is too short for the sum to be taken in 32 bits.  A narrow output has few blocks, and slices of K of at least one
+  // unit per wavefront then fill the chip.  Otherwise only a contraction of more than 4 units per wavefront is cut.  (No ReLU in a
+  // deferred reduction.)
+  const int least = 64 * THIN_WAVES, need = thin_least_splits(a.K);
+  const size_t slice = (size_t)a.M * a.N * 4;
+  q.defer = a.deferred_splits && !a.relu && a.splitk_ws && need * slice <= a.splitk_ws_bytes;
+  int splits = need;
+  if (q.defer) {
+    splits = std::max(splits, std::min(std::min(256 / ((a.N + 15) / 16), a.K / least), 4));
+    while (splits > need && splits * slice > a.splitk_ws_bytes) --splits;
+  }
+  q.kblock = ((a.K + splits - 1) / splits + least - 1) / least * least;
+  q.splits = (a.K + q.kblock - 1) / q.kblock;
+  return q;
+}
+
 template <typename T>
-static void thin_dispatch(hipStream_t s, const ThinParams& p, int splits, bool wide) {
+static void thin_dispatch(hipStream_t s, const ThinParams& p, const ThinPlan& q) {
   constexpr int U = THIN_UNITS;
-  const int rt = (p.R + 15) / 16;
-  if (rt == 1) { if (wide) thin_launch<T, 1, 4, false, U>(s, p, splits); else thin_launch<T, 1, 1, false, U>(s, p, splits); }
-  else if (rt == 2) { if (wide) thin_launch<T, 2, 4, false, U>(s, p, splits); else thin_launch<T, 2, 1, false, U>(s, p, splits); }
-  else { if (wide) thin_launch<T, 4, 2, false, U>(s, p, splits); else thin_launch<T, 4, 1, false, U>(s, p, splits); }
+  if (q.rt == 1) { if (q.nt == 4) thin_launch<T, 1, 4, false, U>(s, p, q.splits); else thin_launch<T, 1, 1, false, U>(s, p, q.splits); }
+  else if (q.rt == 2) { if (q.nt == 4) thin_launch<T, 2, 4, false, U>(s, p, q.splits); else thin_launch<T, 2, 1, false, U>(s, p, q.splits); }
+  else { if (q.nt == 2) thin_launch<T, 4, 2, false, U>(s, p, q.splits); else thin_launch<T, 4, 1, false, U>(s, p, q.splits); }
 }
 // LN with 4 column tiles: up to 2 units a wavefront (K = 1024); beyond, the row in the making and the weights no longer fit
 // 256 registers (100-430 spilled).  A decoder-only model of 6 blocks, width 1536, inner size 8192, 32 steps: 1 row 10.7 -> 10.1 ms,
@@ -276,15 +303,26 @@ static void thin_norm_dispatch(hipStream_t s, const ThinParams& p, bool wide) {
   else thin_launch<T, 1, 1, true, THIN_NORM_UNITS>(s, p, 1);
 }
 
-static int thin_least_splits(int K) { return (K + THIN_UNITS * THIN_WAVES * THIN_UNIT - 1) / (THIN_UNITS * THIN_WAVES * THIN_UNIT); }
-static bool thin_wide(int N) { return N >= 8192; }       // enough columns for a block to own several tiles of them
-
 // What the kernel takes: X W^T, at most THIN_ROWS rows, no epilogue but bias and ReLU.  Slices are at most 4 units per
 // wavefront, so a longer contraction needs the split-K workspace.  (Alignment and strides as gemm_mfma_supported.)
 bool gemm_thin_supported(const GemmArgs& a) {
   if (a.form != 0 || a.M > THIN_ROWS || a.mask || a.residual || a.drop_p != 0.f) return false;
   const int least = thin_least_splits(a.K);
   return least == 1 || (least <= 8 && a.splitk_ws && (size_t)least * a.M * a.N * 4 <= a.splitk_ws_bytes);
+}
+// Whether it is faster than the tiled kernel.  Both wait for what a compute unit has to fetch, some 33 KiB per us: here 256 blocks
+// at a time, each its weights and all the rows again; there 512 tiles at a time, whose 64 rows are no more than that.  A few tiles
+// are cut along K, and a reduction kernel of about 2.5 us (80 KiB) follows unless somebody else adds the slices up; the ring's walk
+// through K makes up for the other 80 KiB.  Measured, us here / there: 4 rows of 1024 x 1024 4.1 / 6.6; 64 rows of 3072 x 1024
+// 7.7 / 9.1; 12 of 4608 x 1536 8.3 / 8.5, 20 of it 9.5 / 8.6; 16 of 32768 x 1024 13.8 / 13.9, 24 of it 14.9 / 14.0, 48 of it
+// 23.5 / 13.9; 9 of 8192 x 2048 13.5 / 10.9.  Over 940 products of 1 to 64 rows, N 256 to 207744 and K 64 to 8192 it loses 1 % to the
+// better of both (always this kernel: 16 %, never: 13 %) and is more than 5 % behind the tiled kernel in 15, by 0.8 us on average.
+bool gemm_thin_pays(const GemmArgs& a) {
+  const ThinPlan q = thin_plan(a);
+  const double kib = 1024.0, tiles = (a.N + 63) / 64, rounds = std::ceil(q.blocks * q.splits / 256.0);
+  const double here = rounds * std::min(q.kblock, a.K) * 2.0 * (16 * q.nt + 16 * q.rt) + (q.splits > 1 && !q.defer ? 40 * kib : 0.0);
+  const double there = (tiles <= 512 ? tiles / 512 : std::ceil(tiles / 512)) * 256.0 * a.K;
+  return here <= there + 80 * kib + (tiles <= 128 && a.K >= 512 && !q.defer ? 80 * kib : 0.0);
 }
 // ... and with the rows made by the product itself: a wavefront each (8 rows of at most 1536 values: 25 KB of LDS), the contraction
 // in one slice.  Width 2048, 4 units a wavefront, spilled 60-100 registers: 15.2 ms for 32 steps of a 6-block model and 1 row, 18.9 for 8
@@ -312,25 +350,12 @@ void launch_gemm_thin_norm(hipStream_t s, const GemmArgs& a, const ThinNorm& q) 
 
 void launch_gemm_thin(hipStream_t s, const GemmArgs& a) {
   ThinParams p = thin_params(a);
-  const int nb = (a.N + 15) / 16, least = 64 * THIN_WAVES;
-  // Deferred (the next kernel adds the slices up, with the residual): the result stays in fp32 even as a single slice, so that no
-  // contraction is too short for the sum to be taken in 32 bits.  A narrow output has few blocks, and slices of K of at least one
-  // unit per wavefront then fill the chip.  Otherwise only a contraction of more than 4 units per wavefront is cut.  (No ReLU in a
-  // deferred reduction.)
-  const int need = thin_least_splits(a.K);
-  const size_t slice = (size_t)a.M * a.N * 4;
-  const bool defer = a.deferred_splits && !a.relu && a.splitk_ws && need * slice <= a.splitk_ws_bytes;
-  int splits = need;
-  if (defer) {
-    splits = std::max(splits, std::min(std::min(256 / nb, a.K / least), 4));
-    while (splits > need && splits * slice > a.splitk_ws_bytes) --splits;
-  }
-  p.kblock = ((a.K + splits - 1) / splits + least - 1) / least * least;
-  splits = (a.K + p.kblock - 1) / p.kblock;
-  p.partial = splits > 1 || defer ? (float*)a.splitk_ws : nullptr;
-  if (a.dt == F16) thin_dispatch<half_t>(s, p, splits, thin_wide(a.N)); else thin_dispatch<bf16_t>(s, p, splits, thin_wide(a.N));
-  if (a.deferred_splits) *a.deferred_splits = defer ? splits : 0;
-  if (splits > 1 && !defer) launch_splitk_reduce(s, a.dt, p.partial, splits, a.M, a.N, a.C, a.ldc, a.bias, a.relu);
+  const ThinPlan q = thin_plan(a);
+  p.kblock = q.kblock;
+  p.partial = q.splits > 1 || q.defer ? (float*)a.splitk_ws : nullptr;
+  if (a.dt == F16) thin_dispatch<half_t>(s, p, q); else thin_dispatch<bf16_t>(s, p, q);
+  if (a.deferred_splits) *a.deferred_splits = q.defer ? q.splits : 0;
+  if (q.splits > 1 && !q.defer) launch_splitk_reduce(s, a.dt, p.partial, q.splits, a.M, a.N, a.C, a.ldc, a.bias, a.relu);
 }
 
 }  // namespace tfm

@@ -62,6 +62,7 @@ void launch_gemm(hipStream_t s, const GemmArgs& a);
 // X W^T for at most THIN_ROWS rows (gemm_thin.hip)
 constexpr int THIN_ROWS = 64;
 bool gemm_thin_supported(const GemmArgs& a);                  // on top of gemm_mfma_supported(a)
+bool gemm_thin_pays(const GemmArgs& a);                       // ... and is it the faster one for these sizes?
 void launch_gemm_thin(hipStream_t s, const GemmArgs& a);
 // the same with the rows made by the product (a.A is not read, C is complete, a.deferred_splits is not used): see ThinNorm
 bool gemm_thin_norm_supported(const GemmArgs& a, const ThinNorm& q);

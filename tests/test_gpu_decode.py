@@ -499,8 +499,9 @@ def _normed(d, heads, pre, enc, vocab=96, cutoffs=()):
 def test_layernorm_inside_the_product_of_a_few_rows(shape, rows, prec, tol):
     """At most 8 rows are normalised by the product that reads them: against the oracle, and, where the other products are the same
     ones (no cross-attention, whose query is cut into slices), against a batch of 16 rows, which has a LayerNorm kernel: to the bit
-    in bf16.  In fp16 the compiler fuses some of the last multiply-adds with the conversion, not the same ones in both kernels, so
-    that now and then one is rounded once and not twice; that moves a logit below 8 by at most two steps of 2^-8."""
+    in bf16 with a small vocabulary.  In fp16 the compiler fuses some of the last multiply-adds with the conversion, not the same
+    ones in both kernels, and a large vocabulary's scores of 16 rows may come from the tiled kernel: now and then a value is rounded
+    the other way, which moves a logit below 8 by at most two of its steps (2^-8 and 2^-5)."""
     import paper_1904_01038_amd as T
     p = {"fp16": T.FP16, "bf16": T.BF16}[prec]
     params = rounded(init_params(shape, 7, generic=True), p)
@@ -521,5 +522,5 @@ def test_layernorm_inside_the_product_of_a_few_rows(shape, rows, prec, tol):
         check_step(lp, top_lp, top_id, np.stack([oracle.next_logprobs(mems[r], list(fed[:t + 1, r])) for r in range(rows)]), tol)
         if same:
             many.step(fed[t])
-            assert np.max(np.abs(many.logprobs()[:rows] - lp)) <= (0.0 if p == T.BF16 else 2 * 2.0 ** -8)
+            assert np.max(np.abs(many.logprobs()[:rows] - lp)) <= (2 * 2.0 ** -8 if p == T.FP16 else 2 * 2.0 ** -5 if shape.vocab > 4096 else 0.0)
     ctx.close()
