@@ -183,7 +183,7 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
   int off[U];                                            // positions g, g + 8, ... of the chunk; past the end: the last one, with weight 0
 #pragma unroll
   for (int u = 0; u < U; ++u) off[u] = row_of(min(8 * u + g, n - 1));
-  Pack<T, 8> qh;                                         // this lane's piece of the query
+  uint4 qh;                                              // this lane's piece of the query
   if (p.q_partial) {                                     // the query arrives as the slices of a split-K product (at most 8)
     const size_t at = (size_t)r * p.H * dh + h * dh + lane, slice = (size_t)p.rows * p.H * dh;
     float part[8];
@@ -195,15 +195,9 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
     if (p.q_bias) qv += to_f<T>(reinterpret_cast<const T*>(p.q_bias)[h * dh + lane]);
     qs[lane] = from_f<T>(qv);                            // rounded as the stored projection would be
     __syncthreads();                                     // (every row of the launch comes this way, or none does)
-    qh = reinterpret_cast<const Pack<T, 8>*>(qs)[f];
+    qh = reinterpret_cast<const uint4*>(qs)[f];
   } else {
-    qh = reinterpret_cast<const Pack<T, 8>*>(reinterpret_cast<const T*>(p.q) + (size_t)r * p.ldq + h * dh)[f];
-  }
-  float q[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    q[i] = to_f<T>(qh.v[i]);
-    asm("" : "+v"(q[i]));                                // (seen as halves, the compiler would pair the FMAs into v_dot2_f32_f16)
+    qh = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(p.q) + (size_t)r * p.ldq + h * dh)[f];
   }
   auto add = [](float x, float y) { return x + y; };
   auto larger = [](float x, float y) { return fmaxf(x, y); };
@@ -220,7 +214,19 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
 #pragma unroll
       for (int u = 0; u < U; ++u) off[u] = row_of(min(s0 + 8 * U + 8 * u + g, n - 1));
     }
-    float sc[U], mn = m;
+    // The query is looked at only now, when the chunk's loads are on their way (its conversion ahead of the loop would wait for it
+    // first: 0.35 us of 4.7), and its values are opaque: seen as halves, the FMAs would be paired into v_dot2_f32_f16.
+    asm volatile("" : "+v"(qh.x), "+v"(qh.y), "+v"(qh.z), "+v"(qh.w));
+    float q[8], sc[U], mn = m;
+    {
+      Pack<T, 8> x;
+      __builtin_memcpy(&x, &qh, 16);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        q[i] = to_f<T>(x.v[i]);
+        asm("" : "+v"(q[i]));
+      }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       sc[u] = over_lanes(dot8_acc<T>(q, kv[u], 0.f), add);
