@@ -177,12 +177,20 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
     knew = reinterpret_cast<const T*>(p.k_new) + (size_t)r * p.ld_new + h * dh;
     vnew = reinterpret_cast<const T*>(p.v_new) + (size_t)r * p.ld_new + h * dh;
   }
-  auto row_of = [&](int s) -> int {                      // element offset of position s (the host checks that it fits)
-    return p.anc ? (p.anc[(size_t)r * p.max_steps + s] * p.max_steps + s) * p.row_stride : (base + s) * p.row_stride;
-  };
-  int off[U];                                            // positions g, g + 8, ... of the chunk; past the end: the last one, with weight 0
+  // Position s is row first[u] * per + s of the caches, s = g, g + 8, ... of the chunk (past the end: the last one, with weight 0).
+  // The choice between the two tables is made once for all U of them: made for each, it put a wait behind every single load.
+  const int per = p.anc ? p.max_steps : 1;
+  int first[U];
+  auto look_up = [&](int s0) {
+    if (p.anc) {
 #pragma unroll
-  for (int u = 0; u < U; ++u) off[u] = row_of(min(8 * u + g, n - 1));
+      for (int u = 0; u < U; ++u) first[u] = p.anc[(size_t)r * p.max_steps + min(s0 + 8 * u + g, n - 1)];
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) first[u] = base;
+    }
+  };
+  look_up(0);
   uint4 qh;                                              // this lane's piece of the query
   if (p.q_partial) {                                     // the query arrives as the slices of a split-K product (at most 8)
     const size_t at = (size_t)r * p.H * dh + h * dh + lane, slice = (size_t)p.rows * p.H * dh;
@@ -206,14 +214,14 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
   for (int s0 = 0; s0 < n; s0 += 8 * U) {
     uint4 kv[U], vv[U];
+    int off[U];                                          // (the host checks that they fit)
+#pragma unroll
+    for (int u = 0; u < U; ++u) off[u] = (first[u] * per + min(s0 + 8 * u + g, n - 1)) * p.row_stride;
 #pragma unroll
     for (int u = 0; u < U; ++u) kv[u] = *reinterpret_cast<const uint4*>(((knew && s0 + 8 * u + g >= p.t) ? knew : K + off[u]) + f * 8);
 #pragma unroll
     for (int u = 0; u < U; ++u) vv[u] = *reinterpret_cast<const uint4*>(((vnew && s0 + 8 * u + g >= p.t) ? vnew : V + off[u]) + f * 8);
-    if (s0 + 8 * U < n) {                                   // the next chunk's rows
-#pragma unroll
-      for (int u = 0; u < U; ++u) off[u] = row_of(min(s0 + 8 * U + 8 * u + g, n - 1));
-    }
+    if (s0 + 8 * U < n) look_up(s0 + 8 * U);             // the next chunk's rows
     // The query is looked at only now, when the chunk's loads are on their way (its conversion ahead of the loop would wait for it
     // first: 0.35 us of 4.7), and its values are opaque: seen as halves, the FMAs would be paired into v_dot2_f32_f16.
     asm volatile("" : "+v"(qh.x), "+v"(qh.y), "+v"(qh.z), "+v"(qh.w));

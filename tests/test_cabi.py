@@ -102,3 +102,15 @@ def test_no_instance_of_the_few_row_product_spills_registers():
     spills = re.findall(r"\.name: +(\S*gemm_thin_kernel\S*).*?\.vgpr_spill_count: +(\d+)", assembly("gemm_thin.hip"), flags=re.S)
     assert len(spills) >= 50
     assert [name for name, n in spills if int(n)] == []
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_decoding_attention_fetches_the_rows_of_a_chunk_together():
+    """The rows' places in the caches come from a table: 4 or 8 words, asked for one after the other and waited for once.  (A wait
+    behind every word made a chunk of 64 positions nine trips to memory.)"""
+    kernels = re.findall(r"^(\S*decode_attention64_kernel\S*):(.*?)s_endpgm", assembly("decode.hip"), flags=re.S | re.M)
+    assert len(kernels) == 4
+    for name, body in kernels:
+        lines = [l.strip() for l in body.splitlines() if l.strip() and not l.strip().startswith((";", "."))]
+        waits = sum(a.startswith("global_load_dword v") and b.startswith("s_waitcnt vmcnt(0)") for a, b in zip(lines, lines[1:]))
+        assert waits <= 1, (name, waits)
