@@ -11,6 +11,8 @@ enum DType : int { F32 = 0, F16 = 1, BF16 = 2 };
 typedef _Float16 half_t;
 struct bf16_t { uint16_t x; };
 
+constexpr float LN_EPS = 1e-5f;                          // of every LayerNorm
+
 static inline size_t dtype_size(int dt) { return dt == F32 ? 4 : 2; }
 
 // ---- conversions (round to nearest even; a value beyond the half range becomes inf, which is what the

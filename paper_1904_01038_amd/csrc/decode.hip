@@ -17,10 +17,10 @@ namespace tfm {
 // memory: two words per row in one trip, where a copy to the device first was a launch of its own (3.3 us and the host's time
 // for it; the ancestry table another 1.7 us).
 template <typename T>
-__global__ __launch_bounds__(128) void decode_begin_kernel(const int* __restrict__ prev, const int* __restrict__ parent, const int* __restrict__ anc_old,
-                                                           int* __restrict__ anc_new, int max_steps, int t, const T* __restrict__ E,
-                                                           const T* __restrict__ alt, const float* __restrict__ pe, T* __restrict__ out, int d,
-                                                           float scale) {
+__global__ __launch_bounds__(128) void decode_begin_kernel(const int* __restrict__ prev, const int* __restrict__ parent,
+                                                           const int* __restrict__ anc_old, int* __restrict__ anc_new, int max_steps,
+                                                           int t, const T* __restrict__ E, const T* __restrict__ alt,
+                                                           const float* __restrict__ pe, T* __restrict__ out, int d, float scale) {
   const int r = blockIdx.x;
   const int id = prev[r], from = parent[r];
   for (int s = threadIdx.x; s <= t; s += 128) anc_new[(size_t)r * max_steps + s] = s < t ? anc_old[(size_t)from * max_steps + s] : r;
@@ -35,12 +35,12 @@ __global__ __launch_bounds__(128) void decode_begin_kernel(const int* __restrict
     store_f<T, 8>(out + (size_t)r * d + col, v);
   }
 }
-void launch_decode_begin(hipStream_t s, int dt, const int* prev, const int* parent, const int* anc_old, int* anc_new, int rows, int max_steps, int t,
-                         const void* E, const void* alt, const float* pe, void* out, int d) {
+void launch_decode_begin(hipStream_t s, int dt, const int* prev, const int* parent, const int* anc_old, int* anc_new, int rows,
+                         int max_steps, int t, const void* E, const void* alt, const float* pe, void* out, int d) {
   const float scale = sqrtf((float)d);
-#define DB(T)                                                                                                                                \
-  hipLaunchKernelGGL(decode_begin_kernel<T>, dim3(rows), dim3(128), 0, s, prev, parent, anc_old, anc_new, max_steps, t, (const T*)E, (const T*)alt, \
-                     pe, (T*)out, d, scale)
+#define DB(T)                                                                                                                     \
+  hipLaunchKernelGGL(decode_begin_kernel<T>, dim3(rows), dim3(128), 0, s, prev, parent, anc_old, anc_new, max_steps, t, (const T*)E, \
+                     (const T*)alt, pe, (T*)out, d, scale)
   if (dt == F32) DB(float); else if (dt == F16) DB(half_t); else DB(bf16_t);
 #undef DB
 }
@@ -128,13 +128,22 @@ __global__ __launch_bounds__(64) void decode_attention_kernel(DecodeAttnArgs p) 
 }
 
 // The same for head width 64 and 2-byte elements, one wavefront and two trips to memory: the position table and the query,
-// then the keys AND the values of 64 positions together, so that the values travel while the scores are formed.  Lane = (group
-// g = lane / 8, 16-byte piece f = lane % 8): a load fetches 8 whole 128-byte rows, where a lane per position made it touch 64
-// lines (11.1 -> 9.9 us for 268 rows x 16 heads), and a group's weights are where its value rows arrive.  Longer histories go
-// on in chunks with a running maximum.  Chunks of 64 positions hold 128 registers; launches of more than 2048 wavefronts, which
-// would need a second round then, take chunks of 32 (9.9 -> 8.5 us; small launches keep the single trip: 4.2 us for 4 rows).  Lane exchanges only, no LDS but for a query that arrives in slices.
+// then the keys AND the values of a chunk of positions together, so that the values travel while the scores are formed.  Lane =
+// (group g = lane / 8, 16-byte piece f = lane % 8): a load fetches 8 whole 128-byte rows, where a lane per position made it touch
+// 64 lines (11.1 -> 9.9 us for 268 rows x 16 heads), and a group's weights are where its value rows arrive.  Longer histories go
+// on in chunks with a running maximum.  Lane exchanges only, no LDS but for a query that arrives in slices.
 // The beams of a sentence are the wavefronts of one block: they read the same source positions (and mostly the same history),
 // which then come into one L1 and one L2 once, where blocks of one row each were dealt out to different XCDs.
+//
+// Chunks of 64 positions hold 134 registers (3072 wavefronts on the chip at once), chunks of 32 hold 81 (6144): a trip less for
+// 33-64 and 97-128 positions, against half the work for the others.  us with chunks of 64 / of 32, fp16, 16 heads, 4 beams, for
+// histories of 1-32 | 33-64 | 65-96 | 97-128 and sources of 38-45:
+//     64 wavefronts  4.4/3.9 | 4.3/4.6 |  5.6/5.5 |  5.7/6.2   4.2/4.1
+//   1024             4.5/3.8 | 4.4/4.6 |  5.9/5.7 |  5.9/6.4   4.8/5.0
+//   2048             5.6/4.6 | 5.7/5.6 |  8.2/6.9 |  8.3/7.9   6.0/5.9
+//   3072             6.2/5.0 | 6.2/6.6 |  9.6/8.2 |  9.8/9.7   6.8/7.1
+//   4096             7.6/5.6 | 8.0/7.7 | 12.3/9.5 | 12.7/11.7  9.0/7.9
+// From 2048 on chunks of 32 are as good or better but for 33-64 positions at 3072; below, each has its lengths.  bf16 alike.
 // 8 elements of a key against 8 of the query, in 32-bit FMAs.  (v_dot2_f32_f16 truncates what lies far below the larger term and
 // below a fixed floor: 1.6e-5 of the result with subnormal keys, where FMAs are off by 6e-8.)
 template <typename T> __device__ __forceinline__ float dot8_acc(const float (&q)[8], uint4 k, float c) {

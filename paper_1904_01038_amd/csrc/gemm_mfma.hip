@@ -576,8 +576,8 @@ static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a) {
     if (splits > 8) splits = 8;
   } else if (a.form == 0 && BM == 64 && BN == 64 && a.splitk_ws && !a.mask && !a.residual && !p.drop_thr && p.tiles_total <= 128 && nk >= 8 &&
              !(a.deferred_splits && a.relu)) {                // (a deferred reduction has no ReLU)
-    // X W^T with few rows (a decoding step): the weights stream through more CUs; every slice keeps >= 4 K-steps and
-    // bias / ReLU move into the reduction
+    // X W^T with few rows (a decoding step of more than 64 rows, or of fewer where the few-row kernel is not the faster one): the
+    // weights stream through more CUs; every slice keeps >= 4 K-steps and bias / ReLU move into the reduction
     splits = std::min(std::min(256 / p.tiles_total, nk / 4), 8);
   }
   while (splits > 1 && (size_t)splits * a.M * a.N * sizeof(float) > a.splitk_ws_bytes) --splits;
@@ -652,7 +652,8 @@ void launch_wgrad_grouped(hipStream_t s, int dt, const WgradJob* jobs, int n) {
 //   14  192x256      8         64     2      1      X W^T and dY W only: where 256x256 leaves compute units idle (a 3072-wide
 //                                                   output of ~3200 rows has 156 tiles of 256x256 but 204 of 192x256 for
 //                                                   256 CUs: 31.5 -> 28.0 us; 3000 rows: 37.6 -> 27.3 us)
-//   20   64x64       4         64     4      2      fewer than 128 tiles of 128x128 (a decoding step's few rows)
+//   20   64x64       4         64     4      2      fewer than 128 tiles of 128x128 (a decoding step's rows that
+//                                                   the few-row kernel does not take)
 //   22   64x128      8         64     4      1      X W^T and dY W with many rows but a narrow output and K >= 1024 (the 512-wide
 //                                                   products of the base model: 116 tiles of 128x128 become 232; 15.8 -> 13.3 us
 //                                                   at K = 2048, 14.1 -> 11.7 us at K = 1536; slower than the others at K = 512)
@@ -662,7 +663,7 @@ void launch_wgrad_grouped(hipStream_t s, int dt, const WgradJob* jobs, int n) {
 static int choose_tile(const GemmArgs& a) {
   const long t1 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
   if (a.form != 2 && a.M >= 1024 && a.K >= 1024 && t1 <= 160) return 22;
-  if (t1 < 128 && a.form == 0) return 20;               // few rows (a decoding step, X W^T): smaller tiles reach more CUs
+  if (t1 < 128 && a.form == 0) return 20;               // few rows (X W^T): smaller tiles reach more CUs
   const long t3 = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
   const long t4 = (long)((a.M + 191) / 192) * ((a.N + 255) / 256);
   const double ks = (double)((a.K + 63) / 64);

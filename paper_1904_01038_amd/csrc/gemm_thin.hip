@@ -1,16 +1,17 @@
-// X W^T for few rows (a decoding step, a handful of sentences): C[R,N] = epilogue(X[R,K] W[N,K]^T), R <= 64, fp16/bf16.
+// X W^T for few rows (a decoding step, a handful of sentences): C[R,N] = epilogue(X[R,K] W[N,K]^T), R <= 64, fp16/bf16, where
+// that is faster than the tiled kernel (gemm_thin_pays).
 //
 // Such a product is one pass over the weights, and on this chip a dependent chain: launch, one trip to memory, reduction,
-// store.  The tiled kernel walks K step by step through an LDS ring (4.4 us for 4 rows of a 1024 x 1024 layer, 2.3 us of it
-// the walk); here every load of a block is in flight at once.  A block owns 16 * NT output columns; its 8 wavefronts split K,
-// fetch their weights and rows straight into the registers of 16x16x32 MFMAs (weights as the left operand, so that a lane
-// ends up with 4 consecutive columns of one row), and LDS adds up the 8 partial tiles.  The contraction index is dealt so that
-// a lane reads 32 and four lanes 128 contiguous bytes of a weight row: lanes of group g take k = 16 g .. 16 g + 15 of every
-// 64-wide unit.  MFMA only needs both operands to agree on the order.
+// store.  The tiled kernel walks K step by step through an LDS ring (6.6 us for 4 rows of a 1024 x 1024 layer, with the kernel
+// that adds its slices of K up); here every load of a block is in flight at once (4.1 us).  A block owns 16 * NT output columns;
+// its 8 wavefronts split K, fetch their weights and rows straight into the registers of 16x16x32 MFMAs (weights as the left
+// operand, so that a lane ends up with 4 consecutive columns of one row), and LDS adds up the 8 partial tiles.  The contraction
+// index is dealt so that a lane reads 32 and four lanes 128 contiguous bytes of a weight row: lanes of group g take
+// k = 16 g .. 16 g + 15 of every 64-wide unit.  MFMA only needs both operands to agree on the order.
 //
 // With LN the rows are not read but made: s = x + bias + y (y in the compute dtype or as fp32 split-K slices), LayerNorm, into
 // LDS, one wavefront per row.  Every block repeats that, for at most 8 rows, while its weights are on their way: 5.1 us for a
-// 3072 x 1024 layer and 4 rows, against 4.7 + 4.4 us for a LayerNorm kernel and the product after it.  (16 rows a block, for
+// 3072 x 1024 layer and 4 rows, against 4.3 + 4.4 us for a LayerNorm kernel and the product after it.  (16 rows a block, for
 // products of more rows, cost 13.4 us against 5.0 + 5.9: a block then reads 130-260 KB of slices.)
 #include <algorithm>
 #include <cmath>
@@ -125,7 +126,7 @@ template <typename T, int NCH> struct NormRow {
 #pragma unroll
         for (int e = 0; e < 8; ++e) { const float t = v[c][e] - mu; sq += t * t; }
       }
-    const float rs = rsqrtf(wave_sum(sq) / (float)d + 1e-5f);
+    const float rs = rsqrtf(wave_sum(sq) / (float)d + LN_EPS);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int col = (lane + 64 * c) * 8;
@@ -262,8 +263,13 @@ static void thin_launch(hipStream_t s, const ThinParams& p, int splits) {
 }
 // How a product is cut: 16-row tiles rt and 16-column tiles nt of a block, blocks along N, slices of K and their length.
 struct ThinPlan { int rt, nt, blocks, splits, kblock; bool defer; };
-static int thin_least_splits(int K) { return (K + THIN_UNITS * THIN_WAVES * THIN_UNIT - 1) / (THIN_UNITS * THIN_WAVES * THIN_UNIT); }
-static bool thin_wide(int N) { return N >= 8192; }       // enough columns for a block to own several tiles of them
+static int thin_least_splits(int K) {
+  constexpr int most = THIN_UNITS * THIN_WAVES * THIN_UNIT;
+  return (K + most - 1) / most;
+}
+// Enough columns for a block to own several tiles of them, us with several / with one, K = 512: 16 rows N = 4096 5.0 / 3.8, 8192
+// 5.3 / 4.9, 16384 6.7 / 7.3, 65536 12.9 / 17.5; 64 rows N = 4096 5.9 / 5.4, 8192 6.4 / 7.9, 65536 26 / 39.  K = 768 and 1024 alike.
+static bool thin_wide(int N) { return N >= 8192; }
 static ThinPlan thin_plan(const GemmArgs& a) {
   ThinPlan q;
   const bool wide = thin_wide(a.N);
@@ -290,9 +296,11 @@ static ThinPlan thin_plan(const GemmArgs& a) {
 template <typename T>
 static void thin_dispatch(hipStream_t s, const ThinParams& p, const ThinPlan& q) {
   constexpr int U = THIN_UNITS;
-  if (q.rt == 1) { if (q.nt == 4) thin_launch<T, 1, 4, false, U>(s, p, q.splits); else thin_launch<T, 1, 1, false, U>(s, p, q.splits); }
-  else if (q.rt == 2) { if (q.nt == 4) thin_launch<T, 2, 4, false, U>(s, p, q.splits); else thin_launch<T, 2, 1, false, U>(s, p, q.splits); }
-  else { if (q.nt == 2) thin_launch<T, 4, 2, false, U>(s, p, q.splits); else thin_launch<T, 4, 1, false, U>(s, p, q.splits); }
+#define THIN(RT, NT) thin_launch<T, RT, NT, false, U>(s, p, q.splits)
+  if (q.rt == 1) { if (q.nt == 4) THIN(1, 4); else THIN(1, 1); }
+  else if (q.rt == 2) { if (q.nt == 4) THIN(2, 4); else THIN(2, 1); }
+  else { if (q.nt == 2) THIN(4, 2); else THIN(4, 1); }
+#undef THIN
 }
 // LN with 4 column tiles: up to 2 units a wavefront (K = 1024); beyond, the row in the making and the weights no longer fit
 // 256 registers (100-430 spilled).  A decoder-only model of 6 blocks, width 1536, inner size 8192, 32 steps: 1 row 10.7 -> 10.1 ms,
@@ -320,13 +328,16 @@ bool gemm_thin_supported(const GemmArgs& a) {
 bool gemm_thin_pays(const GemmArgs& a) {
   const ThinPlan q = thin_plan(a);
   const double kib = 1024.0, tiles = (a.N + 63) / 64, rounds = std::ceil(q.blocks * q.splits / 256.0);
-  const double here = rounds * std::min(q.kblock, a.K) * 2.0 * (16 * q.nt + 16 * q.rt) + (q.splits > 1 && !q.defer ? 40 * kib : 0.0);
+  const double reduced = q.splits > 1 && !q.defer ? 40 * kib : 0.0;
+  const double here = rounds * std::min(q.kblock, a.K) * 2.0 * (16 * q.nt + 16 * q.rt) + reduced;
   const double there = (tiles <= 512 ? tiles / 512 : std::ceil(tiles / 512)) * 256.0 * a.K;
   return here <= there + 80 * kib + (tiles <= 128 && a.K >= 512 && !q.defer ? 80 * kib : 0.0);
 }
 // ... and with the rows made by the product itself: a wavefront each (8 rows of at most 1536 values: 25 KB of LDS), the contraction
-// in one slice.  Width 2048, 4 units a wavefront, spilled 60-100 registers: 15.2 ms for 32 steps of a 6-block model and 1 row, 18.9 for 8
-// rows; with a LayerNorm kernel before the product 12.7 and 13.6
+// in one slice.  32 steps of a decoder-only model of 6 blocks (inner size 4 times the width, vocabulary 32768), ms with the rows made
+// inside / by a LayerNorm kernel, for 1, 4 and 8 rows: width 512 5.0 / 6.1, 5.3 / 6.4, 5.8 / 6.6; 768 5.7 / 7.0, 6.0 / 7.5, 6.6 / 7.9;
+// 1024 6.0 / 7.4, 6.4 / 7.8, 6.9 / 7.9; 1536 9.5 / 9.8, 9.8 / 10.4, 11.1 / 10.6.  At 2048, 4 units a wavefront, 60-100 registers were
+// spilled (inner size 8192: 15.2 / 12.7 and 18.9 / 13.6 for 1 and 8 rows).
 bool gemm_thin_norm_supported(const GemmArgs& a, const ThinNorm& q) {
   return gemm_mfma_supported(a) && gemm_thin_supported(a) && a.M <= THIN_WAVES && a.K <= THIN_NORM_UNITS * THIN_WAVES * THIN_UNIT &&
          q.splits <= THIN_NORM_SPLITS;
@@ -345,7 +356,8 @@ void launch_gemm_thin_norm(hipStream_t s, const GemmArgs& a, const ThinNorm& q) 
   ThinParams p = thin_params(a);
   p.ln = q;
   p.kblock = (a.K + 64 * THIN_WAVES - 1) / (64 * THIN_WAVES) * (64 * THIN_WAVES);
-  if (a.dt == F16) thin_norm_dispatch<half_t>(s, p, thin_wide(a.N)); else thin_norm_dispatch<bf16_t>(s, p, thin_wide(a.N));
+  if (a.dt == F16) thin_norm_dispatch<half_t>(s, p, thin_wide(a.N));
+  else thin_norm_dispatch<bf16_t>(s, p, thin_wide(a.N));
 }
 
 void launch_gemm_thin(hipStream_t s, const GemmArgs& a) {

@@ -7,7 +7,6 @@
 namespace tfm {
 
 constexpr int LN_VEC = 8;
-constexpr float LN_EPS = 1e-5f;
 
 // s = x + drop(y); n = gamma * (s - mean) * rstd + beta.  NCH = chunks of 8 elements per lane (d <= NCH * 512).
 template <typename T, int NCH>

@@ -83,7 +83,8 @@ def test_parameter_list_matches_the_shared_shape_module(T):
 
 def assembly(source):
     from paper_1904_01038_amd import build
-    r = subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", "-"], capture_output=True, text=True)
+    r = subprocess.run(["hipcc", *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", "-"],
+                       capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     return r.stdout
 

@@ -423,7 +423,8 @@ def test_steps_do_not_depend_on_the_default_coherence_of_pinned_memory(tmp_path)
     import sys
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     out = str(tmp_path / "steps.npz")
-    code = "import sys, numpy as np; sys.path.insert(0, %r); from tests.test_gpu_decode import _thirty_steps; v, i = _thirty_steps(); np.savez(%r, v=v, i=i)" % (root, out)
+    code = ("import sys, numpy as np; sys.path.insert(0, %r); from tests.test_gpu_decode import _thirty_steps; "
+            "v, i = _thirty_steps(); np.savez(%r, v=v, i=i)" % (root, out))
     subprocess.run([sys.executable, "-c", code], check=True, timeout=100, env=dict(os.environ, HIP_HOST_COHERENT="0"))
     got, (v, i) = np.load(out), _thirty_steps()
     assert np.array_equal(got["v"], v) and np.array_equal(got["i"], i)
