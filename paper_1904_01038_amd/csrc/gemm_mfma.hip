@@ -360,22 +360,30 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaGemmParams& p, int tile
         }
       }
     asm volatile("" ::: "memory");                        // (LDS operations of one wavefront complete in order)
-    constexpr int LPR = SW / 8, RPP = 64 / LPR;           // lanes per row, rows per pass
-    const int c = (lane % LPR) * 8, n = n0 + wn * (BN / WN) + c;
-    if (n < p.N) {                                        // 8 columns entirely inside or outside N
+    constexpr int LPR = SW / 8, RPP = 64 / LPR, PASSES = TM * 32 / RPP;                  // lanes per row, rows and number of passes
+    const int cr = (lane % LPR) * 8, nr = n0 + wn * (BN / WN) + cr, mr = m0 + wm * (BM / WM) + lane / LPR;
+    // The masks are asked for all at once: between the stores, which may alias them, each pass would wait for its own.  (Here and
+    // not further up: beside the accumulators they would not fit.)
+    u32x4 keep[PASSES];
+    if (mask && nr < p.N) {
 #pragma unroll
-      for (int ps = 0; ps < TM * 32 / RPP; ++ps) {
-        const int r = ps * RPP + lane / LPR, m = m0 + wm * (BM / WM) + r;
-        u32x4 v = *reinterpret_cast<const u32x4*>(box + r * HP + c);
+      for (int ps = 0; ps < PASSES; ++ps)
+        keep[ps] = *reinterpret_cast<const u32x4*>(mask + (size_t)min(mr + ps * RPP, p.M - 1) * p.ldc + nr);
+    }
+    if (nr < p.N) {                                       // 8 columns entirely inside or outside N
+#pragma unroll
+      for (int ps = 0; ps < PASSES; ++ps) {
+        const int r = ps * RPP + lane / LPR, m = mr + ps * RPP;
+        u32x4 v = *reinterpret_cast<const u32x4*>(box + r * HP + cr);
         if (m >= p.M) continue;
-        const size_t o = (size_t)m * p.ldc + n;
         if (mask) {
-          float k[8];
-          load_f<T, 8>(mask + o, k);
+          Pack<T, 8> k;
+          __builtin_memcpy(&k, &keep[ps], 16);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] &= (k[2 * e] > 0.f ? 0x0000ffffu : 0u) | (k[2 * e + 1] > 0.f ? 0xffff0000u : 0u);
+          for (int e = 0; e < 4; ++e)
+            v[e] &= (to_f<T>(k.v[2 * e]) > 0.f ? 0x0000ffffu : 0u) | (to_f<T>(k.v[2 * e + 1]) > 0.f ? 0xffff0000u : 0u);
         }
-        *reinterpret_cast<u32x4*>(C + o) = v;
+        *reinterpret_cast<u32x4*>(C + (size_t)m * p.ldc + nr) = v;
       }
     }
     return;

@@ -115,3 +115,14 @@ def test_decoding_attention_fetches_the_rows_of_a_chunk_together():
         lines = [l.strip() for l in body.splitlines() if l.strip() and not l.strip().startswith((";", "."))]
         waits = sum(a.startswith("global_load_dword v") and b.startswith("s_waitcnt vmcnt(0)") for a, b in zip(lines, lines[1:]))
         assert waits <= 1, (name, waits)
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_masks_of_a_product_are_fetched_together():
+    """Input gradients behind a ReLU: a wavefront of the 192x256 tile reads back 12 pieces, whose masks are asked for ahead of the
+    first store (between the stores, which may alias them, each would be waited for: 39.8 us against 36.6)."""
+    kernels = re.findall(r"^(\S*gemm_mfma_kernel\S*Li192ELi256E\S*):(.*?)s_endpgm", assembly("gemm_mfma.hip"), flags=re.S | re.M)
+    assert len(kernels) >= 4
+    for name, body in kernels:
+        runs = [len(re.findall("global_load_dwordx4", part)) for part in body.split("global_store")]
+        assert max(runs) >= 12, (name, max(runs))
