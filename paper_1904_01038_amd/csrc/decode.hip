@@ -251,14 +251,15 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
       mn = fmaxf(mn, sc[u]);
     }
     mn = over_groups(mn, larger);
-    const float keep = __expf(m - mn);
+    const float top = mn > -INFINITY ? mn : 0.f;         // scores of -infinity alone, so far: weight 0, as beside others
+    const float keep = __expf(m - top);
     m = mn;
     l *= keep;                                           // (l: this group's share; the groups are added up at the end)
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] *= keep;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float w = __expf(sc[u] - mn);
+      const float w = __expf(sc[u] - top);
       l += w;
       Pack<T, 8> x;
       __builtin_memcpy(&x, &vv[u], 16);

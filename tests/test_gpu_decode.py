@@ -525,3 +525,37 @@ def test_layernorm_inside_the_product_of_a_few_rows(shape, rows, prec, tol):
             many.step(fed[t])
             assert np.max(np.abs(many.logprobs()[:rows] - lp)) <= (2 * 2.0 ** -8 if p == T.FP16 else 2 * 2.0 ** -5 if shape.vocab > 4096 else 0.0)
     ctx.close()
+
+
+@pytest.mark.parametrize("heads,rows", [(1, 3), (16, 144)])                  # chunks of 64 and (more than 2048 wavefronts) of 32 positions
+def test_positions_whose_score_is_minus_infinity_have_no_weight(heads, rows):
+    """One token's key overflows to infinity, against which every query gives -infinity.  64 such positions, whole chunks, come first;
+    the steps after them must attend to the others alone.  Tolerance: the fp16 one, and half a step each (2^-5) for a token's logit and
+    for the largest, which token 5 brings up to 64-128."""
+    import paper_1904_01038_amd as T
+    d = 64 * heads
+    shape = ModelShape(0, 1, d, heads, 64, 96)
+    params = init_params(shape, 5, generic=True)
+    params["embed"][5] *= 0.5
+    params["embed"][5, ::64] = 3.0                                             # token 5, and no other, is large in every 64th place
+    params["embed"][6:] *= 4.0
+    params["embed"][6:, ::64] = 0.0
+    first = np.arange(0, d, 64)                                                # the heads' first features
+    params["dec.0.self.wqkv"][first] = 0.0
+    params["dec.0.self.bqkv"][first] = -0.01                                   # queries: a constant
+    params["dec.0.self.wqkv"][d + first] = 0.0
+    params["dec.0.self.wqkv"][d + first, first] = 4000.0                       # keys: 92000 and more for token 5, at most 4000 else
+    params = rounded(params, T.FP16)
+    ctx = T.Tfm(T.make_config(shape, precision=T.FP16, max_sentences=rows, max_len=72, max_tokens=64))
+    ctx.set_params(params)
+    dec, oracle = T.Decoder(ctx, rows, 72, 1, 4), DecodingOracle(shape, params)
+    dec.begin(None, None, 1, rows)
+    fed = np.random.default_rng(0).integers(6, 96, (72, rows)).astype(np.int32)
+    fed[:64] = 5
+    for t in range(72):
+        dec.step(fed[t])
+        if t >= 64:
+            lp = dec.logprobs()
+            for r in (0, rows - 1):
+                assert np.max(np.abs(lp[r] - oracle.next_logprobs(None, list(fed[:t + 1, r])))) <= 3e-2 + 2 * 2.0 ** -5
+    ctx.close()
