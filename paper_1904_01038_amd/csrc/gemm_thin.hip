@@ -35,7 +35,8 @@ static __device__ __forceinline__ f32x4 mfma16(bf16_t, u32x4 a, u32x4 b, f32x4 c
 
 constexpr int THIN_WAVES = 8, THIN_UNIT = 64;            // wavefronts per block; K elements of a unit
 constexpr int THIN_NORM_SPLITS = 4;                      // LN: slices a row's y may come in
-constexpr int THIN_UNITS = 4;                            // units a wavefront holds, and beside a row that it makes (LN):
+constexpr int THIN_UNITS = 4, THIN_UNITS_4 = 3;          // units a wavefront holds, and with four tiles of rows (more never
+                                                         // pays there); beside a row that it makes (LN):
 constexpr int THIN_NORM_UNITS = 3, THIN_NORM_WIDE_UNITS = 2;                   // with one and with four column tiles
 
 struct ThinParams {
@@ -295,8 +296,7 @@ static ThinPlan thin_plan(const GemmArgs& a) {
 
 template <typename T>
 static void thin_dispatch(hipStream_t s, const ThinParams& p, const ThinPlan& q) {
-  constexpr int U = THIN_UNITS;
-#define THIN(RT, NT) thin_launch<T, RT, NT, false, U>(s, p, q.splits)
+#define THIN(RT, NT) thin_launch<T, RT, NT, false, RT == 4 ? THIN_UNITS_4 : THIN_UNITS>(s, p, q.splits)
   if (q.rt == 1) { if (q.nt == 4) THIN(1, 4); else THIN(1, 1); }
   else if (q.rt == 2) { if (q.nt == 4) THIN(2, 4); else THIN(2, 1); }
   else { if (q.nt == 2) THIN(4, 2); else THIN(4, 1); }
@@ -327,6 +327,7 @@ bool gemm_thin_supported(const GemmArgs& a) {
 // better of both (always this kernel: 16 %, never: 13 %) and is more than 5 % behind the tiled kernel in 15, by 0.8 us on average.
 bool gemm_thin_pays(const GemmArgs& a) {
   const ThinPlan q = thin_plan(a);
+  if (q.rt == 4 && q.kblock > THIN_UNITS_4 * THIN_WAVES * THIN_UNIT) return false;
   const double kib = 1024.0, tiles = (a.N + 63) / 64, rounds = std::ceil(q.blocks * q.splits / 256.0);
   const double reduced = q.splits > 1 && !q.defer ? 40 * kib : 0.0;
   const double here = rounds * std::min(q.kblock, a.K) * 2.0 * (16 * q.nt + 16 * q.rt) + reduced;

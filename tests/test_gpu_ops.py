@@ -114,6 +114,14 @@ def test_gemm_few_rows(prec, M, N, K):
         assert torch.all(out[M:] == -7.0) and torch.all(out[:, N:] == -7.0)
 
 
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("M,N,K", [(64, 4096, 1280), (33, 4096, 1288), (64, 8192, 1280), (40, 8200, 1280), (32, 4096, 2048), (17, 4096, 2560),
+                                   (32, 16384, 2040), (17, 16384, 2568), (16, 1536, 4096), (9, 6144, 1536), (16, 6144, 1544)])
+def test_gemm_few_rows_around_the_change_of_kernels(prec, M, N, K):
+    """The longest contractions that the few-row kernel takes for one, two and four tiles of rows, and the next ones."""
+    test_gemm_few_rows(prec, M, N, K)
+
+
 @pytest.mark.parametrize("rows", [24, 40, 64])
 @pytest.mark.parametrize("N,K", [(65536, 1024), (32768, 2048), (32768, 1536)])
 def test_few_rows_of_a_large_product_are_not_slower_than_more(rows, N, K):
