@@ -1,36 +1,40 @@
 // MFMA GEMM for gfx950: C[M,N] = epilogue(op(A) op(B)), fp16 or bf16 operands, fp32 accumulation in the matrix
 // cores (v_mfma_f32_32x32x16_{f16,bf16}).
 //
-// Measured on MI355X, what bounds these GEMMs is neither the matrix pipe nor LDS but the rate at which tiles can
-// be pulled from L2 into the CUs (about 8 TB/s in aggregate), so the design minimises bytes fetched per flop and
-// keeps the fetch path as cheap as possible:
+// What bounds them on MI355X: a long one the power that the chip may draw (with normally distributed operands an MFMA loop alone stops at 1.64
+// PFLOP/s and 1.65 GHz, one that also reads its fragments from LDS at 1.42; a K-step costs the same whether its tiles come from L2 or from
+// beyond), a short one the 4-7 us around the K loop.  So the design moves few bytes per flop, spreads what it moves evenly and keeps
+// the instructions that run once per launch few.
 //
-//  * Tiles: BM x BN output tile per block, K walked in steps of 32 or 64.  128x128 (4 wavefronts, 64x64 each) for
-//    outputs with few tiles, 256x256 (8 wavefronts, 128x64 each) for large outputs: a 256x256 tile fetches half as
-//    many bytes per flop as a 128x128 one.  A K-step of 64 fetches whole 128-byte lines per row.
+//  * Tiles: BM x BN output tile per block, K walked in steps of 32 or 64.  4 wavefronts up to 128x128 and for 192x128, 8 for larger ones, so
+//    that a wavefront has 64x64 or more (32x64 of the smallest): it reads (1/64 + 1/64) fragment bytes per flop where one of 32x32 reads twice that.  Which
+//    tiling: see choose_tiling.
 //  * Fetch: CDNA4 direct-to-LDS buffer loads (buffer_load_dwordx4 ... lds): no staging registers and no ds_write on
-//    the load path; range-checked, so ragged M, N, K read zeros without branches.  A 2- or 3-stage LDS ring keeps one
-//    or two K-steps in flight; one barrier per K-step.  The loads are issued as assembly and tracked with s_waitcnt vmcnt by
-//    hand, because the compiler would otherwise drain every outstanding direct-to-LDS load before each LDS read.
+//    the load path; range-checked, so ragged M and N read zeros without branches, and a ragged K is taken care of in the first K-step.  A
+//    ring of 3 or 4 stages keeps one or two K-steps in flight; one barrier per K-step.  A lane's offsets never change (the K-step is the
+//    scalar offset), and the loads are issued a few behind every MFMA: in one burst after the barrier they held up the wavefront
+//    that issued them (256x256: 2550 clocks per 64 of K, spread 2300, the MFMAs alone 2048).  They are issued as assembly and tracked
+//    with s_waitcnt vmcnt by hand, because the compiler would otherwise drain every outstanding direct-to-LDS load before each LDS read.
 //  * LDS layout: unpadded tiles (the direct-to-LDS path writes 1 KB per wavefront contiguously), XOR-swizzled on the
 //    global-address side so that fragment reads are bank-conflict free.  An operand whose contraction index is
 //    contiguous in memory (A of "NT"/"NN", B of "NT") is staged [row][k] and read with ds_read_b128; an operand
 //    whose contraction index is the slow one (B of "NN", both of "TN") is staged as it lies, [k][row], and read with
 //    the LDS transpose read ds_read_b64_tr_b16 (a 16-lane group reads a 4(k) x 16(row) patch, each lane receives
 //    the 4 k-values of one row).
-//  * Math: fragments of the next half K-step are read while the MFMAs of the current one execute (software pipeline
+//  * Math: fragments of a later sub-step of 16 k are read while the MFMAs of the current one execute (software pipeline
 //    across the barrier, pinned with scheduling fences).  Accumulators are produced transposed (B fragment first), so
-//    a lane holds 4 consecutive columns of one output row; the epilogue bounces 32-row strips through LDS so that the
+//    a lane holds 4 consecutive columns of one output row; the epilogue turns the tile around in LDS so that the
 //    bias / ReLU / ReLU-mask / residual reads and the stores are whole 128-byte lines.
 //  * Block ids are re-mapped so that each XCD (blocks are dealt round-robin to the 8 XCDs, each with its own L2) works
 //    on a contiguous run of tiles.
 //  * Weight gradients: a single projection's dY^T X has 16-256 output tiles, too few for 256 compute units.  The training
 //    step therefore queues them and launches the tiles of up to 48 products end to end as ONE grouped launch
 //    (gemm_mfma_grouped_kernel; problem table in the kernel arguments; the first tile column of each product also sums
-//    the rows of dY^T it already holds as fragments, which is the bias gradient).  A weight gradient launched on its
-//    own can instead split K across blockIdx.y; fp32 partial tiles are then added in a fixed order by a second kernel
-//    (no atomics, reproducible).
+//    the rows of dY^T it already holds as fragments, which is the bias gradient).
+//  * Outputs with few tiles and a long contraction (input gradients of few rows, scores of a tail cluster, a weight gradient launched on
+//    its own) split K across blockIdx.y; fp32 partial tiles are then added in a fixed order by a second kernel (no atomics, reproducible).
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -59,6 +63,15 @@ template <> struct Mfma<bf16_t> {
   }
 };
 
+// x / d by one multiplication for x < limit: with m = ceil(2^32 / d), x * m / 2^32 exceeds x / d by less than x / 2^32, which does
+// not reach the next whole number while x * d < 2^32.  (Beyond: m = 0, a division.)
+struct Divisor {
+  uint32_t d, m;
+  __host__ void set(uint32_t by, uint32_t limit) { d = by; m = by > 1 && (uint64_t)by * limit < 0x100000000ull ? (uint32_t)((0x100000000ull + by - 1) / by) : 0u; }
+  __device__ __forceinline__ uint32_t quotient(uint32_t x) const { return m ? __umulhi(x, m) : x / d; }
+};
+constexpr int GROUP_M = 8;
+
 struct MfmaGemmParams {
   int M, N, K;
   const uint16_t* A; int lda;
@@ -68,7 +81,8 @@ struct MfmaGemmParams {
   int relu;
   const uint16_t* mask;
   const uint16_t* residual;
-  int tiles_n, tiles_m, tiles_total, group_m;
+  int tiles_m, tiles_total;
+  Divisor per_band, last_band;                           // tiles of a full band; tile rows of the last one if it is not full
   int ksteps_per_split;                                  // split-K: K-steps per blockIdx.y slice
   float* partial;                                        // split-K: fp32 partial tiles [split][M][N], else null
   uint32_t a_bytes, b_bytes;                             // extents for the range-checked loads
@@ -103,72 +117,114 @@ template <> struct FragSum<bf16_t> {
   }
 };
 
-// One operand's path from global memory through the LDS ring into MFMA fragments.
+template <int I, int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) { f(std::integral_constant<int, I>{}); static_for<I + 1, N>(f); }
+}
+
+// One operand's path from global memory into the LDS ring.
 //   ROWS: tile rows (M or N extent of the block tile);  NW: wavefronts in the block;  TR: see the file comment.
-// A direct-to-LDS load writes the wavefront's 64 x 16 bytes contiguously, so load g of a stage fills bytes
+// A direct-to-LDS load writes the wavefront's 64 x 16 bytes contiguously, so piece g of a stage fills bytes
 // [g*1024, (g+1)*1024) of the tile; each lane chooses WHICH global vector it fetches so that the tile ends up swizzled:
 //   [row][k] tile, 2*BK-byte rows:   16-byte slot s of row r holds k-vector    s ^ swz(r)
-//   [k][row] tile, ROWS*2-byte rows: 16-byte slot s of k-row k holds row-vector s ^ ((k & 3) << 2)
+//   [k][row] tile, ROWS*2-byte rows: 16-byte slot s of k-row k holds row-vector s ^ tswz(k)
+// Every wavefront issues LOADS loads a stage, so that one vmcnt serves all of them; where the pieces do not divide by the wavefronts
+// (192 rows on 8 of them), the last load of some fetches nothing and lands beside the ring.
 template <int ROWS, int BK, int NW, bool TR>
 struct Operand {
   static constexpr int TILE_BYTES = ROWS * BK * 2;
-  static constexpr int LOADS = TILE_BYTES / 1024 / NW;   // direct-to-LDS loads per wavefront per stage
-  static_assert(LOADS >= 1 && LOADS * 1024 * NW == TILE_BYTES, "every wavefront loads a whole number of 1 KB pieces of the tile");
+  static constexpr int PIECES = TILE_BYTES / 1024;
+  static constexpr int LOADS = (PIECES + NW - 1) / NW;
+  static constexpr bool EVEN = PIECES % NW == 0;
+  static_assert(PIECES * 1024 == TILE_BYTES, "whole 1 KB pieces");
   static constexpr int ROW_BYTES = ROWS * 2;             // [k][row] layout only
   static constexpr int KROW_BYTES = BK * 2;              // [row][k] layout only: 64 or 128
   static constexpr int VPR = BK / 8;                     // 16-byte vectors per [row][k] row: 4 or 8
   // swizzle of the [row][k] layout: slot ^= f(row) with f chosen so that 16 consecutive rows cover 16 distinct
   // 16-byte bank groups: 64-byte rows: (row >> 2) & 3;  128-byte rows: (row >> 1) & 7
   static __device__ __forceinline__ int swz(int row) { return BK == 32 ? ((row >> 2) & 3) : ((row >> 1) & 7); }
+  // of the [k][row] layout: the 4 k-rows of a transposing read lie in distinct 32-byte bank groups; rows of 256 bytes and more
+  // start at the same bank, rows of 128 bytes at two
+  static __device__ __forceinline__ int tswz(int k) { return ROWS == 64 ? (k & 3) << 1 : (k & 3) << 2; }
+  static_assert(NW % 2 == 0 || NW == 1, "the swizzle repeats after one or two pieces, so that a lane's loads differ by a constant only");
+  static constexpr int KPP = TR ? 1024 / ROW_BYTES : 0, RPPC = TR ? 0 : 64 / VPR;          // k-rows or rows of a piece
   uint32_t off[LOADS];                                   // byte offset of this lane's vector in K-step 0
-  int kfirst[LOADS];                                     // its k index inside the K-step (for the K-tail test)
+  int kfirst;                                            // load 0's k index inside the K-step (for a ragged last K-step)
   uint32_t step;                                         // byte stride between K-steps
-  int kend;
 
-  __device__ __forceinline__ void init(int ld, int row0, int kend_, int wave, int lane) {
-    kend = kend_;
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-      const int g = wave * LOADS + i;
-      if (!TR) {
-        const int row = g * (64 / VPR) + lane / VPR;
-        kfirst[i] = ((lane % VPR) ^ swz(row)) * 8;
-        off[i] = ((uint32_t)(row0 + row) * (uint32_t)ld + (uint32_t)kfirst[i]) * 2u;
-      } else {
-        const int byte = g * 1024 + lane * 16;
-        const int k = byte / ROW_BYTES, slot = (byte % ROW_BYTES) / 16;
-        const int vec = slot ^ ((k & 3) << 2);
-        kfirst[i] = k;
-        off[i] = ((uint32_t)k * (uint32_t)ld + (uint32_t)(row0 + vec * 8)) * 2u;
-      }
+  // Bounds: the hardware compares these offsets, without the scalar one, with the operand's extent.  Rows beyond the matrix lie beyond
+  // it; columns beyond the width of a [k][row] operand would not, so they get an offset that does; k beyond the end, see issue_ragged.
+  __device__ __forceinline__ void init(int ld, int row0, int width, int wave, int lane) {
+    if (!TR) {
+      const int row = wave * RPPC + lane / VPR;
+      kfirst = ((lane % VPR) ^ swz(row)) * 8;
+      off[0] = ((uint32_t)(row0 + row) * (uint32_t)ld + (uint32_t)kfirst) * 2u;
+    } else {
+      const int slot = lane % (ROW_BYTES / 16);
+      kfirst = wave * KPP + lane / (ROW_BYTES / 16);
+      const int col = row0 + (slot ^ tswz(kfirst)) * 8;
+      off[0] = col < width ? ((uint32_t)kfirst * (uint32_t)ld + (uint32_t)col) * 2u : OOB;
     }
+    const uint32_t by = (uint32_t)(NW * (TR ? KPP : RPPC)) * (uint32_t)ld * 2u;
+#pragma unroll
+    for (int i = 1; i < LOADS; ++i) off[i] = off[i - 1] + by;                              // (OOB + less than 2^31 stays out of range)
+    if (!EVEN && (LOADS - 1) * NW + wave >= PIECES) off[LOADS - 1] = OOB;
     step = TR ? (uint32_t)BK * (uint32_t)ld * 2u : (uint32_t)BK * 2u;
   }
-  // Issued as assembly on purpose (see the file comment).  lds_stage: LDS byte address of the stage's tile.
-  __device__ __forceinline__ void issue(const u32x4& rsrc, int kt, uint32_t lds_stage, int wave) const {
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-      const uint32_t o = (kt * BK + kfirst[i] < kend) ? off[i] + (uint32_t)kt * step : OOB;
-      const uint32_t dst = lds_stage + (uint32_t)(wave * LOADS + i) * 1024u;
-      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(__builtin_amdgcn_readfirstlane(dst)), "v"(o),
-                   "s"(rsrc)
-                   : "memory", "m0");
-    }
+  // Load i of a stage: `soff` = byte offset of the K-step, `dst` = LDS address of the stage's tile plus wave * 1024, `dump` = 1 KB of
+  // LDS for a load without a piece.  Issued as assembly on purpose (see the file comment); the instruction between the write of m0
+  // and the load that reads it is a required wait state.
+  template <int i> __device__ __forceinline__ void issue(const u32x4& rsrc, uint32_t soff, uint32_t dst, uint32_t dump, int wave, uint32_t o) const {
+    uint32_t to = dst + i * NW * 1024;
+    if (!EVEN && i == LOADS - 1) to = i * NW + wave < PIECES ? to : dump;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(__builtin_amdgcn_readfirstlane(to)), "v"(o),
+                 "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff))
+                 : "memory", "m0");
   }
-  // Fragment of tile rows r0..r0+31 for k = kk*16 .. kk*16+15: lane l gets row r0 + l%32, k-group l/32 (8 k-values).
-  static __device__ __forceinline__ u32x4 frag(const unsigned char* S, int r0, int kk, int lane) {
-    if (!TR) {
+  template <int i> __device__ __forceinline__ void issue(const u32x4& rsrc, uint32_t soff, uint32_t dst, uint32_t dump, int wave) const {
+    issue<i>(rsrc, soff, dst, dump, wave, off[i]);
+  }
+  // the same for K-step kt, of which only the k below kend are read
+  template <int i> __device__ __forceinline__ void issue_ragged(const u32x4& rsrc, int kt, int kend, uint32_t dst, uint32_t dump, int wave) const {
+    const bool in = kt * BK + kfirst + i * NW * KPP < kend && off[i] < OOB;
+    issue<i>(rsrc, 0u, dst, dump, wave, in ? off[i] + (uint32_t)kt * step : OOB);
+  }
+};
+
+// The fragments a wavefront reads of one operand: TILES row tiles of 32, KKW sub-steps of 16 k.  The addresses follow the ring (one
+// addition each per K-step); the row tile or the sub-step, whichever the swizzle does not depend on, is an immediate offset.
+template <int ROWS, int BK, bool TR, int TILES, int KKW>
+struct Frags {
+  static constexpr int NA = TR ? TILES : KKW;
+  typedef Operand<ROWS, BK, 1, TR> O;
+  uint32_t at[NA];
+  // rows r0 .. r0 + 32 * TILES - 1 of the tile at LDS address `base`
+  __device__ __forceinline__ void init(uint32_t base, int r0, int lane) {
+    if constexpr (!TR) {
       const int row = r0 + (lane & 31);
-      const int slot = (kk * 2 + (lane >> 5)) ^ swz(row);
-      return *reinterpret_cast<const u32x4*>(S + row * KROW_BYTES + slot * 16);
+#pragma unroll
+      for (int k = 0; k < KKW; ++k) at[k] = base + row * O::KROW_BYTES + ((k * 2 + (lane >> 5)) ^ O::swz(row)) * 16;
     } else {
       const int s = lane & 15, ibase = lane & 16;
-      const int k = kk * 16 + (lane >> 5) * 8 + (s >> 2);
-      const int seg = ((r0 + ibase) >> 4) ^ ((s >> 2) << 1);           // 32-byte segment, swizzled by k & 3
-      const unsigned char* p = S + k * ROW_BYTES + seg * 32 + (s & 3) * 8;
+      const int k = (lane >> 5) * 8 + (s >> 2);
+#pragma unroll
+      for (int i = 0; i < TILES; ++i)                    // (32-byte segments)
+        at[i] = base + k * O::ROW_BYTES + (((r0 + i * 32 + ibase) >> 4) ^ (O::tswz(k) >> 1)) * 32 + (s & 3) * 8;
+    }
+  }
+  __device__ __forceinline__ void move(uint32_t by) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) at[i] += by;
+  }
+  // Row tile i, sub-step kk: lane l gets row 32 i + l % 32, k-group l / 32 (8 k-values).
+  __device__ __forceinline__ u32x4 get(int i, int kk) const {
+    if constexpr (!TR) {
+      typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+      return *(lds_u32x4*)(uintptr_t)(at[kk] + i * 32 * O::KROW_BYTES);
+    } else {
       typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * ROW_BYTES));
+      const uint32_t p = at[i] + kk * 16 * O::ROW_BYTES;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)p);
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(p + 4 * O::ROW_BYTES));
       const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
       return u32x4{l2[0], l2[1], h2[0], h2[1]};
     }
@@ -176,20 +232,25 @@ struct Operand {
 };
 
 // One output tile (or one K-slice of it).  `tile` is the tile id inside this problem after the XCD re-mapping, `slice`
-// the split-K slice.  CS: the block column tn == 0 also sums A's rows over K (see MfmaGemmParams::colsum).
-template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES, bool ATR, bool BTR, bool CS>
+// the split-K slice.  AHEAD: sub-steps between a fragment's read and its use.  CS: the block column tn == 0 also sums A's rows
+// over K (see MfmaGemmParams::colsum).
+template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES, int AHEAD, bool ATR, bool BTR, bool CS>
 __device__ __forceinline__ void gemm_mfma_tile(const MfmaGemmParams& p, int tile, int slice) {
   constexpr int NW = WM * WN;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;    // MFMA tiles per wavefront
-  constexpr int KK = BK / 16;                            // MFMA sub-steps per K-step (2 or 4)
+  constexpr int KK = BK / 16;                            // MFMA sub-steps per K-step
   constexpr int D = STAGES - 1;                          // K-steps in flight ahead of the one being consumed
+  constexpr int SETS = AHEAD == 1 ? 2 : KK;              // register sets of fragments
+  static_assert(KK % SETS == 0 && AHEAD < SETS, "a sub-step uses the same registers in every K-step, and never those that are being filled");
+  static_assert(STAGES >= 3, "the loads of a K-step are spread over the one before the last that needs the slot");
   typedef Operand<BM, BK, NW, ATR> OA;
   typedef Operand<BN, BK, NW, BTR> OB;
-  // One LDS block: the A ring, the B ring, and (re-using both once the K loop is over) the epilogue's staging area, which can
-  // be a little larger than the rings.
+  // One LDS block: the ring (a slot holds a stage of A and of B), and (re-using it once the K loop is over) the epilogue's
+  // staging area.
   constexpr int SW = TN * 32;                             // epilogue strip width in columns
   constexpr int SP = SW + 4;                              // its padded pitch in floats: conflict-free for both passes
-  constexpr int RING_BYTES = STAGES * (OA::TILE_BYTES + OB::TILE_BYTES);
+  constexpr uint32_t SLOT = OA::TILE_BYTES + OB::TILE_BYTES;
+  constexpr int RING_BYTES = STAGES * SLOT + (OA::EVEN && OB::EVEN ? 0 : 1024);
   constexpr int STRIP_BYTES = NW * 32 * SP * 4;
   constexpr int HP = SW + 8;                              // pitch in elements of the tile turned around in the output type
   constexpr int BOX_BYTES = NW * TM * 32 * HP * 2;
@@ -197,35 +258,42 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaGemmParams& p, int tile
   constexpr int LDS_BYTES = RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES;
   static_assert(LDS_BYTES <= 160 * 1024, "LDS per CU");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS_BYTES];
-  unsigned char(*As)[OA::TILE_BYTES] = reinterpret_cast<unsigned char(*)[OA::TILE_BYTES]>(smem);
-  unsigned char(*Bs)[OB::TILE_BYTES] = reinterpret_cast<unsigned char(*)[OB::TILE_BYTES]>(smem + STAGES * OA::TILE_BYTES);
-  // Tile ids run column-major inside bands of group_m tile rows, so the run of ids an XCD works on at one time
+  // Tile ids run column-major inside bands of GROUP_M tile rows, so the run of ids an XCD works on at one time
   // covers a compact patch of the output and shares its A and B panels in that XCD's L2.
-  int tm, tn;
-  {
-    const int per_band = p.group_m * p.tiles_n, band = tile / per_band, in_band = tile - band * per_band;
-    const int gm = min(p.group_m, p.tiles_m - band * p.group_m);
-    tm = band * p.group_m + in_band % gm;
-    tn = in_band / gm;
-  }
+  const uint32_t band = p.per_band.quotient(tile), in_band = tile - band * p.per_band.d;
+  const bool full = (band + 1) * GROUP_M <= (uint32_t)p.tiles_m;
+  const int tn = full ? in_band / GROUP_M : p.last_band.quotient(in_band);
+  const int tm = band * GROUP_M + (full ? in_band % GROUP_M : in_band - tn * p.last_band.d);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave / WN, wn = wave % WN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
 
   // raw buffer descriptors: base, stride 0, byte extent, format word
-  const u32x4 ra = {(uint32_t)(uintptr_t)p.A, (uint32_t)((uintptr_t)p.A >> 32) & 0xffffu, p.a_bytes, 0x00020000u};
-  const u32x4 rb = {(uint32_t)(uintptr_t)p.B, (uint32_t)((uintptr_t)p.B >> 32) & 0xffffu, p.b_bytes, 0x00020000u};
-  // split-K: this block covers K-steps kt0 .. ; everything at or beyond kend reads as zero
+  u32x4 ra = {(uint32_t)(uintptr_t)p.A, (uint32_t)((uintptr_t)p.A >> 32) & 0xffffu, p.a_bytes, 0x00020000u};
+  u32x4 rb = {(uint32_t)(uintptr_t)p.B, (uint32_t)((uintptr_t)p.B >> 32) & 0xffffu, p.b_bytes, 0x00020000u};
+  // split-K: this block covers K-steps kt0 .. kt0 + nk - 1 (nk may be 0).  A ragged last K-step is taken first: only the first one's loads test k.
   const int kt0 = slice * p.ksteps_per_split;
-  const int kend = min(p.K, (kt0 + p.ksteps_per_split) * BK);
-  const int nk = max(0, (kend - kt0 * BK + BK - 1) / BK);
+  const int nk = max(0, min(p.ksteps_per_split, (p.K + BK - 1) / BK - kt0));
+  const bool ragged = nk > 0 && (kt0 + nk) * BK > p.K;
   OA oa;
   OB ob;
-  oa.init(p.lda, m0, kend, wave, lane);
-  ob.init(p.ldb, n0, kend, wave, lane);
-  const uint32_t lds_a = (uint32_t)(uintptr_t)(lds_ptr)(&As[0][0]), lds_b = (uint32_t)(uintptr_t)(lds_ptr)(&Bs[0][0]);
-  auto issue = [&](int kt, int stage) {
-    oa.issue(ra, kt0 + kt, lds_a + stage * OA::TILE_BYTES, wave);
-    ob.issue(rb, kt0 + kt, lds_b + stage * OB::TILE_BYTES, wave);
+  oa.init(p.lda, m0, p.M, wave, lane);
+  ob.init(p.ldb, n0, p.N, wave, lane);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)(&smem[0]), dump = lds0 + STAGES * SLOT;
+  const uint32_t lds_a = lds0 + wave * 1024, lds_b = lds0 + OA::TILE_BYTES + wave * 1024;
+  constexpr int LT = OA::LOADS + OB::LOADS;
+  uint32_t sa = (uint32_t)kt0 * oa.step, sb = (uint32_t)kt0 * ob.step;                     // byte offsets of the K-step that is fetched next
+  int fetched = 0;                                        // K-steps asked for
+  auto issue = [&](auto l, uint32_t slot) __attribute__((always_inline)) {
+    constexpr int L = decltype(l)::value;
+    if constexpr (L < OA::LOADS) oa.template issue<L>(ra, sa, lds_a + slot, dump, wave);
+    else ob.template issue<L - OA::LOADS>(rb, sb, lds_b + slot, dump, wave);
+  };
+  // K-steps beyond the last fetch nothing: no bytes in range, and no scalar offset either
+  auto next_step = [&]() __attribute__((always_inline)) {
+    sa += oa.step;
+    sb += ob.step;
+    if (++fetched >= nk) { sa = sb = 0u; ra[2] = rb[2] = 0u; }
   };
 
   f32x16 acc[TM][TN];
@@ -236,75 +304,94 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaGemmParams& p, int tile
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  auto read_frags = [&](int stage, int kk, u32x4 (&fa)[TM], u32x4 (&fb)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) fa[i] = OA::frag(As[stage], wm * (BM / WM) + i * 32, kk, lane);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) fb[j] = OB::frag(Bs[stage], wn * (BN / WN) + j * 32, kk, lane);
+  u32x4 fa[SETS][TM], fb[SETS][TN];
+  Frags<BM, BK, ATR, TM, KK> ga;
+  Frags<BN, BK, BTR, TN, KK> gb;
+  ga.init(lds0, wm * (BM / WM), lane);
+  gb.init(lds0 + OA::TILE_BYTES, wn * (BN / WN), lane);
+  // fragment r of a sub-step, in the order in which its MFMAs need them
+  auto read = [&](int set, int kk, int r) __attribute__((always_inline)) {
+    if (r == 0) fa[set][0] = ga.get(0, kk);
+    else if (r <= TN) fb[set][r - 1] = gb.get(r - 1, kk);
+    else fa[set][r - TN] = ga.get(r - TN, kk);
   };
+  constexpr int R = TM + TN, NM = TM * TN;
   // Row sums of A: the wavefronts of the first tile column that hold the first column strip see every A fragment of
   // their rows exactly once (K-steps beyond the slice read zeros), so they add them up on the vector ALU beside the MFMAs.
   const bool do_cs = CS && p.colsum != nullptr && tn == 0 && wn == 0;
   float cs[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) cs[i] = 0.f;
-  auto mfmas = [&](const u32x4 (&fa)[TM], const u32x4 (&fb)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::run(fb[j], fa[i], acc[i][j]);   // transposed product: D'[n][m]
-    if (CS && do_cs) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) cs[i] = FragSum<T>::run(fa[i], cs[i]);
-    }
-  };
 
-  constexpr int WAIT = (OA::LOADS + OB::LOADS) * (D - 1);   // loads that may still be in flight when a K-step must have landed
+  constexpr int WAIT = LT * (D - 1);                      // loads that may still be in flight when a K-step must have landed
   static_assert(WAIT <= 63, "vmcnt is a 6-bit count");
-  // s_waitcnt immediate: vmcnt[3:0] in bits 3:0 and vmcnt[5:4] in bits 15:14; expcnt (6:4) and lgkmcnt (11:8) left at
-  // their maxima, i.e. not waited for
-  constexpr int WAITCNT = 0x0F70 | (WAIT & 15) | ((WAIT >> 4) << 14);
-#pragma unroll
-  for (int t = 0; t < D; ++t) issue(t, t);
-  u32x4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-  __builtin_amdgcn_s_waitcnt(WAITCNT);                   // K-step 0 has landed
-  __syncthreads();
-  issue(D, D % STAGES);
-  read_frags(0, 0, fa0, fb0);
-  read_frags(0, 1, fa1, fb1);
-  // Software pipeline: sub-step j runs its MFMAs from register set j%2 while set j%2 is refilled with sub-step j+2
-  // (of the same stage, or after the barrier of the next one).  LDS latency is therefore always covered by matrix work.
-  // The trip count is rounded up to the ring size: K-steps beyond the slice read zeros, so the extra MFMAs add nothing.
-  const int nkr = (nk + STAGES - 1) / STAGES * STAGES;
-  for (int base = 0; base < nkr; base += STAGES) {
-#pragma unroll
-    for (int u = 0; u < STAGES; ++u) {
-      const int kt = base + u;
-#pragma unroll
-      for (int j = 0; j < KK; ++j) {
-        // (the scheduling fences keep the compiler from sinking the LDS reads back next to the MFMAs that use them)
-        if (j % 2 == 0) mfmas(fa0, fb0); else mfmas(fa1, fb1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (j + 2 < KK) {
-          if (j % 2 == 0) read_frags(u, j + 2, fa0, fb0); else read_frags(u, j + 2, fa1, fb1);
-        } else if (j == KK - 2) {
-          __builtin_amdgcn_s_waitcnt(WAITCNT);           // K-step kt+1 has landed for this wavefront ...
-          __syncthreads();                               // ... and for all of them; stage u is no longer read
-          read_frags((u + 1) % STAGES, 0, fa0, fb0);
-          issue(kt + 1 + D, u);
-        } else {
-          read_frags((u + 1) % STAGES, 1, fa1, fb1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+  // s_waitcnt immediate: vmcnt[3:0] in bits 3:0 and vmcnt[5:4] in bits 15:14, expcnt (6:4) at its maximum, lgkmcnt (11:8) 0: this
+  // wavefront's reads of the slot that is given up have returned as well
+  constexpr int WAITCNT = 0x0070 | (WAIT & 15) | ((WAIT >> 4) << 14);
+  if (ragged || nk == 0) {
+    const int kt = kt0 + nk - 1, kend = nk > 0 ? p.K : 0;
+    static_for<0, OA::LOADS>([&](auto l) { oa.template issue_ragged<decltype(l)::value>(ra, kt, kend, lds_a, dump, wave); });
+    static_for<0, OB::LOADS>([&](auto l) { ob.template issue_ragged<decltype(l)::value>(rb, kt, kend, lds_b, dump, wave); });
+    sa -= oa.step;
+    sb -= ob.step;
+  } else {
+    static_for<0, LT>([&](auto l) { issue(l, 0u); });
   }
-  __builtin_amdgcn_s_waitcnt(0x0F70);                    // drain the trailing (zero-fill) loads before LDS is released
-
+  next_step();
+  static_for<1, D>([&](auto t) {
+    static_for<0, LT>([&](auto l) { issue(l, decltype(t)::value * SLOT); });
+    next_step();
+  });
+  __builtin_amdgcn_s_waitcnt(WAITCNT);                    // K-step 0 has landed
+  asm volatile("s_barrier" ::: "memory");
+  static_for<0, AHEAD>([&](auto j) { static_for<0, R>([&](auto r) { read(decltype(j)::value, decltype(j)::value, decltype(r)::value); }); });
+  // Software pipeline: while the MFMAs of one sub-step run, the fragments of the sub-step AHEAD of it are read from LDS and a few
+  // of the loads of K-step kt + D are issued, one behind every MFMA (the scheduling fences keep that order), so that neither LDS
+  // nor the loads' path sees a burst.  In sub-step KK - AHEAD the next K-step must have landed: wait, barrier, and the slot of this
+  // one is free; its successor D K-steps on is asked for during the next K-step.
+  uint32_t slot = 0, freed = (STAGES - 1) * SLOT;
+  for (int kt = 0; kt < nk; ++kt) {
+    const uint32_t next = slot == (STAGES - 1) * SLOT ? 0u : slot + SLOT, by = next - slot;
+    static_for<0, KK>([&](auto jc) {
+      constexpr int j = decltype(jc)::value, to = j + AHEAD, set = j % SETS;
+      constexpr int Q = NM / 2;                           // the barrier stands before this MFMA of its sub-step
+      static_for<0, NM>([&](auto qc) {
+        constexpr int q = decltype(qc)::value, i = q / TN, jj = q % TN;
+        if constexpr (to == KK && q == Q) {
+          ga.move(by);
+          gb.move(by);
+          __builtin_amdgcn_s_waitcnt(WAITCNT);
+          asm volatile("s_barrier" ::: "memory");
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        acc[i][jj] = Mfma<T>::run(fb[set][jj], fa[set][i], acc[i][jj]);                   // transposed product: D'[n][m]
+        if constexpr (to != KK) {
+          static_for<q * R / NM, (q + 1) * R / NM>([&](auto r) { read(to % SETS, to % KK, decltype(r)::value); });
+        } else if constexpr (q >= Q) {
+          static_for<(q - Q) * R / (NM - Q), (q - Q + 1) * R / (NM - Q)>([&](auto r) { read(to % SETS, 0, decltype(r)::value); });
+        }
+        constexpr int g = j * NM + q, G = (KK - AHEAD) * NM + Q;                           // G MFMAs stand before the barrier
+        if constexpr (g < G) static_for<g * LT / G, (g + 1) * LT / G>([&](auto l) { issue(l, freed); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if (CS && do_cs) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) cs[i] = FragSum<T>::run(fa[set][i], cs[i]);
+      }
+    });
+    freed = slot;
+    slot = next;
+    next_step();
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);                    // drain the trailing (empty) loads before the ring is re-used
+  __syncthreads();
   // Epilogue.  The accumulators hold, per lane, 4 consecutive columns of one row, which would make every store an
   // 8-byte fragment of a different cache line.  Each wavefront therefore turns its tile around in its own slice of LDS (free
   // now: every wavefront is past its last fragment read), so that 8 lanes store one whole 128-byte line of the output.
-  __syncthreads();
+  // The steps that few products have (dropout, a factor behind the mask) are compiled apart: the instructions of an epilogue are
+  // fetched as it runs, once per launch and compute unit, and jumping over unrolled steps took 3 us of a launch (128x128 of
+  // X W^T, K = 1024: 13.7 us against 10.7 us; 256x256 34.1 against 30.8).
+  const int mw = m0 + wm * (BM / WM) ;   // first row of this wavefront's tile
   const T* bias = reinterpret_cast<const T*>(p.bias);
   const T* mask = reinterpret_cast<const T*>(p.mask);
   const T* res = reinterpret_cast<const T*>(p.residual);
@@ -318,141 +405,154 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaGemmParams& p, int tile
       if (lane < 32 && m < p.M) reinterpret_cast<T*>(p.colsum)[m] = from_f<T>(t);
     }
   }
+  constexpr int LPR = SW / 8, RPP = 64 / LPR;             // lanes per row and rows per pass when re-reading: 8 columns a lane
+  const int cr = (lane % LPR) * 8, nr = n0 + wn * (BN / WN) + cr, mr = mw + lane / LPR;    // (8 columns entirely inside or outside N)
   if (!res && !P) {
     // Bias, ReLU, dropout and the mask's factor are applied to the accumulators and the finished values go through LDS in the
     // output type, the whole tile before the first of it is read back.  (Against fp32 strips with the epilogue's steps on the far
-    // side, averages inside a step: 192x256 tiles of X W^T 37.9 -> 35.5 us, 128x128 of a 1536-wide dY W 159 -> 145; 128x128 of X W^T
-    // on 16 wavefronts 22.9 -> 23.3.)
+    // side, averages inside a step: 192x256 tiles of X W^T 37.9 -> 35.5 us, 128x128 of a 1536-wide dY W 159 -> 145.)
     T* box = reinterpret_cast<T*>(smem) + wave * (TM * 32 * HP);
     const int nw = n0 + wn * (BN / WN) + (lane >> 5) * 4;
-    Pack<T, 4> braw[TN][4];
-    if (bias) {                                           // all of a lane's pieces in one trip to memory
+    auto fill = [&](auto relu, auto general) __attribute__((always_inline)) {
+      Pack<T, 4> braw[TN][4];
+      if (bias) {                                         // all of a lane's pieces in one trip to memory
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int rg = 0; rg < 4; ++rg) braw[j][rg] = *reinterpret_cast<const Pack<T, 4>*>(bias + min(nw + j * 32 + rg * 8, p.N - 4));
+      } else {
+        __builtin_memset(braw, 0, sizeof(braw));
+      }
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) braw[j][rg] = *reinterpret_cast<const Pack<T, 4>*>(bias + min(nw + j * 32 + rg * 8, p.N - 4));
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int c = j * 32 + rg * 8 + (lane >> 5) * 4, n = nw + j * 32 + rg * 8;
-        float bb[4] = {0.f, 0.f, 0.f, 0.f};
-        if (bias) {
+        for (int rg = 0; rg < 4; ++rg) {
+          const int c = j * 32 + rg * 8 + (lane >> 5) * 4, n = nw + j * 32 + rg * 8;
+          float bb[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) bb[e] = to_f<T>(braw[j][rg].v[e]);
-        }
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int r = i * 32 + (lane & 31);
-          float v[4];
+          for (int i = 0; i < TM; ++i) {
+            const int r = i * 32 + (lane & 31);
+            float v[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[i][j][rg * 4 + e] + bb[e];
-          if (p.relu) {
+            for (int e = 0; e < 4; ++e) v[e] = acc[i][j][rg * 4 + e] + bb[e];
+            if (decltype(relu)::value || (decltype(general)::value && p.relu)) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+              for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+            }
+            if constexpr (decltype(general)::value) {
+              if (p.drop_thr) drop_apply<4>(v, p.drop_key, (uint64_t)(mw + r) * p.N + n, p.drop_thr, p.inv_keep);
+              if (mask) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] *= p.mask_scale;
+              }
+            }
+            store_f<T, 4>(box + r * HP + c, v);
           }
-          if (p.drop_thr) drop_apply<4>(v, p.drop_key, (uint64_t)(m0 + wm * (BM / WM) + r) * p.N + n, p.drop_thr, p.inv_keep);
-          if (mask) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= p.mask_scale;
-          }
-          store_f<T, 4>(box + r * HP + c, v);
         }
-      }
+    };
+    if (p.drop_thr || (mask && p.mask_scale != 1.f)) fill(std::false_type{}, std::true_type{});
+    else if (p.relu) fill(std::true_type{}, std::false_type{});
+    else fill(std::false_type{}, std::false_type{});
     asm volatile("" ::: "memory");                        // (LDS operations of one wavefront complete in order)
-    constexpr int LPR = SW / 8, RPP = 64 / LPR, PASSES = TM * 32 / RPP;                  // lanes per row, rows and number of passes
-    const int cr = (lane % LPR) * 8, nr = n0 + wn * (BN / WN) + cr, mr = m0 + wm * (BM / WM) + lane / LPR;
-    // The masks are asked for all at once: between the stores, which may alias them, each pass would wait for its own.  (Here and
-    // not further up: beside the accumulators they would not fit.)
-    u32x4 keep[PASSES];
-    if (mask && nr < p.N) {
+    constexpr int PASSES = TM * 32 / RPP;
+    if (nr >= p.N) return;
+    if (mask) {
+      // The masks are asked for all at once: between the stores, which may alias them, each pass would wait for its own.  (Here and
+      // not further up: beside the accumulators they would not fit.)
+      u32x4 keep[PASSES];
 #pragma unroll
       for (int ps = 0; ps < PASSES; ++ps)
         keep[ps] = *reinterpret_cast<const u32x4*>(mask + (size_t)min(mr + ps * RPP, p.M - 1) * p.ldc + nr);
-    }
-    if (nr < p.N) {                                       // 8 columns entirely inside or outside N
+      asm volatile("" ::: "memory");
 #pragma unroll
       for (int ps = 0; ps < PASSES; ++ps) {
-        const int r = ps * RPP + lane / LPR, m = mr + ps * RPP;
-        u32x4 v = *reinterpret_cast<const u32x4*>(box + r * HP + cr);
-        if (m >= p.M) continue;
-        if (mask) {
-          Pack<T, 8> k;
-          __builtin_memcpy(&k, &keep[ps], 16);
+        u32x4 v = *reinterpret_cast<const u32x4*>(box + (ps * RPP + lane / LPR) * HP + cr);
+        if (mr + ps * RPP >= p.M) continue;
+        Pack<T, 8> k;
+        __builtin_memcpy(&k, &keep[ps], 16);
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            v[e] &= (to_f<T>(k.v[2 * e]) > 0.f ? 0x0000ffffu : 0u) | (to_f<T>(k.v[2 * e + 1]) > 0.f ? 0xffff0000u : 0u);
-        }
-        *reinterpret_cast<u32x4*>(C + (size_t)m * p.ldc + nr) = v;
+        for (int e = 0; e < 4; ++e)
+          v[e] &= (to_f<T>(k.v[2 * e]) > 0.f ? 0x0000ffffu : 0u) | (to_f<T>(k.v[2 * e + 1]) > 0.f ? 0xffff0000u : 0u);
+        *reinterpret_cast<u32x4*>(C + (size_t)(mr + ps * RPP) * p.ldc + nr) = v;
+      }
+    } else {
+#pragma unroll
+      for (int ps = 0; ps < PASSES; ++ps) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(box + (ps * RPP + lane / LPR) * HP + cr);
+        if (mr + ps * RPP < p.M) *reinterpret_cast<u32x4*>(C + (size_t)(mr + ps * RPP) * p.ldc + nr) = v;
       }
     }
     return;
   }
   // With a residual to add before the one rounding, or as a split-K slice: in fp32, one 32 x (TN*32) strip at a time.
-  float* strip = reinterpret_cast<float*>(smem) + wave * (32 * SP);
-  constexpr int LPR = SW / 16;                            // lanes per row when re-reading (4 for a 64-column strip)
-  constexpr int RPP = 64 / LPR;                           // rows per pass
+  // out(i, ps, m, w): the 8 values from column nr of row m, pass ps of row tile i
+  constexpr int PASSES = 32 / RPP;
+  auto strips = [&](auto out) __attribute__((always_inline)) {
+    float* strip = reinterpret_cast<float*>(smem) + wave * (32 * SP);
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
+    for (int i = 0; i < TM; ++i) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        float4 v = {acc[i][j][rg * 4], acc[i][j][rg * 4 + 1], acc[i][j][rg * 4 + 2], acc[i][j][rg * 4 + 3]};
-        *reinterpret_cast<float4*>(strip + (lane & 31) * SP + j * 32 + rg * 8 + (lane >> 5) * 4) = v;
-      }
-    // (LDS operations of one wavefront complete in order: the reads below see the writes above)
-#pragma unroll
-    for (int ps = 0; ps < 32 / RPP; ++ps) {
-      const int r = ps * RPP + lane / LPR, c = (lane % LPR) * 16;
-      float v[16];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 t = *reinterpret_cast<const float4*>(strip + r * SP + c + q * 4);
-        v[q * 4] = t.x; v[q * 4 + 1] = t.y; v[q * 4 + 2] = t.z; v[q * 4 + 3] = t.w;
-      }
-      const int m = m0 + wm * (BM / WM) + i * 32 + r;
-      const int n = n0 + wn * (BN / WN) + c;
-      if (m >= p.M) continue;
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {                    // two groups of 8 columns, each entirely inside or outside N
-        const int nn = n + hf * 8;
-        if (nn >= p.N) continue;
-        float w[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) w[e] = v[hf * 8 + e];
-        if (P) {                                          // split-K: raw fp32 tile, summed by splitk_reduce_kernel
-          store_f<float, 8>(P + (size_t)m * p.N + nn, w);
-          continue;
+        for (int rg = 0; rg < 4; ++rg) {
+          float4 v = {acc[i][j][rg * 4], acc[i][j][rg * 4 + 1], acc[i][j][rg * 4 + 2], acc[i][j][rg * 4 + 3]};
+          *reinterpret_cast<float4*>(strip + (lane & 31) * SP + j * 32 + rg * 8 + (lane >> 5) * 4) = v;
         }
-        if (bias) {
-          float bb[8];
-          load_f<T, 8>(bias + nn, bb);
+      // (LDS operations of one wavefront complete in order: the reads below see the writes above)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) w[e] += bb[e];
-        }
-        if (p.relu) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) w[e] = fmaxf(w[e], 0.f);
-        }
-        if (p.drop_thr) drop_apply<8>(w, p.drop_key, (uint64_t)m * p.N + nn, p.drop_thr, p.inv_keep);
-        const size_t o = (size_t)m * p.ldc + nn;
-        if (mask) {
-          float k[8];
-          load_f<T, 8>(mask + o, k);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) w[e] = k[e] > 0.f ? w[e] * p.mask_scale : 0.f;
-        }
-        if (res) {
-          float k[8];
-          load_f<T, 8>(res + o, k);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) w[e] += k[e];
-        }
-        store_f<T, 8>(C + o, w);
+      for (int ps = 0; ps < PASSES; ++ps) {
+        const int m = mr + i * 32 + ps * RPP;
+        const float* at = strip + (ps * RPP + lane / LPR) * SP + cr;
+        const float4 lo = *reinterpret_cast<const float4*>(at), hi = *reinterpret_cast<const float4*>(at + 4);
+        float w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        if (m < p.M && nr < p.N) out(i, ps, m, w);
       }
     }
+  };
+  if (P) {                                                // split-K: raw fp32 tile, summed by splitk_reduce_kernel
+    strips([&](int, int, int m, float (&w)[8]) __attribute__((always_inline)) { store_f<float, 8>(P + (size_t)m * p.N + nr, w); });
+  } else if (!bias && !p.relu && !p.drop_thr && !mask) {  // an input gradient
+    u32x4 add[TM][PASSES];                               // the whole tile's in one trip to memory: behind a store each strip's would be waited for
+    if (nr < p.N) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int ps = 0; ps < PASSES; ++ps)
+          add[i][ps] = *reinterpret_cast<const u32x4*>(res + (size_t)min(mr + i * 32 + ps * RPP, p.M - 1) * p.ldc + nr);
+    }
+    strips([&](int i, int ps, int m, float (&w)[8]) __attribute__((always_inline)) {
+      Pack<T, 8> k;
+      __builtin_memcpy(&k, &add[i][ps], 16);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] += to_f<T>(k.v[e]);
+      store_f<T, 8>(C + (size_t)m * p.ldc + nr, w);
+    });
+  } else {
+    strips([&](int, int, int m, float (&w)[8]) __attribute__((always_inline)) {
+      float k[8];
+      if (bias) {
+        load_f<T, 8>(bias + nr, k);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] += k[e];
+      }
+      if (p.relu) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = fmaxf(w[e], 0.f);
+      }
+      if (p.drop_thr) drop_apply<8>(w, p.drop_key, (uint64_t)m * p.N + nr, p.drop_thr, p.inv_keep);
+      const size_t o = (size_t)m * p.ldc + nr;
+      if (mask) {
+        load_f<T, 8>(mask + o, k);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = k[e] > 0.f ? w[e] * p.mask_scale : 0.f;
+      }
+      load_f<T, 8>(res + o, k);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] += k[e];
+      store_f<T, 8>(C + o, w);
+    });
   }
 }
 
@@ -462,9 +562,9 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
   return x * q + (x < r ? x : r) + (b >> 3);
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES, bool ATR, bool BTR>
-__global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4) ? 2 : 1) void gemm_mfma_kernel(MfmaGemmParams p) {
-  gemm_mfma_tile<T, BM, BN, WM, WN, BK, STAGES, ATR, BTR, false>(p, xcd_tile(blockIdx.x, p.tiles_total), blockIdx.y);
+template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES, int AHEAD, bool ATR, bool BTR>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(MfmaGemmParams p) {
+  gemm_mfma_tile<T, BM, BN, WM, WN, BK, STAGES, AHEAD, ATR, BTR, false>(p, xcd_tile(blockIdx.x, p.tiles_total), blockIdx.y);
 }
 
 // Grouped weight gradients: one launch covers the tiles of up to GROUP_MAX independent products C_i = A_i^T B_i (each
@@ -475,8 +575,7 @@ constexpr int GROUP_MAX = 48;
 struct GroupedProblem {
   const uint16_t* A; const uint16_t* B; uint16_t* C; uint16_t* colsum;
   int M, N, K, lda, ldb, ldc, tile_begin, tiles_m, tiles_n;
-  uint32_t a_bytes, b_bytes;
-  int pad_;
+  uint32_t band_m, last_m;                               // multipliers of the two Divisors
 };
 struct GroupedTable {
   int n, tiles_total;
@@ -485,7 +584,7 @@ struct GroupedTable {
 static_assert(sizeof(GroupedTable) <= 4096, "kernel argument space");
 
 template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES>
-__global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4) ? 2 : 1) void gemm_mfma_grouped_kernel(GroupedTable tab) {
+__global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_grouped_kernel(GroupedTable tab) {
   const int tile = xcd_tile(blockIdx.x, tab.tiles_total);
   int pi = 0;
   for (int i = 1; i < tab.n; ++i) pi = tile >= tab.pr[i].tile_begin ? i : pi;
@@ -494,19 +593,19 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4) ? 2 : 1) void gemm_mfm
   p.M = g.M; p.N = g.N; p.K = g.K;
   p.A = g.A; p.lda = g.lda; p.B = g.B; p.ldb = g.ldb; p.C = g.C; p.ldc = g.ldc;
   p.bias = nullptr; p.relu = 0; p.mask = nullptr; p.residual = nullptr;
-  p.tiles_n = g.tiles_n; p.tiles_m = g.tiles_m; p.tiles_total = g.tiles_m * g.tiles_n; p.group_m = 8;
+  p.tiles_m = g.tiles_m; p.tiles_total = 0; p.per_band = {(uint32_t)(GROUP_M * g.tiles_n), g.band_m}; p.last_band = {(uint32_t)g.tiles_m % GROUP_M, g.last_m};
   p.ksteps_per_split = (g.K + BK - 1) / BK;
   p.partial = nullptr;
-  p.a_bytes = g.a_bytes; p.b_bytes = g.b_bytes;
+  p.a_bytes = (uint32_t)(((g.K - 1) * g.lda + g.M) * 2); p.b_bytes = (uint32_t)(((g.K - 1) * g.ldb + g.N) * 2);   // (below 2^31: wgrad_group_supported)
   p.colsum = g.colsum;
   p.drop_key = 0; p.drop_thr = 0; p.inv_keep = 1.f; p.mask_scale = 1.f;
-  gemm_mfma_tile<T, BM, BN, WM, WN, BK, STAGES, true, true, true>(p, tile - g.tile_begin, 0);
+  gemm_mfma_tile<T, BM, BN, WM, WN, BK, STAGES, 1, true, true, true>(p, tile - g.tile_begin, 0);
 }
 
-// C[m, n] = epilogue(sum over splits (fixed order) of partial[s][m][n]); epilogue = optional bias[n], optional ReLU
+// C[m, n] = epilogue(sum over splits (fixed order) of partial[s][m][n]); epilogue = optional bias[n], ReLU, residual [M, N] of stride ldc
 template <typename T>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int M, int N, T* __restrict__ C, int ldc,
-                                                            const T* __restrict__ bias, int relu) {
+                                                            const T* __restrict__ bias, int relu, const T* __restrict__ residual) {
   const size_t idx = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   const size_t total = (size_t)M * N;
   if (idx >= total) return;
@@ -527,14 +626,21 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
   }
+  if (residual) {
+    float k[4];
+    load_f<T, 4>(residual + (size_t)m * ldc + n, k);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += k[e];
+  }
   store_f<T, 4>(C + (size_t)m * ldc + n, v);
 }
 
-void launch_splitk_reduce(hipStream_t s, int dt, const float* partial, int splits, int M, int N, void* C, int ldc, const void* bias, int relu) {
+void launch_splitk_reduce(hipStream_t s, int dt, const float* partial, int splits, int M, int N, void* C, int ldc, const void* bias, int relu,
+                          const void* residual) {
   const size_t quads = ((size_t)M * N + 3) / 4;
   dim3 grid((unsigned)((quads + 255) / 256)), block(256);
-  if (dt == F16) hipLaunchKernelGGL((splitk_reduce_kernel<half_t>), grid, block, 0, s, partial, splits, M, N, (half_t*)C, ldc, (const half_t*)bias, relu);
-  else if (dt == BF16) hipLaunchKernelGGL((splitk_reduce_kernel<bf16_t>), grid, block, 0, s, partial, splits, M, N, (bf16_t*)C, ldc, (const bf16_t*)bias, relu);
+  if (dt == F16) hipLaunchKernelGGL((splitk_reduce_kernel<half_t>), grid, block, 0, s, partial, splits, M, N, (half_t*)C, ldc, (const half_t*)bias, relu, (const half_t*)residual);
+  else if (dt == BF16) hipLaunchKernelGGL((splitk_reduce_kernel<bf16_t>), grid, block, 0, s, partial, splits, M, N, (bf16_t*)C, ldc, (const bf16_t*)bias, relu, (const bf16_t*)residual);
 }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -561,7 +667,69 @@ bool gemm_mfma_supported(const GemmArgs& a) {
   return true;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES>
+// The tilings, and what a launch of each costs.  In a round (one tile on every compute unit, two of 64x64) a K-step of 64 takes `step` us
+// when the round is full and `few` when hardly a tile runs: the clock follows the power that is drawn (2.4 GHz on zeros, 1.5-1.7 on
+// normally distributed operands with all matrix cores busy), and the memory system is shared.  `first` us is launch, fetch of the
+// instructions, first trip to memory and epilogue; later rounds overlap some of that.  Fitted to 60 products of 280-4096 rows with
+// 512-32768 columns and K = 512-8192 in fp16, launches back to back over operands that no cache holds: within 10 % but for a few outliers.
+//   tiling     wavefronts  K-step  ring      measured: rows x columns x K (us; in brackets the tilings before: 128x128 on 16 wavefronts, 64x128 on 8 of
+//                                            32x32, 192x256 and 256x256 with a ring of two, loads issued in one burst after the barrier)
+//   256x256      2 x 4       32     4        4096 x 4096 x 1024 NN 35.2 (38.7); A^T B 32768 x 1024 x 3264 187 (226)
+//   256x128      4 x 2       64     3        3000 x 8192 x 1536 74.8 (93)
+//   192x256      2 x 4       32     4        3264 x 3072 x 1024 25-27 (27.9)
+//   192x128      2 x 2       64     3        3000 x 1536 x 4608 NN 42.6, 3000 x 1536 x 8192 90 (288 tiles of 128x128 in two rounds: 64, 108)
+//   128x128      2 x 2       64     4        4096 x 1024 x 4096 NN 35.1 (40.0), 3264 x 1024 x 1024 11.2 (12.0)
+//    64x128      2 x 2       64     4        3520 x 512 x 1536 NN 10.7 (12.2)
+//    64x64       2 x 2       64     4        280 x 1024 x 3072 NN, K in 3 slices, 10.3 (24 tiles of 128x128: 20)
+// Wavefronts of 64x64 or more read half of the LDS bytes per flop of 32x32 ones.  Measured and dropped: 256x256 on 4 wavefronts of 128x128 (one per
+// SIMD: 8 % slower), rings of five slots (equal), two groups of wavefronts with half of the K-steps each (2 us more per launch for
+// the exchange, 3 % less per K-step).
+enum Tiling { T256x256, T256x128, T192x256, T192x128, T128x128, T64x128, T64x64, TILINGS };
+struct TilingCost { int bm, bn; float first, later, few, step; };
+static const TilingCost TILING[TILINGS] = {{256, 256, 7.f, 7.f, 0.72f, 1.75f}, {256, 128, 5.f, 5.f, 0.35f, 0.87f},
+    {192, 256, 6.f, 6.f, 0.63f, 1.4f}, {192, 128, 5.f, 5.f, 0.3f, 0.65f}, {128, 128, 4.2f, 2.f, 0.29f, 0.475f}, {64, 128, 5.2f, 2.5f, 0.23f, 0.24f},
+    {64, 64, 5.f, 2.5f, 0.11f, 0.3f}};
+static long tiles_of(Tiling t, int M, int N) { return (long)((M + TILING[t].bm - 1) / TILING[t].bm) * ((N + TILING[t].bn - 1) / TILING[t].bn); }
+static double launch_cost(Tiling t, long tiles, double ksteps) {
+  const long per_round = t == T64x64 ? 512 : 256, full = tiles / per_round, rest = tiles % per_round;
+  const TilingCost& c = TILING[t];
+  double us = c.first + (double)(full + (rest ? 1 : 0) - 1) * c.later + full * c.step * ksteps;
+  if (rest) us += ksteps * (c.few + (c.step - c.few) * rest / per_round);
+  return us;
+}
+
+// K-slices of a 64x64 tiling of X W^T or dY W with too few tiles for the chip (few rows, or a narrow output): the other operand streams through
+// more compute units.  Every slice keeps >= 4 K-steps; bias, ReLU and residual move into the reduction, a kernel of some 3 us unless
+// the caller's next one does it: 280 x 1024, K = 1024: 7.4 us in one piece, 10.3 in 3 slices; K = 3072: 11.3 and 10.3;
+// 400 x 256, K = 40000: 113 and 32.
+static int k_slices(const GemmArgs& a) {
+  const long tiles = tiles_of(T64x64, a.M, a.N);
+  const int nk = (a.K + 63) / 64;
+  if (a.form == 2 || !a.splitk_ws || a.mask || a.drop_p > 0.f || tiles > 128 || nk < 8) return 1;
+  if (a.deferred_splits ? a.relu || a.residual : nk < 40) return 1;                       // (a deferred reduction has neither ReLU nor residual)
+  long n = std::min(std::min(256 / tiles, (long)nk / 4), 64l);
+  while (n > 1 && (size_t)n * a.M * a.N * sizeof(float) > a.splitk_ws_bytes) --n;
+  return (int)n;
+}
+
+static Tiling choose_tiling(const GemmArgs& a) {
+  const double ks = (a.K + 63) / 64;
+  Tiling best = T128x128;
+  double cost = 1e30;
+  for (int i = 0; i < TILINGS; ++i) {
+    const Tiling t = (Tiling)i;
+    if (a.form == 2 && t != T256x256 && t != T128x128) continue;                            // (a [k][row] tile of A has 128 or 256 rows)
+    double c = launch_cost(t, tiles_of(t, a.M, a.N), ks);
+    if (t == T64x64) {
+      const int n = k_slices(a);
+      if (n > 1) c = launch_cost(t, n * tiles_of(t, a.M, a.N), (ks + n - 1) / n) + (a.deferred_splits ? 0.0 : 3.0);
+    }
+    if (c < cost) { cost = c; best = t; }
+  }
+  return best;
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES, int AHEAD>
 static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a) {
   MfmaGemmParams p;
   p.M = a.M; p.N = a.N; p.K = a.K;
@@ -570,37 +738,30 @@ static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a) {
   p.colsum = nullptr;
   p.drop_key = a.drop_key; p.drop_thr = a.drop_p > 0.f ? drop_threshold(a.drop_p) : 0u; p.inv_keep = 1.f / (1.f - a.drop_p);
   p.mask_scale = a.mask_scale;
-  p.tiles_n = (a.N + BN - 1) / BN;
+  const int tiles_n = (a.N + BN - 1) / BN;
   p.tiles_m = (a.M + BM - 1) / BM;
-  p.tiles_total = p.tiles_n * p.tiles_m;
-  p.group_m = 8;
+  p.tiles_total = tiles_n * p.tiles_m;
+  p.per_band.set(GROUP_M * tiles_n, p.tiles_total);
+  p.last_band.set(p.tiles_m % GROUP_M, GROUP_M * tiles_n);
   p.a_bytes = (uint32_t)(a.form == 2 ? extent_bytes(a.K, a.M, a.lda) : extent_bytes(a.M, a.K, a.lda));
   p.b_bytes = (uint32_t)(a.form == 0 ? extent_bytes(a.N, a.K, a.ldb) : extent_bytes(a.K, a.N, a.ldb));
-  // Split-K for weight-gradient shapes whose output has too few tiles to fill the chip: slices of K go to
-  // blockIdx.y, fp32 partial tiles go to the caller's workspace and are added in a fixed order.
+  // Split-K: slices of K go to blockIdx.y, fp32 partial tiles go to the caller's workspace and are added in a fixed order.
   const int nk = (a.K + BK - 1) / BK;
-  int splits = 1;
-  if (a.form == 2 && a.splitk_ws && !a.bias && !a.relu && !a.mask && !a.residual && !p.drop_thr && p.tiles_total <= 128 && nk >= 32) {
-    splits = 256 / p.tiles_total;
-    if (splits > 8) splits = 8;
-  } else if (a.form == 0 && BM == 64 && BN == 64 && a.splitk_ws && !a.mask && !a.residual && !p.drop_thr && p.tiles_total <= 128 && nk >= 8 &&
-             !(a.deferred_splits && a.relu)) {                // (a deferred reduction has no ReLU)
-    // X W^T with few rows (a decoding step of more than 64 rows, or of fewer where the few-row kernel is not the faster one): the
-    // weights stream through more CUs; every slice keeps >= 4 K-steps and bias / ReLU move into the reduction
-    splits = std::min(std::min(256 / p.tiles_total, nk / 4), 8);
+  int splits = BM == 64 && BN == 64 ? k_slices(a) : 1;
+  if (a.form == 2 && a.splitk_ws && !a.bias && !a.relu && !a.mask && !a.residual && !p.drop_thr && p.tiles_total <= 128 && nk * BK >= 2048) {
+    splits = std::min(256 / p.tiles_total, 8);            // a weight gradient on its own, whose output has too few tiles to fill the chip
+    while (splits > 1 && (size_t)splits * a.M * a.N * sizeof(float) > a.splitk_ws_bytes) --splits;
   }
-  while (splits > 1 && (size_t)splits * a.M * a.N * sizeof(float) > a.splitk_ws_bytes) --splits;
   p.ksteps_per_split = (nk + splits - 1) / splits;
   p.partial = splits > 1 ? (float*)a.splitk_ws : nullptr;
   dim3 grid(p.tiles_total, splits), block(64 * WM * WN);
-  if (a.form == 0) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, false, false>), grid, block, 0, s, p);
-  else if constexpr (BN >= 128) {                        // the [k][row] swizzle spans 16 vectors = 128 rows: B of dY W ...
-    if (a.form == 1) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, false, true>), grid, block, 0, s, p);
-    else if constexpr (BM >= 128)                        // ... and A as well for A^T B
-      hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, true, true>), grid, block, 0, s, p);
-  }
+  if (a.form == 0) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, false>), grid, block, 0, s, p);
+  else if constexpr (BN == BM && BM >= 128) {
+    if (a.form == 1) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, true, true>), grid, block, 0, s, p);
+  } else if (a.form == 1) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, true>), grid, block, 0, s, p);
   if (a.deferred_splits) *a.deferred_splits = splits > 1 ? splits : 0;
-  if (splits > 1 && !a.deferred_splits) launch_splitk_reduce(s, a.dt, (const float*)a.splitk_ws, splits, a.M, a.N, a.C, a.ldc, a.bias, a.relu);
+  if (splits > 1 && !a.deferred_splits) launch_splitk_reduce(s, a.dt, (const float*)a.splitk_ws, splits, a.M, a.N, a.C, a.ldc, a.bias, a.relu, a.residual);
 }
 
 // ---- grouped weight gradients ---------------------------------------------------------------------------------------------
@@ -619,84 +780,50 @@ static void wgrad_grouped_launch(hipStream_t s, const WgradJob* jobs, int n) {
     GroupedProblem& g = tab.pr[i];
     g.A = (const uint16_t*)j.A; g.B = (const uint16_t*)j.B; g.C = (uint16_t*)j.C; g.colsum = (uint16_t*)j.colsum;
     g.M = j.M; g.N = j.N; g.K = j.K; g.lda = j.lda; g.ldb = j.ldb; g.ldc = j.ldc;
-    g.tiles_m = (j.M + BM - 1) / BM; g.tiles_n = (j.N + BN - 1) / BN;
+    const int tiles_n = (j.N + BN - 1) / BN;
+    g.tiles_m = (j.M + BM - 1) / BM;
+    Divisor per_band, last_band;
+    per_band.set(GROUP_M * tiles_n, g.tiles_m * tiles_n);
+    last_band.set(g.tiles_m % GROUP_M, GROUP_M * tiles_n);
+    g.tiles_n = tiles_n; g.band_m = per_band.m; g.last_m = last_band.m;
     g.tile_begin = tiles;
-    tiles += g.tiles_m * g.tiles_n;
-    g.a_bytes = (uint32_t)extent_bytes(j.K, j.M, j.lda);
-    g.b_bytes = (uint32_t)extent_bytes(j.K, j.N, j.ldb);
-    g.pad_ = 0;
+    tiles += g.tiles_m * tiles_n;
   }
   tab.n = n; tab.tiles_total = tiles;
   hipLaunchKernelGGL((gemm_mfma_grouped_kernel<T, BM, BN, WM, WN, BK, STAGES>), dim3(tiles), dim3(64 * WM * WN), 0, s, tab);
 }
 
-// 256x256 tiles fetch half as many bytes per flop as 128x128 ones but come in coarser rounds over the 256 compute units:
-// compare the rounds each tiling needs, weighted by what a tile of each kind was measured to cost (103 vs 31 us at K = 3264).
+// (the cost of the launch with either tiling, see launch_cost; K of the longest product)
 void launch_wgrad_grouped(hipStream_t s, int dt, const WgradJob* jobs, int n) {
   if (n <= 0) return;
   long t256 = 0, t128 = 0;
+  int K = 0;
   for (int i = 0; i < n; ++i) {
-    t256 += (long)((jobs[i].M + 255) / 256) * ((jobs[i].N + 255) / 256);
-    t128 += (long)((jobs[i].M + 127) / 128) * ((jobs[i].N + 127) / 128);
+    t256 += tiles_of(T256x256, jobs[i].M, jobs[i].N);
+    t128 += tiles_of(T128x128, jobs[i].M, jobs[i].N);
+    K = std::max(K, jobs[i].K);
   }
-  const double c256 = (double)((t256 + 255) / 256) * 103.0, c128 = (double)((t128 + 255) / 256) * 31.0;
-  const bool big = c256 <= c128;
+  const double ks = (K + 63) / 64;
+  const bool big = launch_cost(T256x256, t256, ks) <= launch_cost(T128x128, t128, ks);
   if (dt == F16) {
-    if (big) wgrad_grouped_launch<half_t, 256, 256, 2, 4, 64, 2>(s, jobs, n);
-    else wgrad_grouped_launch<half_t, 128, 128, 4, 4, 64, 3>(s, jobs, n);
+    if (big) wgrad_grouped_launch<half_t, 256, 256, 2, 4, 32, 4>(s, jobs, n);
+    else wgrad_grouped_launch<half_t, 128, 128, 2, 2, 64, 4>(s, jobs, n);
   } else {
-    if (big) wgrad_grouped_launch<bf16_t, 256, 256, 2, 4, 64, 2>(s, jobs, n);
-    else wgrad_grouped_launch<bf16_t, 128, 128, 4, 4, 64, 3>(s, jobs, n);
+    if (big) wgrad_grouped_launch<bf16_t, 256, 256, 2, 4, 32, 4>(s, jobs, n);
+    else wgrad_grouped_launch<bf16_t, 128, 128, 2, 2, 64, 4>(s, jobs, n);
   }
-}
-
-// Configuration choice, from measurements on the projection shapes of the big and base Transformers (M ~ 3000-3700 tokens):
-//   id  tile     wavefronts  K-step  ring   resident blocks per CU
-//    1  128x128      4         32     3      3      more than 256 tiles and K < 3072: several blocks per CU keep it fed
-//   12  128x128     16         64     4      1      K >= 3072, or at most 256 tiles (one block per CU anyway): 16 wavefronts
-//                                                   of 32x32 hide the fetch latency that 4 of 64x64 exposed (10-15 % faster);
-//                                                   a 4-slot ring is 2-4 % faster than 3 slots, 5 slots are slower again
-//   13  256x256      8         64     2      1      half the bytes fetched per flop (16 wavefronts are slower here: more LDS
-//                                                   traffic per flop)
-//   14  192x256      8         64     2      1      X W^T and dY W only: where 256x256 leaves compute units idle (a 3072-wide
-//                                                   output of ~3200 rows has 156 tiles of 256x256 but 204 of 192x256 for
-//                                                   256 CUs: 31.5 -> 28.0 us; 3000 rows: 37.6 -> 27.3 us)
-//   20   64x64       4         64     4      2      fewer than 128 tiles of 128x128 (a decoding step's rows that
-//                                                   the few-row kernel does not take)
-//   22   64x128      8         64     4      1      X W^T and dY W with many rows but a narrow output and K >= 1024 (the 512-wide
-//                                                   products of the base model: 116 tiles of 128x128 become 232; 15.8 -> 13.3 us
-//                                                   at K = 2048, 14.1 -> 11.7 us at K = 1536; slower than the others at K = 512)
-// A launch costs about rounds x (fixed + slope x K-steps), rounds = tiles over the 256 compute units rounded up (the last,
-// partly filled round takes as long as a full one); fixed / slope in us per round and 64-wide K-step, measured with
-// M = 3264: 11 / 1.45 for 256x256, 9.5 / 1.16 for 192x256, 4.4 / 0.48 for 128x128.
-static int choose_tile(const GemmArgs& a) {
-  const long t1 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-  if (a.form != 2 && a.M >= 1024 && a.K >= 1024 && t1 <= 160) return 22;
-  if (t1 < 128 && a.form == 0) return 20;               // few rows (X W^T): smaller tiles reach more CUs
-  const long t3 = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
-  const long t4 = (long)((a.M + 191) / 192) * ((a.N + 255) / 256);
-  const double ks = (double)((a.K + 63) / 64);
-  const double c128 = (double)((t1 + 255) / 256) * (4.4 + 0.48 * ks);
-  const double c256 = (double)((t3 + 255) / 256) * (11.0 + 1.45 * ks);
-  const double c192 = a.form == 2 ? 1e30 : (double)((t4 + 255) / 256) * (9.5 + 1.16 * ks);
-  if (c192 < c256 && c192 < c128) return 14;
-  if (t3 >= 150) return 13;
-  if (a.K >= 3072 || t1 <= 256) return 12;
-  return 1;
 }
 
 template <typename T>
 static void gemm_mfma_dispatch(hipStream_t s, const GemmArgs& a) {
-  switch (choose_tile(a)) {
-    case 13: gemm_mfma_launch<T, 256, 256, 2, 4, 64, 2>(s, a); break;
-    case 12: gemm_mfma_launch<T, 128, 128, 4, 4, 64, 4>(s, a); break;
-    case 14: gemm_mfma_launch<T, 192, 256, 2, 4, 64, 2>(s, a); break;   // (never chosen for A^T B: its A tile would be [k][192])
-    case 22: gemm_mfma_launch<T, 64, 128, 2, 4, 64, 4>(s, a); break;    // (nor this one: [k][64])
-    case 20:                                            // (the [k][row] swizzle spans 16 vectors: NT form only)
-      if (a.form == 0) gemm_mfma_launch<T, 64, 64, 2, 2, 64, 4>(s, a);
-      else gemm_mfma_launch<T, 128, 128, 2, 2, 32, 3>(s, a);
-      break;
-    default: gemm_mfma_launch<T, 128, 128, 2, 2, 32, 3>(s, a); break;
+  switch (choose_tiling(a)) {
+    case T256x256: gemm_mfma_launch<T, 256, 256, 2, 4, 32, 4, 1>(s, a); break;
+    case T256x128: gemm_mfma_launch<T, 256, 128, 4, 2, 64, 3, 1>(s, a); break;
+    case T192x256: gemm_mfma_launch<T, 192, 256, 2, 4, 32, 4, 1>(s, a); break;
+    case T192x128: gemm_mfma_launch<T, 192, 128, 2, 2, 64, 3, 1>(s, a); break;
+    case T64x128: gemm_mfma_launch<T, 64, 128, 2, 2, 64, 4, 1>(s, a); break;
+    case T64x64: gemm_mfma_launch<T, 64, 64, 2, 2, 64, 4, 2>(s, a); break;
+    default: gemm_mfma_launch<T, 128, 128, 2, 2, 64, 4, 1>(s, a); break;
   }
 }
 

@@ -72,7 +72,8 @@ void launch_gemm_naive(hipStream_t s, const GemmArgs& a);
 void launch_gemm_mfma(hipStream_t s, const GemmArgs& a);      // requires gemm_mfma_supported(a)
 // C[m, n] = bias[n] + sum over s of partial[s][m][n] (fixed order): the second half of a split-K product whose reduction was
 // deferred (2-byte types only)
-void launch_splitk_reduce(hipStream_t s, int dt, const float* partial, int splits, int M, int N, void* C, int ldc, const void* bias, int relu);
+void launch_splitk_reduce(hipStream_t s, int dt, const float* partial, int splits, int M, int N, void* C, int ldc, const void* bias, int relu,
+                          const void* residual = nullptr);
 
 // Grouped weight gradients (half precision): one launch computes C_i[M_i, N_i] = A_i^T B_i over K_i rows for every job and,
 // where colsum is set, colsum_i[M_i] = the column sums of A_i (the bias gradient that goes with the weight gradient).

@@ -173,6 +173,35 @@ def test_gemm_split_k_weight_gradient_is_exact_and_reproducible(prec, shape):
     assert np.array_equal(out.float().cpu().numpy().astype(np.float64), want)
 
 
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("form", [0, 1])
+@pytest.mark.parametrize("shape", [
+    (2825, 1544, 136), (3330, 2056, 136), (2820, 520, 1032),   # 192x128, 256x128 and 64x128 tiles, ragged in every direction
+    (65, 72, 2568), (280, 264, 2600), (7, 8, 20008),           # 64x64 tiles with K in 2 to 64 slices, the last one ragged
+])
+def test_gemm_tilings_of_many_rows_and_slices_of_a_long_contraction(prec, form, shape):
+    """Bias and ReLU, residual and mask of every tiling that the shapes elsewhere do not reach; exact on small integers (the sums of
+    a long contraction stay below 2048 in magnitude).  With a workspace and without: the same bits."""
+    import torch
+    import paper_1904_01038_amd as T
+    M, N, K = shape
+    dt = _dtypes()[prec]
+    rng = np.random.default_rng(M + K + form)
+    A = rng.integers(-1, 2, (M, K)).astype(np.float64)
+    B = rng.integers(-1, 2, (K, N)).astype(np.float64)
+    bias, res, mask = rng.integers(-4, 5, N).astype(np.float64), rng.integers(-8, 9, (M, N)).astype(np.float64), rng.integers(-1, 2, (M, N)).astype(np.float64)
+    tA, tB = _t(A, dt), _t(B if form else B.T.copy(), dt)
+    ws = torch.empty(4 << 20, dtype=torch.float32, device="cuda")
+    for kw, ref in ((dict(bias=_t(bias, dt), relu=True), np.maximum(A @ B + bias, 0)), (dict(residual=_t(res, dt)), A @ B + res),
+                    (dict(mask=_t(mask, dt)), (A @ B) * (mask > 0))):
+        assert np.abs(ref).max() < 2048
+        want = _t(ref, dt).float().cpu().numpy().astype(np.float64)
+        for w in (ws, None):
+            out = torch.full((M, N), 7.0, dtype=dt, device="cuda")
+            T.ops.gemm(form, tA, tB, out, M, N, K, workspace=w, **kw)
+            assert np.array_equal(out.float().cpu().numpy().astype(np.float64), want), (list(kw), w is None)
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("shape", [(200, 136, 72), (333, 264, 200), (257, 4096, 64)])
 def test_gemm_result_dropout_and_scaled_mask_are_exact(prec, shape):
