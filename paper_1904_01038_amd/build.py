@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtfm.so")
-SOURCES = ["tfm.hip", "dispatch.hip", "gemm_naive.hip", "gemm_mfma.hip", "gemm_thin.hip", "attention_naive.hip", "attention_mfma.hip", "norm.hip", "loss.hip", "embed.hip",
+SOURCES = ["tfm.hip", "dispatch.hip", "gemm_naive.hip", "gemm_f32.hip", "gemm_mfma.hip", "gemm_thin.hip", "attention_naive.hip", "attention_mfma.hip", "norm.hip", "loss.hip", "embed.hip",
            "optim.hip", "batching.hip", "decode.hip", "adaptive.hip", "probe.hip"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-Wno-unused-result", "-Wno-unused-value",

@@ -766,6 +766,7 @@ static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a) {
 
 // ---- grouped weight gradients ---------------------------------------------------------------------------------------------
 bool wgrad_group_supported(int dt, const WgradJob& j) {
+  if (dt == F32) return true;
   GemmArgs a{dt, 2, j.M, j.N, j.K, j.A, j.lda, j.B, j.ldb, j.C, j.ldc, nullptr, 0, nullptr, nullptr};
   if (!gemm_mfma_supported(a)) return false;
   return j.colsum == nullptr || ((uintptr_t)j.colsum & 1) == 0;
@@ -795,6 +796,7 @@ static void wgrad_grouped_launch(hipStream_t s, const WgradJob* jobs, int n) {
 
 // (the cost of the launch with either tiling, see launch_cost; K of the longest product)
 void launch_wgrad_grouped(hipStream_t s, int dt, const WgradJob* jobs, int n) {
+  if (dt == F32) return launch_wgrad_grouped_f32(s, jobs, n);
   if (n <= 0) return;
   long t256 = 0, t128 = 0;
   int K = 0;

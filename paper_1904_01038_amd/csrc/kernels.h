@@ -68,14 +68,15 @@ void launch_gemm_thin(hipStream_t s, const GemmArgs& a);
 bool gemm_thin_norm_supported(const GemmArgs& a, const ThinNorm& q);
 void launch_gemm_thin_norm(hipStream_t s, const GemmArgs& a, const ThinNorm& q);   // requires gemm_thin_norm_supported(a, q)
 bool gemm_mfma_supported(const GemmArgs& a);
-void launch_gemm_naive(hipStream_t s, const GemmArgs& a);
+void launch_gemm_naive(hipStream_t s, const GemmArgs& a);     // 2-byte types
+void launch_gemm_f32(hipStream_t s, const GemmArgs& a);       // fp32, any shape
 void launch_gemm_mfma(hipStream_t s, const GemmArgs& a);      // requires gemm_mfma_supported(a)
 // C[m, n] = bias[n] + sum over s of partial[s][m][n] (fixed order): the second half of a split-K product whose reduction was
 // deferred (2-byte types only)
 void launch_splitk_reduce(hipStream_t s, int dt, const float* partial, int splits, int M, int N, void* C, int ldc, const void* bias, int relu,
                           const void* residual = nullptr);
 
-// Grouped weight gradients (half precision): one launch computes C_i[M_i, N_i] = A_i^T B_i over K_i rows for every job and,
+// Grouped weight gradients: one launch computes C_i[M_i, N_i] = A_i^T B_i over K_i rows for every job and,
 // where colsum is set, colsum_i[M_i] = the column sums of A_i (the bias gradient that goes with the weight gradient).
 struct WgradJob {
   int M, N, K;
@@ -87,6 +88,7 @@ struct WgradJob {
 constexpr int WGRAD_GROUP_MAX = 48;      // jobs per launch
 bool wgrad_group_supported(int dt, const WgradJob& j);
 void launch_wgrad_grouped(hipStream_t s, int dt, const WgradJob* jobs, int n);   // n <= WGRAD_GROUP_MAX, every job supported
+void launch_wgrad_grouped_f32(hipStream_t s, const WgradJob* jobs, int n);
 
 struct AttnArgs {
   int dt;

@@ -563,7 +563,7 @@ void flush_wgrads(tfm_ctx* c) {
 void wgrad(tfm_ctx* c, int M, int N, int K, const void* A, int lda, const void* B, int ldb, void* C, int ldc, void* bias_grad = nullptr) {
   if (M <= 0 || N <= 0) return;
   WgradJob j{M, N, K, A, lda, B, ldb, C, ldc, bias_grad};
-  if (c->dt != F32 && K > 0 && wgrad_group_supported(c->dt, j)) {
+  if (K > 0 && wgrad_group_supported(c->dt, j)) {
     c->wq.push_back(j);
     c->wq_tiles += (long)((M + 127) / 128) * ((N + 127) / 128);
     if ((int)c->wq.size() == WGRAD_GROUP_MAX || c->wq_tiles >= c->wq_flush_tiles) flush_wgrads(c);

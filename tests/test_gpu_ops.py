@@ -69,6 +69,28 @@ def test_gemm_forms_and_epilogues(prec, form, shape):
             assert not out[:, N:].any()
 
 
+@pytest.mark.parametrize("form", [0, 1, 2])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (33, 31, 7), (32, 32, 256), (31, 65, 257), (130, 66, 1001), (1025, 1023, 9), (1056, 1024, 36)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_gemm_fp32_any_size_and_alignment_is_exact(form, shape, shift):
+    """4 and 8 wavefronts on a 32x32 tile, 64x64 blocks, K in and out of step with 4 and 8, operands on and off a 16-byte boundary."""
+    import torch
+    import paper_1904_01038_amd as T
+    M, N, K = shape
+    rng = np.random.default_rng(M + N + K + form)
+    A, B, bias = rng.integers(-3, 4, (M, K)).astype(np.float64), rng.integers(-3, 4, (K, N)).astype(np.float64), rng.integers(-4, 5, N).astype(np.float64)
+    views = []
+    for x in (A.T if form == 2 else A, B if form else B.T):
+        buf = torch.full((x.shape[0] * (x.shape[1] + shift) + shift,), float("nan"), device="cuda")
+        v = buf[shift:].view(x.shape[0], x.shape[1] + shift)[:, :x.shape[1]]
+        v.copy_(_t(x.copy(), torch.float32))
+        views.append(v)
+    out = torch.full((M, N + shift), 7.0, device="cuda")
+    T.ops.gemm(form, *views, out, M, N, K, ldc=N + shift, bias=_t(bias, torch.float32), relu=True)
+    assert np.array_equal(out[:, :N].cpu().numpy().astype(np.float64), np.maximum(A @ B + bias, 0))
+    assert not shift or bool((out[:, N:] == 7.0).all())
+
+
 @pytest.mark.parametrize("d", [64, 264, 512, 1024, 2048])
 def test_sums_over_a_wavefront_keep_their_order(d):
     """To the bit: a lane adds its own 8-element pieces in order, then lanes 32, 16, 8, 4, 2 and 1 apart are added."""
