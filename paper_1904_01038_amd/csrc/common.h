@@ -18,12 +18,8 @@ static inline size_t dtype_size(int dt) { return dt == F32 ? 4 : 2; }
 // ---- conversions (round to nearest even; a value beyond the half range becomes inf, which is what the
 // overflow detection of the mixed-precision path relies on) -------------------------------------------------------
 __device__ __forceinline__ float bf16_bits_to_f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-__device__ __forceinline__ uint16_t f_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40);   // NaN stays NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+// (v_cvt_pk_bf16_f32: to nearest even, NaN stays NaN; checked against the integer arithmetic for all 2^32 floats)
+__device__ __forceinline__ uint16_t f_to_bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 template <typename T> __device__ __forceinline__ float to_f(T v);
 template <> __device__ __forceinline__ float to_f<float>(float v) { return v; }
 template <> __device__ __forceinline__ float to_f<half_t>(half_t v) { return (float)v; }
