@@ -71,6 +71,7 @@ struct Arena {
 };
 
 constexpr int STAGE_SLOTS = 4;
+constexpr long long BESIDE_MIN = 1 << 21;          // rows x width from which a sub-batch uses the second stream, see tfm_ctx::beside
 
 // Adaptive input embeddings / adaptive softmax (language model).  Cluster 0 is the head, clusters 1..n the tails.
 struct Adaptive {
@@ -105,6 +106,10 @@ struct tfm_ctx {
   // second stream beside the chain of input gradients and fill the compute units that chain leaves idle.
   hipStream_t side;
   bool overlap;
+  // Does the current sub-batch use it?  Waiting for events and sharing compute units costs a small one more than the idle units
+  // bring: rows x width 128 x 64 0.445 ms a step with the second stream and 0.33 without, 280 x 1024 3.89 and 3.56, 3520 x 512 3.84 and
+  // 3.79; 3264 x 1024 6.78 and 6.92, 4096 x 1024 36.7 and 36.7 (4 sub-batches), 3000 x 1536 7.43 and 7.66.
+  bool beside;
   std::vector<hipEvent_t> sync_ev;                  // ordering events, handed out in sequence within a step
   size_t sync_used;
   // Deferred weight gradients: queued while the chain of input gradients runs, launched as grouped GEMMs (one launch
@@ -125,7 +130,7 @@ struct tfm_ctx {
   void *kv_all, *dkv_all;
   int ld_kv;                                        // layers * 2d
   hipEvent_t kv_ready;                              // side-stream mark after that product (null: it ran on the main stream)
-  // The Adam step also runs on the side stream, cut into chunks in the order the forward pass first touches the
+  // The Adam step of an update that is not waited for also runs on the side stream, cut into chunks in the order the forward pass first touches the
   // parameters (the flat order), so the next sub-batch's forward pass starts while later layers are still being
   // updated: it waits chunk by chunk.  Every other entry point first waits for the whole update.
   struct Chunk { int64_t off, n; int last_param; };
@@ -481,12 +486,12 @@ hipEvent_t mark(tfm_ctx* c, hipStream_t on) {
 }
 // what has been enqueued on `from` so far happens before what is enqueued on `to` from now on
 inline void order(tfm_ctx* c, hipStream_t from, hipStream_t to) { hipStreamWaitEvent(to, mark(c, from), 0); }
-inline hipStream_t wstream(tfm_ctx* c) { return c->overlap ? c->side : c->stream; }
+inline hipStream_t wstream(tfm_ctx* c) { return c->beside ? c->side : c->stream; }
 // main -> side: the operands of the weight-gradient work enqueued next are ready
-inline void side_begin(tfm_ctx* c) { if (c->overlap) order(c, c->stream, c->side); }
+inline void side_begin(tfm_ctx* c) { if (c->beside) order(c, c->stream, c->side); }
 // main waits for a side mark
 inline void main_wait(tfm_ctx* c, hipEvent_t& e) {
-  if (c->overlap && e) hipStreamWaitEvent(c->stream, e, 0);
+  if (c->beside && e) hipStreamWaitEvent(c->stream, e, 0);
   e = nullptr;
 }
 
@@ -526,7 +531,7 @@ void gemm(tfm_ctx* c, int form, int M, int N, int K, const void* A, int lda, con
   if (M <= 0 || N <= 0) return;
   GemmArgs a{c->dt, form, M, N, K, A, lda, B, ldb, C, ldc, bias, relu, mask, residual};
   a.drop_key = drop_key; a.drop_p = drop_p; a.mask_scale = mask_scale; a.deferred_splits = deferred_splits;
-  side = side && c->overlap;
+  side = side && c->beside;
   hipStream_t stream = side ? c->side : c->stream;
   a.splitk_ws = side ? c->splitk_ws_side : c->splitk_ws;
   a.splitk_ws_bytes = c->splitk_bytes;
@@ -573,7 +578,7 @@ void wgrad(tfm_ctx* c, int M, int N, int K, const void* A, int lda, const void* 
   gemm(c, 2, M, N, K, A, lda, B, ldb, C, ldc, nullptr, 0, nullptr, nullptr, true);
   if (bias_grad) {
     hipStream_t stream = wstream(c);
-    void* scratch = c->overlap ? c->red_scratch_side : c->red_scratch;
+    void* scratch = c->beside ? c->red_scratch_side : c->red_scratch;
     run(c, TFM_PROF_NORM, 0.0, (double)c->esz * K * M, [&] { launch_colsum(stream, c->dt, A, lda, K, M, bias_grad, scratch); }, stream);
   }
 }
@@ -1308,6 +1313,7 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
     run(c, TFM_PROF_OPTIM, 0.0, (double)c->P * (c->esz + 4.0), [&] { launch_convert(c->stream, c->dt, c->g, F32, c->G, c->P); });
 
   // ---- forward
+  c->beside = c->overlap && Tt * (long long)d >= BESIDE_MIN;
   c->sync_used = 0;
   c->wq.clear();
   c->wq_tiles = 0;
@@ -1321,9 +1327,9 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
     // the first cross-attention block waits for it.
     const void* mem = c->enc.norm[c->enc.blocks.size()];
     need(c, c->kv_b0 + cf.dec_layers - 1);
-    if (c->overlap) side_begin(c);
+    side_begin(c);
     gemm(c, 0, c->enc.rows, c->ld_kv, d, mem, d, wh(c, c->kv_w0), d, c->kv_all, c->ld_kv, wh(c, c->kv_b0), 0, nullptr, nullptr, true);
-    if (c->overlap) c->kv_ready = mark(c, c->side);
+    if (c->beside) c->kv_ready = mark(c, c->side);
   }
   stream_fwd(s, c->dec);
   Stream& de = c->dec;
@@ -1357,7 +1363,7 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
   flush_wgrads(c);                                 // the decoder's weight gradients run beside the encoder's backward pass
   if (has_enc) denc = stream_bwd(s, c->enc, c->dmem);
   flush_wgrads(c);
-  if (c->overlap) order(c, c->side, c->stream);                            // join: every weight gradient is in g
+  if (c->beside) order(c, c->side, c->stream);                             // join: every weight gradient is in g
   if (ad.n) adaptive_embed_bwd(s, ddec);
   run(c, TFM_PROF_EMBED, 0.0, (double)c->esz * d * ((double)Ts + Tt + 2.0 * nu), [&] {
     EmbedBwdArgs ea{};
@@ -1412,7 +1418,7 @@ int tfm_apply_update(tfm_ctx* c, float lr, tfm_update_out* out) {
   a.half_copy = c->dt == F32 ? nullptr : c->Wh; a.hdt = c->dt;
   a.lr = lr; a.beta1 = cf.adam_beta1; a.beta2 = cf.adam_beta2; a.eps = cf.adam_eps; a.weight_decay = cf.weight_decay; a.st = c->st;
   const double bpp = 24.0 + (single ? c->esz : 4.0) + (c->dt == F32 ? 0.0 : 2.0);
-  if (!c->overlap) {
+  if (!c->overlap || out) {                        // (a caller that waits for the update gains nothing from its pieces: 33 launches, 0.1 ms)
     run(c, TFM_PROF_OPTIM, 0.0, (double)c->P * bpp, [&] { launch_adam(c->stream, a); });
   } else {
     c->sync_used = 0;

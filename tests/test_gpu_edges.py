@@ -131,6 +131,30 @@ def test_side_stream_gives_bit_identical_gradients():
         assert np.array_equal(runs[0][1][k], runs[1][1][k]), k
 
 
+def test_side_stream_beside_sub_batches_on_one_stream_gives_bit_identical_results():
+    """Sub-batches on either side of the size from which they use the second stream, in one window and across updates that are and are
+    not waited for."""
+    import paper_1904_01038_amd as T
+    shape = ModelShape(1, 1, 2048, 32, 264, 520)
+    large = make_batches("base", 2, shape=shape, max_tokens=1500, lo=20, hi=90)
+    small = make_batches("base", 2, shape=shape, max_tokens=300, lo=5, hi=40)
+    rows = [int(b.tgt_lens.sum()) * 2048 for b in large + small]
+    assert min(rows[:2]) >= 1 << 21 > max(rows[2:])
+    runs = []
+    for on in (True, False):
+        gpu, _ = make_pair(shape, T.FP16, dropout=0.1, init_loss_scale=4.0, max_sentences=64, max_len=96, max_tokens=2048, seed=5)
+        gpu.set_overlap(on)
+        for i, b in enumerate((large[0], small[0], small[1], large[1], small[0])):
+            gpu.train_step(b.src, b.tgt, b.src_lens, b.tgt_lens, sync=False)
+            if i in (1, 2):
+                gpu.apply_update(1e-3, sync=i == 2)
+        runs.append((gpu.get_grads(), gpu.get_params()))
+        gpu.close()
+    for k in runs[0][0]:
+        assert np.array_equal(runs[0][0][k], runs[1][0][k]), k
+        assert np.array_equal(runs[0][1][k], runs[1][1][k]), k
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp16"])
 def test_model_width_1536(prec):
     """The larger language model's width: three 512-column chunks per row in the normalisation and embedding kernels,
