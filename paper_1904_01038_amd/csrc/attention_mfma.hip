@@ -9,22 +9,18 @@
 // contraction index is the slow one in memory (V for O^T = V^T P^T, K for dQ^T = K^T dS^T, Q and dO for
 // dK^T/dV^T) are staged as they lie and fetched with the CDNA4 LDS transpose read (ds_read_b64_tr_b16).
 //
-// Forward: grid (query chunks of 64, heads, sentences), 2 wavefronts x 32 queries, online softmax over key chunks,
-//          stores the row log-sum-exp.
-// Backward (one launch): blocks [0, nq) along x compute dQ with the forward's decomposition, recomputing P from the
-//           saved log-sum-exp; blocks [nq, nq+nk) own 64-key chunks and loop over query chunks for dK/dV.  No atomics.
+// Forward: up to 64 query rows of a (sentence, head) on 2 wavefronts; longer sentences on blocks of 4 wavefronts and 128 rows.  Online
+//          softmax over key chunks; stores the row log-sum-exp.
+// Backward, longer sentences (one launch): blocks of 128 query rows compute dQ, recomputing P from the saved log-sum-exp; blocks of 128 key
+//           rows loop over query chunks for dK/dV.  No atomics.
 //           Launches whose sentences all fit one chunk use a kernel that forms all three gradients in one block.
 #include "common.h"
 #include "kernels.h"
 
-// Minimum wavefronts per SIMD the register allocation must leave room for.  Left to itself the compiler gives the
-// backward kernel more than 256 registers (one wavefront per SIMD, two blocks per CU), and the kernel is bound by the
-// latency of its dependent load -> product -> softmax chains, which only more resident wavefronts hide.
+// Minimum wavefronts per SIMD the register allocation must leave room for: these kernels are bound by the latency of their dependent
+// load -> product -> softmax chains, which only more resident wavefronts hide.
 #ifndef ATT_FWD_MIN_WAVES
 #define ATT_FWD_MIN_WAVES 3
-#endif
-#ifndef ATT_BWD_MIN_WAVES
-#define ATT_BWD_MIN_WAVES 2
 #endif
 namespace tfm {
 
@@ -303,201 +299,389 @@ __global__ __launch_bounds__(ATT_THREADS, ATT_FWD_MIN_WAVES) void attn_fwd_mfma_
   store_rows<PT>(p.out + (size_t)q0 * p.ldo + h * DH, p.ldo, qstart, lq, Ks);
 }
 
-// ---- backward: dQ ---------------------------------------------------------------------------------------------------------
+// ---- longer sentences ----------------------------------------------------------------------------------------------------
+// Blocks of 4 wavefronts own 128 query rows (forward, dQ) or 128 key rows (dK and dV), 32 a wavefront, and walk the other side in chunks of 64
+// rows.  A chunk's rows are fetched into registers two chunks ahead of their use and written to one of two LDS buffers one ahead, so that
+// a chunk costs one barrier and no wait for memory; 128 own rows halve the chunks that are fetched per product against 64.
+//
+// What bounds these kernels then are the dependent chains of two wavefronts per SIMD (vector ALU 34 % busy, matrix cores 21 %, LDS 35 %), above all
+// the 16 weights a lane between the two products of a 32x32 tile.  So the two tiles of a chunk are in flight together, exponentials are
+// taken to base 2 (one multiply-add and v_exp a weight), only chunks that the causal diagonal or the end of a sentence cuts test their
+// positions, dP's accumulator starts at -delta so that dS = P dP', rows beyond the last query have a log-sum-exp of +infinity and so no
+// weight, and the forward's accumulators are only rescaled when a maximum of the wavefront has moved.
+// us, before (2 wavefronts on 64 rows, every weight tested, the dK/dV half without a chunk in flight) and now: 8 sentences of 512 tokens, 16 heads,
+// causal, forward 21.5 and 16.8, backward 48.6 and 36.9; 3 of 1000, 24 heads, bf16, 54.7 and 32.5, 124 and 69; 4 of 1024, 16 heads, not
+// causal, 47.2 and 33.3, 161 and 97; 30 of 110 12.8 and 12.1, 23.4 and 21.3; 40 of 80 10.6 and 10.4, 24.5 and 25.8.
+constexpr int LT_THREADS = 256, LT_ROWS = 128;
+constexpr float LOG2E = 1.44269504088896341f, LN2 = 0.693147180559945309f;
+
+// 64 rows of 64 columns, 2 vectors a thread (zero beyond nvalid rows; rows at or beyond it are not read)
+__device__ __forceinline__ void fetch_chunk(u32x4 (&x)[2], const uint16_t* __restrict__ G, int ld, int row0, int nvalid) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int v = threadIdx.x + LT_THREADS * i, r = row0 + (v >> 3);
+    const u32x4 y = *reinterpret_cast<const u32x4*>(G + (size_t)min(r, nvalid - 1) * ld + (v & 7) * 8);
+    const uint32_t keep = r < nvalid ? 0xffffffffu : 0u;
+    x[i] = u32x4{y[0] & keep, y[1] & keep, y[2] & keep, y[3] & keep};
+  }
+}
+__device__ __forceinline__ void put_chunk(uint16_t* S, const u32x4 (&x)[2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int v = threadIdx.x + LT_THREADS * i;
+    *reinterpret_cast<u32x4*>(S + (v >> 3) * PT + (v & 7) * 8) = x[i];
+  }
+}
+// 128 parked rows to G, rows at or beyond nvalid left out
+__device__ __forceinline__ void store_rows_long(uint16_t* __restrict__ G, int ld, int row0, int nvalid, const uint16_t* S) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int v = threadIdx.x + LT_THREADS * i;
+    const int r = v >> 3, c = (v & 7) * 8;
+    if (row0 + r < nvalid) *reinterpret_cast<u32x4*>(G + (size_t)(row0 + r) * ld + c) = *reinterpret_cast<const u32x4*>(S + r * PT + c);
+  }
+}
+
 template <typename T, bool DROP>
-__device__ __forceinline__ void attn_bwd_dq_body(const AttnP& p, int b, int h, int chunk, uint16_t* Ks, uint16_t* Vs) {
+__global__ __launch_bounds__(LT_THREADS, 3) void attn_fwd_long_kernel(AttnP p, int H) {
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][CH * PT];                         // (afterwards the parked result: 128 rows)
+  __shared__ __attribute__((aligned(16))) uint16_t Vs[2][CH * PT];
+  // x walks the (sentence, head) pairs and y the query chunks from the last one down: under a causal mask the longest blocks start first
+  const int b = blockIdx.x / H, h = blockIdx.x - b * H;
   const int q0 = p.q_off[b], lq = p.q_off[b + 1] - q0, k0 = p.k_off[b], lk = p.k_off[b + 1] - k0;
-  const int qstart = chunk * 64;
+  const int qstart = ((int)gridDim.y - 1 - (int)blockIdx.y) * LT_ROWS;
   if (qstart >= lq) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
-  const int qi0 = qstart + wave * 32;
-  const bool active = qi0 < lq;
-  const int qi = qi0 + (lane & 31);
+  const int qi0 = qstart + wave * 32, qi = qi0 + (lane & 31);
   const uint16_t* K = p.k + (size_t)k0 * p.ldk + h * DH;
   const uint16_t* V = p.v + (size_t)k0 * p.ldv + h * DH;
-  u32x4 qf[4], gf[4], of[4];
+  const int kend = p.causal ? min(lk, qstart + LT_ROWS) : lk;
+  const int own_end = qi0 >= lq ? 0 : p.causal ? min(lk, qi0 + 32) : lk;                   // keys that this wavefront's queries admit
+  const float c = p.scale * LOG2E;
+  u32x4 kx[2], vx[2], qf[4];
+  fetch_chunk(kx, K, p.ldk, 0, lk);
+  fetch_chunk(vx, V, p.ldv, 0, lk);
   load_frags(qf, p.q + (size_t)q0 * p.ldq + h * DH, p.ldq, qi0, lq, lane);
-  load_frags(gf, p.d_o + (size_t)q0 * p.lddo + h * DH, p.lddo, qi0, lq, lane);
-  load_frags(of, p.o + (size_t)q0 * p.ldo + h * DH, p.ldo, qi0, lq, lane);
-  float delta = 0.f;
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) delta += dot8<T>(gf[kk], of[kk]);
-  delta += __shfl_xor(delta, 32, 64);
-  const float L = qi < lq ? p.lse[(size_t)h * p.total_q + q0 + qi] : 0.f;
+  float m = -INFINITY, lsum = 0.f;                        // running maximum of the scaled scores times log2(e); sum of 2^(score - m)
   f32x16 acc[2];
 #pragma unroll
   for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
-  const int kend = p.causal ? min(lk, qstart + 64) : lk;
-  u32x4 kx[4], vx[4];
-  fetch_tile(kx, K, p.ldk, 0, lk);
-  fetch_tile(vx, V, p.ldv, 0, lk);
-  for (int kc = 0; kc < kend; kc += CH) {
-    __syncthreads();
-    put_tile(Ks, kx);
-    put_tile(Vs, vx);
-    __syncthreads();
-    if (kc + CH < kend) {
-      fetch_tile(kx, K, p.ldk, kc + CH, lk);
-      fetch_tile(vx, V, p.ldv, kc + CH, lk);
-    }
-    if (!active) continue;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const int j0 = kc + kb * 32;
-      if (j0 >= kend) break;
-      f32x16 s, dp;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        s = AMfma<T>::run(frag_direct(Ks, kb * 32, kk, lane), qf[kk], s);
-        dp = AMfma<T>::run(frag_direct(Vs, kb * 32, kk, lane), gf[kk], dp);
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const uint64_t w = DROP ? attn_drop_word(p, q0 + qi, h, j0 + 8 * g + 4 * half) : 0;
-#pragma unroll
-        for (int f = 0; f < 4; ++f) {
-          const int r = g * 4 + f;
-          const int j = j0 + 8 * g + 4 * half + f;
-          const bool ok = j < lk && qi < lq && (!p.causal || j <= qi);
-          const float pr = ok ? __expf(s[r] * p.scale - L) : 0.f;
-          const float dpd = !DROP ? dp[r] : (drop_keep(w, f, p.drop_thr) ? dp[r] * p.inv_keep : 0.f);   // d/d(softmax output)
-          s[r] = pr * (dpd - delta);
-        }
-      }
-      u32x4 df[2];
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) df[ks][w] = AMfma<T>::pack2(s[ks * 8 + 2 * w], s[ks * 8 + 2 * w + 1]);
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int db = 0; db < 2; ++db) acc[db] = AMfma<T>::run(frag_tr(Ks, db * 32, kb * 32 + ks * 16, lane), df[ks], acc[db]);
-    }
+  put_chunk(Ks[0], kx);
+  put_chunk(Vs[0], vx);
+  if (CH < kend) {
+    fetch_chunk(kx, K, p.ldk, CH, lk);
+    fetch_chunk(vx, V, p.ldv, CH, lk);
   }
   __syncthreads();
-  park_rows<T, PT>(Ks, wave * 32 + (lane & 31), half, acc, p.scale);
+  for (int kc = 0, u = 0; kc < kend; kc += CH, u ^= 1) {
+    if (kc + CH < kend) {                                 // (the buffer was last read before the barrier)
+      put_chunk(Ks[u ^ 1], kx);
+      put_chunk(Vs[u ^ 1], vx);
+      if (kc + 2 * CH < kend) {
+        fetch_chunk(kx, K, p.ldk, kc + 2 * CH, lk);
+        fetch_chunk(vx, V, p.ldv, kc + 2 * CH, lk);
+      }
+    }
+    if (kc < own_end) {
+      f32x16 s[2];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[kb][e] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) s[kb] = AMfma<T>::run(frag_direct(Ks[u], kb * 32, kk, lane), qf[kk], s[kb]);
+      }
+      if (kc + CH > lk || (p.causal && kc + CH - 1 > qi0)) {
+        const int last = (p.causal ? min(lk - 1, qi) : lk - 1) - kc - 4 * half;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[kb][r] = kb * 32 + 8 * (r >> 2) + (r & 3) <= last ? s[kb][r] : -INFINITY;
+      }
+      float bm = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+      for (int r = 1; r < 16; ++r) bm = fmaxf(fmaxf(bm, s[0][r]), s[1][r]);
+      bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
+      const float mn = fmaxf(m, bm * c);                  // finite: the first key of a chunk is admitted by every query that takes the chunk
+      if (__any(mn > m)) {
+        const float alpha = __builtin_amdgcn_exp2f(m - mn);
+        lsum *= alpha;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { acc[0][e] *= alpha; acc[1][e] *= alpha; }
+        m = mn;
+      }
+      float ps[2] = {0.f, 0.f};
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { s[kb][r] = __builtin_amdgcn_exp2f(fmaf(s[kb][r], c, -m)); ps[kb] += s[kb][r]; }
+        if (DROP) {                                       // the row sum keeps every weight; only the weights that average V are dropped
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const uint64_t w = attn_drop_word(p, q0 + qi, h, kc + kb * 32 + 8 * g + 4 * half);
+#pragma unroll
+            for (int f = 0; f < 4; ++f) s[kb][g * 4 + f] = drop_keep(w, f, p.drop_thr) ? s[kb][g * 4 + f] * p.inv_keep : 0.f;
+          }
+        }
+        u32x4 pf[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) pf[ks][w] = AMfma<T>::pack2(s[kb][ks * 8 + 2 * w], s[kb][ks * 8 + 2 * w + 1]);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int db = 0; db < 2; ++db) acc[db] = AMfma<T>::run(frag_tr(Vs[u], db * 32, kb * 32 + ks * 16, lane), pf[ks], acc[db]);
+      }
+      lsum += ps[0] + ps[1];
+    }
+    __syncthreads();
+  }
+  lsum += __shfl_xor(lsum, 32, 64);
+  uint16_t* S = &Ks[0][0];
+  park_rows<T, PT>(S, wave * 32 + (lane & 31), half, acc, qi < lq ? 1.f / lsum : 0.f);
+  if (qi < lq && half == 0) p.lse[(size_t)h * p.total_q + q0 + qi] = m * LN2 + logf(lsum);
   __syncthreads();
-  store_rows<PT>(p.dq + (size_t)q0 * p.lddq + h * DH, p.lddq, qstart, lq, Ks);
+  store_rows_long(p.out + (size_t)q0 * p.ldo + h * DH, p.ldo, qstart, lq, S);
 }
 
-// ---- backward: dK, dV -------------------------------------------------------------------------------------------------------
+// dQ of 128 queries
 template <typename T, bool DROP>
-__device__ __forceinline__ void attn_bwd_dkv_body(const AttnP& p, int b, int h, int chunk, uint16_t* Qs, uint16_t* Gs, float* Ls, float* Ds) {
+__device__ __forceinline__ void attn_bwd_dq_body(const AttnP& p, int b, int h, int chunk, uint16_t (*Ks)[CH * PT], uint16_t (*Vs)[CH * PT]) {
   const int q0 = p.q_off[b], lq = p.q_off[b + 1] - q0, k0 = p.k_off[b], lk = p.k_off[b + 1] - k0;
-  const int kstart = chunk * 64;
+  const int qstart = chunk * LT_ROWS;
+  if (qstart >= lq) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const int qi0 = qstart + wave * 32, qi = qi0 + (lane & 31);
+  const uint16_t* K = p.k + (size_t)k0 * p.ldk + h * DH;
+  const uint16_t* V = p.v + (size_t)k0 * p.ldv + h * DH;
+  const int kend = p.causal ? min(lk, qstart + LT_ROWS) : lk;
+  const int own_end = qi0 >= lq ? 0 : p.causal ? min(lk, qi0 + 32) : lk;
+  const float c = p.scale * LOG2E;
+  u32x4 kx[2], vx[2], qf[4], gf[4];
+  fetch_chunk(kx, K, p.ldk, 0, lk);
+  fetch_chunk(vx, V, p.ldv, 0, lk);
+  load_frags(qf, p.q + (size_t)q0 * p.ldq + h * DH, p.ldq, qi0, lq, lane);
+  load_frags(gf, p.d_o + (size_t)q0 * p.lddo + h * DH, p.lddo, qi0, lq, lane);
+  float delta = 0.f;
+  {
+    u32x4 of[4];
+    load_frags(of, p.o + (size_t)q0 * p.ldo + h * DH, p.ldo, qi0, lq, lane);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) delta += dot8<T>(gf[kk], of[kk]);
+    delta += __shfl_xor(delta, 32, 64);
+  }
+  const float L = qi < lq ? p.lse[(size_t)h * p.total_q + q0 + qi] * -LOG2E : 0.f;
+  f32x16 acc[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
+  put_chunk(Ks[0], kx);
+  put_chunk(Vs[0], vx);
+  if (CH < kend) {
+    fetch_chunk(kx, K, p.ldk, CH, lk);
+    fetch_chunk(vx, V, p.ldv, CH, lk);
+  }
+  __syncthreads();
+  for (int kc = 0, u = 0; kc < kend; kc += CH, u ^= 1) {
+    if (kc + CH < kend) {
+      put_chunk(Ks[u ^ 1], kx);
+      put_chunk(Vs[u ^ 1], vx);
+      if (kc + 2 * CH < kend) {
+        fetch_chunk(kx, K, p.ldk, kc + 2 * CH, lk);
+        fetch_chunk(vx, V, p.ldv, kc + 2 * CH, lk);
+      }
+    }
+    if (kc < own_end) {
+      f32x16 s[2], dp[2];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { s[kb][e] = 0.f; dp[kb][e] = DROP ? 0.f : -delta; }
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          s[kb] = AMfma<T>::run(frag_direct(Ks[u], kb * 32, kk, lane), qf[kk], s[kb]);
+          dp[kb] = AMfma<T>::run(frag_direct(Vs[u], kb * 32, kk, lane), gf[kk], dp[kb]);
+        }
+      }
+      if (kc + CH > lk || (p.causal && kc + CH - 1 > qi0)) {
+        const int last = (p.causal ? min(lk - 1, qi) : lk - 1) - kc - 4 * half;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[kb][r] = kb * 32 + 8 * (r >> 2) + (r & 3) <= last ? s[kb][r] : -INFINITY;
+      }
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const uint64_t w = DROP ? attn_drop_word(p, q0 + qi, h, kc + kb * 32 + 8 * g + 4 * half) : 0;
+#pragma unroll
+          for (int f = 0; f < 4; ++f) {
+            const int r = g * 4 + f;
+            const float pr = __builtin_amdgcn_exp2f(fmaf(s[kb][r], c, L));
+            s[kb][r] = pr * (!DROP ? dp[kb][r] : (drop_keep(w, f, p.drop_thr) ? dp[kb][r] * p.inv_keep : 0.f) - delta);
+          }
+        }
+        u32x4 df[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) df[ks][w] = AMfma<T>::pack2(s[kb][ks * 8 + 2 * w], s[kb][ks * 8 + 2 * w + 1]);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int db = 0; db < 2; ++db) acc[db] = AMfma<T>::run(frag_tr(Ks[u], db * 32, kb * 32 + ks * 16, lane), df[ks], acc[db]);
+      }
+    }
+    __syncthreads();
+  }
+  park_rows<T, PT>(Ks[0], wave * 32 + (lane & 31), half, acc, p.scale);
+  __syncthreads();
+  store_rows_long(p.dq + (size_t)q0 * p.lddq + h * DH, p.lddq, qstart, lq, Ks[0]);
+}
+
+// dK and dV of 128 keys.  Ls, Ds: -log2(e) times the log-sum-exp and -delta of a chunk's queries.
+template <typename T, bool DROP>
+__device__ __forceinline__ void attn_bwd_dkv_body(const AttnP& p, int b, int h, int chunk, uint16_t (*Qs)[CH * PT], uint16_t (*Gs)[CH * PT], float (*Ls)[CH],
+                                                  float (*Ds)[CH]) {
+  const int q0 = p.q_off[b], lq = p.q_off[b + 1] - q0, k0 = p.k_off[b], lk = p.k_off[b + 1] - k0;
+  const int kstart = chunk * LT_ROWS;
   if (kstart >= lk) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
-  const int kj0 = kstart + wave * 32;
-  const bool active = kj0 < lk;
-  const int kj = kj0 + (lane & 31);
+  const int kj0 = kstart + wave * 32, kj = kj0 + (lane & 31);
   const uint16_t* Q = p.q + (size_t)q0 * p.ldq + h * DH;
   const uint16_t* G = p.d_o + (size_t)q0 * p.lddo + h * DH;
   const uint16_t* O = p.o + (size_t)q0 * p.ldo + h * DH;
-  u32x4 kf[4], vf[4];
-  load_frags(kf, p.k + (size_t)k0 * p.ldk + h * DH, p.ldk, kj0, lk, lane);
-  load_frags(vf, p.v + (size_t)k0 * p.ldv + h * DH, p.ldv, kj0, lk, lane);
+  const float* lse = p.lse + (size_t)h * p.total_q + q0;
+  const float c = p.scale * LOG2E;
   f32x16 ak[2], av[2];
 #pragma unroll
   for (int e = 0; e < 16; ++e) { ak[0][e] = ak[1][e] = av[0][e] = av[1][e] = 0.f; }
-  const int qbeg = p.causal ? kstart : 0;     // queries before the chunk's first key see none of its keys
-  for (int qc = qbeg; qc < lq; qc += CH) {
+  const int qbeg = p.causal ? kstart : 0;                 // queries before the chunk's first key see none of its keys
+  if (qbeg < lq) {
+    u32x4 qx[2], gx[2], ox[2], kf[4], vf[4];
+    float lx[2];
+    auto fetch = [&](int qc) __attribute__((always_inline)) {
+      fetch_chunk(qx, Q, p.ldq, qc, lq);
+      fetch_chunk(gx, G, p.lddo, qc, lq);
+      fetch_chunk(ox, O, p.ldo, qc, lq);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {                       // (a query beyond the last has no weight: 2^-infinity)
+        const int r = qc + ((threadIdx.x + LT_THREADS * i) >> 3);
+        const float l = lse[min(r, lq - 1)];
+        lx[i] = r < lq ? l * -LOG2E : -INFINITY;
+      }
+    };
+    // the 8 threads that share a row also form delta = dO . O for it
+    auto put = [&](int u) __attribute__((always_inline)) {
+      put_chunk(Qs[u], qx);
+      put_chunk(Gs[u], gx);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        float dl = dot8<T>(gx[i], ox[i]);
+        dl += __shfl_xor(dl, 1, 64);
+        dl += __shfl_xor(dl, 2, 64);
+        dl += __shfl_xor(dl, 4, 64);
+        const int v = threadIdx.x + LT_THREADS * i;
+        if ((v & 7) == 0) { Ds[u][v >> 3] = -dl; Ls[u][v >> 3] = lx[i]; }
+      }
+    };
+    fetch(qbeg);
+    load_frags(kf, p.k + (size_t)k0 * p.ldk + h * DH, p.ldk, kj0, lk, lane);
+    load_frags(vf, p.v + (size_t)k0 * p.ldv + h * DH, p.ldv, kj0, lk, lane);
+    put(0);
+    if (qbeg + CH < lq) fetch(qbeg + CH);
     __syncthreads();
-    // stage Q and dO; the 8 threads that share a row also form delta = dO . O for it
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int v = threadIdx.x + ATT_THREADS * i;
-      const int r = v >> 3, c = (v & 7) * 8;
-      u32x4 xq = {0u, 0u, 0u, 0u}, xg = xq, xo = xq;
-      if (qc + r < lq) {
-        xq = *reinterpret_cast<const u32x4*>(Q + (size_t)(qc + r) * p.ldq + c);
-        xg = *reinterpret_cast<const u32x4*>(G + (size_t)(qc + r) * p.lddo + c);
-        xo = *reinterpret_cast<const u32x4*>(O + (size_t)(qc + r) * p.ldo + c);
+    for (int qc = qbeg, u = 0; qc < lq; qc += CH, u ^= 1) {
+      if (qc + CH < lq) {
+        put(u ^ 1);
+        if (qc + 2 * CH < lq) fetch(qc + 2 * CH);
       }
-      *reinterpret_cast<u32x4*>(Qs + r * PT + c) = xq;
-      *reinterpret_cast<u32x4*>(Gs + r * PT + c) = xg;
-      float dl = dot8<T>(xg, xo);
-      dl += __shfl_xor(dl, 1, 64);
-      dl += __shfl_xor(dl, 2, 64);
-      dl += __shfl_xor(dl, 4, 64);
-      if ((v & 7) == 0) {
-        Ds[r] = dl;
-        Ls[r] = qc + r < lq ? p.lse[(size_t)h * p.total_q + q0 + qc + r] : 0.f;
-      }
-    }
-    __syncthreads();
-    if (!active) continue;
+      if (kj0 < lk && !(p.causal && qc + CH - 1 < kj0)) {
+        f32x16 s[2], dp[2];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      const int i0 = qc + qb * 32;
-      if (i0 >= lq) break;
-      if (p.causal && i0 + 31 < kj0) continue;       // every query of this block precedes every key of this wavefront
-      f32x16 s, dp;
+        for (int qb = 0; qb < 2; ++qb) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+          for (int rg = 0; rg < 4; ++rg) {
+            const float4 d4 = *reinterpret_cast<const float4*>(&Ds[u][qb * 32 + rg * 8 + half * 4]);
+            const float dv[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        s = AMfma<T>::run(frag_direct(Qs, qb * 32, kk, lane), kf[kk], s);
-        dp = AMfma<T>::run(frag_direct(Gs, qb * 32, kk, lane), vf[kk], dp);
-      }
-      u32x4 pf[2], df[2];
+            for (int e = 0; e < 4; ++e) { s[qb][rg * 4 + e] = 0.f; dp[qb][rg * 4 + e] = DROP ? 0.f : dv[e]; }
+          }
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int il = qb * 32 + rg * 8 + half * 4;
-        const float4 l4 = *reinterpret_cast<const float4*>(Ls + il);
-        const float4 d4 = *reinterpret_cast<const float4*>(Ds + il);
-        const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv[4] = {d4.x, d4.y, d4.z, d4.w};
-        float pr[4], dsv[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = qc + il + e;
-          const bool ok = i < lq && kj < lk && (!p.causal || kj <= i);
-          pr[e] = ok ? __expf(s[rg * 4 + e] * p.scale - lv[e]) : 0.f;
-          float dpd = dp[rg * 4 + e];
-          if (DROP) {                                  // this lane's key, one query per register: a word per element
-            const bool keep = drop_keep(attn_drop_word(p, q0 + i, h, kj), kj & 3, p.drop_thr);
-            dpd = keep ? dpd * p.inv_keep : 0.f;
-            dsv[e] = pr[e] * (dpd - dv[e]);
-            pr[e] = keep ? pr[e] * p.inv_keep : 0.f;  // dV averages dO with the dropped weights
-          } else {
-            dsv[e] = pr[e] * (dpd - dv[e]);
+          for (int kk = 0; kk < 4; ++kk) {
+            s[qb] = AMfma<T>::run(frag_direct(Qs[u], qb * 32, kk, lane), kf[kk], s[qb]);
+            dp[qb] = AMfma<T>::run(frag_direct(Gs[u], qb * 32, kk, lane), vf[kk], dp[qb]);
           }
         }
-        pf[rg >> 1][(rg & 1) * 2] = AMfma<T>::pack2(pr[0], pr[1]);
-        pf[rg >> 1][(rg & 1) * 2 + 1] = AMfma<T>::pack2(pr[2], pr[3]);
-        df[rg >> 1][(rg & 1) * 2] = AMfma<T>::pack2(dsv[0], dsv[1]);
-        df[rg >> 1][(rg & 1) * 2 + 1] = AMfma<T>::pack2(dsv[2], dsv[3]);
-      }
+        if (p.causal && qc < kj0 + 31) {
+          const int first = kj - qc - 4 * half;
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
+          for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int db = 0; db < 2; ++db) {
-          av[db] = AMfma<T>::run(frag_tr(Gs, db * 32, qb * 32 + ks * 16, lane), pf[ks], av[db]);
-          ak[db] = AMfma<T>::run(frag_tr(Qs, db * 32, qb * 32 + ks * 16, lane), df[ks], ak[db]);
+            for (int r = 0; r < 16; ++r) s[qb][r] = qb * 32 + 8 * (r >> 2) + (r & 3) >= first ? s[qb][r] : -INFINITY;
         }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          u32x4 pf[2], df[2];
+#pragma unroll
+          for (int rg = 0; rg < 4; ++rg) {
+            const int il = qb * 32 + rg * 8 + half * 4;
+            const float4 l4 = *reinterpret_cast<const float4*>(&Ls[u][il]);
+            const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+            float dv[4] = {0.f, 0.f, 0.f, 0.f};
+            if (DROP) {
+              const float4 d4 = *reinterpret_cast<const float4*>(&Ds[u][il]);
+              dv[0] = d4.x; dv[1] = d4.y; dv[2] = d4.z; dv[3] = d4.w;
+            }
+            float pr[4], ds[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              pr[e] = __builtin_amdgcn_exp2f(fmaf(s[qb][rg * 4 + e], c, lv[e]));
+              const float dpe = dp[qb][rg * 4 + e];
+              if (DROP) {                                 // this lane's key, one query per register: a word per element
+                const bool keep = drop_keep(attn_drop_word(p, q0 + qc + il + e, h, kj), kj & 3, p.drop_thr);
+                ds[e] = pr[e] * ((keep ? dpe * p.inv_keep : 0.f) + dv[e]);
+                pr[e] = keep ? pr[e] * p.inv_keep : 0.f;  // dV averages dO with the dropped weights
+              } else {
+                ds[e] = pr[e] * dpe;
+              }
+            }
+            pf[rg >> 1][(rg & 1) * 2] = AMfma<T>::pack2(pr[0], pr[1]);
+            pf[rg >> 1][(rg & 1) * 2 + 1] = AMfma<T>::pack2(pr[2], pr[3]);
+            df[rg >> 1][(rg & 1) * 2] = AMfma<T>::pack2(ds[0], ds[1]);
+            df[rg >> 1][(rg & 1) * 2 + 1] = AMfma<T>::pack2(ds[2], ds[3]);
+          }
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < 2; ++db) {
+              av[db] = AMfma<T>::run(frag_tr(Gs[u], db * 32, qb * 32 + ks * 16, lane), pf[ks], av[db]);
+              ak[db] = AMfma<T>::run(frag_tr(Qs[u], db * 32, qb * 32 + ks * 16, lane), df[ks], ak[db]);
+            }
+        }
+      }
+      __syncthreads();
     }
   }
+  park_rows<T, PT>(Qs[0], wave * 32 + (lane & 31), half, ak, p.scale);
+  park_rows<T, PT>(Gs[0], wave * 32 + (lane & 31), half, av, 1.f);
   __syncthreads();
-  park_rows<T, PT>(Qs, wave * 32 + (lane & 31), half, ak, p.scale);
-  park_rows<T, PT>(Gs, wave * 32 + (lane & 31), half, av, 1.f);
-  __syncthreads();
-  store_rows<PT>(p.dk + (size_t)k0 * p.lddk + h * DH, p.lddk, kstart, lk, Qs);
-  store_rows<PT>(p.dv + (size_t)k0 * p.lddv + h * DH, p.lddv, kstart, lk, Gs);
+  store_rows_long(p.dk + (size_t)k0 * p.lddk + h * DH, p.lddk, kstart, lk, Qs[0]);
+  store_rows_long(p.dv + (size_t)k0 * p.lddv + h * DH, p.lddv, kstart, lk, Gs[0]);
 }
 
 // One launch for the whole backward: nq_chunks blocks per (sentence, head) compute dQ, nk_chunks dK/dV; the two halves are
 // independent, so they run side by side instead of one after the other.  Blocks are dispatched x fastest: x walks the
-// (sentence, head) pairs and y the chunks in the order of decreasing work under a causal mask (dK/dV of key chunk c loops
-// over n - c query chunks, dQ of query chunk c over c + 1 key chunks), so the longest blocks of the whole launch start
+// (sentence, head) pairs and y the chunks in the order of decreasing work under a causal mask (dK/dV of the first keys loop
+// over all query chunks, dQ of the last queries over all key chunks), so the longest blocks of the whole launch start
 // first and the short ones fill the tail.
 template <typename T, bool DROP>
-__global__ __launch_bounds__(ATT_THREADS, ATT_BWD_MIN_WAVES) void attn_bwd_mfma_kernel(AttnP p, int nq_chunks, int nk_chunks, int H) {
-  __shared__ __attribute__((aligned(16))) uint16_t S0[CH * PT];
-  __shared__ __attribute__((aligned(16))) uint16_t S1[CH * PT];
-  __shared__ __attribute__((aligned(16))) float Ls[CH];
-  __shared__ __attribute__((aligned(16))) float Ds[CH];
+__global__ __launch_bounds__(LT_THREADS, 2) void attn_bwd_long_kernel(AttnP p, int nq_chunks, int nk_chunks, int H) {
+  __shared__ __attribute__((aligned(16))) uint16_t S0[2][CH * PT];                         // (afterwards the parked results: 128 rows each)
+  __shared__ __attribute__((aligned(16))) uint16_t S1[2][CH * PT];
+  __shared__ __attribute__((aligned(16))) float Ls[2][CH];
+  __shared__ __attribute__((aligned(16))) float Ds[2][CH];
   const int b = blockIdx.x / H, h = blockIdx.x - b * H;
   // y = 0, 1, 2, 3, ... -> dK/dV chunk 0, dQ chunk nq-1, dK/dV chunk 1, dQ chunk nq-2, ... while both kinds last
   const int r = blockIdx.y, pairs = min(nq_chunks, nk_chunks);
@@ -734,7 +918,18 @@ void launch_attention_fwd_mfma(hipStream_t s, const AttnArgs& a) {
   // three sentences per tile on; below that the group lookup costs what the saved blocks bring)
   const bool packed = a.groups != nullptr && a.n_groups > 0 && !drop && a.max_lq <= 64 && a.max_lk <= 64 && 3 * a.n_groups <= a.B;
   p.groups = packed ? (const int4*)a.groups : nullptr;
-  dim3 grid(a.H * (packed ? a.n_groups : a.B), (a.max_lq + 63) / 64), block(ATT_THREADS);
+  if (a.max_lq > 64) {
+    const dim3 grid(a.H * a.B, (a.max_lq + LT_ROWS - 1) / LT_ROWS), block(LT_THREADS);
+    if (a.dt == F16) {
+      if (drop) hipLaunchKernelGGL((attn_fwd_long_kernel<half_t, true>), grid, block, 0, s, p, a.H);
+      else hipLaunchKernelGGL((attn_fwd_long_kernel<half_t, false>), grid, block, 0, s, p, a.H);
+    } else {
+      if (drop) hipLaunchKernelGGL((attn_fwd_long_kernel<bf16_t, true>), grid, block, 0, s, p, a.H);
+      else hipLaunchKernelGGL((attn_fwd_long_kernel<bf16_t, false>), grid, block, 0, s, p, a.H);
+    }
+    return;
+  }
+  dim3 grid(a.H * (packed ? a.n_groups : a.B), 1), block(ATT_THREADS);
   if (a.dt == F16) {
     if (drop) hipLaunchKernelGGL((attn_fwd_mfma_kernel<half_t, true, false>), grid, block, 0, s, p, a.H);
     else if (packed) hipLaunchKernelGGL((attn_fwd_mfma_kernel<half_t, false, true>), grid, block, 0, s, p, a.H);
@@ -766,13 +961,14 @@ void launch_attention_bwd_mfma(hipStream_t s, const AttnArgs& a) {
     }
     return;
   }
-  dim3 grid(a.H * a.B, nq + nk), block(ATT_THREADS);
+  const int nql = (a.max_lq + LT_ROWS - 1) / LT_ROWS, nkl = (a.max_lk + LT_ROWS - 1) / LT_ROWS;
+  const dim3 grid(a.H * a.B, nql + nkl), block(LT_THREADS);
   if (a.dt == F16) {
-    if (drop) hipLaunchKernelGGL((attn_bwd_mfma_kernel<half_t, true>), grid, block, 0, s, p, nq, nk, a.H);
-    else hipLaunchKernelGGL((attn_bwd_mfma_kernel<half_t, false>), grid, block, 0, s, p, nq, nk, a.H);
+    if (drop) hipLaunchKernelGGL((attn_bwd_long_kernel<half_t, true>), grid, block, 0, s, p, nql, nkl, a.H);
+    else hipLaunchKernelGGL((attn_bwd_long_kernel<half_t, false>), grid, block, 0, s, p, nql, nkl, a.H);
   } else {
-    if (drop) hipLaunchKernelGGL((attn_bwd_mfma_kernel<bf16_t, true>), grid, block, 0, s, p, nq, nk, a.H);
-    else hipLaunchKernelGGL((attn_bwd_mfma_kernel<bf16_t, false>), grid, block, 0, s, p, nq, nk, a.H);
+    if (drop) hipLaunchKernelGGL((attn_bwd_long_kernel<bf16_t, true>), grid, block, 0, s, p, nql, nkl, a.H);
+    else hipLaunchKernelGGL((attn_bwd_long_kernel<bf16_t, false>), grid, block, 0, s, p, nql, nkl, a.H);
   }
 }
 

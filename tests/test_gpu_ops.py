@@ -442,6 +442,19 @@ def test_attention_forward_backward(prec, dh, case, p_drop, packed):
             assert np.abs(lse[h, qs].cpu().numpy() - ref).max() <= max(tol, 1e-4) * 4
 
 
+@pytest.mark.parametrize("p_drop", [0.0, 0.25])
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("case", [
+    ([129, 1, 128, 127, 193], None, True),                     # one row more and less than a block's 128, chunks of 1 and 63 rows
+    # (no sentence of a single key, whose dK, exactly 0, comes out as the sum over its queries of q (dO . rounding of O) / 8: with |q|,
+    # |dO| ~ 1, 64 columns rounded by 2^-12 / 0.75 and 64 queries a random sum of deviation 0.003 and largest values of 0.016)
+    ([257, 64, 65], [300, 2, 130], False), ([31, 320], [65, 32], True),
+    ([65], [63], False), ([40, 64], [200, 129], False),        # a short side against a long one
+])
+def test_attention_of_longer_sentences(prec, case, p_drop):
+    test_attention_forward_backward(prec, 64, case, p_drop, False)
+
+
 @pytest.mark.parametrize("gprec", ["fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("wd", [0.0, 0.05])
 @pytest.mark.parametrize("n", [8, 4096, 13288])          # less than one lane group, exactly one block, a ragged last block
