@@ -707,7 +707,7 @@ static int k_slices(const GemmArgs& a) {
   const int nk = (a.K + 63) / 64;
   if (a.form == 2 || !a.splitk_ws || a.mask || a.drop_p > 0.f || tiles > 128 || nk < 8) return 1;
   if (a.deferred_splits ? a.relu || a.residual : nk < 40) return 1;                       // (a deferred reduction has neither ReLU nor residual)
-  long n = std::min(std::min(256 / tiles, (long)nk / 4), 64l);
+  long n = std::min(std::min(256 / tiles, (long)nk / 4), a.deferred_splits ? (long)DEFERRED_SPLITS_MAX : 64l);
   while (n > 1 && (size_t)n * a.M * a.N * sizeof(float) > a.splitk_ws_bytes) --n;
   return (int)n;
 }

@@ -283,7 +283,7 @@ static ThinPlan thin_plan(const GemmArgs& a) {
   // deferred reduction.)
   const int least = 64 * THIN_WAVES, need = thin_least_splits(a.K);
   const size_t slice = (size_t)a.M * a.N * 4;
-  q.defer = a.deferred_splits && !a.relu && a.splitk_ws && need * slice <= a.splitk_ws_bytes;
+  q.defer = a.deferred_splits && !a.relu && a.splitk_ws && need <= DEFERRED_SPLITS_MAX && need * slice <= a.splitk_ws_bytes;
   int splits = need;
   if (q.defer) {
     splits = std::max(splits, std::min(std::min(256 / ((a.N + 15) / 16), a.K / least), 4));

@@ -58,6 +58,7 @@ struct GemmArgs {
   // *deferred_splits = 0 and C is complete.
   int* deferred_splits = nullptr;
 };
+constexpr int DEFERRED_SPLITS_MAX = 8;   // slices that the kernels that follow a deferred reduction add up
 void launch_gemm(hipStream_t s, const GemmArgs& a);
 // X W^T for at most THIN_ROWS rows (gemm_thin.hip)
 constexpr int THIN_ROWS = 64;

@@ -84,17 +84,17 @@ __global__ __launch_bounds__(256) void splitk_layernorm_fwd_kernel(
     const int col = (lane + 64 * c) * LN_VEC;
     if (col < d) {
       load_f<T, LN_VEC>(x + base + col, v[c]);
-      // all slices' loads are issued together (at most 8 slices: the split-K launch's own limit), then added in order
-      float t[8][LN_VEC], y[LN_VEC];
+      // all slices' loads are issued together, then added in order
+      float t[DEFERRED_SPLITS_MAX][LN_VEC], y[LN_VEC];
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
+      for (int k = 0; k < DEFERRED_SPLITS_MAX; ++k)
         if (k < splits) load_f<float, LN_VEC>(partial + k * slice + base + col, t[k]);
       load_f<T, LN_VEC>(gamma + col, g[c]);              // with the row's loads: one trip to memory, not two
       load_f<T, LN_VEC>(beta + col, b[c]);
 #pragma unroll
       for (int i = 0; i < LN_VEC; ++i) y[i] = t[0][i];
 #pragma unroll
-      for (int k = 1; k < 8; ++k)
+      for (int k = 1; k < DEFERRED_SPLITS_MAX; ++k)
         if (k < splits) {
 #pragma unroll
           for (int i = 0; i < LN_VEC; ++i) y[i] += t[k][i];

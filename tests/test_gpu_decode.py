@@ -9,6 +9,8 @@ from synth.batches import zipf_ids
 pytestmark = pytest.mark.gpu
 
 SHAPES = {
+    "width_768": ModelShape(0, 1, 768, 12, 3072, 96, pre_norm=1),
+    "long_ffn": ModelShape(0, 1, 64, 1, 18432, 96),
     "post": ModelShape(2, 2, 32, 2, 64, 96),
     "pre": ModelShape(1, 2, 32, 4, 48, 80, pre_norm=1),
     "lm": ModelShape(0, 2, 32, 2, 64, 96, pre_norm=1),
@@ -108,6 +110,13 @@ def test_steps_with_reordered_beams_match_the_full_decoder(name, prec, tol, B=4,
 @pytest.mark.parametrize("name,prec,tol", [("wide", "fp16", 3e-2), ("wide", "bf16", 2e-1), ("wide_dh32", "fp16", 3e-2), ("wide_dh32", "bf16", 2e-1)])
 def test_steps_of_more_than_64_rows_match_the_full_decoder(name, prec, tol):
     test_steps_with_reordered_beams_match_the_full_decoder(name, prec, tol, B=16, beam=5)
+
+
+@pytest.mark.parametrize("prec,tol", [("fp16", 3e-2), ("bf16", 2e-1)])
+@pytest.mark.parametrize("name,B,beam", [("width_768", 16, 5), ("long_ffn", 1, 4)])
+def test_contractions_long_enough_for_more_slices_than_the_next_kernel_adds(name, B, beam, prec, tol):
+    """80 rows x 768 columns leave room for 10 slices of K = 3072; K = 18432 needs 9 slices of a few-row product."""
+    test_steps_with_reordered_beams_match_the_full_decoder(name, prec, tol, B=B, beam=beam)
 
 
 def test_beam_search_on_both_sides_finds_the_same_hypotheses():
