@@ -68,45 +68,52 @@ __global__ __launch_bounds__(256) void residual_layernorm_fwd_kernel(
   }
 }
 
-// s = x + (bias + sum of the fp32 slices); n = gamma * (s - mean) * rstd + beta.  One wavefront per row as above.
-template <typename T, int NCH>
-__global__ __launch_bounds__(256) void splitk_layernorm_fwd_kernel(
+// s = x + (bias + sum of the fp32 slices); n = gamma * (s - mean) * rstd + beta.  A block is one wavefront and one row.  Bound by one trip to
+// memory between two kernels of a decoding step, so everything the row needs is asked for before the first of it is looked at: MAXS slices
+// (the last one again where there are fewer) of all its columns.  With a branch around every slice the second 512 columns waited for the first: 24 rows x
+// 1024, 4 slices 4.8 us, now 3.2; 268 rows, 3 slices 4.4 and 3.4.
+template <typename T, int NCH, int MAXS>
+__global__ __launch_bounds__(64) void splitk_layernorm_fwd_kernel(
     const T* __restrict__ x, const float* __restrict__ partial, int splits, const T* __restrict__ bias,
     const T* __restrict__ gamma, const T* __restrict__ beta, T* __restrict__ s_out, T* __restrict__ n_out, int rows, int d) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
+  const int lane = threadIdx.x, row = blockIdx.x;
   const size_t base = (size_t)row * d, slice = (size_t)rows * d;
-  float v[NCH][LN_VEC], g[NCH][LN_VEC], b[NCH][LN_VEC];
+  Pack<T, LN_VEC> xr[NCH], gr[NCH], br[NCH], hr[NCH];
+  float4 t[NCH][MAXS][2];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    const int col = min((lane + 64 * c) * LN_VEC, d - LN_VEC);
+    xr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(x + base + col);
+#pragma unroll
+    for (int k = 0; k < MAXS; ++k) {
+      const float4* p = reinterpret_cast<const float4*>(partial + min(k, splits - 1) * slice + base + col);
+      t[c][k][0] = p[0];
+      t[c][k][1] = p[1];
+    }
+    gr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(gamma + col);
+    br[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(beta + col);
+    hr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>((bias ? bias : gamma) + col);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  float v[NCH][LN_VEC];
   float sum = 0.f;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int col = (lane + 64 * c) * LN_VEC;
     if (col < d) {
-      load_f<T, LN_VEC>(x + base + col, v[c]);
-      // all slices' loads are issued together, then added in order
-      float t[DEFERRED_SPLITS_MAX][LN_VEC], y[LN_VEC];
+      float y[LN_VEC] = {t[c][0][0].x, t[c][0][0].y, t[c][0][0].z, t[c][0][0].w, t[c][0][1].x, t[c][0][1].y, t[c][0][1].z, t[c][0][1].w};
 #pragma unroll
-      for (int k = 0; k < DEFERRED_SPLITS_MAX; ++k)
-        if (k < splits) load_f<float, LN_VEC>(partial + k * slice + base + col, t[k]);
-      load_f<T, LN_VEC>(gamma + col, g[c]);              // with the row's loads: one trip to memory, not two
-      load_f<T, LN_VEC>(beta + col, b[c]);
-#pragma unroll
-      for (int i = 0; i < LN_VEC; ++i) y[i] = t[0][i];
-#pragma unroll
-      for (int k = 1; k < DEFERRED_SPLITS_MAX; ++k)
+      for (int k = 1; k < MAXS; ++k)                      // in order
         if (k < splits) {
-#pragma unroll
-          for (int i = 0; i < LN_VEC; ++i) y[i] += t[k][i];
+          y[0] += t[c][k][0].x; y[1] += t[c][k][0].y; y[2] += t[c][k][0].z; y[3] += t[c][k][0].w;
+          y[4] += t[c][k][1].x; y[5] += t[c][k][1].y; y[6] += t[c][k][1].z; y[7] += t[c][k][1].w;
         }
       if (bias) {
-        float t[LN_VEC];
-        load_f<T, LN_VEC>(bias + col, t);
 #pragma unroll
-        for (int i = 0; i < LN_VEC; ++i) y[i] += t[i];
+        for (int i = 0; i < LN_VEC; ++i) y[i] += to_f<T>(hr[c].v[i]);
       }
 #pragma unroll
-      for (int i = 0; i < LN_VEC; ++i) v[c][i] += y[i];
+      for (int i = 0; i < LN_VEC; ++i) v[c][i] = to_f<T>(xr[c].v[i]) + y[i];
       if (s_out) {
         store_f<T, LN_VEC>(s_out + base + col, v[c]);
 #pragma unroll
@@ -123,7 +130,7 @@ __global__ __launch_bounds__(256) void splitk_layernorm_fwd_kernel(
     const int col = (lane + 64 * c) * LN_VEC;
     if (col < d) {
 #pragma unroll
-      for (int i = 0; i < LN_VEC; ++i) { const float t = v[c][i] - mu; sq += t * t; }
+      for (int i = 0; i < LN_VEC; ++i) { const float u = v[c][i] - mu; sq += u * u; }
     }
   }
   const float rs = rsqrtf(wave_sum(sq) / (float)d + LN_EPS);
@@ -133,28 +140,35 @@ __global__ __launch_bounds__(256) void splitk_layernorm_fwd_kernel(
     if (col < d) {
       float o[LN_VEC];
 #pragma unroll
-      for (int i = 0; i < LN_VEC; ++i) o[i] = g[c][i] * ((v[c][i] - mu) * rs) + b[c][i];
+      for (int i = 0; i < LN_VEC; ++i) o[i] = to_f<T>(gr[c].v[i]) * ((v[c][i] - mu) * rs) + to_f<T>(br[c].v[i]);
       store_f<T, LN_VEC>(n_out + base + col, o);
     }
   }
 }
 
-template <typename T>
+template <typename T, int MAXS>
 static void splitk_ln_dispatch(hipStream_t s, const void* x, const float* partial, int splits, const void* bias, const void* gamma,
                                const void* beta, void* s_out, void* n_out, int rows, int d) {
-  dim3 grid((rows + 3) / 4), block(256);
   const int nch = (d + 511) / 512;
-#define SLN(N)                                                                                                             \
-  hipLaunchKernelGGL((splitk_layernorm_fwd_kernel<T, N>), grid, block, 0, s, (const T*)x, partial, splits, (const T*)bias, \
+#define SLN(N)                                                                                                                                  \
+  hipLaunchKernelGGL((splitk_layernorm_fwd_kernel<T, N, MAXS>), dim3(rows), dim3(64), 0, s, (const T*)x, partial, splits, (const T*)bias, \
                      (const T*)gamma, (const T*)beta, (T*)s_out, (T*)n_out, rows, d)
   if (nch <= 1) SLN(1); else if (nch == 2) SLN(2); else if (nch == 3) SLN(3); else SLN(4);
 #undef SLN
 }
+template <typename T>
+static void splitk_ln_splits(hipStream_t s, const void* x, const float* partial, int splits, const void* bias, const void* gamma,
+                             const void* beta, void* s_out, void* n_out, int rows, int d) {
+  static_assert(DEFERRED_SPLITS_MAX == 8, "the widest instance");
+  if (splits <= 2) splitk_ln_dispatch<T, 2>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
+  else if (splits <= 4) splitk_ln_dispatch<T, 4>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
+  else splitk_ln_dispatch<T, 8>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
+}
 void launch_splitk_layernorm_fwd(hipStream_t s, int dt, const void* x, const float* partial, int splits, const void* bias,
                                  const void* gamma, const void* beta, void* s_out, void* n_out, int rows, int d) {
   if (rows <= 0) return;
-  if (dt == F16) splitk_ln_dispatch<half_t>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
-  else if (dt == BF16) splitk_ln_dispatch<bf16_t>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
+  if (dt == F16) splitk_ln_splits<half_t>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
+  else if (dt == BF16) splitk_ln_splits<bf16_t>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
   // (split-K launches exist for the 2-byte types only)
 }
 
@@ -296,7 +310,7 @@ __host__ __device__ __forceinline__ int ln_slot_column(int p) { return ((p & 63)
 // The same computation when every row can have a wavefront of its own (rows <= LNB_MAX_BLOCKS * LNR_WAVES): 16
 // wavefronts per block, one row each, no loop.  Nothing is accumulated across rows, so the three per-column
 // quantities go from the row's registers straight into the block's LDS reduction, the register footprint stays below
-// 128 and a row's two dependent passes are the whole critical path.
+// 128 and a row's two dependent passes are the whole critical path.  (d = 512 NCH: every lane has all its columns.)
 constexpr int LNR_WAVES = 16;
 
 template <typename T, int NCH>
@@ -304,7 +318,7 @@ __global__ __launch_bounds__(64 * LNR_WAVES) void layernorm_bwd_row_kernel(
     const T* __restrict__ dn, const T* __restrict__ add, const T* __restrict__ sres, const float* __restrict__ mean,
     const float* __restrict__ rstd, const T* __restrict__ gamma, T* __restrict__ ds, T* __restrict__ ds_drop,
     float* __restrict__ partial, int rows, int d, uint64_t key, uint32_t thr, float inv_keep, int nk) {
-  extern __shared__ float lds[];     // [LNR_WAVES][d]
+  __shared__ float lds[2][LNR_WAVES][512];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int row = blockIdx.x * LNR_WAVES + w;
   const bool live = row < rows;
@@ -315,66 +329,69 @@ __global__ __launch_bounds__(64 * LNR_WAVES) void layernorm_bwd_row_kernel(
 #pragma unroll
     for (int i = 0; i < LN_VEC; ++i) a[c][i] = xh[c][i] = o[c][i] = 0.f;
   if (live) {
+    // all of the row's operands in one trip to memory, also what is only added at the end
     const float mu = mean[row], rs = rstd[row];
-    float s1 = 0.f, s2 = 0.f;
+    Pack<T, LN_VEC> ar[NCH], br[NCH], gr[NCH], tr[NCH];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int col = (lane + 64 * c) * LN_VEC;
-      if (col < d) {
-        float b[LN_VEC], g[LN_VEC];
-        load_f<T, LN_VEC>(dn + base + col, a[c]);
-        load_f<T, LN_VEC>(sres + base + col, b);
-        load_f<T, LN_VEC>(gamma + col, g);
+      ar[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(dn + base + col);
+      br[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(sres + base + col);
+      tr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>((add ? add : dn) + base + col);
+      gr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(gamma + col);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-        for (int i = 0; i < LN_VEC; ++i) {
-          xh[c][i] = (b[i] - mu) * rs;
-          o[c][i] = a[c][i] * g[i];                      // dxhat, turned into ds below
-          s1 += o[c][i];
-          s2 += o[c][i] * xh[c][i];
-        }
+    for (int c = 0; c < NCH; ++c) {
+#pragma unroll
+      for (int i = 0; i < LN_VEC; ++i) {
+        a[c][i] = to_f<T>(ar[c].v[i]);
+        xh[c][i] = (to_f<T>(br[c].v[i]) - mu) * rs;
+        o[c][i] = a[c][i] * to_f<T>(gr[c].v[i]);         // dxhat, turned into ds below
+        s1 += o[c][i];
+        s2 += o[c][i] * xh[c][i];
       }
     }
     const float c1 = wave_sum(s1) / (float)d, c2 = wave_sum(s2) / (float)d;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int col = (lane + 64 * c) * LN_VEC;
-      if (col < d) {
 #pragma unroll
-        for (int i = 0; i < LN_VEC; ++i) o[c][i] = rs * (o[c][i] - c1 - xh[c][i] * c2);
-        if (add) {
-          float t[LN_VEC];
-          load_f<T, LN_VEC>(add + base + col, t);
+      for (int i = 0; i < LN_VEC; ++i) o[c][i] = rs * (o[c][i] - c1 - xh[c][i] * c2);
+      if (add) {
 #pragma unroll
-          for (int i = 0; i < LN_VEC; ++i) o[c][i] += t[i];
-        }
-        store_f<T, LN_VEC>(ds + base + col, o[c]);
-        if (thr) {
-          drop_apply<LN_VEC>(o[c], key, base + col, thr, inv_keep);
-          store_f<T, LN_VEC>(ds_drop + base + col, o[c]);
-        }
-        // the consumers read the rounded value; sum exactly what they will see
-#pragma unroll
-        for (int i = 0; i < LN_VEC; ++i) o[c][i] = to_f<T>(from_f<T>(o[c][i]));
+        for (int i = 0; i < LN_VEC; ++i) o[c][i] += to_f<T>(tr[c].v[i]);
       }
+      store_f<T, LN_VEC>(ds + base + col, o[c]);
+      if (thr) {
+        drop_apply<LN_VEC>(o[c], key, base + col, thr, inv_keep);
+        store_f<T, LN_VEC>(ds_drop + base + col, o[c]);
+      }
+      // the consumers read the rounded value; sum exactly what they will see
+#pragma unroll
+      for (int i = 0; i < LN_VEC; ++i) o[c][i] = to_f<T>(from_f<T>(o[c][i]));
     }
   }
-  for (int k = 0; k < nk; ++k) {                        // nk = 2: the bias sum is not wanted
-    __syncthreads();
+  // 512 columns of one quantity at a time, in two LDS stages by turns: a stage is written again only after the barrier behind which every
+  // wavefront has read it, so that a stage costs one barrier.
+  int u = 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if (k == nk) break;                                   // nk = 2: the bias sum is not wanted
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int col = (lane + 64 * c) * LN_VEC;
-      if (col < d) {
 #pragma unroll
-        for (int i = 0; i < LN_VEC; ++i)                  // slot (c, i, lane): consecutive lanes, consecutive banks
-          lds[w * d + c * 512 + i * 64 + lane] = k == 0 ? a[c][i] * xh[c][i] : (k == 1 ? a[c][i] : o[c][i]);
+      for (int i = 0; i < LN_VEC; ++i)                    // slot (c, i, lane): consecutive lanes, consecutive banks
+        lds[u][w][i * 64 + lane] = k == 0 ? a[c][i] * xh[c][i] : (k == 1 ? a[c][i] : o[c][i]);
+      __syncthreads();
+      if (threadIdx.x < 512) {                            // partials stay in slot order (see ln_slot_column)
+        float t = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < LNR_WAVES; ++ww) t += lds[u][ww][threadIdx.x];
+        partial[((size_t)blockIdx.x * 3 + k) * d + c * 512 + threadIdx.x] = t;
       }
-    }
-    __syncthreads();
-    for (int slot = threadIdx.x; slot < d; slot += 64 * LNR_WAVES) {    // partials stay in slot order (see ln_slot_column)
-      float t = 0.f;
-#pragma unroll
-      for (int ww = 0; ww < LNR_WAVES; ++ww) t += lds[ww * d + slot];
-      partial[((size_t)blockIdx.x * 3 + k) * d + slot] = t;
+      u ^= 1;
     }
   }
 }
@@ -441,14 +458,15 @@ static void ln_bwd_dispatch(hipStream_t s, const void* dn, const void* add, cons
   const uint32_t thr = (p > 0.f && ds_drop) ? drop_threshold(p) : 0u;
   const float inv_keep = 1.f / (1.f - p);
   const int nch = (d + 511) / 512;
-  if (rows <= LNB_MAX_BLOCKS * LNR_WAVES && d % 512 == 0 && nch <= 2) {   // a wavefront per row (its LDS stage stays within 64 KB)
+  // A wavefront per row, as far as its registers allow 16 of them: 3000 rows of 1536 34.0 us in the looping kernel, now 14.2.  (3264 rows of
+  // 1024 11.5 us before the LDS stages took turns and the added gradient came with the row, now 10.2; 280 rows 8.6 and 7.2.)
+  if (rows <= LNB_MAX_BLOCKS * LNR_WAVES && d % 512 == 0 && nch <= 3) {
     const int nbr = (rows + LNR_WAVES - 1) / LNR_WAVES;
-    const size_t shr = (size_t)LNR_WAVES * d * sizeof(float);
 #define LN_BWD_ROW(N)                                                                                                   \
-  hipLaunchKernelGGL((layernorm_bwd_row_kernel<T, N>), dim3(nbr), dim3(64 * LNR_WAVES), shr, s, (const T*)dn, (const T*)add,        \
+  hipLaunchKernelGGL((layernorm_bwd_row_kernel<T, N>), dim3(nbr), dim3(64 * LNR_WAVES), 0, s, (const T*)dn, (const T*)add,        \
                      (const T*)sres, mean, rstd, (const T*)gamma, (T*)ds, (T*)ds_drop, (float*)scratch, rows, d, key, thr, \
                      inv_keep, nk)
-    if (nch <= 1) LN_BWD_ROW(1); else LN_BWD_ROW(2);
+    if (nch <= 1) LN_BWD_ROW(1); else if (nch == 2) LN_BWD_ROW(2); else LN_BWD_ROW(3);
 #undef LN_BWD_ROW
     if (defer) { *defer = LnReduceJob{(const float*)scratch, nbr, 1, dgamma, dbeta, dbias}; return; }
     hipLaunchKernelGGL((reduce_partials_kernel<T>), dim3((d + 31) / 32, 3), dim3(32 * RP_LANES), 0, s, (const float*)scratch, nbr, 3, d,
