@@ -98,19 +98,8 @@ __device__ __forceinline__ u32x4 frag_tr(const uint16_t* S, int c0, int kbase, i
   const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
   return u32x4{l2[0], l2[1], h2[0], h2[1]};
 }
-// 64 rows x 64 columns from global (row stride ld) into LDS, zero beyond nvalid rows.  128 threads, 4 vectors each.
-template <int P = PT>
-__device__ __forceinline__ void stage_tile(uint16_t* S, const uint16_t* __restrict__ G, int ld, int row0, int nvalid) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int v = threadIdx.x + ATT_THREADS * i;
-    const int r = v >> 3, c = (v & 7) * 8;
-    u32x4 x = {0u, 0u, 0u, 0u};
-    if (row0 + r < nvalid) x = *reinterpret_cast<const u32x4*>(G + (size_t)(row0 + r) * ld + c);
-    *reinterpret_cast<u32x4*>(S + r * P + c) = x;
-  }
-}
-// The same in two halves, so that the next chunk's rows travel from memory while the current chunk is being used.
+// 64 rows x 64 columns (row stride ld) from global into registers and from there into LDS, zero beyond nvalid rows, 128 threads: the next
+// chunk's rows travel from memory while the current chunk is being used.
 __device__ __forceinline__ void fetch_tile(u32x4 (&x)[4], const uint16_t* __restrict__ G, int ld, int row0, int nvalid) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -174,11 +163,11 @@ __device__ __forceinline__ void park_rows(uint16_t* S, int r, int half, const f3
                 acc[db][rg * 4 + 3] * mul);
 }
 // rows [row0, row0 + 64) of the parked tile to G (row stride ld), rows at or beyond nvalid left out
-template <int P>
+template <int P, int THREADS = ATT_THREADS>
 __device__ __forceinline__ void store_rows(uint16_t* __restrict__ G, int ld, int row0, int nvalid, const uint16_t* S) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int v = threadIdx.x + ATT_THREADS * i;
+  for (int i = 0; i < 512 / THREADS; ++i) {
+    const int v = threadIdx.x + THREADS * i;
     const int r = v >> 3, c = (v & 7) * 8;
     if (row0 + r < nvalid) *reinterpret_cast<u32x4*>(G + (size_t)(row0 + r) * ld + c) = *reinterpret_cast<const u32x4*>(S + r * P + c);
   }
@@ -325,11 +314,12 @@ __device__ __forceinline__ void fetch_chunk(u32x4 (&x)[2], const uint16_t* __res
     x[i] = u32x4{y[0] & keep, y[1] & keep, y[2] & keep, y[3] & keep};
   }
 }
+template <int P = PT>
 __device__ __forceinline__ void put_chunk(uint16_t* S, const u32x4 (&x)[2]) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int v = threadIdx.x + LT_THREADS * i;
-    *reinterpret_cast<u32x4*>(S + (v >> 3) * PT + (v & 7) * 8) = x[i];
+    *reinterpret_cast<u32x4*>(S + (v >> 3) * P + (v & 7) * 8) = x[i];
   }
 }
 // 128 parked rows to G, rows at or beyond nvalid left out
@@ -701,15 +691,19 @@ __global__ __launch_bounds__(LT_THREADS, 2) void attn_bwd_long_kernel(AttnP p, i
 // keys against Q, dO (dK, dV).  The scores are formed in both orientations by the matrix cores, which are nearly idle in
 // this kernel anyway, so nothing is transposed through LDS; the operand fragments of the block's own rows also come from
 // the staged tiles, so every input is read from memory exactly once.  Four tiles at a 144-byte pitch (16 rows x 16
-// bytes cover the 64 banks once) keep four blocks resident per CU.
-constexpr int PF = 72;
+// bytes cover the 64 banks once) keep four blocks resident per CU.  Bound by the chain load -> products -> weights -> products -> store of a
+// block, so two wavefronts form dQ while two others form dK and dV (on the 64 + 64 rows, 32 each), and weights are exponentials to base 2 of
+// one multiply-add, with dP's accumulator starting at -delta.  us inside a training step, both halves on two wavefronts and now: 64 sentences of ~50,
+// 16 heads 21.0 and 18.3; 88 of ~40, 8 heads, bf16 18.7 and 12.5; 13 in 5 tiles 15.3 and 6.7.  (Three wavefronts a SIMD: held to four, the
+// registers of the dK/dV half spill and the first two become 20.4 and 15.8.)
+constexpr int PF = 72, SG_THREADS = 256;
 
 // Short sentences are packed: a block serves a run of consecutive sentences whose query rows and key rows (contiguous in the
 // packed token layout) fill at most one 64-row tile each.  The products are formed over the whole tile; a weight counts
 // only where query and key belong to the same sentence, which each row looks up as the range of admissible partners
 // (QR: keys of a query's sentence, KR: queries of a key's sentence, both relative to the tile).
 template <typename T, bool DROP, bool PACK>
-__global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_single_kernel(AttnP p) {
+__global__ __launch_bounds__(SG_THREADS, 3) void attn_bwd_single_kernel(AttnP p) {
   __shared__ __attribute__((aligned(16))) uint16_t Ks[CH * PF];
   __shared__ __attribute__((aligned(16))) uint16_t Vs[CH * PF];
   __shared__ __attribute__((aligned(16))) uint16_t Qs[CH * PF];
@@ -745,50 +739,51 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_single_kernel(AttnP p
     KR[r] = kr;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
-  const int own0 = wave * 32;                        // first own row of this wavefront (a query for dQ, a key for dK/dV)
+  const int own0 = (wave & 1) * 32;                  // first own row of this wavefront (a query for dQ, a key for dK/dV)
   const int own = own0 + (lane & 31);
-  const uint16_t* Q = p.q + (size_t)q0 * p.ldq + h * DH;
-  const uint16_t* G = p.d_o + (size_t)q0 * p.lddo + h * DH;
-  const uint16_t* O = p.o + (size_t)q0 * p.ldo + h * DH;
-  stage_tile<PF>(Ks, p.k + (size_t)k0 * p.ldk + h * DH, p.ldk, 0, lk);
-  stage_tile<PF>(Vs, p.v + (size_t)k0 * p.ldv + h * DH, p.ldv, 0, lk);
-  // stage Q and dO; the 8 threads that share a row also form delta = dO . O for it
+  const bool queries = wave < 2;
+  const float c = p.scale * LOG2E;
+  {
+    u32x4 kx[2], vx[2], qx[2], gx[2], ox[2];
+    fetch_chunk(kx, p.k + (size_t)k0 * p.ldk + h * DH, p.ldk, 0, lk);
+    fetch_chunk(vx, p.v + (size_t)k0 * p.ldv + h * DH, p.ldv, 0, lk);
+    fetch_chunk(qx, p.q + (size_t)q0 * p.ldq + h * DH, p.ldq, 0, lq);
+    fetch_chunk(gx, p.d_o + (size_t)q0 * p.lddo + h * DH, p.lddo, 0, lq);
+    fetch_chunk(ox, p.o + (size_t)q0 * p.ldo + h * DH, p.ldo, 0, lq);
+    float lx[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int v = threadIdx.x + ATT_THREADS * i;
-    const int r = v >> 3, cc = (v & 7) * 8;
-    u32x4 xq = {0u, 0u, 0u, 0u}, xg = xq, xo = xq;
-    if (r < lq) {
-      xq = *reinterpret_cast<const u32x4*>(Q + (size_t)r * p.ldq + cc);
-      xg = *reinterpret_cast<const u32x4*>(G + (size_t)r * p.lddo + cc);
-      xo = *reinterpret_cast<const u32x4*>(O + (size_t)r * p.ldo + cc);
-    }
-    *reinterpret_cast<u32x4*>(Qs + r * PF + cc) = xq;
-    *reinterpret_cast<u32x4*>(Gs + r * PF + cc) = xg;
-    float dl = dot8<T>(xg, xo);
-    dl += __shfl_xor(dl, 1, 64);
-    dl += __shfl_xor(dl, 2, 64);
-    dl += __shfl_xor(dl, 4, 64);
-    if ((v & 7) == 0) {
-      Ds[r] = dl;
-      Ls[r] = r < lq ? p.lse[(size_t)h * p.total_q + q0 + r] : 0.f;
+    for (int i = 0; i < 2; ++i) lx[i] = p.lse[(size_t)h * p.total_q + q0 + min((int)(threadIdx.x + SG_THREADS * i) >> 3, lq - 1)];
+    put_chunk<PF>(Ks, kx);
+    put_chunk<PF>(Vs, vx);
+    put_chunk<PF>(Qs, qx);
+    put_chunk<PF>(Gs, gx);
+    // the 8 threads that share a row also form delta = dO . O for it
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int v = threadIdx.x + SG_THREADS * i, r = v >> 3;
+      float dl = dot8<T>(gx[i], ox[i]);
+      dl += __shfl_xor(dl, 1, 64);
+      dl += __shfl_xor(dl, 2, 64);
+      dl += __shfl_xor(dl, 4, 64);
+      if ((v & 7) == 0) { Ds[r] = -dl; Ls[r] = lx[i] * -LOG2E; }
     }
   }
   __syncthreads();
-  f32x16 aq[2], ak[2], av[2];
+  f32x16 a0[2], a1[2];                               // dQ, or dK and dV
 #pragma unroll
-  for (int e = 0; e < 16; ++e) { aq[0][e] = aq[1][e] = ak[0][e] = ak[1][e] = av[0][e] = av[1][e] = 0.f; }
-  if (own0 < lq) {
+  for (int e = 0; e < 16; ++e) { a0[0][e] = a0[1][e] = a1[0][e] = a1[1][e] = 0.f; }
+  if (queries && own0 < lq) {
     // dQ^T[d][query] = K^T dS^T with S^T[key][query]: a lane owns one query, 16 keys in registers
-    const float delta = Ds[own], L = Ls[own];
+    const float delta = Ds[own], L = Ls[own];        // (-delta, -log2(e) lse)
     const int klo = QR[own] & 0xff, khi = (QR[own] >> 8) & 0xff, qpos = own - (QR[own] >> 16);   // position inside the sentence
+    const int kfirst = klo - 4 * half, klast = (p.causal ? min(khi - 1, klo + qpos) : khi - 1) - 4 * half;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       const int j0 = kb * 32;
       if (j0 >= lk) break;
       f32x16 s, dp;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = DROP ? 0.f : delta; }
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         s = AMfma<T>::run(frag_direct<PF>(Ks, j0, kk, lane), frag_direct<PF>(Qs, own0, kk, lane), s);
@@ -800,12 +795,10 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_single_kernel(AttnP p
         const uint64_t w = DROP ? attn_drop_word(p, q0 + own, h, j0 + 8 * g + 4 * half) : 0;
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
-          const int r = g * 4 + f;
-          const int jj = j0 + 8 * g + 4 * half + f;
-          const bool ok = jj >= klo && jj < khi && (!p.causal || jj - klo <= qpos);
-          const float pr = ok ? __expf(s[r] * p.scale - L) : 0.f;
-          const float dpd = !DROP ? dp[r] : (drop_keep(w, f, p.drop_thr) ? dp[r] * p.inv_keep : 0.f);
-          s[r] = pr * (dpd - delta);
+          const int r = g * 4 + f, jj = j0 + 8 * g + f;
+          const bool ok = jj <= klast && (!PACK || jj >= kfirst);
+          const float pr = ok ? __builtin_amdgcn_exp2f(fmaf(s[r], c, L)) : 0.f;
+          s[r] = pr * (!DROP ? dp[r] : (drop_keep(w, f, p.drop_thr) ? dp[r] * p.inv_keep : 0.f) + delta);
         }
       }
       u32x4 df[2];
@@ -816,12 +809,13 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_single_kernel(AttnP p
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int db = 0; db < 2; ++db) aq[db] = AMfma<T>::run(frag_tr<PF>(Ks, db * 32, j0 + ks * 16, lane), df[ks], aq[db]);
+        for (int db = 0; db < 2; ++db) a0[db] = AMfma<T>::run(frag_tr<PF>(Ks, db * 32, j0 + ks * 16, lane), df[ks], a0[db]);
     }
   }
-  if (own0 < lk) {
+  if (!queries && own0 < lk) {
     // dK^T[d][key] = Q^T dS, dV^T[d][key] = dO^T P with S[query][key]: a lane owns one key, 16 queries in registers
     const int qlo = KR[own] & 0xff, qhi = (KR[own] >> 8) & 0xff, kpos = own - (KR[own] >> 16);
+    const int qfirst = (p.causal ? qlo + kpos : qlo) - 4 * half, qlast = qhi - 1 - 4 * half;
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
       const int i0 = qb * 32;
@@ -829,7 +823,12 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_single_kernel(AttnP p
       if (p.causal && !PACK && i0 + 31 < own0) continue;      // (one sentence) every query of this block precedes every key of this wavefront
       f32x16 s, dp;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+      for (int rg = 0; rg < 4; ++rg) {
+        const float4 d4 = *reinterpret_cast<const float4*>(Ds + i0 + rg * 8 + half * 4);
+        const float dv[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { s[rg * 4 + e] = 0.f; dp[rg * 4 + e] = DROP ? 0.f : dv[e]; }
+      }
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         s = AMfma<T>::run(frag_direct<PF>(Qs, i0, kk, lane), frag_direct<PF>(Ks, own0, kk, lane), s);
@@ -840,22 +839,25 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_single_kernel(AttnP p
       for (int rg = 0; rg < 4; ++rg) {
         const int il = i0 + rg * 8 + half * 4;
         const float4 l4 = *reinterpret_cast<const float4*>(Ls + il);
-        const float4 d4 = *reinterpret_cast<const float4*>(Ds + il);
-        const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv[4] = {d4.x, d4.y, d4.z, d4.w};
+        const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+        float dv[4] = {0.f, 0.f, 0.f, 0.f};
+        if (DROP) {
+          const float4 d4 = *reinterpret_cast<const float4*>(Ds + il);
+          dv[0] = d4.x; dv[1] = d4.y; dv[2] = d4.z; dv[3] = d4.w;
+        }
         float pr[4], dsv[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int i = il + e;
-          const bool ok = i >= qlo && i < qhi && (!p.causal || kpos <= i - qlo);
-          pr[e] = ok ? __expf(s[rg * 4 + e] * p.scale - lv[e]) : 0.f;
-          float dpd = dp[rg * 4 + e];
+          const int i = i0 + rg * 8 + e;
+          const bool ok = i >= qfirst && i <= qlast;
+          pr[e] = ok ? __builtin_amdgcn_exp2f(fmaf(s[rg * 4 + e], c, lv[e])) : 0.f;
+          const float dpe = dp[rg * 4 + e];
           if (DROP) {
-            const bool keep = drop_keep(attn_drop_word(p, q0 + i, h, own), own & 3, p.drop_thr);
-            dpd = keep ? dpd * p.inv_keep : 0.f;
-            dsv[e] = pr[e] * (dpd - dv[e]);
+            const bool keep = drop_keep(attn_drop_word(p, q0 + il + e, h, own), own & 3, p.drop_thr);
+            dsv[e] = pr[e] * ((keep ? dpe * p.inv_keep : 0.f) + dv[e]);
             pr[e] = keep ? pr[e] * p.inv_keep : 0.f;
           } else {
-            dsv[e] = pr[e] * (dpd - dv[e]);
+            dsv[e] = pr[e] * dpe;
           }
         }
         pf[rg >> 1][(rg & 1) * 2] = AMfma<T>::pack2(pr[0], pr[1]);
@@ -867,19 +869,21 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_single_kernel(AttnP p
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int db = 0; db < 2; ++db) {
-          av[db] = AMfma<T>::run(frag_tr<PF>(Gs, db * 32, i0 + ks * 16, lane), pf[ks], av[db]);
-          ak[db] = AMfma<T>::run(frag_tr<PF>(Qs, db * 32, i0 + ks * 16, lane), df[ks], ak[db]);
+          a1[db] = AMfma<T>::run(frag_tr<PF>(Gs, db * 32, i0 + ks * 16, lane), pf[ks], a1[db]);
+          a0[db] = AMfma<T>::run(frag_tr<PF>(Qs, db * 32, i0 + ks * 16, lane), df[ks], a0[db]);
         }
     }
   }
   __syncthreads();                                   // the tiles are no longer needed: park the three results in them
-  park_rows<T, PF>(Qs, own, half, aq, p.scale);
-  park_rows<T, PF>(Ks, own, half, ak, p.scale);
-  park_rows<T, PF>(Vs, own, half, av, 1.f);
+  if (queries) park_rows<T, PF>(Qs, own, half, a0, p.scale);
+  else {
+    park_rows<T, PF>(Ks, own, half, a0, p.scale);
+    park_rows<T, PF>(Vs, own, half, a1, 1.f);
+  }
   __syncthreads();
-  store_rows<PF>(p.dq + (size_t)q0 * p.lddq + h * DH, p.lddq, 0, lq, Qs);
-  store_rows<PF>(p.dk + (size_t)k0 * p.lddk + h * DH, p.lddk, 0, lk, Ks);
-  store_rows<PF>(p.dv + (size_t)k0 * p.lddv + h * DH, p.lddv, 0, lk, Vs);
+  store_rows<PF, SG_THREADS>(p.dq + (size_t)q0 * p.lddq + h * DH, p.lddq, 0, lq, Qs);
+  store_rows<PF, SG_THREADS>(p.dk + (size_t)k0 * p.lddk + h * DH, p.lddk, 0, lk, Ks);
+  store_rows<PF, SG_THREADS>(p.dv + (size_t)k0 * p.lddv + h * DH, p.lddv, 0, lk, Vs);
 }
 
 static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -949,7 +953,7 @@ void launch_attention_bwd_mfma(hipStream_t s, const AttnArgs& a) {
     // (the backward kernel gains from 1.5 sentences per tile on: 41 -> 20 us at 11-token sentences, 27 -> 19 us at 21 tokens)
     const bool packed = a.groups != nullptr && a.n_groups > 0 && !drop && 3 * a.n_groups <= 2 * a.B;
     p.groups = packed ? (const int4*)a.groups : nullptr;
-    dim3 grid(1, a.H, packed ? a.n_groups : a.B), block(ATT_THREADS);
+    dim3 grid(1, a.H, packed ? a.n_groups : a.B), block(SG_THREADS);
     if (a.dt == F16) {
       if (drop) hipLaunchKernelGGL((attn_bwd_single_kernel<half_t, true, false>), grid, block, 0, s, p);
       else if (packed) hipLaunchKernelGGL((attn_bwd_single_kernel<half_t, false, true>), grid, block, 0, s, p);
