@@ -22,6 +22,7 @@ struct DevState {
   // last scan
   float scan_flag;           // 1.0 if a non-finite value was seen
   double scan_sumsq;         // sum of squares of the scanned buffer
+  double window_sumsq;       // sum of squares of the window's accumulated gradient, from its second sub-batch on
   // last tfm_apply_update
   int skipped;
   float grad_norm;
@@ -176,9 +177,12 @@ void launch_embed_bwd(hipStream_t s, const EmbedBwdArgs& a);
 
 size_t scan_scratch_bytes(int64_t n);
 // flag/sumsq of x[n] -> result[0], result[1] (fp32) and, if st != null, st->scan_flag / scan_sumsq and
-// st->step_overflow / window_overflow (|=).  If acc != null: acc = x (acc_mode 1) or acc += x (acc_mode 2), fp32.
-void launch_scan(hipStream_t s, int dt, const void* x, int64_t n, float* result, DevState* st, float* acc, int acc_mode,
-                 void* scratch);
+// st->step_overflow / window_overflow (|=).
+void launch_scan(hipStream_t s, int dt, const void* x, int64_t n, float* result, DevState* st, void* scratch);
+size_t accumulate_scratch_bytes(int64_t n);
+// The same for the second or a later sub-batch of a window: also acc += x, or acc = first + x where `first` is given, in fp32, and
+// st->window_sumsq = the sum of squares of acc.  n a multiple of 8.
+void launch_accumulate(hipStream_t s, int dt, const void* x, const void* first, float* acc, int64_t n, DevState* st, void* scratch);
 void launch_convert(hipStream_t s, int src_dt, const void* src, int dst_dt, void* dst, int64_t n);
 
 struct AdamArgs {
@@ -189,9 +193,10 @@ struct AdamArgs {
   float grad_mult, bc1, bc2;
 };
 void launch_adam(hipStream_t s, const AdamArgs& a);
-// One-thread kernel: the loss-scale state machine and the Adam step scalars.
+// One-thread kernel: the loss-scale state machine and the Adam step scalars.  accumulated: the window's gradient is the sum that
+// launch_accumulate left, otherwise the one that launch_scan has seen.
 void launch_scaler_update(hipStream_t s, DevState* st, long long ntokens, float clip_norm, float beta1, float beta2,
-                          int scale_window, float min_scale, int dynamic);
+                          int scale_window, float min_scale, int dynamic, int accumulated);
 void launch_dropout_mask(hipStream_t s, uint64_t key, float p, uint8_t* out, int64_t n);
 
 // ---- incremental decoding ---------------------------------------------------------------------------------------------

@@ -1,4 +1,4 @@
-// Inf/nan scan (+ optional accumulation into the fp32 window buffer), the loss-scale state machine, and the fp32
+// Inf/nan scan, accumulation into the fp32 window buffer, the loss-scale state machine, and the fp32
 // master-weight Adam update.  All HBM-bound streaming kernels with 16-byte accesses; reductions use per-block
 // partials added in a fixed order (no floating-point atomics), so every result is reproducible.
 #include <mutex>
@@ -20,10 +20,9 @@ static int scan_blocks(int64_t n) {
 }
 size_t scan_scratch_bytes(int64_t n) { return (size_t)scan_blocks(n) * 2 * sizeof(float); }
 
-// ACC: 0 none, 1 acc = x, 2 acc += x.  n must be a multiple of SCAN_VEC (buffers are padded by the caller).
-template <typename T, int ACC>
-__global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(const T* __restrict__ x, int64_t n, float* __restrict__ acc,
-                                                            float* __restrict__ partial) {
+// n must be a multiple of SCAN_VEC (buffers are padded by the caller).
+template <typename T>
+__global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(const T* __restrict__ x, int64_t n, float* __restrict__ partial) {
   __shared__ float sh[16];
   float bad = 0.f, sq = 0.f;
   // two vectors in flight per lane, non-temporal: the data is on its way through, nothing here reads it twice
@@ -38,11 +37,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(const T* __restrict_
 #pragma unroll
       for (int k = 0; k < SCAN_VEC; ++k) v[1][k] = 0.f;
     }
-    float a[2][SCAN_VEC] = {};
-    if (ACC == 2) {
-      load_f_nt<float, SCAN_VEC>(acc + i, a[0]);
-      if (two) load_f_nt<float, SCAN_VEC>(acc + i1, a[1]);
-    }
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -50,15 +44,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(const T* __restrict_
         if (!(fabsf(v[u][k]) <= 3.402823466e38f)) bad = 1.f;
         sq += v[u][k] * v[u][k];
       }
-    if (ACC == 1) {
-      store_f_nt<float, SCAN_VEC>(acc + i, v[0]);
-      if (two) store_f_nt<float, SCAN_VEC>(acc + i1, v[1]);
-    } else if (ACC == 2) {
-#pragma unroll
-      for (int k = 0; k < SCAN_VEC; ++k) { a[0][k] += v[0][k]; a[1][k] += v[1][k]; }
-      store_f_nt<float, SCAN_VEC>(acc + i, a[0]);
-      if (two) store_f_nt<float, SCAN_VEC>(acc + i1, a[1]);
-    }
   }
   bad = block_max(bad, sh);
   sq = block_sum(sq, sh);
@@ -93,21 +78,107 @@ __global__ __launch_bounds__(256) void scan_finish_kernel(const float* __restric
 }
 
 template <typename T>
-static void scan_dispatch(hipStream_t s, const void* x, int64_t n, float* result, DevState* st, float* acc, int acc_mode,
-                          void* scratch) {
+static void scan_dispatch(hipStream_t s, const void* x, int64_t n, float* result, DevState* st, void* scratch) {
   const int nb = scan_blocks(n);
-  dim3 grid(nb), block(SCAN_THREADS);
-  if (acc_mode == 1) hipLaunchKernelGGL((scan_kernel<T, 1>), grid, block, 0, s, (const T*)x, n, acc, (float*)scratch);
-  else if (acc_mode == 2) hipLaunchKernelGGL((scan_kernel<T, 2>), grid, block, 0, s, (const T*)x, n, acc, (float*)scratch);
-  else hipLaunchKernelGGL((scan_kernel<T, 0>), grid, block, 0, s, (const T*)x, n, acc, (float*)scratch);
+  hipLaunchKernelGGL(scan_kernel<T>, dim3(nb), dim3(SCAN_THREADS), 0, s, (const T*)x, n, (float*)scratch);
   hipLaunchKernelGGL(scan_finish_kernel, dim3(1), dim3(256), 0, s, (const float*)scratch, nb, result, st);
 }
 
-void launch_scan(hipStream_t s, int dt, const void* x, int64_t n, float* result, DevState* st, float* acc, int acc_mode,
-                 void* scratch) {
-  if (dt == F32) scan_dispatch<float>(s, x, n, result, st, acc, acc_mode, scratch);
-  else if (dt == F16) scan_dispatch<half_t>(s, x, n, result, st, acc, acc_mode, scratch);
-  else scan_dispatch<bf16_t>(s, x, n, result, st, acc, acc_mode, scratch);
+void launch_scan(hipStream_t s, int dt, const void* x, int64_t n, float* result, DevState* st, void* scratch) {
+  if (dt == F32) scan_dispatch<float>(s, x, n, result, st, scratch);
+  else if (dt == F16) scan_dispatch<half_t>(s, x, n, result, st, scratch);
+  else scan_dispatch<bf16_t>(s, x, n, result, st, scratch);
+}
+
+// ---- accumulation over a window --------------------------------------------------------------------------------------------
+// The gradient x of a window's second or later sub-batch joins the window's sum in fp32, and what the scan and the update need to know is
+// formed on the way: the sums of squares of x and of the new sum, either of which is not finite if a value is not.  FIRST: the sum so far
+// is the first sub-batch's gradient, which lies in a buffer of its own since the second began.
+// One pass, no loop, non-temporal, every load of a thread issued before the first result is needed (as the Adam kernel, and for the same
+// reason).  Bound by memory: 10 bytes per parameter with 2-byte gradients, 8 for FIRST.  us, fp16: FIRST over 246 M
+// parameters 364 (5.4 TB/s), without over 235 M 434 (5.4 TB/s).  (Before, the first gradient was converted into the sum, 311 and 284 us, each other one
+// added by a scan with a grid-stride loop, 502 and 493, and the finished sum scanned once more, 169 and 161.)
+constexpr int ACCUM_VEC = 8, ACCUM_UN = 4, ACCUM_TILE = SCAN_THREADS * ACCUM_VEC * ACCUM_UN, ACCUM_FINISH_THREADS = 1024;
+static int accum_blocks(int64_t n) { return (int)((n + ACCUM_TILE - 1) / ACCUM_TILE); }
+size_t accumulate_scratch_bytes(int64_t n) { return (size_t)accum_blocks(n) * sizeof(float2); }
+
+template <typename T, bool FIRST>
+__global__ __launch_bounds__(SCAN_THREADS) void accumulate_kernel(const T* __restrict__ x, const T* __restrict__ first, float* __restrict__ acc, int64_t n,
+                                                                  float2* __restrict__ partial) {
+  __shared__ float sh[16];
+  const int64_t i0 = (int64_t)blockIdx.x * ACCUM_TILE + threadIdx.x * ACCUM_VEC;
+  float v[ACCUM_UN][ACCUM_VEC], a[ACCUM_UN][ACCUM_VEC];
+#pragma unroll
+  for (int u = 0; u < ACCUM_UN; ++u) {
+    const int64_t i = i0 + u * SCAN_THREADS * ACCUM_VEC;
+    if (i < n) {
+      load_f_nt<T, ACCUM_VEC>(x + i, v[u]);
+      if constexpr (FIRST) load_f_nt<T, ACCUM_VEC>(first + i, a[u]);
+      else load_f_nt<float, ACCUM_VEC>(acc + i, a[u]);
+    }
+  }
+  float sx = 0.f, sa = 0.f;
+#pragma unroll
+  for (int u = 0; u < ACCUM_UN; ++u) {
+    const int64_t i = i0 + u * SCAN_THREADS * ACCUM_VEC;
+    if (i < n) {
+#pragma unroll
+      for (int k = 0; k < ACCUM_VEC; ++k) {
+        a[u][k] += v[u][k];
+        sx += v[u][k] * v[u][k];
+        sa += a[u][k] * a[u][k];
+      }
+      store_f_nt<float, ACCUM_VEC>(acc + i, a[u]);
+    }
+  }
+  sx = block_sum(sx, sh);
+  sa = block_sum(sa, sh);
+  if (threadIdx.x == 0) partial[blockIdx.x] = float2{sx, sa};
+}
+
+__global__ __launch_bounds__(ACCUM_FINISH_THREADS) void accumulate_finish_kernel(const float2* __restrict__ partial, int nb, DevState* __restrict__ st) {
+  __shared__ double shx[ACCUM_FINISH_THREADS], sha[ACCUM_FINISH_THREADS];
+  constexpr int UN = 8;
+  double sx = 0.0, sa = 0.0;
+  for (int i0 = threadIdx.x; i0 < nb; i0 += UN * ACCUM_FINISH_THREADS) {
+    float2 q[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int i = i0 + u * ACCUM_FINISH_THREADS;
+      q[u] = i < nb ? partial[i] : float2{0.f, 0.f};
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) { sx += (double)q[u].x; sa += (double)q[u].y; }
+  }
+  shx[threadIdx.x] = sx;
+  sha[threadIdx.x] = sa;
+  __syncthreads();
+  for (int o = ACCUM_FINISH_THREADS / 2; o > 0; o >>= 1) {
+    if (threadIdx.x < o) { shx[threadIdx.x] += shx[threadIdx.x + o]; sha[threadIdx.x] += sha[threadIdx.x + o]; }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    const bool bad = !(fabs(shx[0]) <= 1.7e308);
+    st->scan_flag = bad ? 1.f : 0.f;
+    st->scan_sumsq = shx[0];
+    st->step_overflow = bad ? 1 : 0;
+    if (bad) st->window_overflow = 1;
+    st->window_sumsq = sha[0];                            // (not finite: the window is skipped, see scaler_update_kernel)
+  }
+}
+
+template <typename T>
+static void accumulate_typed(hipStream_t s, const void* x, const void* first, float* acc, int64_t n, DevState* st, void* scratch) {
+  const int nb = accum_blocks(n);
+  const dim3 grid(nb), block(SCAN_THREADS);
+  if (first) hipLaunchKernelGGL((accumulate_kernel<T, true>), grid, block, 0, s, (const T*)x, (const T*)first, acc, n, (float2*)scratch);
+  else hipLaunchKernelGGL((accumulate_kernel<T, false>), grid, block, 0, s, (const T*)x, (const T*)nullptr, acc, n, (float2*)scratch);
+  hipLaunchKernelGGL(accumulate_finish_kernel, dim3(1), dim3(ACCUM_FINISH_THREADS), 0, s, (const float2*)scratch, nb, st);
+}
+void launch_accumulate(hipStream_t s, int dt, const void* x, const void* first, float* acc, int64_t n, DevState* st, void* scratch) {
+  if (dt == F32) accumulate_typed<float>(s, x, first, acc, n, st, scratch);
+  else if (dt == F16) accumulate_typed<half_t>(s, x, first, acc, n, st, scratch);
+  else accumulate_typed<bf16_t>(s, x, first, acc, n, st, scratch);
 }
 
 // ---- the scan for callers that cannot allocate ------------------------------------------------------------------------------
@@ -182,8 +253,10 @@ void launch_convert(hipStream_t s, int src_dt, const void* src, int dst_dt, void
 // Overflow anywhere in the window: skip, halve the scale, restart the clean counter.  Otherwise take an optimiser
 // step and double the scale after `scale_window` clean updates (Implementation, Mixed precision).
 __global__ void scaler_update_kernel(DevState* st, long long ntokens, float clip_norm, float beta1, float beta2,
-                                     int scale_window, float min_scale, int dynamic) {
+                                     int scale_window, float min_scale, int dynamic, int accumulated) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  const double sumsq = accumulated ? st->window_sumsq : st->scan_sumsq;
+  if (!(fabs(sumsq) <= 1.7e308)) st->window_overflow = 1;  // (gradients that are finite one by one may add up to infinity)
   if (st->window_overflow) {
     st->skipped = 1;
     st->grad_norm = __uint_as_float(0x7fc00000u);
@@ -193,7 +266,7 @@ __global__ void scaler_update_kernel(DevState* st, long long ntokens, float clip
   } else {
     st->skipped = 0;
     const double inv = 1.0 / ((double)st->loss_scale * (double)(ntokens > 0 ? ntokens : 1));
-    const double gnorm = sqrt(st->scan_sumsq) * inv;
+    const double gnorm = sqrt(sumsq) * inv;
     double coef = 1.0;
     if (clip_norm > 0.f && gnorm > (double)clip_norm) coef = (double)clip_norm / gnorm;
     st->grad_norm = (float)gnorm;
@@ -209,8 +282,8 @@ __global__ void scaler_update_kernel(DevState* st, long long ntokens, float clip
   st->scale_too_small = st->loss_scale < min_scale ? 1 : 0;       // (cleared again once the scale is back at or above the minimum)
 }
 void launch_scaler_update(hipStream_t s, DevState* st, long long ntokens, float clip_norm, float beta1, float beta2,
-                          int scale_window, float min_scale, int dynamic) {
-  hipLaunchKernelGGL(scaler_update_kernel, dim3(1), dim3(64), 0, s, st, ntokens, clip_norm, beta1, beta2, scale_window, min_scale, dynamic);
+                          int scale_window, float min_scale, int dynamic, int accumulated) {
+  hipLaunchKernelGGL(scaler_update_kernel, dim3(1), dim3(64), 0, s, st, ntokens, clip_norm, beta1, beta2, scale_window, min_scale, dynamic, accumulated);
 }
 
 // ---- Adam -------------------------------------------------------------------------------------------------------------------
@@ -287,7 +360,7 @@ extern "C" int tfm_op_scan_noalloc(int32_t dtype, const void* x, int64_t n, floa
   hipError_t e = hipSuccess;
   float* scratch = scan_static_address(&e);
   if (!scratch) { set_global_error(hipGetErrorString(e)); return TFM_EHIP; }
-  launch_scan((hipStream_t)stream, dtype, x, n, result, nullptr, nullptr, 0, scratch);
+  launch_scan((hipStream_t)stream, dtype, x, n, result, nullptr, scratch);
   e = hipGetLastError();
   if (e != hipSuccess) { set_global_error(hipGetErrorString(e)); return TFM_EHIP; }
   return TFM_OK;

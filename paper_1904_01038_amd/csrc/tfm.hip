@@ -146,6 +146,7 @@ struct tfm_ctx {
   int64_t P;               // padded flat length
   float *W, *M, *V, *G;    // fp32 master, Adam moments, window accumulator
   void *Wh, *g;            // model copy and sub-batch gradient in compute dtype (Wh == W in fp32 mode)
+  void *g_first;           // the gradient of the window's first sub-batch from the start of its second one until both are added into G
   DevState* st;
   Stream enc, dec;
   int R;                   // row capacity
@@ -351,6 +352,7 @@ size_t carve(tfm_ctx* c, char* base) {
   c->V = (float*)a.take(c->P * 4);
   c->G = (float*)a.take(c->P * 4);
   c->g = a.take(c->P * esz);
+  c->g_first = a.take(c->P * esz);
   c->Wh = c->dt == F32 ? (void*)c->W : a.take(c->P * esz);
   c->st = (DevState*)a.take(sizeof(DevState));
   c->ld_kv = cf.enc_layers ? cf.dec_layers * 2 * (int)d : 0;
@@ -423,7 +425,7 @@ size_t carve(tfm_ctx* c, char* base) {
   c->ln_slices = (int)(c->enc.blocks.size() + c->dec.blocks.size()) + 2;      // one LayerNorm backward per block, plus final norms
   c->ln_pool = (char*)a.take(c->ln_slice * c->ln_slices);
   c->red_scratch_side = a.take(colsum_scratch_bytes((int)R, (int)wide));
-  c->scan_scratch = a.take(scan_scratch_bytes(c->P));
+  c->scan_scratch = a.take(std::max(scan_scratch_bytes(c->P), accumulate_scratch_bytes(c->P)));
   c->splitk_bytes = c->dt == F32 ? 0 : (size_t)8 * 128 * 128 * 128 * sizeof(float);   // 8 slices of up to 128 tiles
   c->splitk_ws = c->splitk_bytes ? a.take(c->splitk_bytes) : nullptr;
   c->splitk_ws_side = c->splitk_bytes ? a.take(c->splitk_bytes) : nullptr;
@@ -1308,9 +1310,8 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
   c->dec.rows = (int)Tt; c->dec.max_len = maxt;
 
   const int d = cf.d_model, V = cf.vocab;
-  // a second sub-batch in the window: move the first one's gradient into the fp32 accumulator before g is reused
-  if (c->window_mb == 1)
-    run(c, TFM_PROF_OPTIM, 0.0, (double)c->P * (c->esz + 4.0), [&] { launch_convert(c->stream, c->dt, c->g, F32, c->G, c->P); });
+  // a second sub-batch in the window: the first one's gradient stays where it is until both are added up
+  if (c->window_mb == 1) std::swap(c->g, c->g_first);
 
   // ---- forward
   c->beside = c->overlap && Tt * (long long)d >= BESIDE_MIN;
@@ -1376,9 +1377,10 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
   });
 
   // ---- inf/nan scan of this sub-batch's gradient (+ accumulation from the second sub-batch on)
-  const int acc_mode = c->window_mb >= 1 ? 2 : 0;
-  run(c, TFM_PROF_OPTIM, 0.0, (double)c->P * (c->esz + (acc_mode ? 8.0 : 0.0)), [&] {
-    launch_scan(c->stream, c->dt, c->g, c->P, nullptr, c->st, acc_mode ? c->G : nullptr, acc_mode, c->scan_scratch);
+  const double acc_bytes = c->window_mb == 0 ? 0.0 : c->window_mb == 1 ? c->esz + 4.0 : 8.0;
+  run(c, TFM_PROF_OPTIM, 0.0, (double)c->P * (c->esz + acc_bytes), [&] {
+    if (c->window_mb == 0) launch_scan(c->stream, c->dt, c->g, c->P, nullptr, c->st, c->scan_scratch);
+    else launch_accumulate(c->stream, c->dt, c->g, c->window_mb == 1 ? c->g_first : nullptr, c->G, c->P, c->st, c->scan_scratch);
   });
   c->window_mb += 1;
   c->window_tokens += Tt;
@@ -1404,14 +1406,8 @@ int tfm_apply_update(tfm_ctx* c, float lr, tfm_update_out* out) {
   c->generation += 1;
   const tfm_config& cf = c->cfg;
   const bool single = c->window_mb == 1;
-  // the scan of a single sub-batch already produced the sum of squares; an accumulated window is scanned again
-  if (!single)
-    run(c, TFM_PROF_OPTIM, 0.0, (double)c->P * 4.0, [&] {
-      // window_overflow is sticky (|=) so this scan cannot clear an earlier sub-batch's flag
-      launch_scan(c->stream, F32, c->G, c->P, nullptr, c->st, nullptr, 0, c->scan_scratch);
-    });
   launch_scaler_update(c->stream, c->st, c->window_tokens, cf.clip_norm, cf.adam_beta1, cf.adam_beta2, cf.scale_window,
-                       cf.min_loss_scale, cf.precision == TFM_FP16 ? 1 : 0);
+                       cf.min_loss_scale, cf.precision == TFM_FP16 ? 1 : 0, single ? 0 : 1);
   AdamArgs a{};
   a.w = c->W; a.m = c->M; a.v = c->V; a.n = c->P;
   a.g = single ? c->g : (const void*)c->G; a.gdt = single ? c->dt : (int)F32;
@@ -1945,7 +1941,7 @@ size_t tfm_op_scan_scratch(int64_t n) { return scan_scratch_bytes(n); }
 
 int tfm_op_scan(int32_t dtype, const void* x, int64_t n, float* result, void* scratch, void* stream) {
   if (dtype < 0 || dtype > 2 || !x || !result || !scratch || n < 0 || n % 8) return TFM_EINVAL;
-  launch_scan((hipStream_t)stream, dtype, x, n, result, nullptr, nullptr, 0, scratch);
+  launch_scan((hipStream_t)stream, dtype, x, n, result, nullptr, scratch);
   return op_done();
 }
 

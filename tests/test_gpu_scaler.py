@@ -151,3 +151,42 @@ def test_scale_below_the_minimum_is_reported_and_recovers():
     u = gpu.apply_update(1e-3)
     assert (u["skipped"], u["loss_scale_after"]) == (0, 8.0)
     gpu.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("adaptive", [False, True])
+def test_window_gradient_is_the_fp32_sum_of_its_sub_batches(prec, adaptive):
+    """Windows of 3, 1, 2, 4 and 1 sub-batches in turn, so that each starts with either of the two gradient buffers; a step of size 0 between them
+    leaves the parameters alone.  Sub-batches that lack most of the vocabulary (and of an adaptive one whole clusters) must not see
+    what an earlier one left.  The sum of squares is added up in fp32 over 32 values a thread and 256 threads, from there in fp64."""
+    import paper_1904_01038_amd as T
+    from tests.test_gpu_adaptive import HALF, lm_batch
+    precision = {"fp32": T.FP32, "fp16": T.FP16, "bf16": T.BF16}[prec]
+    shape = HALF if adaptive else ModelShape(1, 1, 64, 1, 256, 400)
+    gpu, _ = make_pair(shape, precision, init_loss_scale=4.0, label_smoothing=0.0 if adaptive else 0.1, max_sentences=8, max_len=24, max_tokens=128)
+    if adaptive:
+        batches = [lm_batch(shape, s, lens, hi=hi) for s, lens, hi in [(1, (9, 14, 5), 254), (2, (24, 3), 60), (3, (1,), 124), (4, (20, 20), 254)]]
+    else:
+        batches = [small_batch(shape, 300 + s) for s in range(4)]
+    step = lambda b: gpu.train_step(b.src, b.tgt, b.src_lens, b.tgt_lens)
+    alone = []
+    for b in batches:
+        step(b)
+        alone.append(gpu.get_grads())
+        assert gpu.apply_update(0.0)["skipped"] == 0
+    for window in ([0, 1, 2], [3], [2, 0], [1, 1, 3, 2], [0]):
+        for i in window:
+            r = step(batches[i])
+        u = gpu.apply_update(0.0) if len(window) == 1 else None
+        if u is None:
+            got = gpu.get_grads()
+            for k in got:
+                want = alone[window[0]][k].astype(np.float32)
+                for i in window[1:]:
+                    want = want + alone[i][k]
+                assert np.array_equal(got[k], want), (window, k)
+            u = gpu.apply_update(0.0)
+        else:
+            got = alone[window[0]]
+        norm = np.sqrt(sum(float(np.sum(got[k].astype(np.float64) ** 2)) for k in got)) / (r["loss_scale"] * u["ntokens_total"])
+        assert u["skipped"] == 0 and abs(u["grad_norm"] - norm) <= 1e-6 * norm, window
