@@ -304,7 +304,7 @@ __global__ __launch_bounds__(ATT_THREADS, ATT_FWD_MIN_WAVES) void attn_fwd_mfma_
 constexpr int LT_THREADS = 256, LT_ROWS = 128;
 constexpr float LOG2E = 1.44269504088896341f, LN2 = 0.693147180559945309f;
 
-// 64 rows of 64 columns, 2 vectors a thread (zero beyond nvalid rows; rows at or beyond it are not read)
+// 64 rows of 64 columns, 2 vectors a thread (zero beyond nvalid >= 1 rows; rows at or beyond it are not read)
 __device__ __forceinline__ void fetch_chunk(u32x4 (&x)[2], const uint16_t* __restrict__ G, int ld, int row0, int nvalid) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -349,15 +349,19 @@ __global__ __launch_bounds__(LT_THREADS, 3) void attn_fwd_long_kernel(AttnP p, i
   const int own_end = qi0 >= lq ? 0 : p.causal ? min(lk, qi0 + 32) : lk;                   // keys that this wavefront's queries admit
   const float c = p.scale * LOG2E;
   u32x4 kx[2], vx[2], qf[4];
-  fetch_chunk(kx, K, p.ldk, 0, lk);
-  fetch_chunk(vx, V, p.ldv, 0, lk);
+  if (kend > 0) {                                         // (a sentence without keys has no row to read)
+    fetch_chunk(kx, K, p.ldk, 0, lk);
+    fetch_chunk(vx, V, p.ldv, 0, lk);
+  }
   load_frags(qf, p.q + (size_t)q0 * p.ldq + h * DH, p.ldq, qi0, lq, lane);
   float m = -INFINITY, lsum = 0.f;                        // running maximum of the scaled scores times log2(e); sum of 2^(score - m)
   f32x16 acc[2];
 #pragma unroll
   for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
-  put_chunk(Ks[0], kx);
-  put_chunk(Vs[0], vx);
+  if (kend > 0) {
+    put_chunk(Ks[0], kx);
+    put_chunk(Vs[0], vx);
+  }
   if (CH < kend) {
     fetch_chunk(kx, K, p.ldk, CH, lk);
     fetch_chunk(vx, V, p.ldv, CH, lk);
@@ -449,8 +453,10 @@ __device__ __forceinline__ void attn_bwd_dq_body(const AttnP& p, int b, int h, i
   const int own_end = qi0 >= lq ? 0 : p.causal ? min(lk, qi0 + 32) : lk;
   const float c = p.scale * LOG2E;
   u32x4 kx[2], vx[2], qf[4], gf[4];
-  fetch_chunk(kx, K, p.ldk, 0, lk);
-  fetch_chunk(vx, V, p.ldv, 0, lk);
+  if (kend > 0) {                                         // (a sentence without keys has no row to read)
+    fetch_chunk(kx, K, p.ldk, 0, lk);
+    fetch_chunk(vx, V, p.ldv, 0, lk);
+  }
   load_frags(qf, p.q + (size_t)q0 * p.ldq + h * DH, p.ldq, qi0, lq, lane);
   load_frags(gf, p.d_o + (size_t)q0 * p.lddo + h * DH, p.lddo, qi0, lq, lane);
   float delta = 0.f;
@@ -465,8 +471,10 @@ __device__ __forceinline__ void attn_bwd_dq_body(const AttnP& p, int b, int h, i
   f32x16 acc[2];
 #pragma unroll
   for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
-  put_chunk(Ks[0], kx);
-  put_chunk(Vs[0], vx);
+  if (kend > 0) {
+    put_chunk(Ks[0], kx);
+    put_chunk(Vs[0], vx);
+  }
   if (CH < kend) {
     fetch_chunk(kx, K, p.ldk, CH, lk);
     fetch_chunk(vx, V, p.ldv, CH, lk);
@@ -712,13 +720,22 @@ __global__ __launch_bounds__(SG_THREADS, 3) void attn_bwd_single_kernel(AttnP p)
   __shared__ __attribute__((aligned(16))) float Ds[CH];
   __shared__ int QR[CH], KR[CH];                     // partner range lo | hi << 8, own sentence's first row << 16
   const int h = blockIdx.y;
-  int b0, b1, q0, lq, k0, lk;                        // lq, lk in [1, 64]
+  int b0, b1, q0, lq, k0, lk;                        // lq, lk up to 64
   if (PACK) {
     const int4 g0 = p.groups[blockIdx.z], g1 = p.groups[blockIdx.z + 1];
     b0 = g0.x; b1 = g1.x; q0 = g0.y; lq = g1.y - q0; k0 = g0.z; lk = g1.z - k0;
   } else {
     b0 = blockIdx.z; b1 = b0 + 1;
     q0 = p.q_off[b0]; lq = p.q_off[b1] - q0; k0 = p.k_off[b0]; lk = p.k_off[b1] - k0;
+  }
+  if (lq <= 0 || lk <= 0) {                          // nothing on one side: no weights, and no row there to read
+    for (int v = threadIdx.x; v < lq * 8; v += SG_THREADS)
+      *reinterpret_cast<u32x4*>(p.dq + (size_t)(q0 + (v >> 3)) * p.lddq + h * DH + (v & 7) * 8) = u32x4{0u, 0u, 0u, 0u};
+    for (int v = threadIdx.x; v < lk * 8; v += SG_THREADS) {
+      *reinterpret_cast<u32x4*>(p.dk + (size_t)(k0 + (v >> 3)) * p.lddk + h * DH + (v & 7) * 8) = u32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4*>(p.dv + (size_t)(k0 + (v >> 3)) * p.lddv + h * DH + (v & 7) * 8) = u32x4{0u, 0u, 0u, 0u};
+    }
+    return;
   }
   if (threadIdx.x < CH) {                            // (the first wavefront: one lane per tile row)
     const int r = threadIdx.x;

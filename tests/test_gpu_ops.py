@@ -455,6 +455,44 @@ def test_attention_of_longer_sentences(prec, case, p_drop):
     test_attention_forward_backward(prec, 64, case, p_drop, False)
 
 
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("lq,lk", [([30, 0, 40, 20, 0], [0, 50, 40, 20, 9]), ([90, 0, 40, 20, 0], [0, 150, 70, 20, 9])])
+def test_attention_with_nothing_on_one_side_of_a_sentence(prec, causal, lq, lk):
+    """No queries: no gradient for the keys and values; no keys: none for the queries.  The other sentences come out as without them."""
+    import torch
+    import paper_1904_01038_amd as T
+    H, d = 2, 128
+    dt = _dtypes()[prec]
+    rng = np.random.default_rng(5)
+    q, do = (rng.normal(size=(sum(lq), d)) for _ in range(2))
+    k, v = (rng.normal(size=(sum(lk), d)) for _ in range(2))
+
+    def go(lq, lk, q, k, v, do):
+        q, k, v, do = (_t(x, dt) for x in (q, k, v, do))
+        q_off, k_off = (torch.tensor(np.concatenate([[0], np.cumsum(l)]), dtype=torch.int32).cuda() for l in (lq, lk))
+        o, lse = torch.zeros_like(q), torch.zeros(H, len(q), device="cuda")
+        T.ops.attention_fwd(q, k, v, o, lse, q_off, k_off, H, 64, max(lq), max(lk), causal, 0, 0.0, None)
+        dq, dk, dv = (torch.full_like(x, 7.0) for x in (q, k, v))
+        T.ops.attention_bwd(q, k, v, o, do, lse, dq, dk, dv, q_off, k_off, H, 64, max(lq), max(lk), len(k), causal, 0, 0.0, None)
+        return [x.float().cpu().numpy() for x in (o, dq, dk, dv)]
+
+    o, dq, dk, dv = go(lq, lk, q, k, v, do)
+    whole = [b for b in range(len(lq)) if lq[b] and lk[b]]
+    qr = np.repeat(np.isin(np.arange(len(lq)), whole), lq)
+    kr = np.repeat(np.isin(np.arange(len(lk)), whole), lk)
+    assert not dq[~qr].any() and not dk[~kr].any() and not dv[~kr].any()
+    longest = [max(lq), max(lk)]
+    if max(longest) > 64:                                     # (the same kernels: one more sentence of the longest length)
+        lq, lk = [lq[b] for b in whole] + [longest[0]], [lk[b] for b in whole] + [longest[1]]
+        more = lambda x, keep, n: np.concatenate([x[keep], rng.normal(size=(n, d))])
+        alone = go(lq, lk, more(q, qr, longest[0]), more(k, kr, longest[1]), more(v, kr, longest[1]), more(do, qr, longest[0]))
+    else:
+        alone = go([lq[b] for b in whole], [lk[b] for b in whole], q[qr], k[kr], v[kr], do[qr])
+    for got, keep, ref in zip((o, dq, dk, dv), (qr, qr, kr, kr), alone):
+        assert np.array_equal(got[keep], ref[:keep.sum()])
+
+
 @pytest.mark.parametrize("gprec", ["fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("wd", [0.0, 0.05])
 @pytest.mark.parametrize("n", [8, 4096, 13288])          # less than one lane group, exactly one block, a ragged last block
