@@ -325,13 +325,19 @@ __device__ __forceinline__ bool better(float v, int i, float w, int j) { return 
 // itself: that is its place.  Should more than TOPK_LIST survive (many equal values), or too few (values of -infinity, or NaN),
 // the block falls back to k rounds over all of its values.  -infinity is a value like any other, after the finite ones; NaN is
 // never a candidate and makes the row's log-sum-exp NaN.
+//
+// An adaptive softmax has its scores in several segments, the head's tokens and each tail cluster's, whose blocks share the first launch; the second one
+// knows every block's (maximum, sum) pair, so it adds log p(cluster), the head's score of the cluster less the cluster's own log-sum-exp, to a
+// tail's candidates, in 32 bits.  24 rows of 267742 scores: 11.2 + 10.6 us, where a pass for each tail's log-sum-exp, a copy of all
+// the scores into one row and the passes over that row were 9 launches and 60 us.
 constexpr int TOPK_THREADS = 256, TOPK_PER = 16, TOPK_TILE = TOPK_THREADS * TOPK_PER, TOPK_LIST = 256;
 
 struct TopkList { float* v; int* id; float *m, *s; };    // per row: n * k candidates, n (maximum, sum of exp(value - maximum)) pairs
 
-// VEC > 0: values of z, VEC per load; VEC == 0: candidates of the `n_in` lists of `in`, TOPK_TILE / k lists per block
-template <typename T, int VEC>
-__global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restrict__ z, int ldz, int V, TopkList in, int n_in, int k, TopkList out,
+// VEC > 0: values of the segments, VEC per load; VEC == 0: candidates of the `n_in` lists of `in`, TOPK_TILE / k lists per block, with CLUSTERS those
+// of the launch over several segments (a flag of both: over one segment the search for a block's cost a step of one sentence 1 %)
+template <typename T, int VEC, bool CLUSTERS>
+__global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(TopkSegments sg, TopkList in, int n_in, int k, TopkList out,
                                                       float* __restrict__ top_logp, int* __restrict__ top_id, float* __restrict__ lse_out) {
   constexpr int NT = TOPK_THREADS, PER = TOPK_PER, NW = NT / 64;
   static_assert(NT >= TOPK_LIST, "one survivor per thread");
@@ -339,23 +345,33 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
   __shared__ __attribute__((aligned(16))) float list_v[TOPK_LIST];
   __shared__ __attribute__((aligned(16))) int list_i[TOPK_LIST];
   __shared__ int list_n;
+  __shared__ float sh_off[TOPK_SEGMENTS], sh_m[TOPK_SEGMENTS], sh_s;
+  static_assert(TOPK_SEGMENTS <= NW, "a wavefront per segment");
   const int row = blockIdx.x, blk = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float c[PER];
   int id0 = 0;                                           // VEC > 0: id of this thread's first value (the others follow from it)
   int ids[VEC == 0 ? PER : 1];
   int l0 = 0, l1 = 0;                                    // VEC == 0: the lists of this block
+  int V = 0, base = 0;                                   // VEC > 0: values of this block's segment from the block's first on; that one's id
   if constexpr (VEC > 0) {
-    const T* zr = z + (size_t)row * ldz;
-    id0 = blk * NT * PER + (wave * 64 * (PER / VEC) + lane) * VEC;
+    int g = 0;
+    if constexpr (CLUSTERS) {
+      for (int i = 1; i < sg.n; ++i) g = blk >= sg.blk0[i] ? i : g;
+    }
+    const int at = (blk - sg.blk0[g]) * NT * PER, width = sg.ld[g] - at;
+    V = sg.V[g] - at;
+    base = sg.lo[g] + at;
+    const T* zr = reinterpret_cast<const T*>(sg.z[g]) + (size_t)row * sg.ld[g] + at;
+    id0 = (wave * 64 * (PER / VEC) + lane) * VEC;
 #pragma unroll
     for (int i = 0; i < PER / VEC; ++i) {
       const int col = id0 + i * 64 * VEC;
       float t[VEC];
 #pragma unroll
       for (int j = 0; j < VEC; ++j) t[j] = -INFINITY;
-      if (col + VEC <= V) load_f<T, VEC>(zr + col, t);
+      if (col + VEC <= width) load_f<T, VEC>(zr + col, t);
 #pragma unroll
-      for (int j = 0; j < VEC; ++j) c[i * VEC + j] = t[j];
+      for (int j = 0; j < VEC; ++j) c[i * VEC + j] = !CLUSTERS || col + j < V ? t[j] : -INFINITY;       // (one segment: V == ld)
     }
   } else {
     const int per = TOPK_TILE / k;
@@ -368,6 +384,35 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
       const bool ok = q < l1 * k;
       c[e] = ok ? in.v[at + q] : -INFINITY;
       ids[e] = ok ? in.id[at + q] : 0x7fffffff;
+    }
+    if constexpr (CLUSTERS) {
+      if (wave < sg.n) {                                 // a segment's log-sum-exp, in one trip to memory
+        const float entry = wave == 0 ? 0.f : to_f<T>(reinterpret_cast<const T*>(sg.z[0])[(size_t)row * sg.ld[0] + sg.V[0] + wave - 1]);
+        const size_t first = (size_t)row * n_in;
+        auto scaled = [](float s, float m, float to) { return s * (m > -INFINITY ? __expf(m - to) : 1.f); };         // (0 or NaN times 1)
+        float m = -INFINITY, se = 0.f;
+        for (int l = sg.blk0[wave] + lane; l < sg.blk0[wave + 1]; l += 64) {
+          const float lm = in.m[first + l], ls = in.s[first + l], mn = fmaxf(m, lm);
+          se = scaled(se, m, mn) + scaled(ls, lm, mn);
+          m = mn;
+        }
+        const float top = wave_max(m);
+        se = wave_sum(scaled(se, m, top));
+        if (lane == 0) {
+          const float off = wave == 0 ? 0.f : entry - (top + logf(se));
+          sh_off[wave] = off;
+          sh_m[wave] = wave == 0 ? top : entry;
+          if (wave == 0) sh_s = se;
+          if (blk == 0) sg.off[(size_t)row * TOPK_SEGMENTS + wave] = off;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        float off = 0.f;
+        for (int i = 1; i < sg.n; ++i) off = ids[e] >= sg.lo[i] ? sh_off[i] : off;
+        c[e] = ids[e] == 0x7fffffff ? c[e] : c[e] + off;
+      }
     }
   }
   auto id_of = [&](int e) { return VEC > 0 ? id0 + (e / (VEC > 0 ? VEC : 1)) * 64 * VEC + e % (VEC > 0 ? VEC : 1) : ids[VEC > 0 ? 0 : e]; };
@@ -397,6 +442,16 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
       for (int e = 0; e < PER; ++e) se += c[e] != c[e] ? c[e] : 0.f;
     }
     gs = block_sum(se, sh);
+  } else if constexpr (CLUSTERS) {                       // the head's tokens and clusters share its distribution
+    gm = sh_m[0];
+    for (int i = 1; i < sg.n; ++i) gm = fmaxf(gm, sh_m[i]);
+    gs = sh_s * (sh_m[0] > -INFINITY ? __expf(sh_m[0] - gm) : 1.f);
+    for (int i = 1; i < sg.n; ++i) {
+      gs += gm > -INFINITY ? __expf(sh_m[i] - gm) : sh_m[i] != sh_m[i] ? sh_m[i] : 0.f;
+      if (!(sh_off[i] < INFINITY)) gs = __uint_as_float(0x7fc00000u);           // NaN in a tail, or a tail of -infinity alone
+    }
+    if (blk > 0) { gm = -INFINITY; gs = 0.f; }           // (the next launch adds the blocks' sums up)
+    __syncthreads();                                     // publishes sh_bound and list_n
   } else {
     float m = -INFINITY;
     for (int l = l0 + tid; l < l1; l += NT) m = fmaxf(m, in.m[(size_t)row * n_in + l]);
@@ -433,6 +488,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
     else { out.m[(size_t)row * lists + blk] = gm; out.s[(size_t)row * lists + blk] = gs; }
   }
   auto emit = [&](int r, float v, int id) {
+    id = id == 0x7fffffff ? id : id + base;
     if (last) {
       top_logp[(size_t)row * k + r] = v - lse;
       top_id[(size_t)row * k + r] = id;
@@ -441,7 +497,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
       out.id[((size_t)row * lists + blk) * k + r] = id;
     }
   };
-  const int n = list_n, least = VEC > 0 ? min(k, V - blk * NT * PER) : k;
+  const int n = list_n, least = VEC > 0 ? min(k, V) : k;
   if (n <= TOPK_LIST && n >= least) {
     if (tid < 16 && n + tid < TOPK_LIST) { list_v[n + tid] = -INFINITY; list_i[n + tid] = 0x7fffffff; }     // whole groups of 16 below
     __syncthreads();
@@ -490,60 +546,78 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(const T* __restr
 
 static int topk_blocks(int n, int per) { return (n + per - 1) / per; }
 static size_t topk_list_bytes(int rows, int n, int k) { return (size_t)rows * n * (k + 1) * 8; }
-size_t row_topk_scratch_bytes(int rows, int V, int k) {
-  const int n0 = topk_blocks(V, TOPK_TILE);
+size_t row_topk_scratch_bytes(int rows, const TopkSegments& sg, int k) {
+  int n0 = 0;
+  for (int i = 0; i < sg.n; ++i) n0 += topk_blocks(sg.V[i], TOPK_TILE);
   if (n0 == 1) return 0;
   return topk_list_bytes(rows, n0, k) + topk_list_bytes(rows, topk_blocks(n0, TOPK_TILE / k), k);
 }
 
 template <typename T>
-static void row_topk_typed(hipStream_t s, const void* z, int ldz, int rows, int V, int k, float* top_logp, int* top_id, float* lse, void* scratch) {
+static void row_topk_typed(hipStream_t s, TopkSegments sg, int rows, int k, float* top_logp, int* top_id, float* lse, void* scratch) {
   auto list_at = [&](char* p, int n) {
     TopkList l;
     const size_t c = (size_t)rows * n * k, h = (size_t)rows * n;
     l.v = (float*)p; l.id = (int*)(p + c * 4); l.m = (float*)(p + c * 8); l.s = (float*)(p + c * 8 + h * 4);
     return l;
   };
-  int n = topk_blocks(V, TOPK_TILE), n_in = 0;
+  int n = 0, n_in = 0;
+  uintptr_t al = 0;                                      // what every load's address is a multiple of
+  for (int i = 0; i < sg.n; ++i) {
+    sg.blk0[i] = n;
+    n += topk_blocks(sg.V[i], TOPK_TILE);
+    al |= (uintptr_t)sg.z[i] | (uintptr_t)sg.ld[i] * sizeof(T);
+  }
+  sg.blk0[sg.n] = n;
   char* bufs[2] = {(char*)scratch, (char*)scratch + (n > 1 ? topk_list_bytes(rows, n, k) : 0)};
   TopkList out = list_at(bufs[0], n), in{};
-  const uintptr_t al = (uintptr_t)z | (uintptr_t)ldz * sizeof(T) | (uintptr_t)V * sizeof(T);       // what every load's address is a multiple of
   // (rows along x: y and z of a grid end at 65536)
-#define TK(VEC) \
-  hipLaunchKernelGGL((row_topk_kernel<T, VEC>), dim3(rows, n), dim3(TOPK_THREADS), 0, s, (const T*)z, ldz, V, in, n_in, k, out, top_logp, top_id, lse)
-  if (al % (8 * sizeof(T)) == 0) TK(8); else if (al % (2 * sizeof(T)) == 0) TK(2); else TK(1);
+#define TK(VEC, CLUSTERS) \
+  hipLaunchKernelGGL((row_topk_kernel<T, VEC, CLUSTERS>), dim3(rows, n), dim3(TOPK_THREADS), 0, s, sg, in, n_in, k, out, top_logp, top_id, lse)
+#define TKS(CLUSTERS) do { if (al % (8 * sizeof(T)) == 0) TK(8, CLUSTERS); else if (al % (2 * sizeof(T)) == 0) TK(2, CLUSTERS); else TK(1, CLUSTERS); } while (0)
+  const bool clusters = sg.n > 1;
+  if (clusters) TKS(true); else TKS(false);
+#undef TKS
   for (int which = 1; n > 1; which ^= 1) {
+    const bool first = n_in == 0;
     n_in = n;
     in = out;
     n = topk_blocks(n, TOPK_TILE / k);
     out = list_at(bufs[which], n);
-    TK(0);
+    if (clusters && first) TK(0, true); else TK(0, false);
   }
 #undef TK
 }
 
-void launch_row_topk(hipStream_t s, int dt, const void* z, int ldz, int rows, int V, int k, float* top_logp, int* top_id, float* lse,
-                     void* scratch) {
+void launch_row_topk(hipStream_t s, int dt, const TopkSegments& sg, int rows, int k, float* top_logp, int* top_id, float* lse, void* scratch) {
   if (rows <= 0) return;
-  if (dt == F32) row_topk_typed<float>(s, z, ldz, rows, V, k, top_logp, top_id, lse, scratch);
-  else if (dt == F16) row_topk_typed<half_t>(s, z, ldz, rows, V, k, top_logp, top_id, lse, scratch);
-  else row_topk_typed<bf16_t>(s, z, ldz, rows, V, k, top_logp, top_id, lse, scratch);
+  if (dt == F32) row_topk_typed<float>(s, sg, rows, k, top_logp, top_id, lse, scratch);
+  else if (dt == F16) row_topk_typed<half_t>(s, sg, rows, k, top_logp, top_id, lse, scratch);
+  else row_topk_typed<bf16_t>(s, sg, rows, k, top_logp, top_id, lse, scratch);
 }
 
-// out[r][v] = z[r][v] - lse[r] in fp32 (test access to the full distribution)
+// out[r][col0 + v] = z[r][v] + off[r] - lse[r] in fp32 (test access to the full distribution); off: of row r at r * TOPK_SEGMENTS, or null
 template <typename T>
-__global__ __launch_bounds__(256) void logprob_rows_kernel(const T* __restrict__ z, int ldz, const float* __restrict__ lse,
-                                                           float* __restrict__ out, int V) {
+__global__ __launch_bounds__(256) void logprob_rows_kernel(const T* __restrict__ z, int ldz, const float* __restrict__ off,
+                                                           const float* __restrict__ lse, float* __restrict__ out, int ldo, int V) {
   const int row = blockIdx.y;
   const int col = blockIdx.x * 256 + threadIdx.x;
-  if (col < V) out[(size_t)row * V + col] = to_f<T>(z[(size_t)row * ldz + col]) - lse[row];
+  if (col >= V) return;
+  float v = to_f<T>(z[(size_t)row * ldz + col]);
+  if (off) v += off[(size_t)row * TOPK_SEGMENTS];
+  out[(size_t)row * ldo + col] = v - lse[row];
 }
-void launch_logprob_rows(hipStream_t s, int dt, const void* z, int ldz, const float* lse, float* out, int rows, int V) {
+// rows r0 .. r0 + rows - 1 of the segments
+void launch_logprob_rows(hipStream_t s, int dt, const TopkSegments& sg, const float* lse, float* out, int r0, int rows) {
   if (rows <= 0) return;
-  dim3 grid((V + 255) / 256, rows), block(256);
-  if (dt == F32) hipLaunchKernelGGL(logprob_rows_kernel<float>, grid, block, 0, s, (const float*)z, ldz, lse, out, V);
-  else if (dt == F16) hipLaunchKernelGGL(logprob_rows_kernel<half_t>, grid, block, 0, s, (const half_t*)z, ldz, lse, out, V);
-  else hipLaunchKernelGGL(logprob_rows_kernel<bf16_t>, grid, block, 0, s, (const bf16_t*)z, ldz, lse, out, V);
+  const int ldo = sg.lo[sg.n - 1] + sg.V[sg.n - 1];
+  for (int i = 0; i < sg.n; ++i) {
+    dim3 grid((sg.V[i] + 255) / 256, rows), block(256);
+    const float* off = i ? sg.off + (size_t)r0 * TOPK_SEGMENTS + i : nullptr;
+#define LP(T) hipLaunchKernelGGL(logprob_rows_kernel<T>, grid, block, 0, s, (const T*)sg.z[i] + (size_t)r0 * sg.ld[i], sg.ld[i], off, lse + r0, out + sg.lo[i], ldo, sg.V[i])
+    if (dt == F32) LP(float); else if (dt == F16) LP(half_t); else LP(bf16_t);
+#undef LP
+  }
 }
 
 }  // namespace tfm

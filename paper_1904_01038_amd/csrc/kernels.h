@@ -158,9 +158,6 @@ void launch_gather_rows(hipStream_t s, int dt, const void* src, int ld_src, cons
 void launch_gather_dx(hipStream_t s, int dt, const void* dx, const int* idx, void* dst, int d, int n, float scale, uint64_t key, float p);
 void launch_scatter_add_rows(hipStream_t s, int dt, void* dst, int ld_dst, const int* idx, const void* src, int width, int n);
 void launch_scatter_add_f32(hipStream_t s, float* a, float* b, const int* idx, const float* sa, const float* sb, int n);
-// virt[r][col0 + j] = z[r][j] + (entry >= 0 ? head[r][entry] - lse[r] : 0), j < width, r < rows (decoding with an adaptive softmax)
-void launch_adaptive_virtual(hipStream_t s, int dt, const void* z, int ldz, int width, void* virt, int ldv, int col0, const void* head, int ldh,
-                             int entry, const float* lse, int rows);
 void launch_segsum_add_rows(hipStream_t s, int dt, void* dst, const void* src, int width, const int* tok, const int* beg, const int* end,
                             const int* entries, int n_seg);
 // Adds sqrt(d) * dropout-backward(dx) of every occurrence of a token to its row of the embedding gradient.
@@ -227,12 +224,22 @@ struct DecodeAttnArgs {
 };
 void launch_decode_attention(hipStream_t s, const DecodeAttnArgs& a);
 bool decode_attention_appends(const DecodeAttnArgs& a);   // would this launch append k_new / v_new to the caches itself?
+// The scores of a row: one segment, z[0][row][ld] of which the first V columns are tokens 0 .. V - 1.  Or those of an adaptive softmax: segment 0
+// holds the head's tokens and behind them a score for each further segment, a tail cluster with the tokens from lo on; off
+// [rows][TOPK_SEGMENTS] receives what joins a segment's scores, so that all of them are scores of one distribution.
+constexpr int TOPK_SEGMENTS = 4;
+struct TopkSegments {
+  int n;
+  const void* z[TOPK_SEGMENTS];
+  int ld[TOPK_SEGMENTS], V[TOPK_SEGMENTS], lo[TOPK_SEGMENTS];
+  float* off;
+  int blk0[TOPK_SEGMENTS + 1];                           // (the launch's: first block of a segment)
+};
 // per row: log-sum-exp and the k (<= 16) largest logits as log-probabilities, best first, ties by ascending id
 // (scratch: row_topk_scratch_bytes)
-size_t row_topk_scratch_bytes(int rows, int V, int k);
-void launch_row_topk(hipStream_t s, int dt, const void* z, int ldz, int rows, int V, int k, float* top_logp, int* top_id, float* lse,
-                     void* scratch);
-void launch_logprob_rows(hipStream_t s, int dt, const void* z, int ldz, const float* lse, float* out, int rows, int V);
+size_t row_topk_scratch_bytes(int rows, const TopkSegments& sg, int k);
+void launch_row_topk(hipStream_t s, int dt, const TopkSegments& sg, int rows, int k, float* top_logp, int* top_id, float* lse, void* scratch);
+void launch_logprob_rows(hipStream_t s, int dt, const TopkSegments& sg, const float* lse, float* out, int r0, int rows);
 
 uint64_t dropout_site_key(uint64_t seed, uint64_t step, int stream, int layer, int sub);
 

@@ -1459,10 +1459,9 @@ struct tfm_decoder {
   int* anc[2];
   int* src_off;                                    // [max_sentences + 1]: this batch's source offsets (the context's are re-used by training)
   // adaptive inputs / adaptive softmax (null without clusters)
-  void *a_head, *a_tail, *a_u, *a_xc, *a_y;        // head scores [R, v0]; one tail cluster's scores [R, vmax]; projected state [R, wmax];
+  void *a_head, *a_u, *a_xc, *a_y;                 // head scores [R, v0] (the tails' are in `logits`, [R, cluster size] each); projected state [R, wmax];
                                                    // gathered narrow input rows [R, wmax]; projected input vectors [R, d]
-  float *a_lse, *a_lp1;                            // [R]: a cluster's log-sum-exp; throw-away best value of that pass
-  int* a_id1;                                      // [R]: throw-away best id
+  float* a_off;                                    // [R, TOPK_SEGMENTS]: log p(cluster) less the cluster's log-sum-exp
   std::vector<void*> Kc, Vc, xkv;                  // per decoder layer
   // Pinned host memory that the step's kernels read and write in place, with the device's addresses of it
   int* h_src;                                      // tfm_decoder_begin: source ids / pos / offsets, copied to the device
@@ -1476,6 +1475,23 @@ struct tfm_decoder {
 
 namespace {
 
+// where a step's scores lie
+TopkSegments decode_scores(const tfm_decoder* D) {
+  const tfm_ctx* c = D->c;
+  const Adaptive& ad = c->ad;
+  static_assert(sizeof(ad.lo) / sizeof(ad.lo[0]) <= TOPK_SEGMENTS, "a segment per cluster");
+  TopkSegments s{};
+  s.n = 1 + ad.n;
+  if (!ad.n) { s.z[0] = D->logits; s.ld[0] = s.V[0] = c->cfg.vocab; return s; }
+  s.z[0] = D->a_head; s.ld[0] = ad.v0; s.V[0] = ad.hi[0];
+  for (int k = 1; k <= ad.n; ++k) {
+    s.z[k] = (const char*)D->logits + (size_t)D->rows * (ad.lo[k] - ad.lo[1]) * c->esz;
+    s.ld[k] = s.V[k] = ad.hi[k] - ad.lo[k]; s.lo[k] = ad.lo[k];
+  }
+  s.off = D->a_off;
+  return s;
+}
+
 size_t decoder_carve(tfm_decoder* D, char* base) {
   tfm_ctx* c = D->c;
   const tfm_config& cf = c->cfg;
@@ -1487,11 +1503,11 @@ size_t decoder_carve(tfm_decoder* D, char* base) {
   D->att = a.take(R * d * esz);
   D->q = a.take(R * d * esz);
   D->inter = a.take(R * F * esz);
-  D->logits = a.take(R * (size_t)cf.vocab * esz);
+  D->logits = a.take(R * (size_t)(cf.vocab - (c->ad.n ? c->ad.hi[0] : 0)) * esz);
   D->mean = (float*)a.take(R * 4);
   D->rstd = (float*)a.take(R * 4);
   D->lse = (float*)a.take(R * 4);
-  D->topk_ws = a.take(std::max(row_topk_scratch_bytes((int)R, cf.vocab, D->topk), row_topk_scratch_bytes((int)R, std::max(c->ad.vmax, 1), 1)));
+  D->topk_ws = a.take(row_topk_scratch_bytes((int)R, decode_scores(D), D->topk));
   D->lp_stage = (float*)a.take((size_t)16 * cf.vocab * 4);
   D->anc[0] = (int*)a.take(R * D->max_steps * 4);
   D->anc[1] = (int*)a.take(R * D->max_steps * 4);
@@ -1501,13 +1517,10 @@ size_t decoder_carve(tfm_decoder* D, char* base) {
     size_t wmax = 0;
     for (int k = 1; k <= ad.n; ++k) wmax = std::max(wmax, (size_t)ad.width[k]);
     D->a_head = a.take(R * (size_t)ad.v0 * esz);
-    D->a_tail = a.take(R * (size_t)ad.vmax * esz);
     D->a_u = a.take(R * wmax * esz);
     D->a_xc = a.take(R * wmax * esz);
     D->a_y = a.take(R * d * esz);
-    D->a_lse = (float*)a.take(R * 4);
-    D->a_lp1 = (float*)a.take(R * 4);
-    D->a_id1 = (int*)a.take(R * 4);
+    D->a_off = (float*)a.take(R * TOPK_SEGMENTS * 4);
   }
   D->Kc.assign(cf.dec_layers, nullptr); D->Vc.assign(cf.dec_layers, nullptr); D->xkv.assign(cf.dec_layers, nullptr);
   for (int l = 0; l < cf.dec_layers; ++l) {
@@ -1778,29 +1791,23 @@ int tfm_decoder_step(tfm_decoder* D, const int32_t* prev, const int32_t* parent,
     pending = true;
   }
   const void* top = D->norm[K & 1];
+  const TopkSegments scores = decode_scores(D);
   if (!ad.n) {
     decode_gemm(D, V, d, top, 0, nullptr, D->logits, 0, nullptr, &norm);
   } else {
     // Adaptive softmax: the head scores its tokens and one entry per tail cluster; a tail cluster projects the state down
-    // and scores its own tokens.  All scores are assembled into one row of virtual logits over the vocabulary (see
-    // launch_adaptive_virtual), which the ordinary top-k / log-softmax pass then reads.
-    const int v0 = ad.v0, c0 = ad.hi[0];
+    // and scores its own tokens.  The top-k / log-softmax pass makes one distribution of them.
+    const int v0 = ad.v0;
     decode_gemm(D, v0, d, top, 0, nullptr, D->a_head, 0, nullptr, &norm);
-    run(c, TFM_PROF_LOSS, 0.0, (double)c->esz * R * c0 * 2.0,
-        [&] { launch_adaptive_virtual(c->stream, c->dt, D->a_head, v0, c0, D->logits, V, 0, nullptr, 0, -1, nullptr, R); });
     for (int k = 1; k <= ad.n; ++k) {
       const int w = ad.width[k], Vk = ad.hi[k] - ad.lo[k];
       gemm(c, 1, R, w, d, top, d, wh(c, ad.P[k]), w, D->a_u, w);                      // u = P^T h
-      gemm(c, 0, R, Vk, w, D->a_u, w, wh(c, ad.E[k]), w, D->a_tail, Vk);              // z = E u
-      run(c, TFM_PROF_LOSS, 0.0, (double)c->esz * R * Vk * 3.0, [&] {
-        launch_row_topk(c->stream, c->dt, D->a_tail, Vk, R, Vk, 1, D->a_lp1, D->a_id1, D->a_lse, D->topk_ws);   // (for its log-sum-exp)
-        launch_adaptive_virtual(c->stream, c->dt, D->a_tail, Vk, Vk, D->logits, V, ad.lo[k], D->a_head, v0, c0 + k - 1, D->a_lse, R);
-      });
+      gemm(c, 0, R, Vk, w, D->a_u, w, wh(c, ad.E[k]), w, const_cast<void*>(scores.z[k]), Vk);                    // z = E u
     }
   }
   const size_t n = (size_t)R * D->topk;                // (the values and ids go straight to the host's memory)
   run(c, TFM_PROF_LOSS, 0.0, (double)c->esz * R * V,
-      [&] { launch_row_topk(c->stream, c->dt, D->logits, V, R, V, D->topk, D->d_out, (int*)(D->d_out + n), D->lse, D->topk_ws); });
+      [&] { launch_row_topk(c->stream, c->dt, scores, R, D->topk, D->d_out, (int*)(D->d_out + n), D->lse, D->topk_ws); });
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   HIP_TRY(c, hipGetLastError());
   std::memcpy(top_logp, D->h_out, n * 4);
@@ -1817,7 +1824,7 @@ int tfm_decoder_get_logprobs(tfm_decoder* D, float* host, int64_t n) {
   if (n != (int64_t)D->rows * V) return fail(c, TFM_EINVAL, "expected rows * vocab = %lld values", (long long)D->rows * V);
   for (int r0 = 0; r0 < D->rows; r0 += 16) {
     const int nr = std::min(16, D->rows - r0);
-    launch_logprob_rows(c->stream, c->dt, (const char*)D->logits + (size_t)r0 * V * c->esz, V, D->lse + r0, D->lp_stage, nr, V);
+    launch_logprob_rows(c->stream, c->dt, decode_scores(D), D->lse, D->lp_stage, r0, nr);
     HIP_TRY(c, hipMemcpyAsync(host + (size_t)r0 * V, D->lp_stage, (size_t)nr * V * 4, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   }

@@ -324,6 +324,54 @@ def test_candidates_are_the_top_of_the_distribution(vocab, k, distinct, prec):
     assert np.allclose(np.exp(lp.astype(np.float64)).sum(axis=1), 1.0, atol=1e-4)
 
 
+@pytest.mark.parametrize("cutoffs,vocab,k,distinct,prec", [
+    ((24,), 32, 8, 0, "fp32"), ((4,), 9, 8, 0, "fp16"),                          # fewer tokens than k in every cluster
+    ((4093, 8189), 12287, 16, 0, "fp16"), ((4097, 4099), 16399, 5, 0, "bf16"),   # blocks of odd rows, one value in a last block, a cluster of two tokens
+    ((5000, 13192), 21384, 8, 3, "fp16"), ((50, 60, 5000), 9096, 4, 2, "fp32"),  # equal values in and across clusters
+    ((24, 600000), 1100000, 16, 0, "fp16")])                                     # more lists than one block merges
+def test_candidates_of_an_adaptive_softmax_are_the_top_of_the_distribution(cutoffs, vocab, k, distinct, prec):
+    """As above, and the distribution against the oracle's, within what the other decoding tests allow."""
+    import paper_1904_01038_amd as T
+    shape = ModelShape(0, 1, 32, 1, 32, vocab, pre_norm=1, cutoffs=cutoffs, factor=2)
+    params = init_params(shape, 3, generic=True)
+    if distinct:
+        for name in list(params):
+            if name.startswith("embed") and not name.endswith("proj"):
+                params[name] = params[name][np.random.default_rng(0).integers(0, distinct, len(params[name]))]
+    p, tol = {"fp32": (T.FP32, 2e-4), "fp16": (T.FP16, 3e-2), "bf16": (T.BF16, 2e-1)}[prec]
+    ctx = T.Tfm(T.make_config(shape, precision=p, max_sentences=4, max_len=4, max_tokens=16, label_smoothing=0.0))
+    ctx.set_params(params)
+    dec = T.Decoder(ctx, 3, 2, 1, k)
+    dec.begin(None, None, 1, 3)
+    fed = np.array([[shape.eos_id] * 3, [3, vocab - 1, cutoffs[0]]], np.int32)
+    dec.step(fed[0])
+    top_lp, top_id = dec.step(fed[1])
+    lp = dec.logprobs()
+    oracle = DecodingOracle(shape, params)
+    for r in range(3):
+        order = np.lexsort((np.arange(vocab), -lp[r]))[:k]
+        assert np.array_equal(top_lp[r], lp[r, order])
+        assert top_id[r].tolist() == order.tolist()
+        assert np.max(np.abs(lp[r] - oracle.next_logprobs(None, list(fed[:, r])))) <= tol
+    assert np.allclose(np.exp(lp.astype(np.float64)).sum(axis=1), 1.0, atol=2e-3)
+
+
+@pytest.mark.parametrize("where", ["tail", "head"])
+def test_nan_scores_of_an_adaptive_softmax_reach_every_log_probability_and_no_candidate_hides(where):
+    import paper_1904_01038_amd as T
+    shape = ModelShape(0, 1, 16, 1, 16, 9000, pre_norm=1, cutoffs=(100, 5000), factor=2)
+    params = init_params(shape, 3, generic=True)
+    tables = [n for n in params if n.startswith("embed") and not n.endswith("proj")]
+    params[tables[0 if where == "head" else -1]][7] = np.nan
+    ctx = T.Tfm(T.make_config(shape, precision=T.FP16, max_sentences=4, max_len=4, max_tokens=16, label_smoothing=0.0))
+    ctx.set_params(params)
+    dec = T.Decoder(ctx, 2, 2, 1, 4)
+    dec.begin(None, None, 1, 2)
+    top_lp, top_id = dec.step(np.full(2, shape.eos_id, np.int32))
+    assert np.isnan(top_lp).all() and all(len(set(row)) == 4 for row in top_id.tolist())
+    assert ((top_id >= 0) & (top_id < (5000 if where == "tail" else 9000)) & ((top_id != 7) | (where == "tail"))).all()
+
+
 @pytest.mark.parametrize("prec,tol", [("fp16", 0.006), ("bf16", 0.03)])
 @pytest.mark.parametrize("d,heads,rows", [(d, h, r) for d, h in ((256, 4), (576, 9), (784, 7), (1024, 16)) for r in (1, 8, 9, 64)]
                          + [(576, 9, 80), (1024, 16, 80)])
