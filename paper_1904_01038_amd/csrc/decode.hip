@@ -562,11 +562,10 @@ static void row_topk_typed(hipStream_t s, TopkSegments sg, int rows, int k, floa
     return l;
   };
   int n = 0, n_in = 0;
-  uintptr_t al = 0;                                      // what every load's address is a multiple of
+  const uintptr_t al = (uintptr_t)sg.z[0] | (uintptr_t)sg.ld[0] * sizeof(T);       // what every load's address is a multiple of
   for (int i = 0; i < sg.n; ++i) {
     sg.blk0[i] = n;
     n += topk_blocks(sg.V[i], TOPK_TILE);
-    al |= (uintptr_t)sg.z[i] | (uintptr_t)sg.ld[i] * sizeof(T);
   }
   sg.blk0[sg.n] = n;
   char* bufs[2] = {(char*)scratch, (char*)scratch + (n > 1 ? topk_list_bytes(rows, n, k) : 0)};
@@ -574,10 +573,8 @@ static void row_topk_typed(hipStream_t s, TopkSegments sg, int rows, int k, floa
   // (rows along x: y and z of a grid end at 65536)
 #define TK(VEC, CLUSTERS) \
   hipLaunchKernelGGL((row_topk_kernel<T, VEC, CLUSTERS>), dim3(rows, n), dim3(TOPK_THREADS), 0, s, sg, in, n_in, k, out, top_logp, top_id, lse)
-#define TKS(CLUSTERS) do { if (al % (8 * sizeof(T)) == 0) TK(8, CLUSTERS); else if (al % (2 * sizeof(T)) == 0) TK(2, CLUSTERS); else TK(1, CLUSTERS); } while (0)
-  const bool clusters = sg.n > 1;
-  if (clusters) TKS(true); else TKS(false);
-#undef TKS
+  const bool clusters = sg.n > 1;                        // (whose loads are always of 8 values)
+  if (clusters) TK(8, true); else if (al % (8 * sizeof(T)) == 0) TK(8, false); else if (al % (2 * sizeof(T)) == 0) TK(2, false); else TK(1, false);
   for (int which = 1; n > 1; which ^= 1) {
     const bool first = n_in == 0;
     n_in = n;

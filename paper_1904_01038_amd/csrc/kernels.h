@@ -226,7 +226,8 @@ void launch_decode_attention(hipStream_t s, const DecodeAttnArgs& a);
 bool decode_attention_appends(const DecodeAttnArgs& a);   // would this launch append k_new / v_new to the caches itself?
 // The scores of a row: one segment, z[0][row][ld] of which the first V columns are tokens 0 .. V - 1.  Or those of an adaptive softmax: segment 0
 // holds the head's tokens and behind them a score for each further segment, a tail cluster with the tokens from lo on; off
-// [rows][TOPK_SEGMENTS] receives what joins a segment's scores, so that all of them are scores of one distribution.
+// [rows][TOPK_SEGMENTS] receives what joins a segment's scores, so that all of them are scores of one distribution.  Several segments begin on
+// 32-byte boundaries, and their ld is a multiple of 8 (what lies between a segment's scores and its ld is not looked at).
 constexpr int TOPK_SEGMENTS = 4;
 struct TopkSegments {
   int n;

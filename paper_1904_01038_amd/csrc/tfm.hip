@@ -1459,7 +1459,7 @@ struct tfm_decoder {
   int* anc[2];
   int* src_off;                                    // [max_sentences + 1]: this batch's source offsets (the context's are re-used by training)
   // adaptive inputs / adaptive softmax (null without clusters)
-  void *a_head, *a_u, *a_xc, *a_y;                 // head scores [R, v0] (the tails' are in `logits`, [R, cluster size] each); projected state [R, wmax];
+  void *a_head, *a_u, *a_xc, *a_y;                 // head scores (the tails' are in `logits`, see decode_scores); projected state [R, wmax];
                                                    // gathered narrow input rows [R, wmax]; projected input vectors [R, d]
   float* a_off;                                    // [R, TOPK_SEGMENTS]: log p(cluster) less the cluster's log-sum-exp
   std::vector<void*> Kc, Vc, xkv;                  // per decoder layer
@@ -1475,7 +1475,10 @@ struct tfm_decoder {
 
 namespace {
 
-// where a step's scores lie
+// Where a step's scores lie.  The segments of an adaptive softmax begin on 256-byte boundaries and their rows hold a multiple of 8 values, whatever
+// the sizes of the clusters and however many rows there are: which kernel a cluster's product runs on, and how wide its scores are read, depends
+// on that cluster's size alone.
+size_t segment_bytes(const tfm_ctx* c, size_t rows, int ld) { return (rows * ld * c->esz + 255) & ~(size_t)255; }
 TopkSegments decode_scores(const tfm_decoder* D) {
   const tfm_ctx* c = D->c;
   const Adaptive& ad = c->ad;
@@ -1483,10 +1486,13 @@ TopkSegments decode_scores(const tfm_decoder* D) {
   TopkSegments s{};
   s.n = 1 + ad.n;
   if (!ad.n) { s.z[0] = D->logits; s.ld[0] = s.V[0] = c->cfg.vocab; return s; }
-  s.z[0] = D->a_head; s.ld[0] = ad.v0; s.V[0] = ad.hi[0];
+  s.z[0] = D->a_head; s.ld[0] = (ad.v0 + 7) & ~7; s.V[0] = ad.hi[0];
+  size_t at = 0;
   for (int k = 1; k <= ad.n; ++k) {
-    s.z[k] = (const char*)D->logits + (size_t)D->rows * (ad.lo[k] - ad.lo[1]) * c->esz;
-    s.ld[k] = s.V[k] = ad.hi[k] - ad.lo[k]; s.lo[k] = ad.lo[k];
+    s.z[k] = (const char*)D->logits + at;
+    s.V[k] = ad.hi[k] - ad.lo[k]; s.lo[k] = ad.lo[k];
+    s.ld[k] = (s.V[k] + 7) & ~7;
+    at += segment_bytes(c, D->rows, s.ld[k]);
   }
   s.off = D->a_off;
   return s;
@@ -1503,11 +1509,14 @@ size_t decoder_carve(tfm_decoder* D, char* base) {
   D->att = a.take(R * d * esz);
   D->q = a.take(R * d * esz);
   D->inter = a.take(R * F * esz);
-  D->logits = a.take(R * (size_t)(cf.vocab - (c->ad.n ? c->ad.hi[0] : 0)) * esz);
+  const TopkSegments scores = decode_scores(D);        // (its sizes; where they lie follows from what is carved here)
+  size_t tails = 0;
+  for (int k = 1; k < scores.n; ++k) tails += segment_bytes(c, R, scores.ld[k]);
+  D->logits = a.take(c->ad.n ? tails : R * (size_t)cf.vocab * esz);
   D->mean = (float*)a.take(R * 4);
   D->rstd = (float*)a.take(R * 4);
   D->lse = (float*)a.take(R * 4);
-  D->topk_ws = a.take(row_topk_scratch_bytes((int)R, decode_scores(D), D->topk));
+  D->topk_ws = a.take(row_topk_scratch_bytes((int)R, scores, D->topk));
   D->lp_stage = (float*)a.take((size_t)16 * cf.vocab * 4);
   D->anc[0] = (int*)a.take(R * D->max_steps * 4);
   D->anc[1] = (int*)a.take(R * D->max_steps * 4);
@@ -1516,7 +1525,7 @@ size_t decoder_carve(tfm_decoder* D, char* base) {
     const Adaptive& ad = c->ad;
     size_t wmax = 0;
     for (int k = 1; k <= ad.n; ++k) wmax = std::max(wmax, (size_t)ad.width[k]);
-    D->a_head = a.take(R * (size_t)ad.v0 * esz);
+    D->a_head = a.take(segment_bytes(c, R, scores.ld[0]));
     D->a_u = a.take(R * wmax * esz);
     D->a_xc = a.take(R * wmax * esz);
     D->a_y = a.take(R * d * esz);
@@ -1555,13 +1564,13 @@ void decode_norm(tfm_decoder* D, const ThinNorm& q) {
   });
 }
 
-// C[rows, N] = rows W^T + bias for the step's rows.  norm (or null): how the rows are made, q.n_out being `fin`: by the product
-// itself where it can, else by a kernel of its own first.
-void decode_gemm(tfm_decoder* D, int N, int K, const void* fin, int w, const void* bias, void* C, int relu, int* deferred, const ThinNorm* norm) {
+// C[rows, N] = rows W^T + bias for the step's rows, N or ldc values apart.  norm (or null): how the rows are made, q.n_out being `fin`: by the
+// product itself where it can, else by a kernel of its own first.
+void decode_gemm(tfm_decoder* D, int N, int K, const void* fin, int w, const void* bias, void* C, int relu, int* deferred, const ThinNorm* norm, int ldc = 0) {
   tfm_ctx* c = D->c;
   const void* W = wh(c, w);
   if (norm) {
-    const GemmArgs a{c->dt, 0, D->rows, N, K, fin, K, W, K, C, N, bias, relu, nullptr, nullptr};
+    const GemmArgs a{c->dt, 0, D->rows, N, K, fin, K, W, K, C, ldc ? ldc : N, bias, relu, nullptr, nullptr};
     if (gemm_thin_norm_supported(a, *norm)) {
       if (deferred) *deferred = 0;
       run(c, TFM_PROF_GEMM, 2.0 * D->rows * N * K, (double)c->esz * ((double)D->rows * K + (double)K * N + (double)D->rows * N),
@@ -1570,7 +1579,7 @@ void decode_gemm(tfm_decoder* D, int N, int K, const void* fin, int w, const voi
     }
     decode_norm(D, *norm);
   }
-  gemm(c, 0, D->rows, N, K, fin, K, W, K, C, N, bias, relu, nullptr, nullptr, false, 0, 0.f, 1.f, deferred);
+  gemm(c, 0, D->rows, N, K, fin, K, W, K, C, ldc ? ldc : N, bias, relu, nullptr, nullptr, false, 0, 0.f, 1.f, deferred);
 }
 
 // qkv_new (self-attention): the step's fused [rows, 3d] projection, whose keys and values are to be appended to the caches k
@@ -1797,12 +1806,11 @@ int tfm_decoder_step(tfm_decoder* D, const int32_t* prev, const int32_t* parent,
   } else {
     // Adaptive softmax: the head scores its tokens and one entry per tail cluster; a tail cluster projects the state down
     // and scores its own tokens.  The top-k / log-softmax pass makes one distribution of them.
-    const int v0 = ad.v0;
-    decode_gemm(D, v0, d, top, 0, nullptr, D->a_head, 0, nullptr, &norm);
+    decode_gemm(D, ad.v0, d, top, 0, nullptr, D->a_head, 0, nullptr, &norm, scores.ld[0]);
     for (int k = 1; k <= ad.n; ++k) {
       const int w = ad.width[k], Vk = ad.hi[k] - ad.lo[k];
       gemm(c, 1, R, w, d, top, d, wh(c, ad.P[k]), w, D->a_u, w);                      // u = P^T h
-      gemm(c, 0, R, Vk, w, D->a_u, w, wh(c, ad.E[k]), w, const_cast<void*>(scores.z[k]), Vk);                    // z = E u
+      gemm(c, 0, R, Vk, w, D->a_u, w, wh(c, ad.E[k]), w, const_cast<void*>(scores.z[k]), scores.ld[k]);          // z = E u
     }
   }
   const size_t n = (size_t)R * D->topk;                // (the values and ids go straight to the host's memory)

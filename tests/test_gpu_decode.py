@@ -356,6 +356,29 @@ def test_candidates_of_an_adaptive_softmax_are_the_top_of_the_distribution(cutof
     assert np.allclose(np.exp(lp.astype(np.float64)).sum(axis=1), 1.0, atol=2e-3)
 
 
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("cutoffs,vocab", [((93, 1030), 9222), ((94, 1031), 9223), ((93, 1000, 4096), 9222)])
+def test_scores_of_a_tail_do_not_depend_on_the_rows_beside_it_nor_on_other_tails(cutoffs, vocab, prec):
+    """To the bit, with 1 to 8 rows: a first tail of 937 or 907 tokens must not take a second one of 8192 (8192, 3096 and 5126) tokens off the
+    16-byte boundary that its matrix-core product needs, whatever rows x 937 comes to.  (The few-row kernel sums a row in the
+    same order for any number of them.)"""
+    import paper_1904_01038_amd as T
+    shape = ModelShape(0, 1, 256, 4, 256, vocab, pre_norm=1, cutoffs=cutoffs, factor=2)
+    p = {"fp16": T.FP16, "bf16": T.BF16}[prec]
+    ctx = T.Tfm(T.make_config(shape, precision=p, max_sentences=8, max_len=4, max_tokens=16, label_smoothing=0.0))
+    ctx.set_params(init_params(shape, 3, generic=True))
+    fed = np.array([shape.eos_id, 3, cutoffs[0], vocab - 1, 7, cutoffs[1], 92, 5], np.int32)
+    got = {}
+    for rows in (8, 5, 3, 2, 1):
+        dec = T.Decoder(ctx, rows, 2, 1, 16)
+        dec.begin(None, None, 1, rows)
+        got[rows] = (*dec.step(fed[:rows]), dec.logprobs())
+        order = [np.lexsort((np.arange(vocab), -r))[:16] for r in got[rows][2]]
+        assert np.array_equal(got[rows][1], order) and np.array_equal(got[rows][0], np.take_along_axis(got[rows][2], np.array(order), 1))
+        for a, b in zip(got[rows], got[8]):
+            assert np.array_equal(a, b[:rows]), rows
+
+
 @pytest.mark.parametrize("where", ["tail", "head"])
 def test_nan_scores_of_an_adaptive_softmax_reach_every_log_probability_and_no_candidate_hides(where):
     import paper_1904_01038_amd as T
