@@ -9,11 +9,14 @@
 // contraction index is the slow one in memory (V for O^T = V^T P^T, K for dQ^T = K^T dS^T, Q and dO for
 // dK^T/dV^T) are staged as they lie and fetched with the CDNA4 LDS transpose read (ds_read_b64_tr_b16).
 //
-// Forward: up to 64 query rows of a (sentence, head) on 2 wavefronts; longer sentences on blocks of 4 wavefronts and 128 rows.  Online
-//          softmax over key chunks; stores the row log-sum-exp.
-// Backward, longer sentences (one launch): blocks of 128 query rows compute dQ, recomputing P from the saved log-sum-exp; blocks of 128 key
-//           rows loop over query chunks for dK/dV.  No atomics.
+// Forward: blocks of 64 query rows on 2 wavefronts, or of 128 on 4 (longer sentences, see rows128).  Online softmax over key chunks; stores
+//          the row log-sum-exp.
+// Backward, sentences of more than 64 tokens (one launch): blocks of 64 or 128 query rows compute dQ, recomputing P from the saved log-sum-exp;
+//           blocks of as many key rows loop over query chunks for dK/dV.  No atomics.
 //           Launches whose sentences all fit one chunk use a kernel that forms all three gradients in one block.
+#include <algorithm>
+#include <cmath>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -21,6 +24,9 @@
 // load -> product -> softmax chains, which only more resident wavefronts hide.
 #ifndef ATT_FWD_MIN_WAVES
 #define ATT_FWD_MIN_WAVES 3
+#endif
+#ifndef ATT_BWD_MIN_WAVES
+#define ATT_BWD_MIN_WAVES 2
 #endif
 namespace tfm {
 
@@ -288,7 +294,214 @@ __global__ __launch_bounds__(ATT_THREADS, ATT_FWD_MIN_WAVES) void attn_fwd_mfma_
   store_rows<PT>(p.out + (size_t)q0 * p.ldo + h * DH, p.ldo, qstart, lq, Ks);
 }
 
-// ---- longer sentences ----------------------------------------------------------------------------------------------------
+// ---- backward: dQ ---------------------------------------------------------------------------------------------------------
+template <typename T, bool DROP>
+__device__ __forceinline__ void attn_bwd_dq64_body(const AttnP& p, int b, int h, int chunk, uint16_t* Ks, uint16_t* Vs) {
+  const int q0 = p.q_off[b], lq = p.q_off[b + 1] - q0, k0 = p.k_off[b], lk = p.k_off[b + 1] - k0;
+  const int qstart = chunk * 64;
+  if (qstart >= lq) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const int qi0 = qstart + wave * 32;
+  const bool active = qi0 < lq;
+  const int qi = qi0 + (lane & 31);
+  const uint16_t* K = p.k + (size_t)k0 * p.ldk + h * DH;
+  const uint16_t* V = p.v + (size_t)k0 * p.ldv + h * DH;
+  u32x4 qf[4], gf[4], of[4];
+  load_frags(qf, p.q + (size_t)q0 * p.ldq + h * DH, p.ldq, qi0, lq, lane);
+  load_frags(gf, p.d_o + (size_t)q0 * p.lddo + h * DH, p.lddo, qi0, lq, lane);
+  load_frags(of, p.o + (size_t)q0 * p.ldo + h * DH, p.ldo, qi0, lq, lane);
+  float delta = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) delta += dot8<T>(gf[kk], of[kk]);
+  delta += __shfl_xor(delta, 32, 64);
+  const float L = qi < lq ? p.lse[(size_t)h * p.total_q + q0 + qi] : 0.f;
+  f32x16 acc[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
+  const int kend = p.causal ? min(lk, qstart + 64) : lk;
+  u32x4 kx[4], vx[4];
+  fetch_tile(kx, K, p.ldk, 0, lk);
+  fetch_tile(vx, V, p.ldv, 0, lk);
+  for (int kc = 0; kc < kend; kc += CH) {
+    __syncthreads();
+    put_tile(Ks, kx);
+    put_tile(Vs, vx);
+    __syncthreads();
+    if (kc + CH < kend) {
+      fetch_tile(kx, K, p.ldk, kc + CH, lk);
+      fetch_tile(vx, V, p.ldv, kc + CH, lk);
+    }
+    if (!active) continue;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const int j0 = kc + kb * 32;
+      if (j0 >= kend) break;
+      f32x16 s, dp;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        s = AMfma<T>::run(frag_direct(Ks, kb * 32, kk, lane), qf[kk], s);
+        dp = AMfma<T>::run(frag_direct(Vs, kb * 32, kk, lane), gf[kk], dp);
+      }
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const uint64_t w = DROP ? attn_drop_word(p, q0 + qi, h, j0 + 8 * g + 4 * half) : 0;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+          const int r = g * 4 + f;
+          const int j = j0 + 8 * g + 4 * half + f;
+          const bool ok = j < lk && qi < lq && (!p.causal || j <= qi);
+          const float pr = ok ? __expf(s[r] * p.scale - L) : 0.f;
+          const float dpd = !DROP ? dp[r] : (drop_keep(w, f, p.drop_thr) ? dp[r] * p.inv_keep : 0.f);   // d/d(softmax output)
+          s[r] = pr * (dpd - delta);
+        }
+      }
+      u32x4 df[2];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) df[ks][w] = AMfma<T>::pack2(s[ks * 8 + 2 * w], s[ks * 8 + 2 * w + 1]);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int db = 0; db < 2; ++db) acc[db] = AMfma<T>::run(frag_tr(Ks, db * 32, kb * 32 + ks * 16, lane), df[ks], acc[db]);
+    }
+  }
+  __syncthreads();
+  park_rows<T, PT>(Ks, wave * 32 + (lane & 31), half, acc, p.scale);
+  __syncthreads();
+  store_rows<PT>(p.dq + (size_t)q0 * p.lddq + h * DH, p.lddq, qstart, lq, Ks);
+}
+
+// ---- backward: dK, dV -------------------------------------------------------------------------------------------------------
+template <typename T, bool DROP>
+__device__ __forceinline__ void attn_bwd_dkv64_body(const AttnP& p, int b, int h, int chunk, uint16_t* Qs, uint16_t* Gs, float* Ls, float* Ds) {
+  const int q0 = p.q_off[b], lq = p.q_off[b + 1] - q0, k0 = p.k_off[b], lk = p.k_off[b + 1] - k0;
+  const int kstart = chunk * 64;
+  if (kstart >= lk) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const int kj0 = kstart + wave * 32;
+  const bool active = kj0 < lk;
+  const int kj = kj0 + (lane & 31);
+  const uint16_t* Q = p.q + (size_t)q0 * p.ldq + h * DH;
+  const uint16_t* G = p.d_o + (size_t)q0 * p.lddo + h * DH;
+  const uint16_t* O = p.o + (size_t)q0 * p.ldo + h * DH;
+  u32x4 kf[4], vf[4];
+  load_frags(kf, p.k + (size_t)k0 * p.ldk + h * DH, p.ldk, kj0, lk, lane);
+  load_frags(vf, p.v + (size_t)k0 * p.ldv + h * DH, p.ldv, kj0, lk, lane);
+  f32x16 ak[2], av[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) { ak[0][e] = ak[1][e] = av[0][e] = av[1][e] = 0.f; }
+  const int qbeg = p.causal ? kstart : 0;     // queries before the chunk's first key see none of its keys
+  for (int qc = qbeg; qc < lq; qc += CH) {
+    __syncthreads();
+    // stage Q and dO; the 8 threads that share a row also form delta = dO . O for it
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int v = threadIdx.x + ATT_THREADS * i;
+      const int r = v >> 3, c = (v & 7) * 8;
+      u32x4 xq = {0u, 0u, 0u, 0u}, xg = xq, xo = xq;
+      if (qc + r < lq) {
+        xq = *reinterpret_cast<const u32x4*>(Q + (size_t)(qc + r) * p.ldq + c);
+        xg = *reinterpret_cast<const u32x4*>(G + (size_t)(qc + r) * p.lddo + c);
+        xo = *reinterpret_cast<const u32x4*>(O + (size_t)(qc + r) * p.ldo + c);
+      }
+      *reinterpret_cast<u32x4*>(Qs + r * PT + c) = xq;
+      *reinterpret_cast<u32x4*>(Gs + r * PT + c) = xg;
+      float dl = dot8<T>(xg, xo);
+      dl += __shfl_xor(dl, 1, 64);
+      dl += __shfl_xor(dl, 2, 64);
+      dl += __shfl_xor(dl, 4, 64);
+      if ((v & 7) == 0) {
+        Ds[r] = dl;
+        Ls[r] = qc + r < lq ? p.lse[(size_t)h * p.total_q + q0 + qc + r] : 0.f;
+      }
+    }
+    __syncthreads();
+    if (!active) continue;
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      const int i0 = qc + qb * 32;
+      if (i0 >= lq) break;
+      if (p.causal && i0 + 31 < kj0) continue;       // every query of this block precedes every key of this wavefront
+      f32x16 s, dp;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        s = AMfma<T>::run(frag_direct(Qs, qb * 32, kk, lane), kf[kk], s);
+        dp = AMfma<T>::run(frag_direct(Gs, qb * 32, kk, lane), vf[kk], dp);
+      }
+      u32x4 pf[2], df[2];
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg) {
+        const int il = qb * 32 + rg * 8 + half * 4;
+        const float4 l4 = *reinterpret_cast<const float4*>(Ls + il);
+        const float4 d4 = *reinterpret_cast<const float4*>(Ds + il);
+        const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv[4] = {d4.x, d4.y, d4.z, d4.w};
+        float pr[4], dsv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = qc + il + e;
+          const bool ok = i < lq && kj < lk && (!p.causal || kj <= i);
+          pr[e] = ok ? __expf(s[rg * 4 + e] * p.scale - lv[e]) : 0.f;
+          float dpd = dp[rg * 4 + e];
+          if (DROP) {                                  // this lane's key, one query per register: a word per element
+            const bool keep = drop_keep(attn_drop_word(p, q0 + i, h, kj), kj & 3, p.drop_thr);
+            dpd = keep ? dpd * p.inv_keep : 0.f;
+            dsv[e] = pr[e] * (dpd - dv[e]);
+            pr[e] = keep ? pr[e] * p.inv_keep : 0.f;  // dV averages dO with the dropped weights
+          } else {
+            dsv[e] = pr[e] * (dpd - dv[e]);
+          }
+        }
+        pf[rg >> 1][(rg & 1) * 2] = AMfma<T>::pack2(pr[0], pr[1]);
+        pf[rg >> 1][(rg & 1) * 2 + 1] = AMfma<T>::pack2(pr[2], pr[3]);
+        df[rg >> 1][(rg & 1) * 2] = AMfma<T>::pack2(dsv[0], dsv[1]);
+        df[rg >> 1][(rg & 1) * 2 + 1] = AMfma<T>::pack2(dsv[2], dsv[3]);
+      }
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+          av[db] = AMfma<T>::run(frag_tr(Gs, db * 32, qb * 32 + ks * 16, lane), pf[ks], av[db]);
+          ak[db] = AMfma<T>::run(frag_tr(Qs, db * 32, qb * 32 + ks * 16, lane), df[ks], ak[db]);
+        }
+    }
+  }
+  __syncthreads();
+  park_rows<T, PT>(Qs, wave * 32 + (lane & 31), half, ak, p.scale);
+  park_rows<T, PT>(Gs, wave * 32 + (lane & 31), half, av, 1.f);
+  __syncthreads();
+  store_rows<PT>(p.dk + (size_t)k0 * p.lddk + h * DH, p.lddk, kstart, lk, Qs);
+  store_rows<PT>(p.dv + (size_t)k0 * p.lddv + h * DH, p.lddv, kstart, lk, Gs);
+}
+
+// One launch for the whole backward: nq_chunks blocks per (sentence, head) compute dQ, nk_chunks dK/dV; the two halves are
+// independent, so they run side by side instead of one after the other.  Blocks are dispatched x fastest: x walks the
+// (sentence, head) pairs and y the chunks in the order of decreasing work under a causal mask (dK/dV of key chunk c loops
+// over n - c query chunks, dQ of query chunk c over c + 1 key chunks), so the longest blocks of the whole launch start
+// first and the short ones fill the tail.
+template <typename T, bool DROP>
+__global__ __launch_bounds__(ATT_THREADS, ATT_BWD_MIN_WAVES) void attn_bwd_mfma_kernel(AttnP p, int nq_chunks, int nk_chunks, int H) {
+  __shared__ __attribute__((aligned(16))) uint16_t S0[CH * PT];
+  __shared__ __attribute__((aligned(16))) uint16_t S1[CH * PT];
+  __shared__ __attribute__((aligned(16))) float Ls[CH];
+  __shared__ __attribute__((aligned(16))) float Ds[CH];
+  const int b = blockIdx.x / H, h = blockIdx.x - b * H;
+  // y = 0, 1, 2, 3, ... -> dK/dV chunk 0, dQ chunk nq-1, dK/dV chunk 1, dQ chunk nq-2, ... while both kinds last
+  const int r = blockIdx.y, pairs = min(nq_chunks, nk_chunks);
+  bool is_dq;
+  int chunk;
+  if (r < 2 * pairs) { is_dq = r & 1; chunk = is_dq ? nq_chunks - 1 - (r >> 1) : (r >> 1); }
+  else if (nq_chunks > nk_chunks) { is_dq = true; chunk = nq_chunks - 1 - (r - pairs); }
+  else { is_dq = false; chunk = r - pairs; }
+  if (is_dq) attn_bwd_dq64_body<T, DROP>(p, b, h, chunk, S0, S1);
+  else attn_bwd_dkv64_body<T, DROP>(p, b, h, chunk, S0, S1, Ls, Ds);
+}
+
+// ---- longer sentences, 128 rows a block ----------------------------------------------------------------------------------------------------
 // Blocks of 4 wavefronts own 128 query rows (forward, dQ) or 128 key rows (dK and dV), 32 a wavefront, and walk the other side in chunks of 64
 // rows.  A chunk's rows are fetched into registers two chunks ahead of their use and written to one of two LDS buffers one ahead, so that
 // a chunk costs one barrier and no wait for memory; 128 own rows halve the chunks that are fetched per product against 64.
@@ -699,7 +912,7 @@ __global__ __launch_bounds__(LT_THREADS, 2) void attn_bwd_long_kernel(AttnP p, i
 // keys against Q, dO (dK, dV).  The scores are formed in both orientations by the matrix cores, which are nearly idle in
 // this kernel anyway, so nothing is transposed through LDS; the operand fragments of the block's own rows also come from
 // the staged tiles, so every input is read from memory exactly once.  Four tiles at a 144-byte pitch (16 rows x 16
-// bytes cover the 64 banks once) keep four blocks resident per CU.  Bound by the chain load -> products -> weights -> products -> store of a
+// bytes cover the 64 banks once) are 36 KB a block; the registers of 4 wavefronts leave room for three blocks per CU.  Bound by the chain load -> products -> weights -> products -> store of a
 // block, so two wavefronts form dQ while two others form dK and dV (on the 64 + 64 rows, 32 each), and weights are exponentials to base 2 of
 // one multiply-add, with dP's accumulator starting at -delta.  us inside a training step, both halves on two wavefronts and now: 64 sentences of ~50,
 // 16 heads 21.0 and 18.3; 88 of ~40, 8 heads, bf16 18.7 and 12.5; 13 in 5 tiles 15.3 and 6.7.  (Three wavefronts a SIMD: held to four, the
@@ -932,6 +1145,21 @@ static AttnP make_params(const AttnArgs& a) {
   return p;
 }
 
+// Rows of a block where a sentence has more than 64.  A block of 128 rows fetches the other side half as often and hides more of its latency, but one
+// with few rows in it keeps 4 wavefronts and 37 KB of LDS from the sentences that wait for a compute unit, where 64 rows take 2 and 18.  What
+// counts is the share of a block's rows that the sentences fill, here that of the mean length (a causal mask leaves more of the last chunk's
+// products out with 64 rows), and whether there are more (sentence, head) pairs than can run at a time.  us, 64 and 128 rows, back to back: 239
+// causal sentences, one of 87 and the others of 5-30, 16 heads, forward 11.3 and 19.4, backward 35.8 and 61.7; 198 of 19 on average, 157 at most, not
+// causal, backward 50.1 and 67.7; 29 of 131, causal, forward 14.8 and 18.0; 40 of 80, 16 heads, not causal, 10.7 and 10.4, 30.0 and 24.9, causal 9.7
+// and 10.1, 25.4 and 25.9; 2 of 194 9.5 and 8.2, 16.7 and 12.2.  Over 750 mixtures of lengths with a longest one of 65-600 this line costs 1.6 % (forward) and
+// 1.8 % (backward) against the better of both, 128 rows throughout 3 and 4 % and up to 82 %.
+static bool rows128(const AttnArgs& a, bool bwd) {
+  if ((long)a.B * a.H < 200) return true;
+  const double mean = (double)(bwd ? std::min(a.total_q, a.total_k) : a.total_q) / a.B;
+  const double fill = mean / (LT_ROWS * std::ceil(mean / LT_ROWS));
+  return fill > (a.causal ? 0.8 : !bwd && mean > LT_ROWS ? 0.57 : 0.45);
+}
+
 void launch_attention_fwd_mfma(hipStream_t s, const AttnArgs& a) {
   AttnP p = make_params(a);
   const bool drop = p.drop_thr != 0;
@@ -939,7 +1167,7 @@ void launch_attention_fwd_mfma(hipStream_t s, const AttnArgs& a) {
   // three sentences per tile on; below that the group lookup costs what the saved blocks bring)
   const bool packed = a.groups != nullptr && a.n_groups > 0 && !drop && a.max_lq <= 64 && a.max_lk <= 64 && 3 * a.n_groups <= a.B;
   p.groups = packed ? (const int4*)a.groups : nullptr;
-  if (a.max_lq > 64) {
+  if (a.max_lq > 64 && rows128(a, false)) {
     const dim3 grid(a.H * a.B, (a.max_lq + LT_ROWS - 1) / LT_ROWS), block(LT_THREADS);
     if (a.dt == F16) {
       if (drop) hipLaunchKernelGGL((attn_fwd_long_kernel<half_t, true>), grid, block, 0, s, p, a.H);
@@ -950,7 +1178,7 @@ void launch_attention_fwd_mfma(hipStream_t s, const AttnArgs& a) {
     }
     return;
   }
-  dim3 grid(a.H * (packed ? a.n_groups : a.B), 1), block(ATT_THREADS);
+  dim3 grid(a.H * (packed ? a.n_groups : a.B), (a.max_lq + 63) / 64), block(ATT_THREADS);
   if (a.dt == F16) {
     if (drop) hipLaunchKernelGGL((attn_fwd_mfma_kernel<half_t, true, false>), grid, block, 0, s, p, a.H);
     else if (packed) hipLaunchKernelGGL((attn_fwd_mfma_kernel<half_t, false, true>), grid, block, 0, s, p, a.H);
@@ -979,6 +1207,17 @@ void launch_attention_bwd_mfma(hipStream_t s, const AttnArgs& a) {
       if (drop) hipLaunchKernelGGL((attn_bwd_single_kernel<bf16_t, true, false>), grid, block, 0, s, p);
       else if (packed) hipLaunchKernelGGL((attn_bwd_single_kernel<bf16_t, false, true>), grid, block, 0, s, p);
       else hipLaunchKernelGGL((attn_bwd_single_kernel<bf16_t, false, false>), grid, block, 0, s, p);
+    }
+    return;
+  }
+  if (!rows128(a, true)) {
+    const dim3 grid(a.H * a.B, nq + nk), block(ATT_THREADS);
+    if (a.dt == F16) {
+      if (drop) hipLaunchKernelGGL((attn_bwd_mfma_kernel<half_t, true>), grid, block, 0, s, p, nq, nk, a.H);
+      else hipLaunchKernelGGL((attn_bwd_mfma_kernel<half_t, false>), grid, block, 0, s, p, nq, nk, a.H);
+    } else {
+      if (drop) hipLaunchKernelGGL((attn_bwd_mfma_kernel<bf16_t, true>), grid, block, 0, s, p, nq, nk, a.H);
+      else hipLaunchKernelGGL((attn_bwd_mfma_kernel<bf16_t, false>), grid, block, 0, s, p, nq, nk, a.H);
     }
     return;
   }

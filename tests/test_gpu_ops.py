@@ -450,6 +450,8 @@ def test_attention_forward_backward(prec, dh, case, p_drop, packed):
     # |dO| ~ 1, 64 columns rounded by 2^-12 / 0.75 and 64 queries a random sum of deviation 0.003 and largest values of 0.016)
     ([257, 64, 65], [300, 2, 130], False), ([31, 320], [65, 32], True),
     ([65], [63], False), ([40, 64], [200, 129], False),        # a short side against a long one
+    # more than 200 (sentence, head) pairs, most of them short: blocks of 64 rows
+    ([129, 65, 64, 63, 33] + [2, 9, 5] * 22, None, True), ([66, 3, 31, 2] * 18, [3, 130, 64, 2] * 18, False),
 ])
 def test_attention_of_longer_sentences(prec, case, p_drop):
     test_attention_forward_backward(prec, 64, case, p_drop, False)
@@ -457,7 +459,8 @@ def test_attention_of_longer_sentences(prec, case, p_drop):
 
 @pytest.mark.parametrize("prec", ["fp16", "bf16"])
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("lq,lk", [([30, 0, 40, 20, 0], [0, 50, 40, 20, 9]), ([90, 0, 40, 20, 0], [0, 150, 70, 20, 9])])
+@pytest.mark.parametrize("lq,lk", [([30, 0, 40, 20, 0], [0, 50, 40, 20, 9]), ([90, 0, 40, 20, 0], [0, 150, 70, 20, 9]),
+                                   ([90, 0, 40, 20, 0] + [7, 3, 12] * 40, [0, 150, 70, 20, 9] + [7, 3, 12] * 40)])
 def test_attention_with_nothing_on_one_side_of_a_sentence(prec, causal, lq, lk):
     """No queries: no gradient for the keys and values; no keys: none for the queries.  The other sentences come out as without them."""
     import torch
