@@ -7,8 +7,8 @@
 // the instructions that run once per launch few.
 //
 //  * Tiles: BM x BN output tile per block, K walked in steps of 32 or 64.  4 wavefronts up to 128x128 and for 192x128, 8 for larger ones, so
-//    that a wavefront has 64x64 or more (32x64 of the smallest): it reads (1/64 + 1/64) fragment bytes per flop where one of 32x32 reads twice that.  Which
-//    tiling: see choose_tiling.
+//    that a wavefront has 64x64 or more, and reads (1/64 + 1/64) fragment bytes per flop, half of what one of 32x32 reads.  (The two smallest tilings are for
+//    launches that leave compute units idle: 64x128 has wavefronts of 32x64, 64x64 of 32x32.)  Which tiling: see plan_gemm.
 //  * Fetch: CDNA4 direct-to-LDS buffer loads (buffer_load_dwordx4 ... lds): no staging registers and no ds_write on
 //    the load path; range-checked, so ragged M and N read zeros without branches, and a ragged K is taken care of in the first K-step.  A
 //    ring of 3 or 4 stages keeps one or two K-steps in flight; one barrier per K-step.  A lane's offsets never change (the K-step is the
@@ -667,70 +667,90 @@ bool gemm_mfma_supported(const GemmArgs& a) {
   return true;
 }
 
-// The tilings, and what a launch of each costs.  In a round (one tile on every compute unit, two of 64x64) a K-step of 64 takes `step` us
-// when the round is full and `few` when hardly a tile runs: the clock follows the power that is drawn (2.4 GHz on zeros, 1.5-1.7 on
-// normally distributed operands with all matrix cores busy), and the memory system is shared.  `first` us is launch, fetch of the
-// instructions, first trip to memory and epilogue; later rounds overlap some of that.  Fitted to 60 products of 280-4096 rows with
-// 512-32768 columns and K = 512-8192 in fp16, launches back to back over operands that no cache holds: within 10 % but for a few outliers.
-//   tiling     wavefronts  K-step  ring      measured: rows x columns x K (us; in brackets the tilings before: 128x128 on 16 wavefronts, 64x128 on 8 of
+// The tilings, and what a launch of each costs.  In a round (one tile on every compute unit, two of 64x64) a K-step of 64 takes `few` us when
+// hardly a tile runs and `one` when every compute unit has one: the clock follows the power that is drawn (2.4 GHz on zeros, 1.5-1.7 on
+// normally distributed operands with all matrix cores busy), and the memory system is shared.  Two tiles on a compute unit take `two`, whether
+// all of them have two or a few (it is the last one that counts).  `first` us is launch, fetch of the instructions, first trip to memory
+// and epilogue; later rounds overlap some of that.  Fitted to 480 products of 65-4100 rows with 64-32768 columns and K = 64-32768 (X W^T with
+// bias and ReLU, dY W with residual or mask; fp16 and bf16), each on every tiling, launches back to back out of a graph over 12 sets of
+// operands, or 600 MB of them: the tiling with the least cost is 0.5 % slower than the best of the seven on average, up to 3 % in 95 of 100 products and 19 % at
+// most (3064 x 20000, K = 256).
+//   tiling     wavefronts  K-step  ring      measured: rows x columns x K (us; in brackets 128x128 on 16 wavefronts, 64x128 on 8 of
 //                                            32x32, 192x256 and 256x256 with a ring of two, loads issued in one burst after the barrier)
-//   256x256      2 x 4       32     4        4096 x 4096 x 1024 NN 35.2 (38.7); A^T B 32768 x 1024 x 3264 187 (226)
-//   256x128      4 x 2       64     3        3000 x 8192 x 1536 74.8 (93)
-//   192x256      2 x 4       32     4        3264 x 3072 x 1024 25-27 (27.9)
-//   192x128      2 x 2       64     3        3000 x 1536 x 4608 NN 42.6, 3000 x 1536 x 8192 90 (288 tiles of 128x128 in two rounds: 64, 108)
-//   128x128      2 x 2       64     4        4096 x 1024 x 4096 NN 35.1 (40.0), 3264 x 1024 x 1024 11.2 (12.0)
-//    64x128      2 x 2       64     4        3520 x 512 x 1536 NN 10.7 (12.2)
-//    64x64       2 x 2       64     4        280 x 1024 x 3072 NN, K in 3 slices, 10.3 (24 tiles of 128x128: 20)
+//   256x256      2 x 4       32     4        4096 x 4096 x 1024 NN 36.5 (39.8); 3264 x 4096 x 1024 33.1 (34.5), NN with a mask 37.9 (43.1)
+//   256x128      4 x 2       64     3        3000 x 8192 x 1536 77.9 (81.9)
+//   192x256      2 x 4       32     4        3264 x 3072 x 1024 28.8 (29.8)
+//   192x128      2 x 2       64     3        3000 x 1536 x 4608 NN 55.3, 3000 x 1536 x 8192 89.3 (288 tiles of 128x128 in two rounds: 76.1, 122)
+//   128x128      2 x 2       64     4        4096 x 1024 x 4096 NN 42.7 (44.3), 3264 x 1024 x 1024 11.2 (11.8)
+//    64x128      2 x 2       64     4        3520 x 512 x 1536 NN 11.0 (11.8)
+//    64x64       2 x 2       64     4        280 x 1024 x 3072 NN, K in 3 slices, 10.4 (24 tiles of 128x128: 22.0)
+//   128x128      2 x 2       32     3        A^T B alone, up to 512 tiles, two on a compute unit: 6144 x 1024 x 190 7.6 (one: 10.1), 3072 x 1536 x 2902
+//                                            41.2 (48.2)
 // Wavefronts of 64x64 or more read half of the LDS bytes per flop of 32x32 ones.  Measured and dropped: 256x256 on 4 wavefronts of 128x128 (one per
 // SIMD: 8 % slower), rings of five slots (equal), two groups of wavefronts with half of the K-steps each (2 us more per launch for
-// the exchange, 3 % less per K-step).
-enum Tiling { T256x256, T256x128, T192x256, T192x128, T128x128, T64x128, T64x64, TILINGS };
-struct TilingCost { int bm, bn; float first, later, few, step; };
-static const TilingCost TILING[TILINGS] = {{256, 256, 7.f, 7.f, 0.72f, 1.75f}, {256, 128, 5.f, 5.f, 0.35f, 0.87f},
-    {192, 256, 6.f, 6.f, 0.63f, 1.4f}, {192, 128, 5.f, 5.f, 0.3f, 0.65f}, {128, 128, 4.2f, 2.f, 0.29f, 0.475f}, {64, 128, 5.2f, 2.5f, 0.23f, 0.24f},
-    {64, 64, 5.f, 2.5f, 0.11f, 0.3f}};
+// the exchange, 3 % less per K-step); over the same 480 products also 128x128 on 16 wavefronts, 128x128 with K-steps of 32 and
+// 64x128 on 8 wavefronts: with them to choose from the best is 0.4-0.8 % faster.
+enum Tiling { T256x256, T256x128, T192x256, T192x128, T128x128, T64x128, T64x64, T128x128_PAIRS, TILINGS };
+struct TilingCost { int bm, bn; float first, later, few, one, two; };
+static const TilingCost TILING[TILINGS] = {{256, 256, 7.6f, 6.5f, 0.895f, 1.82f, 0.f}, {256, 128, 5.65f, 4.f, 0.453f, 0.973f, 0.f},
+    {192, 256, 6.55f, 4.5f, 0.726f, 1.54f, 0.f}, {192, 128, 5.3f, 2.9f, 0.387f, 0.789f, 0.f}, {128, 128, 4.2f, 2.4f, 0.321f, 0.603f, 0.f},
+    {64, 128, 3.2f, 2.f, 0.253f, 0.411f, 0.f}, {64, 64, 2.85f, 2.f, 0.178f, 0.272f, 0.436f}, {128, 128, 3.5f, 2.5f, 0.4f, 0.877f, 1.144f}};
 static long tiles_of(Tiling t, int M, int N) { return (long)((M + TILING[t].bm - 1) / TILING[t].bm) * ((N + TILING[t].bn - 1) / TILING[t].bn); }
-static double launch_cost(Tiling t, long tiles, double ksteps) {
-  const long per_round = t == T64x64 ? 512 : 256, full = tiles / per_round, rest = tiles % per_round;
+static float launch_cost(Tiling t, long tiles, int ksteps) {
   const TilingCost& c = TILING[t];
-  double us = c.first + (double)(full + (rest ? 1 : 0) - 1) * c.later + full * c.step * ksteps;
-  if (rest) us += ksteps * (c.few + (c.step - c.few) * rest / per_round);
-  return us;
+  const bool pairs = c.two > 0.f;
+  const long full = tiles >> (pairs ? 9 : 8), rest = tiles & (pairs ? 511 : 255);
+  float step = (float)full * (pairs ? c.two : c.one);
+  if (rest) step += rest > 256 ? c.two : c.few + (c.one - c.few) * (1.f / 256.f) * (float)rest;
+  return c.first + (float)(full + (rest ? 1 : 0) - 1) * c.later + step * (float)ksteps;
 }
 
-// K-slices of a 64x64 tiling of X W^T or dY W with too few tiles for the chip (few rows, or a narrow output): the other operand streams through
-// more compute units.  Every slice keeps >= 4 K-steps; bias, ReLU and residual move into the reduction, a kernel of some 3 us unless
-// the caller's next one does it: 280 x 1024, K = 1024: 7.4 us in one piece, 10.3 in 3 slices; K = 3072: 11.3 and 10.3;
-// 400 x 256, K = 40000: 113 and 32.
-static int k_slices(const GemmArgs& a) {
+// X W^T and dY W with too few tiles of 64x64 for the chip (few rows, or a narrow output): K in slices, so that the other operand streams through
+// more compute units; bias, ReLU and residual move into the reduction.  That is a kernel of its own unless the caller's next one
+// does it: 1.1 us, 0.26 for every slice, whose additions wait for one another, and 0.56 for a million bytes of partial sums (fitted with the costs above
+// to 250 products in 1 to 64 slices: the count chosen here is 0.1 % slower than the best on average, 5 % at most).  90 x 1056, K = 3072: 11.8
+// in one piece, 8.6 in 4; 255 x 1024, K = 2048: 9.0 and 8.9 in 3; 204 x 512, K = 8192: 25.4, 11.3 in 6, 27.9 in 48; 400 x 256, K = 40000 32.7.
+// More tiles than compute units gain nothing, and where the other operand comes from beyond the caches they lose: 9 x 8192, K = 2048 12.7 us in
+// one piece, 10.4 in 2 (256 tiles), 12.3 in 4.
+struct GemmPlan { Tiling tiling; int slices; float cost; };
+static GemmPlan plan_slices(const GemmArgs& a) {
   const long tiles = tiles_of(T64x64, a.M, a.N);
   const int nk = (a.K + 63) / 64;
-  if (a.form == 2 || !a.splitk_ws || a.mask || a.drop_p > 0.f || tiles > 128 || nk < 8) return 1;
-  if (a.deferred_splits ? a.relu || a.residual : nk < 40) return 1;                       // (a deferred reduction has neither ReLU nor residual)
-  long n = std::min(std::min(256 / tiles, (long)nk / 4), a.deferred_splits ? (long)DEFERRED_SPLITS_MAX : 64l);
-  while (n > 1 && (size_t)n * a.M * a.N * sizeof(float) > a.splitk_ws_bytes) --n;
-  return (int)n;
+  GemmPlan best{T64x64, 1, launch_cost(T64x64, tiles, nk)};
+  if (a.form == 2 || !a.splitk_ws || a.mask || a.drop_p > 0.f || nk < 8) return best;
+  const size_t slice = (size_t)a.M * a.N * sizeof(float);
+  if (a.deferred_splits) {                               // (the next kernel takes at most so many slices, without ReLU or residual, and all at once)
+    if (a.relu || a.residual || tiles > 128) return best;
+    long n = std::min(std::min(256 / tiles, (long)nk / 4), (long)DEFERRED_SPLITS_MAX);
+    while (n > 1 && n * slice > a.splitk_ws_bytes) --n;
+    if (n > 1) best = {T64x64, (int)n, launch_cost(T64x64, n * tiles, (nk + (int)n - 1) / (int)n)};
+    return best;
+  }
+  const float per_slice = 0.26f + 0.56e-6f * (float)slice;
+  for (int n = 2; n <= 16 && n <= nk / 4 && n * tiles <= 256 && n * slice <= a.splitk_ws_bytes; ++n) {
+    const float c = launch_cost(T64x64, n * tiles, (nk + n - 1) / n) + 1.1f + per_slice * (float)n;
+    if (c < best.cost) best = {T64x64, n, c};
+  }
+  return best;
 }
 
-static Tiling choose_tiling(const GemmArgs& a) {
-  const double ks = (a.K + 63) / 64;
-  Tiling best = T128x128;
-  double cost = 1e30;
-  for (int i = 0; i < TILINGS; ++i) {
-    const Tiling t = (Tiling)i;
-    if (a.form == 2 && t != T256x256 && t != T128x128) continue;                            // (a [k][row] tile of A has 128 or 256 rows)
-    double c = launch_cost(t, tiles_of(t, a.M, a.N), ks);
-    if (t == T64x64) {
-      const int n = k_slices(a);
-      if (n > 1) c = launch_cost(t, n * tiles_of(t, a.M, a.N), (ks + n - 1) / n) + (a.deferred_splits ? 0.0 : 3.0);
-    }
-    if (c < cost) { cost = c; best = t; }
+static GemmPlan plan_gemm(const GemmArgs& a) {
+  const int nk = (a.K + 63) / 64;
+  GemmPlan best = a.form == 2 ? GemmPlan{T128x128, 1, launch_cost(T128x128, tiles_of(T128x128, a.M, a.N), nk)} : plan_slices(a);
+  const auto look = [&](Tiling t) {
+    const float c = launch_cost(t, tiles_of(t, a.M, a.N), nk);
+    if (c < best.cost) best = {t, 1, c};
+  };
+  if (a.form != 2) for (const Tiling t : {T256x256, T256x128, T192x256, T192x128, T128x128, T64x128}) look(t);
+  else {                                                 // (a [k][row] tile of A has 128 or 256 rows)
+    look(T256x256);
+    if (tiles_of(T128x128_PAIRS, a.M, a.N) <= 512) look(T128x128_PAIRS);
   }
   return best;
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES, int AHEAD>
-static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a) {
+static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a, int splits) {
   MfmaGemmParams p;
   p.M = a.M; p.N = a.N; p.K = a.K;
   p.A = (const uint16_t*)a.A; p.lda = a.lda; p.B = (const uint16_t*)a.B; p.ldb = a.ldb; p.C = (uint16_t*)a.C; p.ldc = a.ldc;
@@ -747,7 +767,6 @@ static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a) {
   p.b_bytes = (uint32_t)(a.form == 0 ? extent_bytes(a.N, a.K, a.ldb) : extent_bytes(a.K, a.N, a.ldb));
   // Split-K: slices of K go to blockIdx.y, fp32 partial tiles go to the caller's workspace and are added in a fixed order.
   const int nk = (a.K + BK - 1) / BK;
-  int splits = BM == 64 && BN == 64 ? k_slices(a) : 1;
   if (a.form == 2 && a.splitk_ws && !a.bias && !a.relu && !a.mask && !a.residual && !p.drop_thr && p.tiles_total <= 128 && nk * BK >= 2048) {
     splits = std::min(256 / p.tiles_total, 8);            // a weight gradient on its own, whose output has too few tiles to fill the chip
     while (splits > 1 && (size_t)splits * a.M * a.N * sizeof(float) > a.splitk_ws_bytes) --splits;
@@ -755,7 +774,9 @@ static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a) {
   p.ksteps_per_split = (nk + splits - 1) / splits;
   p.partial = splits > 1 ? (float*)a.splitk_ws : nullptr;
   dim3 grid(p.tiles_total, splits), block(64 * WM * WN);
-  if (a.form == 0) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, false>), grid, block, 0, s, p);
+  constexpr bool TN_ONLY = BK == 32 && BM == 128;
+  if constexpr (TN_ONLY) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, true, true>), grid, block, 0, s, p);
+  else if (a.form == 0) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, false>), grid, block, 0, s, p);
   else if constexpr (BN == BM && BM >= 128) {
     if (a.form == 1) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, true>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, true, true>), grid, block, 0, s, p);
@@ -805,7 +826,7 @@ void launch_wgrad_grouped(hipStream_t s, int dt, const WgradJob* jobs, int n) {
     t128 += tiles_of(T128x128, jobs[i].M, jobs[i].N);
     K = std::max(K, jobs[i].K);
   }
-  const double ks = (K + 63) / 64;
+  const int ks = (K + 63) / 64;
   const bool big = launch_cost(T256x256, t256, ks) <= launch_cost(T128x128, t128, ks);
   if (dt == F16) {
     if (big) wgrad_grouped_launch<half_t, 256, 256, 2, 4, 32, 4>(s, jobs, n);
@@ -818,14 +839,16 @@ void launch_wgrad_grouped(hipStream_t s, int dt, const WgradJob* jobs, int n) {
 
 template <typename T>
 static void gemm_mfma_dispatch(hipStream_t s, const GemmArgs& a) {
-  switch (choose_tiling(a)) {
-    case T256x256: gemm_mfma_launch<T, 256, 256, 2, 4, 32, 4, 1>(s, a); break;
-    case T256x128: gemm_mfma_launch<T, 256, 128, 4, 2, 64, 3, 1>(s, a); break;
-    case T192x256: gemm_mfma_launch<T, 192, 256, 2, 4, 32, 4, 1>(s, a); break;
-    case T192x128: gemm_mfma_launch<T, 192, 128, 2, 2, 64, 3, 1>(s, a); break;
-    case T64x128: gemm_mfma_launch<T, 64, 128, 2, 2, 64, 4, 1>(s, a); break;
-    case T64x64: gemm_mfma_launch<T, 64, 64, 2, 2, 64, 4, 2>(s, a); break;
-    default: gemm_mfma_launch<T, 128, 128, 2, 2, 64, 4, 1>(s, a); break;
+  const GemmPlan q = plan_gemm(a);
+  switch (q.tiling) {
+    case T256x256: gemm_mfma_launch<T, 256, 256, 2, 4, 32, 4, 1>(s, a, q.slices); break;
+    case T256x128: gemm_mfma_launch<T, 256, 128, 4, 2, 64, 3, 1>(s, a, q.slices); break;
+    case T192x256: gemm_mfma_launch<T, 192, 256, 2, 4, 32, 4, 1>(s, a, q.slices); break;
+    case T192x128: gemm_mfma_launch<T, 192, 128, 2, 2, 64, 3, 1>(s, a, q.slices); break;
+    case T64x128: gemm_mfma_launch<T, 64, 128, 2, 2, 64, 4, 1>(s, a, q.slices); break;
+    case T64x64: gemm_mfma_launch<T, 64, 64, 2, 2, 64, 4, 2>(s, a, q.slices); break;
+    case T128x128_PAIRS: gemm_mfma_launch<T, 128, 128, 2, 2, 32, 3, 1>(s, a, q.slices); break;
+    default: gemm_mfma_launch<T, 128, 128, 2, 2, 64, 4, 1>(s, a, q.slices); break;
   }
 }
 

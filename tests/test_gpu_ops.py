@@ -20,7 +20,7 @@ GEMM_SHAPES = [  # M, N, K: several tiles plus ragged tails in every dimension
     # large outputs with short contractions: the 192x256 tiling (221 tiles, ragged in both directions) and the 256x256 tiling
     # (221 tiles where 192x256 would need a second round)
     (3200, 3080, 72), (3264, 4104, 40),
-    # many rows, a narrow output, a long contraction: the 64x128 tiling (ragged in every direction)
+    # many rows, a narrow output, a long contraction (ragged in every direction)
     (1100, 520, 1032),
 ]
 
@@ -168,7 +168,8 @@ def test_few_rows_of_a_large_product_are_not_slower_than_more(rows, N, K):
 
 
 @pytest.mark.parametrize("prec", ["fp16", "bf16"])
-@pytest.mark.parametrize("shape", [(256, 128, 1100), (1024, 1024, 3041), (136, 264, 4000), (384, 128, 1024)])
+@pytest.mark.parametrize("shape", [(256, 128, 1100), (1024, 1024, 3041), (136, 264, 4000), (384, 128, 1024),
+                                   (2056, 2184, 41)])               # (306 tiles of 128x128, two on a compute unit; one slice)
 def test_gemm_split_k_weight_gradient_is_exact_and_reproducible(prec, shape):
     import torch
     import paper_1904_01038_amd as T
@@ -199,7 +200,8 @@ def test_gemm_split_k_weight_gradient_is_exact_and_reproducible(prec, shape):
 @pytest.mark.parametrize("form", [0, 1])
 @pytest.mark.parametrize("shape", [
     (2825, 1544, 136), (3330, 2056, 136), (2820, 520, 1032),   # 192x128, 256x128 and 64x128 tiles, ragged in every direction
-    (65, 72, 2568), (280, 264, 2600), (7, 8, 20008),           # 64x64 tiles with K in 2 to 64 slices, the last one ragged
+    (2820, 1032, 264),                                         # 128x128
+    (65, 72, 2568), (280, 264, 2600), (7, 8, 20008),           # 64x64 tiles with K in 6, 4 and 15 slices, the last one ragged
 ])
 def test_gemm_tilings_of_many_rows_and_slices_of_a_long_contraction(prec, form, shape):
     """Bias and ReLU, residual and mask of every tiling that the shapes elsewhere do not reach; exact on small integers (the sums of
