@@ -6,7 +6,7 @@ namespace tfm {
 
 void launch_gemm(hipStream_t s, const GemmArgs& a) {
   if (a.deferred_splits) *a.deferred_splits = 0;       // (only a split-K launch of the matrix-core kernels sets it)
-  if (a.dt == F32) launch_gemm_f32(s, a);
+  if (a.dt == F32 && gemm_f32_pays(a)) launch_gemm_f32(s, a);
   else if (gemm_mfma_supported(a)) { if (gemm_thin_supported(a) && gemm_thin_pays(a)) launch_gemm_thin(s, a); else launch_gemm_mfma(s, a); }
   else launch_gemm_naive(s, a);
 }

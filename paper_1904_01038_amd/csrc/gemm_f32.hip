@@ -1,5 +1,6 @@
 // fp32 GEMM on the matrix cores: C[M,N] = epilogue(op(A) op(B)) with v_mfma_f32_32x32x2_f32, whose products and sums are fp32.  It serves the
-// fp32 precision mode, any shape and alignment.
+// fp32 precision mode, any shape and alignment (large outputs of operands that cannot be read 16 bytes at a time go to the general kernel, see
+// gemm_f32_pays).
 //
 // The products of the small fp32 configurations (128 rows, widths of 64 to 1000) are bound by latency: few tiles, short contractions.  So a
 // block owns one 32x32 tile, its 4 or 8 wavefronts take the contraction in turns of 8 k, and every wavefront loads straight into
@@ -155,10 +156,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_f32_grouped_kernel(F32
 
 static long tiles32(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 32); }
 
-// us a launch, back to back, with 64x64 LDS tiles on the vector ALUs before and now: 128 x 64 x 256 37 and 8, 128 x 64 x 1000 127 and 12, 512^3 73 and 9; with
-// 64x64 blocks here 4096 x 1024 x 1024 244 and 169 (54 TFLOP/s), 2000 x 32768 x 512 1394 and 1321.  The error against 64 bits is 0.4-0.6 of
-// the former where wavefronts share K, equal elsewhere.  Below 1024 tiles of 32 (4 a compute unit) the small blocks keep more of the chip
-// busy; 8 wavefronts take K = 1000 in 4 trips to memory where 4 take 8, and below K = 256 have no second turn to take.
+// us a launch out of a graph, with 64x64 LDS tiles on the vector ALUs (the general kernel) and now, X W^T / dY W / A^T B: 128 x 64 x 256 37 and 4.5 / 32 and
+// 4.3 / 38 and 4.8; 128 x 64 x 1000 224 and 9.7 / 194 and 10.5 / 206 and 9.9; 512^3 93 and 7.9 / 89 and 6.9 / 107 and 7.1; with 64x64 blocks here 4096 x
+// 1024 x 1024 247 and 161 (53 TFLOP/s) / 241 and 154 / 285 and 142; 2000 x 8192 x 512 365 and 323 / 377 and 269 / 368 and 282.  The error against 64 bits
+// is 0.4-0.6 of the former where wavefronts share K, equal elsewhere.  Up to 1024 tiles of 32 (4 a compute unit) the small blocks keep more of the chip
+// busy, small and large: 512^3 7.9 and 20.8 / 6.9 and 22.6 / 7.1 and 26.5, 1024 x 1024 x 512 25.0 and 21.0 / 22.4 and 22.8 / 22.5 and 26.8, 2000 x
+// 1024 x 1024 (2016 tiles) 87 and 74 / 78 and 69 / 75 and 74; 8 wavefronts take K = 1000 in 4 trips to memory where 4 take 8, and
+// below K = 256 have no second turn to take.
 template <int FORM, bool VEC>
 static void gemm_f32_launch(hipStream_t s, const F32Params& p) {
   const dim3 small((p.N + 31) / 32, (p.M + 31) / 32), large((p.N + 63) / 64, (p.M + 63) / 64);
@@ -167,13 +171,26 @@ static void gemm_f32_launch(hipStream_t s, const F32Params& p) {
   else hipLaunchKernelGGL((gemm_f32_kernel<FORM, VEC, 1, 1, 4>), small, dim3(256), 0, s, p);
 }
 
+static bool f32_vec(const GemmArgs& a) {
+  const auto rows16 = [&](const void* q, int ld) { return ((uintptr_t)q & 15) == 0 && ld % 4 == 0; };
+  return a.form != 2 && a.K % 4 == 0 && rows16(a.A, a.lda) && (a.form != 0 || rows16(a.B, a.ldb));
+}
+
+// Whether it is faster than the general kernel, which goes through LDS.  An operand with contiguous K that is read 4 bytes at a time takes four loads of
+// 32 rows each where one of 16 bytes does otherwise; with blocks of 64x64, which have all of K to themselves, that is what bounds them.  us, the general
+// kernel and this one, X W^T: 1642 x 7588 x 645 406 and 823, 2311 x 2623 x 2018 611 and 1196, 391 x 5104 x 191 (2080 tiles of 32) 39 and
+// 48, 1119 x 1760 x 2708 (1925) 627 and 477; dY W (one such operand): 762 x 5624 x 4383 (4224) 1010 and 1512, 1785 x 1811 x 2093 (3192) 514 and 577,
+// 749 x 3996 x 193 (3000) 48.0 and 44.8, 2246 x 952 x 2718 (2130) 613 and 553.
+bool gemm_f32_pays(const GemmArgs& a) {
+  return a.form == 2 || f32_vec(a) || tiles32(a.M, a.N) <= (a.form == 0 ? 2000 : 3100);
+}
+
 void launch_gemm_f32(hipStream_t s, const GemmArgs& a) {
   if (a.M <= 0 || a.N <= 0) return;
   const F32Params p{a.M, a.N, a.K, (const float*)a.A, a.lda, (const float*)a.B, a.ldb, (float*)a.C, a.ldc, (const float*)a.bias, a.relu,
                     (const float*)a.mask, (const float*)a.residual, a.drop_key, a.drop_p > 0.f ? drop_threshold(a.drop_p) : 0u, 1.f / (1.f - a.drop_p),
                     a.mask_scale, nullptr};
-  const auto rows16 = [&](const void* q, int ld) { return ((uintptr_t)q & 15) == 0 && ld % 4 == 0; };
-  const bool vec = a.K % 4 == 0 && (a.form == 2 || rows16(a.A, a.lda)) && (a.form != 0 || rows16(a.B, a.ldb));
+  const bool vec = f32_vec(a);
   if (a.form == 0) { if (vec) gemm_f32_launch<0, true>(s, p); else gemm_f32_launch<0, false>(s, p); }
   else if (a.form == 1) { if (vec) gemm_f32_launch<1, true>(s, p); else gemm_f32_launch<1, false>(s, p); }
   else gemm_f32_launch<2, false>(s, p);
@@ -185,7 +202,9 @@ void launch_wgrad_grouped_f32(hipStream_t s, const WgradJob* jobs, int n) {
   long t32 = 0;
   int K = 0;
   for (int i = 0; i < n; ++i) { t32 += tiles32(jobs[i].M, jobs[i].N); K = std::max(K, jobs[i].K); }
-  const bool large = t32 > 2048;
+  // (small and large blocks, us: 1024 tiles, K = 128 9.9 and 9.0, 512 23 and 26, 2000 72 and 93; 2048 tiles 19 and 13, 46 and 39, 139 and
+  // 141; 4096 tiles 38 and 26, 91 and 76, 280 and 278)
+  const bool large = t32 >= 2048;
   const int edge = large ? 64 : 32;
   int tiles = 0;
   for (int i = 0; i < n; ++i) {

@@ -1,5 +1,6 @@
-// Shape-agnostic GEMM of 2-byte operands with fp32 accumulation on the vector ALUs.  It serves any shape the MFMA kernels do not
-// take (unaligned leading dimensions); it is not on the performance path.  64x64 output tile, 16-deep LDS stages, 4x4 outputs per thread.
+// Shape-agnostic GEMM with fp32 accumulation on the vector ALUs.  It serves any 2-byte shape the MFMA kernels do not take (unaligned leading
+// dimensions) and the fp32 products of gemm_f32_pays; it is not on the performance path.  64x64 output tile, 16-deep LDS stages, 4x4
+// outputs per thread.
 #include "common.h"
 #include "kernels.h"
 
@@ -83,7 +84,8 @@ static void gemm_naive_dispatch(hipStream_t s, const GemmArgs& a) {
 
 void launch_gemm_naive(hipStream_t s, const GemmArgs& a) {
   if (a.M <= 0 || a.N <= 0) return;
-  if (a.dt == F16) gemm_naive_dispatch<half_t>(s, a);
+  if (a.dt == F32) gemm_naive_dispatch<float>(s, a);
+  else if (a.dt == F16) gemm_naive_dispatch<half_t>(s, a);
   else gemm_naive_dispatch<bf16_t>(s, a);
 }
 

@@ -70,8 +70,9 @@ void launch_gemm_thin(hipStream_t s, const GemmArgs& a);
 bool gemm_thin_norm_supported(const GemmArgs& a, const ThinNorm& q);
 void launch_gemm_thin_norm(hipStream_t s, const GemmArgs& a, const ThinNorm& q);   // requires gemm_thin_norm_supported(a, q)
 bool gemm_mfma_supported(const GemmArgs& a);
-void launch_gemm_naive(hipStream_t s, const GemmArgs& a);     // 2-byte types
+void launch_gemm_naive(hipStream_t s, const GemmArgs& a);
 void launch_gemm_f32(hipStream_t s, const GemmArgs& a);       // fp32, any shape
+bool gemm_f32_pays(const GemmArgs& a);
 void launch_gemm_mfma(hipStream_t s, const GemmArgs& a);      // requires gemm_mfma_supported(a)
 // C[m, n] = bias[n] + sum over s of partial[s][m][n] (fixed order): the second half of a split-K product whose reduction was
 // deferred (2-byte types only)

@@ -70,10 +70,11 @@ def test_gemm_forms_and_epilogues(prec, form, shape):
 
 
 @pytest.mark.parametrize("form", [0, 1, 2])
-@pytest.mark.parametrize("shape", [(1, 1, 1), (33, 31, 7), (32, 32, 256), (31, 65, 257), (130, 66, 1001), (1025, 1023, 9), (1056, 1024, 36)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (33, 31, 7), (32, 32, 256), (31, 65, 257), (130, 66, 1001), (1025, 1023, 9), (1056, 1024, 36), (1601, 1567, 9), (1921, 1889, 20)])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_gemm_fp32_any_size_and_alignment_is_exact(form, shape, shift):
-    """4 and 8 wavefronts on a 32x32 tile, 64x64 blocks, K in and out of step with 4 and 8, operands on and off a 16-byte boundary."""
+    """4 and 8 wavefronts on a 32x32 tile, 64x64 blocks, K in and out of step with 4 and 8, operands on and off a 16-byte boundary, outputs beyond
+    what the matrix-core kernel takes of operands read 4 bytes at a time."""
     import torch
     import paper_1904_01038_amd as T
     M, N, K = shape
