@@ -283,7 +283,7 @@ static ThinPlan thin_plan(const GemmArgs& a) {
   // deferred reduction.)
   const int least = 64 * THIN_WAVES, need = thin_least_splits(a.K);
   const size_t slice = (size_t)a.M * a.N * 4;
-  q.defer = a.deferred_splits && !a.relu && a.splitk_ws && need <= DEFERRED_SPLITS_MAX && need * slice <= a.splitk_ws_bytes;
+  q.defer = a.deferred_splits && !a.relu && a.splitk_ws && need * slice <= a.splitk_ws_bytes;
   int splits = need;
   if (q.defer) {
     splits = std::max(splits, std::min(std::min(256 / ((a.N + 15) / 16), a.K / least), 4));
@@ -316,7 +316,7 @@ static void thin_norm_dispatch(hipStream_t s, const ThinParams& p, bool wide) {
 bool gemm_thin_supported(const GemmArgs& a) {
   if (a.form != 0 || a.M > THIN_ROWS || a.mask || a.residual || a.drop_p != 0.f) return false;
   const int least = thin_least_splits(a.K);
-  return least == 1 || (least <= 8 && a.splitk_ws && (size_t)least * a.M * a.N * 4 <= a.splitk_ws_bytes);
+  return least == 1 || (least <= DEFERRED_SPLITS_MAX && a.splitk_ws && (size_t)least * a.M * a.N * 4 <= a.splitk_ws_bytes);
 }
 // Whether it is faster than the tiled kernel.  Both wait for what a compute unit has to fetch, some 33 KiB per us: here 256 blocks
 // at a time, each its weights and all the rows again; there 512 tiles at a time, whose 64 rows are no more than that.  A few tiles

@@ -115,7 +115,8 @@ def test_steps_of_more_than_64_rows_match_the_full_decoder(name, prec, tol):
 @pytest.mark.parametrize("prec,tol", [("fp16", 3e-2), ("bf16", 2e-1)])
 @pytest.mark.parametrize("name,B,beam", [("width_768", 16, 5), ("long_ffn", 1, 4)])
 def test_contractions_long_enough_for_more_slices_than_the_next_kernel_adds(name, B, beam, prec, tol):
-    """80 rows x 768 columns leave room for 10 slices of K = 3072; K = 18432 needs 9 slices of a few-row product."""
+    """80 rows x 768 columns leave room for 10 slices of K = 3072 and 4 rows x 64 columns for 72 of K = 18432 on the tiled kernel, which must leave
+    no more than the next kernel adds (a few-row product would need 9 for the latter, and is refused)."""
     test_steps_with_reordered_beams_match_the_full_decoder(name, prec, tol, B=B, beam=beam)
 
 
