@@ -2,8 +2,8 @@
 // that is faster than the tiled kernel (gemm_thin_pays).
 //
 // Such a product is one pass over the weights, and on this chip a dependent chain: launch, one trip to memory, reduction,
-// store.  The tiled kernel walks K step by step through an LDS ring (6.6 us for 4 rows of a 1024 x 1024 layer, with the kernel
-// that adds its slices of K up); here every load of a block is in flight at once (4.1 us).  A block owns 16 * NT output columns;
+// store.  The tiled kernel walks K step by step through an LDS ring (5.7 us for 4 rows of a 1024 x 1024 layer); here every load of a
+// block is in flight at once (3.5 us).  A block owns 16 * NT output columns;
 // its 8 wavefronts split K, fetch their weights and rows straight into the registers of 16x16x32 MFMAs (weights as the left
 // operand, so that a lane ends up with 4 consecutive columns of one row), and LDS adds up the 8 partial tiles.  The contraction
 // index is dealt so that a lane reads 32 and four lanes 128 contiguous bytes of a weight row: lanes of group g take
@@ -319,20 +319,23 @@ bool gemm_thin_supported(const GemmArgs& a) {
   return least == 1 || (least <= DEFERRED_SPLITS_MAX && a.splitk_ws && (size_t)least * a.M * a.N * 4 <= a.splitk_ws_bytes);
 }
 // Whether it is faster than the tiled kernel.  Both wait for what a compute unit has to fetch, some 33 KiB per us: here 256 blocks
-// at a time, each its weights and all the rows again; there 512 tiles at a time, whose 64 rows are no more than that.  A few tiles
-// are cut along K, and a reduction kernel of about 2.5 us (80 KiB) follows unless somebody else adds the slices up; the ring's walk
-// through K makes up for the other 80 KiB.  Measured, us here / there: 4 rows of 1024 x 1024 4.1 / 6.6; 64 rows of 3072 x 1024
-// 7.7 / 9.1; 12 of 4608 x 1536 8.3 / 8.5, 20 of it 9.5 / 8.6; 16 of 32768 x 1024 13.8 / 13.9, 24 of it 14.9 / 14.0, 48 of it
-// 23.5 / 13.9; 9 of 8192 x 2048 13.5 / 10.9.  Over 940 products of 1 to 64 rows, N 256 to 207744 and K 64 to 8192 it loses 1 % to the
-// better of both (always this kernel: 16 %, never: 13 %) and is more than 5 % behind the tiled kernel in 15, by 0.8 us on average.
+// at a time, each its weights and all the rows again; there 512 tiles at a time, whose 64 rows are no more than that.  The tiled kernel
+// pays 80 KiB more for its walk through K in a ring, and with few tiles as much again for the walk through a longer K, or for the
+// reduction of its slices; where the slices are added up by somebody else it has more and shorter ones, and these are worth 40 and 20 KiB.
+// Measured, us here / there: 4 rows of 1024 x 1024 3.5 / 5.7; 64 rows of 3072 x 1024 7.2 / 6.1; 12 of 4608 x 1536 7.4 / 7.2, 20 of it 9.2 / 7.4;
+// 16 of 32768 x 1024 15.3 / 14.7, 24 of it 16.8 / 15.2, 48 of it 25.1 / 15.8; 9 of 8192 x 2048 12.6 / 10.4; deferred, 24 of 1024 x 1024
+// 3.3 / 3.6, of 1024 x 4096 4.9 / 4.5, 64 of 1024 x 1024 4.7 / 3.8.  Over 480 products of 1 to 64 rows, N 64 to 207744 and K 64 to 8192 it
+// loses 0.7 % to the better of both and is more than 5 % behind it in 26 (always this kernel: 5 % and 125, never: 19 % and 272); deferred 1.0 %
+// and 34 (9 % and 178, 10 % and 214).
 bool gemm_thin_pays(const GemmArgs& a) {
   const ThinPlan q = thin_plan(a);
   if (q.rt == 4 && q.kblock > THIN_UNITS_4 * THIN_WAVES * THIN_UNIT) return false;
   const double kib = 1024.0, tiles = (a.N + 63) / 64, rounds = std::ceil(q.blocks * q.splits / 256.0);
-  const double reduced = q.splits > 1 && !q.defer ? 40 * kib : 0.0;
+  const double reduced = q.splits > 1 && !q.defer ? 20 * kib : 0.0;
   const double here = rounds * std::min(q.kblock, a.K) * 2.0 * (16 * q.nt + 16 * q.rt) + reduced;
   const double there = (tiles <= 512 ? tiles / 512 : std::ceil(tiles / 512)) * 256.0 * a.K;
-  return here <= there + 80 * kib + (tiles <= 128 && a.K >= 512 && !q.defer ? 80 * kib : 0.0);
+  const bool walk = tiles <= 64 && a.K >= 512;
+  return q.defer ? here <= 1.15 * there + (walk ? 60 : 40) * kib : here <= there + (walk ? 160 : 80) * kib;
 }
 // ... and with the rows made by the product itself: a wavefront each (8 rows of at most 1536 values: 25 KB of LDS), the contraction
 // in one slice.  32 steps of a decoder-only model of 6 blocks (inner size 4 times the width, vocabulary 32768), ms with the rows made
