@@ -71,7 +71,7 @@ struct Arena {
 };
 
 constexpr int STAGE_SLOTS = 4;
-constexpr long long BESIDE_MIN = 1 << 21;          // rows x width from which a sub-batch uses the second stream, see tfm_ctx::beside
+constexpr double BESIDE_MIN = 2.5e9;               // rows (of both sides) x width^2 from which a sub-batch uses the second stream, see tfm_ctx::beside
 
 // Adaptive input embeddings / adaptive softmax (language model).  Cluster 0 is the head, clusters 1..n the tails.
 struct Adaptive {
@@ -106,9 +106,12 @@ struct tfm_ctx {
   // second stream beside the chain of input gradients and fill the compute units that chain leaves idle.
   hipStream_t side;
   bool overlap;
-  // Does the current sub-batch use it?  Waiting for events and sharing compute units costs a small one more than the idle units
-  // bring: rows x width 128 x 64 0.445 ms a step with the second stream and 0.33 without, 280 x 1024 3.89 and 3.56, 3520 x 512 3.84 and
-  // 3.79; 3264 x 1024 6.78 and 6.92, 4096 x 1024 36.7 and 36.7 (4 sub-batches), 3000 x 1536 7.43 and 7.66.
+  // Does the current sub-batch use it?  Waiting for events and sharing compute units costs a small one more than the idle units bring; what they
+  // bring goes with the work of a product, rows x width^2, where rows are the source's and the target's.  A train step with the second stream
+  // over one without, 6+6 blocks, sentences of 32: width 512, 2 x 1536 rows 1.029, 2 x 4096 (2.1e9) 1.009; 768, 2 x 1024 1.022, 2 x 2048 (2.4e9)
+  // 0.998, 2 x 4096 0.990; 1024, 2 x 512 1.056, 2 x 1024 (2.1e9) 1.013, 2 x 1536 (3.2e9) 0.996, 2 x 2560 0.989; 1536, 2 x 512 (2.4e9)
+  // 0.994, 2 x 1024 0.967, 2 x 3072 0.977; 8 blocks of a language model, 512, 4096 rows (1.1e9) 1.022; 1024, 2048 (2.1e9) 1.007, 3072
+  // (3.2e9) 1.000.  The shares of the two sides matter little: 1024, 2760 and 460 rows 0.999, 460 and 2760 1.007.
   bool beside;
   std::vector<hipEvent_t> sync_ev;                  // ordering events, handed out in sequence within a step
   size_t sync_used;
@@ -1314,7 +1317,7 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
   if (c->window_mb == 1) std::swap(c->g, c->g_first);
 
   // ---- forward
-  c->beside = c->overlap && Tt * (long long)d >= BESIDE_MIN;
+  c->beside = c->overlap && (double)(Ts + Tt) * d * d >= BESIDE_MIN;
   c->sync_used = 0;
   c->wq.clear();
   c->wq_tiles = 0;

@@ -138,8 +138,8 @@ def test_side_stream_beside_sub_batches_on_one_stream_gives_bit_identical_result
     shape = ModelShape(1, 1, 2048, 32, 264, 520)
     large = make_batches("base", 2, shape=shape, max_tokens=1500, lo=20, hi=90)
     small = make_batches("base", 2, shape=shape, max_tokens=300, lo=5, hi=40)
-    rows = [int(b.tgt_lens.sum()) * 2048 for b in large + small]
-    assert min(rows[:2]) >= 1 << 21 > max(rows[2:])
+    work = [int(b.tgt_lens.sum() + b.src_lens.sum()) * 2048 ** 2 for b in large + small]
+    assert min(work[:2]) >= 2.5e9 > max(work[2:])
     runs = []
     for on in (True, False):
         gpu, _ = make_pair(shape, T.FP16, dropout=0.1, init_loss_scale=4.0, max_sentences=64, max_len=96, max_tokens=2048, seed=5)
