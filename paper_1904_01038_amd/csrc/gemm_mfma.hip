@@ -671,10 +671,10 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 // hardly a tile runs and `one` when every compute unit has one: the clock follows the power that is drawn (2.4 GHz on zeros, 1.5-1.7 on
 // normally distributed operands with all matrix cores busy), and the memory system is shared.  Two tiles on a compute unit take `two`, whether
 // all of them have two or a few (it is the last one that counts).  `first` us is launch, fetch of the instructions, first trip to memory
-// and epilogue; later rounds overlap some of that.  Fitted to 480 products of 65-4100 rows with 64-32768 columns and K = 64-32768 (X W^T with
-// bias and ReLU, dY W with residual or mask; fp16 and bf16), each on every tiling, launches back to back out of a graph over 12 sets of
-// operands, or 600 MB of them: the tiling with the least cost is 0.5 % slower than the best of the seven on average, up to 3 % in 95 of 100 products and 19 % at
-// most (3064 x 20000, K = 256).
+// and epilogue; later rounds overlap some of that.  Fitted to 830 products (X W^T with bias and ReLU, dY W with residual or mask; fp16 and
+// bf16), each on every tiling, launches back to back out of a graph over 12 sets of operands, or 600 MB of them: 350 of the models' (widths 512-2048,
+// 250-4200 rows) and 480 of 65-4100 rows with 64-32768 columns and K = 64-32768.  The tiling with the least cost is 0.4 % slower than the
+// best of the seven on average, up to 2 % in 95 of 100 products and 28 % at most (3064 x 20000, K = 256).
 //   tiling     wavefronts  K-step  ring      measured: rows x columns x K (us; in brackets 128x128 on 16 wavefronts, 64x128 on 8 of
 //                                            32x32, 192x256 and 256x256 with a ring of two, loads issued in one burst after the barrier)
 //   256x256      2 x 4       32     4        4096 x 4096 x 1024 NN 36.5 (39.8); 3264 x 4096 x 1024 33.1 (34.5), NN with a mask 37.9 (43.1)
@@ -688,13 +688,13 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 //                                            41.2 (48.2)
 // Wavefronts of 64x64 or more read half of the LDS bytes per flop of 32x32 ones.  Measured and dropped: 256x256 on 4 wavefronts of 128x128 (one per
 // SIMD: 8 % slower), rings of five slots (equal), two groups of wavefronts with half of the K-steps each (2 us more per launch for
-// the exchange, 3 % less per K-step); over the same 480 products also 128x128 on 16 wavefronts, 128x128 with K-steps of 32 and
+// the exchange, 3 % less per K-step); over the 480 products also 128x128 on 16 wavefronts, 128x128 with K-steps of 32 and
 // 64x128 on 8 wavefronts: with them to choose from the best is 0.4-0.8 % faster.
 enum Tiling { T256x256, T256x128, T192x256, T192x128, T128x128, T64x128, T64x64, T128x128_PAIRS, TILINGS };
 struct TilingCost { int bm, bn; float first, later, few, one, two; };
-static const TilingCost TILING[TILINGS] = {{256, 256, 7.6f, 6.5f, 0.895f, 1.82f, 0.f}, {256, 128, 5.65f, 4.f, 0.453f, 0.973f, 0.f},
-    {192, 256, 6.55f, 4.5f, 0.726f, 1.54f, 0.f}, {192, 128, 5.3f, 2.9f, 0.387f, 0.789f, 0.f}, {128, 128, 4.2f, 2.4f, 0.321f, 0.603f, 0.f},
-    {64, 128, 3.2f, 2.f, 0.253f, 0.411f, 0.f}, {64, 64, 2.85f, 2.f, 0.178f, 0.272f, 0.436f}, {128, 128, 3.5f, 2.5f, 0.4f, 0.877f, 1.144f}};
+static const TilingCost TILING[TILINGS] = {{256, 256, 8.1f, 6.5f, 0.878f, 1.73f, 0.f}, {256, 128, 5.85f, 3.75f, 0.438f, 0.925f, 0.f},
+    {192, 256, 6.85f, 4.45f, 0.711f, 1.48f, 0.f}, {192, 128, 5.25f, 2.8f, 0.37f, 0.77f, 0.f}, {128, 128, 4.2f, 2.4f, 0.327f, 0.58f, 0.f},
+    {64, 128, 3.1f, 1.95f, 0.257f, 0.38f, 0.f}, {64, 64, 2.9f, 1.85f, 0.18f, 0.247f, 0.424f}, {128, 128, 3.5f, 2.5f, 0.4f, 0.877f, 1.144f}};
 static long tiles_of(Tiling t, int M, int N) { return (long)((M + TILING[t].bm - 1) / TILING[t].bm) * ((N + TILING[t].bn - 1) / TILING[t].bn); }
 static float launch_cost(Tiling t, long tiles, int ksteps) {
   const TilingCost& c = TILING[t];
@@ -707,7 +707,7 @@ static float launch_cost(Tiling t, long tiles, int ksteps) {
 
 // X W^T and dY W with too few tiles of 64x64 for the chip (few rows, or a narrow output): K in slices, so that the other operand streams through
 // more compute units; bias, ReLU and residual move into the reduction.  That is a kernel of its own unless the caller's next one
-// does it: 1.1 us, 0.26 for every slice, whose additions wait for one another, and 0.56 for a million bytes of partial sums (fitted with the costs above
+// does it: 1.2 us, 0.26 for every slice, whose additions wait for one another, and 0.56 for a million bytes of partial sums (fitted with the costs above
 // to 250 products in 1 to 64 slices: the count chosen here is 0.1 % slower than the best on average, 5 % at most).  90 x 1056, K = 3072: 11.8
 // in one piece, 8.6 in 4; 255 x 1024, K = 2048: 9.0 and 8.9 in 3; 204 x 512, K = 8192: 25.4, 11.3 in 6, 27.9 in 48; 400 x 256, K = 40000 32.7.
 // More tiles than compute units gain nothing, and where the other operand comes from beyond the caches they lose: 9 x 8192, K = 2048 12.7 us in
@@ -728,7 +728,7 @@ static GemmPlan plan_slices(const GemmArgs& a) {
   }
   const float per_slice = 0.26f + 0.56e-6f * (float)slice;
   for (int n = 2; n <= 16 && n <= nk / 4 && n * tiles <= 256 && n * slice <= a.splitk_ws_bytes; ++n) {
-    const float c = launch_cost(T64x64, n * tiles, (nk + n - 1) / n) + 1.1f + per_slice * (float)n;
+    const float c = launch_cost(T64x64, n * tiles, (nk + n - 1) / n) + 1.2f + per_slice * (float)n;
     if (c < best.cost) best = {T64x64, n, c};
   }
   return best;
