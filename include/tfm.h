@@ -324,7 +324,9 @@ int tfm_decoder_begin(tfm_decoder* dec, const int32_t* src, const int32_t* src_l
  * the one row parent[r] had after the previous step (same sentence; NULL = every row continues itself).
  * prev, parent: host int32 [rows].  Outputs, host, [rows, topk]: the topk largest log-probabilities of the next
  * token (fp32, natural log, computed from the logits in the compute dtype), best first, equal values in ascending
- * id order, and their token ids.  A logit of -infinity is a value like any other: such tokens follow the finite ones, in
+ * id order, and their token ids.  (What is compared are scores before the row's log-sum-exp is subtracted.  A tail cluster of an adaptive
+ * softmax offers the topk largest of its own scores: of tokens whose log-probabilities only the rounding of the cluster's
+ * share makes equal, those are returned that its scores or, among them, the ids put first.)  A logit of -infinity is a value like any other: such tokens follow the finite ones, in
  * ascending id order.  A token whose logit is NaN is never returned (its row's log-probabilities are all NaN); where fewer than
  * topk tokens are left the ids end with 0x7fffffff, which no step accepts.  Synchronises. */
 int tfm_decoder_step(tfm_decoder* dec, const int32_t* prev, const int32_t* parent, float* top_logp,

@@ -237,7 +237,8 @@ struct TopkSegments {
   float* off;
   int blk0[TOPK_SEGMENTS + 1];                           // (the launch's: first block of a segment)
 };
-// per row: log-sum-exp and the k (<= 16) largest logits as log-probabilities, best first, ties by ascending id
+// per row: log-sum-exp and the k (<= 16) largest logits as log-probabilities, best first, ties by ascending id.  Every block of a segment offers
+// the k largest of its own scores, and off is added to those: scores that differ, and are equal once it is added, are not ties to the block.
 // (scratch: row_topk_scratch_bytes)
 size_t row_topk_scratch_bytes(int rows, const TopkSegments& sg, int k);
 void launch_row_topk(hipStream_t s, int dt, const TopkSegments& sg, int rows, int k, float* top_logp, int* top_id, float* lse, void* scratch);

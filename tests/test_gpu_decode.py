@@ -357,6 +357,30 @@ def test_candidates_of_an_adaptive_softmax_are_the_top_of_the_distribution(cutof
     assert np.allclose(np.exp(lp.astype(np.float64)).sum(axis=1), 1.0, atol=2e-3)
 
 
+@pytest.mark.parametrize("vocab", [60, 9000])                   # one block of a tail's scores and three
+def test_candidates_whose_scores_differ_by_less_than_the_sum_resolves(vocab):
+    """fp32, a tail with many more than topk scores a few units in the last place apart around 1/16, which log-probabilities of -3.6 and -9.1 do
+    not tell apart: the values are the largest of the distribution, every id has the value that is returned with it, no id comes twice."""
+    import paper_1904_01038_amd as T
+    shape = ModelShape(0, 1, 32, 1, 32, vocab, pre_norm=1, cutoffs=(24,), factor=2)
+    params, k = init_params(shape, 3, generic=True), 8
+    # the state is some 1 in every column, the head's tokens score -15, the entry of the tail 0 and its tokens around 1/16
+    params["dec.ln_final.g"], params["dec.ln_final.b"] = np.full(32, 1e-2), np.ones(32)
+    params["embed"][:24], params["embed"][24:] = -15.0 / 32, 0.0
+    u = params["embed.1.proj"].sum(axis=0)
+    params["embed.1"] = u / (u @ u) / 16 * (1.0 + np.arange(vocab - 24)[::-1, None] % 23 * 2.0 ** -23)
+    ctx = T.Tfm(T.make_config(shape, precision=T.FP32, max_sentences=4, max_len=4, max_tokens=16, label_smoothing=0.0))
+    ctx.set_params(params)
+    dec = T.Decoder(ctx, 3, 2, 1, k)
+    dec.begin(None, None, 1, 3)
+    top_lp, top_id = dec.step(np.array([shape.eos_id, 3, 7], np.int32))
+    lp = dec.logprobs()
+    for r in range(3):
+        assert top_id[r].min() >= 24 and len(set(top_id[r].tolist())) == k
+        assert np.sum(lp[r] >= top_lp[r, -1]) > k                   # (there is something to choose from)
+        assert np.array_equal(top_lp[r], np.sort(lp[r])[::-1][:k]) and np.array_equal(lp[r, top_id[r]], top_lp[r])
+
+
 @pytest.mark.parametrize("prec", ["fp16", "bf16"])
 @pytest.mark.parametrize("cutoffs,vocab", [((93, 1030), 9222), ((94, 1031), 9223), ((93, 1000, 4096), 9222)])
 def test_scores_of_a_tail_do_not_depend_on_the_rows_beside_it_nor_on_other_tails(cutoffs, vocab, prec):
