@@ -178,7 +178,7 @@ size_t scan_scratch_bytes(int64_t n);
 // st->step_overflow / window_overflow (|=).
 void launch_scan(hipStream_t s, int dt, const void* x, int64_t n, float* result, DevState* st, void* scratch);
 size_t accumulate_scratch_bytes(int64_t n);
-// The same for the second or a later sub-batch of a window: also acc += x, or acc = first + x where `first` is given, in fp32, and
+// The same for the second or a later sub-batch of a window: also acc += x, or acc = first + x where `first` is given (2-byte types), in fp32, and
 // st->window_sumsq = the sum of squares of acc.  n a multiple of 8.
 void launch_accumulate(hipStream_t s, int dt, const void* x, const void* first, float* acc, int64_t n, DevState* st, void* scratch);
 void launch_convert(hipStream_t s, int src_dt, const void* src, int dst_dt, void* dst, int64_t n);

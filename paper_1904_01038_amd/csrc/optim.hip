@@ -171,8 +171,9 @@ template <typename T>
 static void accumulate_typed(hipStream_t s, const void* x, const void* first, float* acc, int64_t n, DevState* st, void* scratch) {
   const int nb = accum_blocks(n);
   const dim3 grid(nb), block(SCAN_THREADS);
-  if (first) hipLaunchKernelGGL((accumulate_kernel<T, true>), grid, block, 0, s, (const T*)x, (const T*)first, acc, n, (float2*)scratch);
-  else hipLaunchKernelGGL((accumulate_kernel<T, false>), grid, block, 0, s, (const T*)x, (const T*)nullptr, acc, n, (float2*)scratch);
+  if (sizeof(T) == 2 && first) {                         // (in fp32 the first gradient is the sum so far)
+    if constexpr (sizeof(T) == 2) hipLaunchKernelGGL((accumulate_kernel<T, true>), grid, block, 0, s, (const T*)x, (const T*)first, acc, n, (float2*)scratch);
+  } else hipLaunchKernelGGL((accumulate_kernel<T, false>), grid, block, 0, s, (const T*)x, (const T*)nullptr, acc, n, (float2*)scratch);
   hipLaunchKernelGGL(accumulate_finish_kernel, dim3(1), dim3(ACCUM_FINISH_THREADS), 0, s, (const float2*)scratch, nb, st);
 }
 void launch_accumulate(hipStream_t s, int dt, const void* x, const void* first, float* acc, int64_t n, DevState* st, void* scratch) {

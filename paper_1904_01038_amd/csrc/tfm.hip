@@ -149,7 +149,7 @@ struct tfm_ctx {
   int64_t P;               // padded flat length
   float *W, *M, *V, *G;    // fp32 master, Adam moments, window accumulator
   void *Wh, *g;            // model copy and sub-batch gradient in compute dtype (Wh == W in fp32 mode)
-  void *g_first;           // the gradient of the window's first sub-batch from the start of its second one until both are added into G
+  void *g_first;           // 2-byte types: the gradient of the window's first sub-batch from the start of its second one until both are added into G
   DevState* st;
   Stream enc, dec;
   int R;                   // row capacity
@@ -355,7 +355,7 @@ size_t carve(tfm_ctx* c, char* base) {
   c->V = (float*)a.take(c->P * 4);
   c->G = (float*)a.take(c->P * 4);
   c->g = a.take(c->P * esz);
-  c->g_first = a.take(c->P * esz);
+  c->g_first = c->dt == F32 ? nullptr : a.take(c->P * esz);
   c->Wh = c->dt == F32 ? (void*)c->W : a.take(c->P * esz);
   c->st = (DevState*)a.take(sizeof(DevState));
   c->ld_kv = cf.enc_layers ? cf.dec_layers * 2 * (int)d : 0;
@@ -1313,8 +1313,11 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
   c->dec.rows = (int)Tt; c->dec.max_len = maxt;
 
   const int d = cf.d_model, V = cf.vocab;
-  // a second sub-batch in the window: the first one's gradient stays where it is until both are added up
-  if (c->window_mb == 1) std::swap(c->g, c->g_first);
+  // a second sub-batch in the window: the first one's gradient stays where it is until both are added up (in fp32 that is the sum so far)
+  if (c->window_mb == 1) {
+    if (c->dt == F32) { void* first = c->g; c->g = c->G; c->G = (float*)first; }
+    else std::swap(c->g, c->g_first);
+  }
 
   // ---- forward
   c->beside = c->overlap && (double)(Ts + Tt) * d * d >= BESIDE_MIN;
@@ -1380,10 +1383,11 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
   });
 
   // ---- inf/nan scan of this sub-batch's gradient (+ accumulation from the second sub-batch on)
-  const double acc_bytes = c->window_mb == 0 ? 0.0 : c->window_mb == 1 ? c->esz + 4.0 : 8.0;
+  const void* first = c->window_mb == 1 ? c->g_first : nullptr;
+  const double acc_bytes = c->window_mb == 0 ? 0.0 : first ? c->esz + 4.0 : 8.0;
   run(c, TFM_PROF_OPTIM, 0.0, (double)c->P * (c->esz + acc_bytes), [&] {
     if (c->window_mb == 0) launch_scan(c->stream, c->dt, c->g, c->P, nullptr, c->st, c->scan_scratch);
-    else launch_accumulate(c->stream, c->dt, c->g, c->window_mb == 1 ? c->g_first : nullptr, c->G, c->P, c->st, c->scan_scratch);
+    else launch_accumulate(c->stream, c->dt, c->g, first, c->G, c->P, c->st, c->scan_scratch);
   });
   c->window_mb += 1;
   c->window_tokens += Tt;
