@@ -150,8 +150,8 @@ int tfm_train_step(tfm_ctx* ctx, const int32_t* src, const int32_t* tgt, const i
  * tfm_train_step with out != NULL, tfm_apply_update with out != NULL or tfm_get_scaler. */
 int tfm_apply_update(tfm_ctx* ctx, float lr, tfm_update_out* out);
 
-/* The backward pass enqueues weight-gradient GEMMs and bias column sums on a second stream that the context owns
- * (non-blocking, default priority), ordered against hip_stream with events and joined before tfm_train_step's
+/* The backward pass of all but small sub-batches enqueues weight-gradient GEMMs and bias column sums on a second stream that
+ * the context owns (non-blocking, default priority), ordered against hip_stream with events and joined before tfm_train_step's
  * inf/nan scan, so callers see one stream's semantics.  on = 0 puts everything on hip_stream; the results are
  * bit-identical either way.  Default: on. */
 int tfm_set_overlap(tfm_ctx* ctx, int32_t on);
@@ -199,9 +199,9 @@ int tfm_op_gemm(int32_t dtype, int32_t form, int32_t M, int32_t N, int32_t K, co
                 const void* B, int32_t ldb, void* C, int32_t ldc, const void* bias, int32_t relu,
                 const void* mask, const void* residual, void* stream);
 
-/* Same as tfm_op_gemm with a caller-owned fp32 device workspace.  With it the "TN" form without epilogue may split K
- * across blocks when the output has few tiles (weight gradients); partial tiles are added in a fixed order, so the
- * result stays reproducible.  workspace may be NULL (then identical to tfm_op_gemm).
+/* Same as tfm_op_gemm with a caller-owned fp32 device workspace.  With it a product of 2-byte operands whose output has few
+ * tiles may split K across blocks (the "TN" form without epilogue; the others with bias, ReLU and residual, not with
+ * mask or dropout); partial tiles are added in a fixed order, so the result stays reproducible.  workspace may be NULL (then identical to tfm_op_gemm).
  * Two more epilogue steps, as the feed-forward layer with dropout on its hidden activations needs them: drop_p > 0
  * applies inverted dropout after bias and ReLU (element m * N + n of the counter-based generator with key drop_key,
  * kept values multiplied by 1 / (1 - drop_p)); with mask, the kept elements are also multiplied by mask_scale (pass 1

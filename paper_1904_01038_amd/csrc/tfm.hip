@@ -116,7 +116,7 @@ struct tfm_ctx {
   std::vector<hipEvent_t> sync_ev;                  // ordering events, handed out in sequence within a step
   size_t sync_used;
   // Deferred weight gradients: queued while the chain of input gradients runs, launched as grouped GEMMs (one launch
-  // for the tiles of many projections) on the side stream.
+  // for the tiles of many projections) on the side stream, where the sub-batch uses it.
   std::vector<WgradJob> wq;
   std::vector<double> wq_flops;
   long wq_tiles;
@@ -544,8 +544,8 @@ void gemm(tfm_ctx* c, int form, int M, int N, int K, const void* A, int lda, con
   const double bytes = (double)c->esz * ((double)M * K + (double)K * N + (double)M * N * (1.0 + (mask ? 1.0 : 0.0) + (residual ? 1.0 : 0.0)));
   run(c, TFM_PROF_GEMM, 2.0 * M * N * K, bytes, [&] { launch_gemm(stream, a); }, stream);
 }
-// Launches the queued weight gradients as one grouped GEMM on the side stream (after everything enqueued on the main
-// stream so far, which produced their operands).
+// Launches the queued weight gradients as one grouped GEMM: on the side stream, after everything enqueued on the main stream so
+// far, which produced their operands, or for a small sub-batch (tfm_ctx::beside) on the main one.
 void flush_wgrads(tfm_ctx* c) {
   if (c->wq.empty() && c->lnq.empty()) return;
   hipStream_t stream = wstream(c);
@@ -569,7 +569,8 @@ void flush_wgrads(tfm_ctx* c) {
 
 // Weight gradient dW[M,N] = A^T B over K rows and, if bias_grad is given, the bias gradient [M] = column sums of A.
 // A and B must stay untouched until the end of the backward pass: the product is queued, not launched.  Shapes the
-// grouped matrix-core kernel does not take (fp32 mode, widths that are not multiples of 8) run at once on the side stream.
+// grouped kernels do not take (2-byte types with widths that are not multiples of 8) run at once, on the stream that the queue
+// would go to.
 void wgrad(tfm_ctx* c, int M, int N, int K, const void* A, int lda, const void* B, int ldb, void* C, int ldc, void* bias_grad = nullptr) {
   if (M <= 0 || N <= 0) return;
   WgradJob j{M, N, K, A, lda, B, ldb, C, ldc, bias_grad};
