@@ -749,6 +749,8 @@ static GemmPlan plan_gemm(const GemmArgs& a) {
   return best;
 }
 
+bool gemm_mfma_slices(const GemmArgs& a) { return plan_gemm(a).slices > 1; }
+
 template <typename T, int BM, int BN, int WM, int WN, int BK, int STAGES, int AHEAD>
 static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a, int splits) {
   MfmaGemmParams p;

@@ -330,6 +330,7 @@ bool gemm_thin_supported(const GemmArgs& a) {
 bool gemm_thin_pays(const GemmArgs& a) {
   const ThinPlan q = thin_plan(a);
   if (q.rt == 4 && q.kblock > THIN_UNITS_4 * THIN_WAVES * THIN_UNIT) return false;
+  if (q.defer && !gemm_mfma_slices(a)) return true;      // (a sum that the next kernel is to take in 32 bits: there it would leave 2-byte values)
   const double kib = 1024.0, tiles = (a.N + 63) / 64, rounds = std::ceil(q.blocks * q.splits / 256.0);
   const double reduced = q.splits > 1 && !q.defer ? 20 * kib : 0.0;
   const double here = rounds * std::min(q.kblock, a.K) * 2.0 * (16 * q.nt + 16 * q.rt) + reduced;

@@ -73,6 +73,7 @@ bool gemm_mfma_supported(const GemmArgs& a);
 void launch_gemm_naive(hipStream_t s, const GemmArgs& a);
 void launch_gemm_f32(hipStream_t s, const GemmArgs& a);       // fp32, any shape
 bool gemm_f32_pays(const GemmArgs& a);
+bool gemm_mfma_slices(const GemmArgs& a);                     // does it cut K, i.e. leave fp32 slices to a deferred reduction?
 void launch_gemm_mfma(hipStream_t s, const GemmArgs& a);      // requires gemm_mfma_supported(a)
 // C[m, n] = bias[n] + sum over s of partial[s][m][n] (fixed order): the second half of a split-K product whose reduction was
 // deferred (2-byte types only)

@@ -421,7 +421,7 @@ def test_nan_scores_of_an_adaptive_softmax_reach_every_log_probability_and_no_ca
 
 
 @pytest.mark.parametrize("prec,tol", [("fp16", 0.006), ("bf16", 0.03)])
-@pytest.mark.parametrize("d,heads,rows", [(d, h, r) for d, h in ((256, 4), (576, 9), (784, 7), (1024, 16)) for r in (1, 8, 9, 64)]
+@pytest.mark.parametrize("d,heads,rows", [(d, h, r) for d, h in ((256, 4), (400, 5), (576, 9), (784, 7), (1024, 16)) for r in (1, 8, 9, 64)]
                          + [(576, 9, 80), (1024, 16, 80)])
 def test_a_sub_layers_result_is_added_to_the_residual_in_32_bits(d, heads, rows, prec, tol):
     """The attention's output projection cancels the residual down to 2e-4 of it; rounded to 2 bytes before the sum, nothing of the
