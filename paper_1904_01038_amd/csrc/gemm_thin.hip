@@ -319,24 +319,25 @@ bool gemm_thin_supported(const GemmArgs& a) {
   return least == 1 || (least <= DEFERRED_SPLITS_MAX && a.splitk_ws && (size_t)least * a.M * a.N * 4 <= a.splitk_ws_bytes);
 }
 // Whether it is faster than the tiled kernel.  Both wait for what a compute unit has to fetch, some 33 KiB per us: here 256 blocks
-// at a time, each its weights and all the rows again; there 512 tiles at a time, whose 64 rows are no more than that.  The tiled kernel
-// pays 80 KiB more for its walk through K in a ring, and with few tiles as much again for the walk through a longer K, or for the
-// reduction of its slices; where the slices are added up by somebody else it has more and shorter ones, and these are worth 40 and 20 KiB.
-// Measured, us here / there: 4 rows of 1024 x 1024 3.5 / 5.7; 64 rows of 3072 x 1024 7.2 / 6.1; 12 of 4608 x 1536 7.4 / 7.2, 20 of it 9.2 / 7.4;
-// 16 of 32768 x 1024 15.3 / 14.7, 24 of it 16.8 / 15.2, 48 of it 25.1 / 15.8; 9 of 8192 x 2048 12.6 / 10.4; deferred, 24 of 1024 x 1024
-// 3.3 / 3.6, of 1024 x 4096 4.9 / 4.5, 64 of 1024 x 1024 4.7 / 3.8.  Over 480 products of 1 to 64 rows, N 64 to 207744 and K 64 to 8192 it
-// loses 0.7 % to the better of both and is more than 5 % behind it in 26 (always this kernel: 5 % and 125, never: 19 % and 272); deferred 1.0 %
-// and 34 (9 % and 178, 10 % and 214).
+// at a time, each its weights and all the rows again, and 1 KiB a row more for the sums of the wavefronts (20 for the reduction of slices);
+// there 512 tiles at a time, whose 64 rows are no more than that.  The tiled kernel pays 60 KiB more for its start, and with few tiles 100 for
+// the walk through a longer K in a ring, or for the reduction of its slices; where the slices are added up by somebody else it has more and
+// shorter ones, and 60 KiB are all that is left.  Measured alone, us here / there: 4 rows of 1024 x 1024 3.5 / 5.7; of 3072 x 1024 32 rows 5.3 / 6.0, 64
+// 7.2 / 6.1; of 1536 x 512 48 rows 4.5 / 4.6; of 5120 x 1280 12 rows 7.3 / 8.6, 20 8.9 / 8.8; of 6144 x 1536 16 8.9 / 10.2; of 32768 x 1024 6 13.2 / 13.3,
+// 16 14.5 / 13.6, 48 23.6 / 15.2; of 207744 x 64 16 10.5 / 19.0, 32 16.6 / 19.6, 48 27.3 / 20.7; deferred, of 1024 x 1024 32 3.7 / 3.6, 64 4.7 / 3.8, of
+// 1024 x 4096 16 4.3 / 4.4, 32 5.3 / 4.5.  Over 930 products of 1 to 64 rows, N 64 to 207744 and K 64 to 8192, it loses 0.5 % to the better of
+// both and is more than 5 % behind it in 33 (always this kernel: 7 % and 279, never: 16 % and 505); deferred, 603 products, 1.2 % and 53 (12 % and
+// 298, 5 % and 176).  In decoder-only models of width 512 to 2048, 9 to 64 rows, where the weights come from memory if there are more than 256 MB of
+// them and the slices' reduction is in the next kernel, each kind of product on either kernel: 0.35 % of the step (5.8 and 6.2 %).
 bool gemm_thin_pays(const GemmArgs& a) {
   const ThinPlan q = thin_plan(a);
   if (q.rt == 4 && q.kblock > THIN_UNITS_4 * THIN_WAVES * THIN_UNIT) return false;
   if (q.defer && !gemm_mfma_slices(a)) return true;      // (a sum that the next kernel is to take in 32 bits: there it would leave 2-byte values)
   const double kib = 1024.0, tiles = (a.N + 63) / 64, rounds = std::ceil(q.blocks * q.splits / 256.0);
-  const double reduced = q.splits > 1 && !q.defer ? 20 * kib : 0.0;
-  const double here = rounds * std::min(q.kblock, a.K) * 2.0 * (16 * q.nt + 16 * q.rt) + reduced;
+  const double per_row = rounds * std::min(q.kblock, a.K) * 2.0;
   const double there = (tiles <= 512 ? tiles / 512 : std::ceil(tiles / 512)) * 256.0 * a.K;
-  const bool walk = tiles <= 64 && a.K >= 512;
-  return q.defer ? here <= 1.15 * there + (walk ? 60 : 40) * kib : here <= there + (walk ? 160 : 80) * kib;
+  if (q.defer) return per_row * (16 * q.nt + 16 * q.rt) <= 1.15 * there + 60 * kib;
+  return per_row * (16 * q.nt + a.M) + (a.M + (q.splits > 1 ? 20 : 0)) * kib <= there + (tiles <= 96 && a.K >= 512 ? 160 : 60) * kib;
 }
 // ... and with the rows made by the product itself: a wavefront each (8 rows of at most 1536 values: 25 KB of LDS), the contraction
 // in one slice.  32 steps of a decoder-only model of 6 blocks (inner size 4 times the width, vocabulary 32768), ms with the rows made
