@@ -669,12 +669,16 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 
 // The tilings, and what a launch of each costs.  In a round (one tile on every compute unit, two of 64x64) a K-step of 64 takes `few` us when
 // hardly a tile runs and `one` when every compute unit has one: the clock follows the power that is drawn (2.4 GHz on zeros, 1.5-1.7 on
-// normally distributed operands with all matrix cores busy), and the memory system is shared.  Two tiles on a compute unit take `two`, whether
-// all of them have two or a few (it is the last one that counts).  `first` us is launch, fetch of the instructions, first trip to memory
+// normally distributed operands with all matrix cores busy), and the memory system is shared.  Two tiles on a compute unit take `two` where
+// all of them have two and `some` where hardly any has.  `first` us is launch, fetch of the instructions, first trip to memory
 // and epilogue; later rounds overlap some of that.  Fitted to 830 products (X W^T with bias and ReLU, dY W with residual or mask; fp16 and
 // bf16), each on every tiling, launches back to back out of a graph over 12 sets of operands, or 600 MB of them: 350 of the models' (widths 512-2048,
-// 250-4200 rows) and 480 of 65-4100 rows with 64-32768 columns and K = 64-32768.  The tiling with the least cost is 0.4 % slower than the
-// best of the seven on average, up to 2 % in 95 of 100 products and 28 % at most (3064 x 20000, K = 256).
+// 250-4200 rows) and 480 of 65-4100 rows with 64-32768 columns and K = 64-32768.  The tiling with the least cost is 1.2 % slower than the
+// best of the seven on average, up to 11 % in 95 of 100 products and 28 % at most (3064 x 20000, K = 256).  Most of that is `some` of 64x64, which is not
+// from these but from training steps of 12 blocks, whose operands come from memory and whose clock is higher; by the products alone 0.424 it
+// would be (0.4 %, 2 %).  ms a step, with 0.424 and 0.3: 264 tiles (2100 x 512) 2.25 and 2.19, 272 (1060 x 1024) 3.70 and 3.58, 288 (720 x 1536) 5.77 and
+// 5.61, 312 (800 x 1536) 5.81 and 5.70, 328 (2600 x 512) 2.33 and 2.34, 336 (1300 x 1024) 3.82 and 3.92, 360 (900 x 1536) 5.89 and 5.93; with 0.28 the last
+// one 6.18.  (Of 4 blocks, whose operands stay in the cache, 0.424 is the better one from 300 tiles on.)
 //   tiling     wavefronts  K-step  ring      measured: rows x columns x K (us; in brackets 128x128 on 16 wavefronts, 64x128 on 8 of
 //                                            32x32, 192x256 and 256x256 with a ring of two, loads issued in one burst after the barrier)
 //   256x256      2 x 4       32     4        4096 x 4096 x 1024 NN 36.5 (39.8); 3264 x 4096 x 1024 33.1 (34.5), NN with a mask 37.9 (43.1)
@@ -691,17 +695,17 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 // the exchange, 3 % less per K-step); over the 480 products also 128x128 on 16 wavefronts, 128x128 with K-steps of 32 and
 // 64x128 on 8 wavefronts: with them to choose from the best is 0.4-0.8 % faster.
 enum Tiling { T256x256, T256x128, T192x256, T192x128, T128x128, T64x128, T64x64, T128x128_PAIRS, TILINGS };
-struct TilingCost { int bm, bn; float first, later, few, one, two; };
-static const TilingCost TILING[TILINGS] = {{256, 256, 8.1f, 6.5f, 0.878f, 1.73f, 0.f}, {256, 128, 5.85f, 3.75f, 0.438f, 0.925f, 0.f},
-    {192, 256, 6.85f, 4.45f, 0.711f, 1.48f, 0.f}, {192, 128, 5.25f, 2.8f, 0.37f, 0.77f, 0.f}, {128, 128, 4.2f, 2.4f, 0.327f, 0.58f, 0.f},
-    {64, 128, 3.1f, 1.95f, 0.257f, 0.38f, 0.f}, {64, 64, 2.9f, 1.85f, 0.18f, 0.247f, 0.424f}, {128, 128, 3.5f, 2.5f, 0.4f, 0.877f, 1.144f}};
+struct TilingCost { int bm, bn; float first, later, few, one, some, two; };
+static const TilingCost TILING[TILINGS] = {{256, 256, 8.1f, 6.5f, 0.878f, 1.73f, 0.f, 0.f}, {256, 128, 5.85f, 3.75f, 0.438f, 0.925f, 0.f, 0.f},
+    {192, 256, 6.85f, 4.45f, 0.711f, 1.48f, 0.f, 0.f}, {192, 128, 5.25f, 2.8f, 0.37f, 0.77f, 0.f, 0.f}, {128, 128, 4.2f, 2.4f, 0.327f, 0.58f, 0.f, 0.f},
+    {64, 128, 3.1f, 1.95f, 0.257f, 0.38f, 0.f, 0.f}, {64, 64, 2.9f, 1.85f, 0.18f, 0.247f, 0.3f, 0.424f}, {128, 128, 3.5f, 2.5f, 0.4f, 0.877f, 1.144f, 1.144f}};
 static long tiles_of(Tiling t, int M, int N) { return (long)((M + TILING[t].bm - 1) / TILING[t].bm) * ((N + TILING[t].bn - 1) / TILING[t].bn); }
 static float launch_cost(Tiling t, long tiles, int ksteps) {
   const TilingCost& c = TILING[t];
   const bool pairs = c.two > 0.f;
   const long full = tiles >> (pairs ? 9 : 8), rest = tiles & (pairs ? 511 : 255);
   float step = (float)full * (pairs ? c.two : c.one);
-  if (rest) step += rest > 256 ? c.two : c.few + (c.one - c.few) * (1.f / 256.f) * (float)rest;
+  if (rest) step += rest > 256 ? c.some + (c.two - c.some) * (1.f / 256.f) * (float)(rest - 256) : c.few + (c.one - c.few) * (1.f / 256.f) * (float)rest;
   return c.first + (float)(full + (rest ? 1 : 0) - 1) * c.later + step * (float)ksteps;
 }
 
