@@ -11,7 +11,7 @@
 //    launches that leave compute units idle: 64x128 has wavefronts of 32x64, 64x64 of 32x32.)  Which tiling: see plan_gemm.
 //  * Fetch: CDNA4 direct-to-LDS buffer loads (buffer_load_dwordx4 ... lds): no staging registers and no ds_write on
 //    the load path; range-checked, so ragged M and N read zeros without branches, and a ragged K is taken care of in the first K-step.  A
-//    ring of 3 or 4 stages keeps one or two K-steps in flight; one barrier per K-step.  A lane's offsets never change (the K-step is the
+//    ring of 3 to 5 stages keeps two to four K-steps in flight; one barrier per K-step.  A lane's offsets never change (the K-step is the
 //    scalar offset), and the loads are issued a few behind every MFMA: in one burst after the barrier they held up the wavefront
 //    that issued them (256x256: 2550 clocks per 64 of K, spread 2300, the MFMAs alone 2048).  They are issued as assembly and tracked
 //    with s_waitcnt vmcnt by hand, because the compiler would otherwise drain every outstanding direct-to-LDS load before each LDS read.
@@ -687,11 +687,13 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 //   192x128      2 x 2       64     3        3000 x 1536 x 4608 NN 55.3, 3000 x 1536 x 8192 89.3 (288 tiles of 128x128 in two rounds: 76.1, 122)
 //   128x128      2 x 2       64     4        4096 x 1024 x 4096 NN 42.7 (44.3), 3264 x 1024 x 1024 11.2 (11.8)
 //    64x128      2 x 2       64     4        3520 x 512 x 1536 NN 11.0 (11.8)
-//    64x64       2 x 2       64     4        280 x 1024 x 3072 NN, K in 3 slices, 10.4 (24 tiles of 128x128: 22.0)
+//    64x64       2 x 2       64     5        280 x 1024 x 3072 NN, K in 3 slices, 10.4 (24 tiles of 128x128: 22.0).  80 KB, so two blocks share a compute unit.
+//                                            Few rows find their weights in memory, and a fourth K-step in flight covers more of that trip: the eight
+//                                            products, LayerNorms and attentions of a decoder block for 268 rows 73.8 -> 71.4 us (6 slots 72.7, 8 74.9, 3 80.1)
 //   128x128      2 x 2       32     3        A^T B alone, up to 512 tiles, two on a compute unit: 6144 x 1024 x 190 7.6 (one: 10.1), 3072 x 1536 x 2902
 //                                            41.2 (48.2)
 // Wavefronts of 64x64 or more read half of the LDS bytes per flop of 32x32 ones.  Measured and dropped: 256x256 on 4 wavefronts of 128x128 (one per
-// SIMD: 8 % slower), rings of five slots (equal), two groups of wavefronts with half of the K-steps each (2 us more per launch for
+// SIMD: 8 % slower), rings of five slots elsewhere (equal; 64x128 up to 4 % slower), two groups of wavefronts with half of the K-steps each (2 us more per launch for
 // the exchange, 3 % less per K-step); over the 480 products also 128x128 on 16 wavefronts, 128x128 with K-steps of 32 and
 // 64x128 on 8 wavefronts: with them to choose from the best is 0.4-0.8 % faster.
 enum Tiling { T256x256, T256x128, T192x256, T192x128, T128x128, T64x128, T64x64, T128x128_PAIRS, TILINGS };
@@ -852,7 +854,7 @@ static void gemm_mfma_dispatch(hipStream_t s, const GemmArgs& a) {
     case T192x256: gemm_mfma_launch<T, 192, 256, 2, 4, 32, 4, 1>(s, a, q.slices); break;
     case T192x128: gemm_mfma_launch<T, 192, 128, 2, 2, 64, 3, 1>(s, a, q.slices); break;
     case T64x128: gemm_mfma_launch<T, 64, 128, 2, 2, 64, 4, 1>(s, a, q.slices); break;
-    case T64x64: gemm_mfma_launch<T, 64, 64, 2, 2, 64, 4, 2>(s, a, q.slices); break;
+    case T64x64: gemm_mfma_launch<T, 64, 64, 2, 2, 64, 5, 2>(s, a, q.slices); break;
     case T128x128_PAIRS: gemm_mfma_launch<T, 128, 128, 2, 2, 32, 3, 1>(s, a, q.slices); break;
     default: gemm_mfma_launch<T, 128, 128, 2, 2, 64, 4, 1>(s, a, q.slices); break;
   }
