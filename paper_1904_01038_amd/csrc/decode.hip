@@ -128,152 +128,167 @@ __global__ __launch_bounds__(64) void decode_attention_kernel(DecodeAttnArgs p) 
 }
 
 // The same for head width 64 and 2-byte elements, one wavefront and two trips to memory: the position table and the query,
-// then the keys AND the values of a chunk of positions together, so that the values travel while the scores are formed.  Lane =
-// (group g = lane / 8, 16-byte piece f = lane % 8): a load fetches 8 whole 128-byte rows, where a lane per position made it touch
-// 64 lines (11.1 -> 9.9 us for 268 rows x 16 heads), and a group's weights are where its value rows arrive.  Longer histories go
-// on in chunks with a running maximum.  Lane exchanges only, no LDS but for a query that arrives in slices.
+// then the keys AND the values of a chunk of positions together, so that the values travel while the scores are formed.  Longer histories go
+// on in chunks with a running maximum.  Bound by that chain (a launch that loads and stores a little takes 1.6-2.5 us) up to some 1000 wavefronts, then
+// by instructions and by the keys and values.  So the instructions are few: the scores of 16 positions are two MFMAs, keys as the left operand
+// (lane = position, group of 8 features), the query in all 16 columns of the right one, and come out 4 positions to a group of 16 lanes,
+// in all of its lanes; a lane then asks for 16 bytes of the values of two of its group's positions, 8 whole rows of 128 bytes a load, and
+// the final sum over lanes halves what a lane holds with every exchange.  (Scores by 8 FMAs and 3 lane exchanges for every 16 bytes of a
+// key, and every lane with the whole sum: 381 -> 560 vector instructions for 32 positions; 64 wavefronts and 21 positions 3.3 us against 2.7,
+// 384 3.1 against 2.7, 1024 and 16 positions 2.9 against 2.7, 4096 5.2 and 5.2.  Relative error of the result against 64 bits, keys from 3e-6 to 8 in size,
+// the same five digits.)
 // The beams of a sentence are the wavefronts of one block: they read the same source positions (and mostly the same history),
 // which then come into one L1 and one L2 once, where blocks of one row each were dealt out to different XCDs.
 //
-// Chunks of 64 positions hold 134 registers (3072 wavefronts on the chip at once), chunks of 32 hold 81 (6144): a trip less for
+// Chunks of 64 positions hold 132 registers (3072 wavefronts on the chip at once), chunks of 32 hold 92 (5120): a trip less for
 // 33-64 and 97-128 positions, against half the work for the others.  us with chunks of 64 / of 32, fp16, 16 heads, 4 beams, for
-// histories of 1-32 | 33-64 | 65-96 | 97-128 and sources of 38-45:
-//     64 wavefronts  4.4/3.9 | 4.3/4.6 |  5.6/5.5 |  5.7/6.2   4.2/4.1
-//   1024             4.5/3.8 | 4.4/4.6 |  5.9/5.7 |  5.9/6.4   4.8/5.0
-//   2048             5.6/4.6 | 5.7/5.6 |  8.2/6.9 |  8.3/7.9   6.0/5.9
-//   3072             6.2/5.0 | 6.2/6.6 |  9.6/8.2 |  9.8/9.7   6.8/7.1
-//   4096             7.6/5.6 | 8.0/7.7 | 12.3/9.5 | 12.7/11.7  9.0/7.9
-// From 2048 on chunks of 32 are as good or better but for 33-64 positions at 3072; below, each has its lengths.  bf16 alike.
-// 8 elements of a key against 8 of the query, in 32-bit FMAs.  (v_dot2_f32_f16 truncates what lies far below the larger term and
-// below a fixed floor: 1.6e-5 of the result with subnormal keys, where FMAs are off by 6e-8.)
-template <typename T> __device__ __forceinline__ float dot8_acc(const float (&q)[8], uint4 k, float c) {
-  Pack<T, 8> x;
-  __builtin_memcpy(&x, &k, 16);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) c = fmaf(q[i], to_f<T>(x.v[i]), c);
-  return c;
+// histories of 16, 32, 48, 64, 80 and 112 positions, and sources of 38-45:
+//     64 wavefronts  2.9/2.5  3.0/2.7  3.2/3.4  3.4/3.6   4.5/ 4.3   4.8/ 5.2   3.0/3.0
+//   1024             3.0/2.7  3.2/2.8  3.7/4.1  4.0/4.4   5.5/ 5.4   5.9/ 6.6   3.1/3.1
+//   2048             3.8/3.3  4.5/3.9  4.8/5.1  5.2/5.5   7.3/ 6.4   8.0/ 7.6   4.4/4.3
+//   3072             5.0/4.0  5.4/4.6  5.8/6.4  6.4/6.6   9.3/ 8.2  10.7/10.9   5.4/5.4
+//   4096             6.2/4.5  7.0/5.2  7.8/7.2  9.3/8.0  14.4/10.6  16.8/14.0   6.2/6.5
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+static __device__ __forceinline__ f32x4 mfma16(half_t, uint4 a, uint4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
-// op over the lanes that differ in bits 0, 1 and 2 of their number (a group of 8), and in bits 3, 4 and 5 (across the groups)
-template <typename Op> __device__ __forceinline__ float over_lanes(float v, Op op) {
-  v = op(v, __int_as_float(dpp_move<0xB1, 0xf>(0, __float_as_int(v))));        // quad_perm 1,0,3,2
-  v = op(v, __int_as_float(dpp_move<0x4E, 0xf>(0, __float_as_int(v))));        // quad_perm 2,3,0,1
-  return op(v, __int_as_float(dpp_move<0x141, 0xf>(0, __float_as_int(v))));    // row_half_mirror
-}
-template <typename Op> __device__ __forceinline__ float over_groups(float v, Op op) {
-  auto bits = [&](uint32_t a, uint32_t b) { return __float_as_uint(op(__uint_as_float(a), __uint_as_float(b))); };
-  return __uint_as_float(with_lane_32(with_lane_16(with_lane_8(__float_as_uint(v), bits), bits), bits));
+static __device__ __forceinline__ f32x4 mfma16(bf16_t, uint4 a, uint4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
 constexpr int DEC_ATT_WAVES = 8;                         // rows per block at most
 
-template <typename T, int U>                             // chunks of 8 * U positions
+template <typename T, int U, bool SELF>                  // chunks of 16 * U positions
 __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(DecodeAttnArgs p) {
   __shared__ __attribute__((aligned(16))) T sq[DEC_ATT_WAVES][64];
   constexpr int dh = 64;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 3, f = lane & 7;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4, odd = (lane >> 3) & 1, f = lane & 7;
   const int r = blockIdx.x * (blockDim.x >> 6) + wave, h = blockIdx.y;
-  T* qs = sq[wave];
   int n, base = 0;
-  if (p.anc) n = p.t + 1;
+  if (SELF) n = p.t + 1;
   else { const int s = r / p.beam; base = p.src_off[s]; n = p.src_off[s + 1] - base; }
   const T* K = reinterpret_cast<const T*>(p.k) + h * dh;
   const T* V = reinterpret_cast<const T*>(p.v) + h * dh;
   // position t of a self-attention step may still be outside the caches: it is read from the new rows, and 16 lanes copy
   // this head's 128 + 128 bytes into the row's own cache lines for the steps to come (nobody reads them during this launch)
-  const T* knew = nullptr;
-  const T* vnew = nullptr;
-  if (p.anc && p.k_new) {
-    knew = reinterpret_cast<const T*>(p.k_new) + (size_t)r * p.ld_new + h * dh;
-    vnew = reinterpret_cast<const T*>(p.v_new) + (size_t)r * p.ld_new + h * dh;
-  }
-  // Position s is row first[u] * per + s of the caches, s = g, g + 8, ... of the chunk (past the end: the last one, with weight 0).
-  // The choice between the two tables is made once for all U of them: made for each, it put a wait behind every single load.
-  const int per = p.anc ? p.max_steps : 1;
-  int first[U];
+  const bool fresh = SELF && p.k_new;
+  const T* knew = reinterpret_cast<const T*>(p.k_new) + (size_t)r * p.ld_new + h * dh;
+  const T* vnew = reinterpret_cast<const T*>(p.v_new) + (size_t)r * p.ld_new + h * dh;
+  // Position s is row first * per + s of the caches (past the end: the last one, with weight 0).  The lane asks for position c of a
+  // tile's keys and for positions 4 g + 2 j + odd of its values, j = 0, 1.
+  const int per = SELF ? p.max_steps : 1;
+  const int* anc = p.anc + (size_t)r * p.max_steps;
+  int kfirst[U], vfirst[U][2];
+  auto k_pos = [&](int s0, int u) { return min(s0 + 16 * u + c, n - 1); };
+  auto v_pos = [&](int s0, int u, int j) { return min(s0 + 16 * u + 4 * g + 2 * j + odd, n - 1); };
   auto look_up = [&](int s0) {
-    if (p.anc) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) first[u] = p.anc[(size_t)r * p.max_steps + min(s0 + 8 * u + g, n - 1)];
-    } else {
+    for (int u = 0; u < U; ++u) kfirst[u] = SELF ? anc[k_pos(s0, u)] : base;
 #pragma unroll
-      for (int u = 0; u < U; ++u) first[u] = base;
-    }
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) vfirst[u][j] = SELF ? anc[v_pos(s0, u, j)] : base;
   };
   look_up(0);
-  uint4 qh;                                              // this lane's piece of the query
-  if (p.q_partial) {                                     // the query arrives as the slices of a split-K product (at most 8)
+  uint4 q[2];                                            // the query's features 32 i + 8 g .. + 7
+  if (p.q_partial) {                                     // it arrives as the slices of a split-K product (at most 8)
     const size_t at = (size_t)r * p.H * dh + h * dh + lane, slice = (size_t)p.rows * p.H * dh;
-    float part[8];
+    float part[8];                                       // (asked for together: the last slice again where there are fewer)
 #pragma unroll
-    for (int k = 0; k < 8; ++k) part[k] = k < p.q_splits ? p.q_partial[k * slice + at] : 0.f;
+    for (int k = 0; k < 8; ++k) part[k] = p.q_partial[min(k, p.q_splits - 1) * slice + at];
     float qv = part[0];
 #pragma unroll
-    for (int k = 1; k < 8; ++k) qv += part[k];
+    for (int k = 1; k < 8; ++k) qv = k < p.q_splits ? qv + part[k] : qv;
     if (p.q_bias) qv += to_f<T>(reinterpret_cast<const T*>(p.q_bias)[h * dh + lane]);
+    T* qs = sq[wave];
     qs[lane] = from_f<T>(qv);                            // rounded as the stored projection would be
     __syncthreads();                                     // (every row of the launch comes this way, or none does)
-    qh = reinterpret_cast<const uint4*>(qs)[f];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) q[i] = reinterpret_cast<const uint4*>(qs)[4 * i + g];
   } else {
-    qh = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(p.q) + (size_t)r * p.ldq + h * dh)[f];
+    const uint4* from = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(p.q) + (size_t)r * p.ldq + h * dh);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) q[i] = from[4 * i + g];
   }
-  auto add = [](float x, float y) { return x + y; };
-  auto larger = [](float x, float y) { return fmaxf(x, y); };
+  auto larger = [](uint32_t a, uint32_t b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); };
+  auto sum = [](uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); };
+  const float scale = 0.125f * 1.44269504088896340736f;  // (exponentials to base 2)
   float m = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  for (int s0 = 0; s0 < n; s0 += 8 * U) {
-    uint4 kv[U], vv[U];
-    int off[U];                                          // (the host checks that they fit)
-#pragma unroll
-    for (int u = 0; u < U; ++u) off[u] = (first[u] * per + min(s0 + 8 * u + g, n - 1)) * p.row_stride;
-#pragma unroll
-    for (int u = 0; u < U; ++u) kv[u] = *reinterpret_cast<const uint4*>(((knew && s0 + 8 * u + g >= p.t) ? knew : K + off[u]) + f * 8);
-#pragma unroll
-    for (int u = 0; u < U; ++u) vv[u] = *reinterpret_cast<const uint4*>(((vnew && s0 + 8 * u + g >= p.t) ? vnew : V + off[u]) + f * 8);
-    if (s0 + 8 * U < n) look_up(s0 + 8 * U);             // the next chunk's rows
-    // The query is looked at only now, when the chunk's loads are on their way (its conversion ahead of the loop would wait for it
-    // first: 0.35 us of 4.7), and its values are opaque: seen as halves, the FMAs would be paired into v_dot2_f32_f16.
-    asm volatile("" : "+v"(qh.x), "+v"(qh.y), "+v"(qh.z), "+v"(qh.w));
-    float q[8], sc[U], mn = m;
-    {
-      Pack<T, 8> x;
-      __builtin_memcpy(&x, &qh, 16);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        q[i] = to_f<T>(x.v[i]);
-        asm("" : "+v"(q[i]));
-      }
-    }
+  // 16 bytes of position s, `piece` bytes into its row (byte offsets are below 2^32, which the host checks)
+  auto fetch = [&](const T* cache, const T* row_new, int first, int s, uint32_t piece) {
+    const uint32_t at = (uint32_t)(first * per + s) * (uint32_t)p.row_stride * 2u + piece;
+    const char* from = reinterpret_cast<const char*>(cache) + at;
+    if (SELF) from = fresh && s >= p.t ? reinterpret_cast<const char*>(row_new) + piece : from;
+    return reinterpret_cast<const uint4*>(from);
+  };
+  for (int s0 = 0; s0 < n; s0 += 16 * U) {
+    uint4 kv[U][2], vv[U][2];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      sc[u] = over_lanes(dot8_acc<T>(q, kv[u], 0.f), add);
-      sc[u] = s0 + 8 * u + g < n ? sc[u] * 0.125f : -INFINITY;
-      mn = fmaxf(mn, sc[u]);
+      const uint4* from = fetch(K, knew, kfirst[u], k_pos(s0, u), 16 * g);
+      kv[u][0] = from[0];
+      kv[u][1] = from[4];
     }
-    mn = over_groups(mn, larger);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) vv[u][j] = *fetch(V, vnew, vfirst[u][j], v_pos(s0, u, j), 16 * f);
+    if (s0 + 16 * U < n) look_up(s0 + 16 * U);           // the next chunk's rows
+    asm volatile("" ::: "memory");                      // (all loads of a chunk are on their way before the first is looked at)
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 sc[U];                                         // of positions 4 g .. 4 g + 3 of a tile, in all lanes of a group; past the end the last one's
+    float mn = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sc[u] = mfma16(T{}, kv[u][1], q[1], mfma16(T{}, kv[u][0], q[0], f32x4{0.f, 0.f, 0.f, 0.f}));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mn = fmaxf(mn, sc[u][e]);
+    }
+    mn = __uint_as_float(with_lane_32(with_lane_16(__float_as_uint(mn), larger), larger));
     const float top = mn > -INFINITY ? mn : 0.f;         // scores of -infinity alone, so far: weight 0, as beside others
-    const float keep = __expf(m - top);
+    const float keep = __builtin_amdgcn_exp2f((m - top) * scale);
     m = mn;
-    l *= keep;                                           // (l: this group's share; the groups are added up at the end)
+    l *= keep;                                           // (l: this lane's share, as of acc; the lanes are added up at the end)
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] *= keep;
+    const int left = n - s0 - 4 * g - odd;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float w = __expf(sc[u] - top);
-      l += w;
-      Pack<T, 8> x;
-      __builtin_memcpy(&x, &vv[u], 16);
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] += w * to_f<T>(x.v[i]);
-    }
+      for (int j = 0; j < 2; ++j) {
+        float w = __builtin_amdgcn_exp2f(((odd ? sc[u][2 * j + 1] : sc[u][2 * j]) - top) * scale);
+        w = left > 16 * u + 2 * j ? w : 0.f;
+        l += w;
+        Pack<T, 8> x;
+        __builtin_memcpy(&x, &vv[u][j], 16);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += w * to_f<T>(x.v[i]);
+      }
   }
-  const float inv = 1.f / over_groups(l, add);
+  // Features 8 f .. 8 f + 7 over the lanes that differ in bits 3, 4 and 5 of their number.  Each exchange halves what a lane is left with: one feature,
+  // 4 odd + 2 (bit 4) + (bit 5).
+  float y[4], z[2];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = over_groups(acc[i], add) * inv;
-  if (g == 0) store_f<T, 8>(reinterpret_cast<T*>(p.o) + (size_t)r * p.ldo + h * dh + f * 8, acc);
-  if (knew && g < 2) {
-    T* cache = const_cast<T*>(g == 0 ? K : V) + ((size_t)r * p.max_steps + p.t) * p.row_stride + f * 8;
-    *reinterpret_cast<uint4*>(cache) = *reinterpret_cast<const uint4*>((g == 0 ? knew : vnew) + f * 8);
+  for (int i = 0; i < 4; ++i) {
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[2 * i]), __float_as_uint(acc[2 * i + 1]), false, false);
+    y[i] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(y[2 * i]), __float_as_uint(y[2 * i + 1]), false, false);
+    z[i] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  }
+  const float sent = odd ? z[0] : z[1];
+  const float o = (odd ? z[1] : z[0]) + __int_as_float(dpp_move<0x128, 0xf>(0, __float_as_int(sent)));       // row_ror:8
+  l = __uint_as_float(with_lane_8(with_lane_16(with_lane_32(__float_as_uint(l), sum), sum), sum));
+  reinterpret_cast<T*>(p.o)[(size_t)r * p.ldo + h * dh + 8 * f + 4 * odd + 2 * (g & 1) + (g >> 1)] = from_f<T>(o * (1.f / l));
+  if (fresh && lane < 16) {
+    T* cache = const_cast<T*>(odd ? V : K) + ((size_t)r * p.max_steps + p.t) * p.row_stride + f * 8;
+    *reinterpret_cast<uint4*>(cache) = *reinterpret_cast<const uint4*>((odd ? vnew : knew) + f * 8);
   }
 }
 
@@ -291,10 +306,13 @@ void launch_decode_attention(hipStream_t s, const DecodeAttnArgs& a) {
     const int w = a.beam <= DEC_ATT_WAVES ? a.beam : 1;  // (rows = sentences * beam)
     grid = dim3(a.rows / w, a.H);
     block = dim3(64 * w);
-    const bool all = a.rows * a.H <= 2048;
-#define DA64(T) do { if (all) hipLaunchKernelGGL((decode_attention64_kernel<T, 8>), grid, block, 0, s, a); \
-                     else hipLaunchKernelGGL((decode_attention64_kernel<T, 4>), grid, block, 0, s, a); } while (0)
-    if (a.dt == F16) DA64(half_t); else DA64(bf16_t);
+    const int halves = (a.n_max + 31) / 32, waves = a.rows * a.H;              // (the line: see the table above)
+    const bool all = halves == 2 ? waves <= 3072 : halves > 3 && waves < 2048;
+#define DA64(T, SELF)                                                                                                        \
+  do { if (all) hipLaunchKernelGGL((decode_attention64_kernel<T, 4, SELF>), grid, block, 0, s, a);                             \
+       else hipLaunchKernelGGL((decode_attention64_kernel<T, 2, SELF>), grid, block, 0, s, a); } while (0)
+    if (a.dt == F16) { if (a.anc) DA64(half_t, true); else DA64(half_t, false); }
+    else if (a.anc) DA64(bf16_t, true); else DA64(bf16_t, false);
 #undef DA64
     return;
   }
