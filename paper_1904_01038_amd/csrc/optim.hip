@@ -95,10 +95,10 @@ void launch_scan(hipStream_t s, int dt, const void* x, int64_t n, float* result,
 // formed on the way: the sums of squares of x and of the new sum, either of which is not finite if a value is not.  FIRST: the sum so far
 // is the first sub-batch's gradient, which lies in a buffer of its own since the second began.
 // One pass, no loop, non-temporal, every load of a thread issued before the first result is needed (as the Adam kernel, and for the same
-// reason).  Bound by memory: 10 bytes per parameter with 2-byte gradients, 8 for FIRST.  us, fp16: FIRST over 246 M
-// parameters 364 (5.4 TB/s), without over 235 M 434 (5.4 TB/s).  (Before, the first gradient was converted into the sum, 311 and 284 us, each other one
-// added by a scan with a grid-stride loop, 502 and 493, and the finished sum scanned once more, 169 and 161.)
-constexpr int ACCUM_VEC = 8, ACCUM_UN = 4, ACCUM_TILE = SCAN_THREADS * ACCUM_VEC * ACCUM_UN, ACCUM_FINISH_THREADS = 1024;
+// reason), 16 bytes a lane of the fp32 sum and the groups of a wavefront side by side.  Bound by memory: 10 bytes per parameter with 2-byte
+// gradients, 8 for FIRST.  us, fp16, 210 M parameters: 342 (6.1 TB/s), FIRST 269 (6.2); with 32 bytes of the sum a lane, in two accesses that
+// each touch half of every line, 385 and 312; with the groups a block's width apart 348 and 271; 8 groups 378 and 308.
+constexpr int ACCUM_VEC = 4, ACCUM_UN = 4, ACCUM_TILE = SCAN_THREADS * ACCUM_VEC * ACCUM_UN, ACCUM_FINISH_THREADS = 1024;
 static int accum_blocks(int64_t n) { return (int)((n + ACCUM_TILE - 1) / ACCUM_TILE); }
 size_t accumulate_scratch_bytes(int64_t n) { return (size_t)accum_blocks(n) * sizeof(float2); }
 
@@ -106,11 +106,12 @@ template <typename T, bool FIRST>
 __global__ __launch_bounds__(SCAN_THREADS) void accumulate_kernel(const T* __restrict__ x, const T* __restrict__ first, float* __restrict__ acc, int64_t n,
                                                                   float2* __restrict__ partial) {
   __shared__ float sh[16];
-  const int64_t i0 = (int64_t)blockIdx.x * ACCUM_TILE + threadIdx.x * ACCUM_VEC;
+  constexpr int STEP = 64 * ACCUM_VEC;
+  const int64_t i0 = (int64_t)blockIdx.x * ACCUM_TILE + (threadIdx.x >> 6) * (ACCUM_UN * STEP) + (threadIdx.x & 63) * ACCUM_VEC;
   float v[ACCUM_UN][ACCUM_VEC], a[ACCUM_UN][ACCUM_VEC];
 #pragma unroll
   for (int u = 0; u < ACCUM_UN; ++u) {
-    const int64_t i = i0 + u * SCAN_THREADS * ACCUM_VEC;
+    const int64_t i = i0 + u * STEP;
     if (i < n) {
       load_f_nt<T, ACCUM_VEC>(x + i, v[u]);
       if constexpr (FIRST) load_f_nt<T, ACCUM_VEC>(first + i, a[u]);
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void accumulate_kernel(const T* __res
   float sx = 0.f, sa = 0.f;
 #pragma unroll
   for (int u = 0; u < ACCUM_UN; ++u) {
-    const int64_t i = i0 + u * SCAN_THREADS * ACCUM_VEC;
+    const int64_t i = i0 + u * STEP;
     if (i < n) {
 #pragma unroll
       for (int k = 0; k < ACCUM_VEC; ++k) {
@@ -140,16 +141,21 @@ __global__ __launch_bounds__(ACCUM_FINISH_THREADS) void accumulate_finish_kernel
   __shared__ double shx[ACCUM_FINISH_THREADS], sha[ACCUM_FINISH_THREADS];
   constexpr int UN = 8;
   double sx = 0.0, sa = 0.0;
-  for (int i0 = threadIdx.x; i0 < nb; i0 += UN * ACCUM_FINISH_THREADS) {
-    float2 q[UN];
+  const int pairs = nb >> 1;                             // (two blocks' sums a load)
+  for (int i0 = threadIdx.x; i0 < pairs; i0 += UN * ACCUM_FINISH_THREADS) {
+    float4 q[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       const int i = i0 + u * ACCUM_FINISH_THREADS;
-      q[u] = i < nb ? partial[i] : float2{0.f, 0.f};
+      q[u] = i < pairs ? reinterpret_cast<const float4*>(partial)[i] : float4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
-    for (int u = 0; u < UN; ++u) { sx += (double)q[u].x; sa += (double)q[u].y; }
+    for (int u = 0; u < UN; ++u) {
+      sx += (double)q[u].x + (double)q[u].z;
+      sa += (double)q[u].y + (double)q[u].w;
+    }
   }
+  if ((nb & 1) && threadIdx.x == 0) { sx += (double)partial[nb - 1].x; sa += (double)partial[nb - 1].y; }
   shx[threadIdx.x] = sx;
   sha[threadIdx.x] = sa;
   __syncthreads();
@@ -289,10 +295,12 @@ void launch_scaler_update(hipStream_t s, DevState* st, long long ntokens, float 
 
 // ---- Adam -------------------------------------------------------------------------------------------------------------------
 // Per parameter: read w, m, v (12 B) and the gradient (2 or 4 B), write w, m, v (12 B) and the half model copy (2 B).
-// One pass, no loop: a thread owns ADAM_UN groups of ADAM_VEC consecutive parameters, a block's width apart, issues all their
+// One pass, no loop: a thread owns ADAM_UN groups of ADAM_VEC consecutive parameters, issues all their
 // loads before the first result is needed, and touches everything with non-temporal accesses (nothing here is read again
-// before the next forward pass has gone through hundreds of megabytes).  Measured on the big model's 210 M parameters
-// against a grid-stride loop over plain accesses: 1.27 -> 1.01 ms (4.6 -> 5.8 TB/s).
+// before the next forward pass has gone through hundreds of megabytes).  The groups of a wavefront lie side by side, 4 KB of each array: a
+// block's width apart 1.03 ms, side by side 1.00 (5.85 TB/s; the big model's 210 M parameters, launches back to back; a copy reaches 6.4).  2 or 8
+// groups 1.00 and 1.10, blocks of 64, 128, 512 and 1024 threads 1.03, 1.00, 1.05 and 1.09, 8 parameters a group 1.6, each XCD a run of
+// blocks 1.07, plain loads or stores 1.10 and 1.06; a grid-stride loop over plain accesses 1.27.
 constexpr int ADAM_VEC = 4, ADAM_UN = 4, ADAM_THREADS = 256;
 template <typename GT, typename HT>
 __global__ __launch_bounds__(ADAM_THREADS) void adam_kernel(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
@@ -304,11 +312,12 @@ __global__ __launch_bounds__(ADAM_THREADS) void adam_kernel(float* __restrict__ 
     grad_mult = st->grad_mult; bc1 = st->bc1; bc2 = st->bc2;
   }
   const float step = lr / bc1, rbc2 = 1.f / bc2;
-  const int64_t i0 = ((int64_t)blockIdx.x * ADAM_UN * ADAM_THREADS + threadIdx.x) * ADAM_VEC;
+  constexpr int STEP = 64 * ADAM_VEC;
+  const int64_t i0 = (int64_t)blockIdx.x * (ADAM_UN * ADAM_THREADS * ADAM_VEC) + (threadIdx.x >> 6) * (ADAM_UN * STEP) + (threadIdx.x & 63) * ADAM_VEC;
   float wv[ADAM_UN][ADAM_VEC], mv[ADAM_UN][ADAM_VEC], vv[ADAM_UN][ADAM_VEC], gv[ADAM_UN][ADAM_VEC];
 #pragma unroll
   for (int u = 0; u < ADAM_UN; ++u) {
-    const int64_t i = i0 + (int64_t)u * ADAM_THREADS * ADAM_VEC;
+    const int64_t i = i0 + u * STEP;
     if (i < n) {
       load_f_nt<float, ADAM_VEC>(w + i, wv[u]);
       load_f_nt<float, ADAM_VEC>(m + i, mv[u]);
@@ -318,7 +327,7 @@ __global__ __launch_bounds__(ADAM_THREADS) void adam_kernel(float* __restrict__ 
   }
 #pragma unroll
   for (int u = 0; u < ADAM_UN; ++u) {
-    const int64_t i = i0 + (int64_t)u * ADAM_THREADS * ADAM_VEC;
+    const int64_t i = i0 + u * STEP;
     if (i < n) {
 #pragma unroll
       for (int k = 0; k < ADAM_VEC; ++k) {
