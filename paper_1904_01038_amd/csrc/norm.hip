@@ -307,20 +307,18 @@ __global__ __launch_bounds__(64 * LNB_WAVES) void layernorm_bwd_kernel(
 // (storing a lane's 8 values side by side would be an 8-way conflict, 16 wavefronts deep).  d must be a multiple of 512.
 __host__ __device__ __forceinline__ int ln_slot_column(int p) { return ((p & 63) + 64 * (p >> 9)) * 8 + ((p >> 6) & 7); }
 
-// The same computation when every row can have a wavefront of its own (rows <= LNB_MAX_BLOCKS * LNR_WAVES): 16
-// wavefronts per block, one row each, no loop.  Nothing is accumulated across rows, so the three per-column
+// The same computation when every row can have a wavefront of its own: WAVES of them per block (see lnr_waves), one row each, no loop.  Nothing is
+// accumulated across rows, so the three per-column
 // quantities go from the row's registers straight into the block's LDS reduction, the register footprint stays below
 // 128 and a row's two dependent passes are the whole critical path.  (d = 512 NCH: every lane has all its columns.)
-constexpr int LNR_WAVES = 16;
-
-template <typename T, int NCH>
-__global__ __launch_bounds__(64 * LNR_WAVES) void layernorm_bwd_row_kernel(
+template <typename T, int NCH, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void layernorm_bwd_row_kernel(
     const T* __restrict__ dn, const T* __restrict__ add, const T* __restrict__ sres, const float* __restrict__ mean,
     const float* __restrict__ rstd, const T* __restrict__ gamma, T* __restrict__ ds, T* __restrict__ ds_drop,
     float* __restrict__ partial, int rows, int d, uint64_t key, uint32_t thr, float inv_keep, int nk) {
-  __shared__ float lds[2][LNR_WAVES][512];
+  __shared__ float lds[2][WAVES][512];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int row = blockIdx.x * LNR_WAVES + w;
+  const int row = blockIdx.x * WAVES + w;
   const bool live = row < rows;
   const size_t base = (size_t)(live ? row : 0) * d;
   float a[NCH][LN_VEC], xh[NCH][LN_VEC], o[NCH][LN_VEC];
@@ -385,11 +383,14 @@ __global__ __launch_bounds__(64 * LNR_WAVES) void layernorm_bwd_row_kernel(
       for (int i = 0; i < LN_VEC; ++i)                    // slot (c, i, lane): consecutive lanes, consecutive banks
         lds[u][w][i * 64 + lane] = k == 0 ? a[c][i] * xh[c][i] : (k == 1 ? a[c][i] : o[c][i]);
       __syncthreads();
-      if (threadIdx.x < 512) {                            // partials stay in slot order (see ln_slot_column)
+#pragma unroll
+      for (int j = 0; j < 512; j += 64 * WAVES) {         // partials stay in slot order (see ln_slot_column)
+        const int at = j + threadIdx.x;
+        if (64 * WAVES > 512 && at >= 512) break;
         float t = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < LNR_WAVES; ++ww) t += lds[u][ww][threadIdx.x];
-        partial[((size_t)blockIdx.x * 3 + k) * d + c * 512 + threadIdx.x] = t;
+        for (int ww = 0; ww < WAVES; ++ww) t += lds[u][ww][at];
+        partial[((size_t)blockIdx.x * 3 + k) * d + c * 512 + at] = t;
       }
       u ^= 1;
     }
@@ -448,7 +449,22 @@ static int lnb_blocks(int rows) {
   int b = (rows + LNB_WAVES - 1) / LNB_WAVES;
   return b > LNB_MAX_BLOCKS ? LNB_MAX_BLOCKS : (b < 1 ? 1 : b);
 }
-size_t layernorm_bwd_scratch_bytes(int rows, int d) { return (size_t)lnb_blocks(rows) * 3 * d * sizeof(float); }
+// Wavefronts per block of the row kernel, 0: the looping one.  A column sum takes a block through LDS row by row, so small blocks are done
+// sooner, and on more compute units, as long as there are not more than LNB_MAX_BLOCKS partials for the reduction behind it (whose share is
+// counted here).  us with 4 / 8 / 16 wavefronts: 280 x 1024 3.8/4.4/6.0, 1020 x 1024 5.9/5.9/7.2, 1500 x 1024 6.9/6.6/7.7, 2000 x 1024 7.9/7.4/8.2, 900 x
+// 512 3.4/3.5/4.4, 1800 x 512 5.0/4.6/5.3, 900 x 1536 7.1/7.5/9.5, 1800 x 1536 10.2/9.8/11.7; 3264 x 1024 -/11.4/11.2, 3700 x 512 -/6.6/6.2.
+constexpr int LNR_FEWEST = 4;
+static int lnr_waves(int rows, int d) {
+  if (d % 512 || d > 1536) return 0;                     // (three 512-column parts of a row are what the registers of 16 wavefronts hold)
+  for (int w = LNR_FEWEST; w <= 16; w *= 2)
+    if (rows <= LNB_MAX_BLOCKS * w) return w;
+  return 0;
+}
+// (enough for any smaller number of rows as well)
+size_t layernorm_bwd_scratch_bytes(int rows, int d) {
+  const int most = (rows + LNR_FEWEST - 1) / LNR_FEWEST;
+  return (size_t)(most > LNB_MAX_BLOCKS ? LNB_MAX_BLOCKS : (most < 1 ? 1 : most)) * 3 * d * sizeof(float);
+}
 
 template <typename T>
 static void ln_bwd_dispatch(hipStream_t s, const void* dn, const void* add, const void* sres, const float* mean,
@@ -458,15 +474,18 @@ static void ln_bwd_dispatch(hipStream_t s, const void* dn, const void* add, cons
   const uint32_t thr = (p > 0.f && ds_drop) ? drop_threshold(p) : 0u;
   const float inv_keep = 1.f / (1.f - p);
   const int nch = (d + 511) / 512;
-  // A wavefront per row, as far as its registers allow 16 of them: 3000 rows of 1536 34.0 us in the looping kernel, now 14.2.  (3264 rows of
-  // 1024 11.5 us before the LDS stages took turns and the added gradient came with the row, now 10.2; 280 rows 8.6 and 7.2.)
-  if (rows <= LNB_MAX_BLOCKS * LNR_WAVES && d % 512 == 0 && nch <= 3) {
-    const int nbr = (rows + LNR_WAVES - 1) / LNR_WAVES;
-#define LN_BWD_ROW(N)                                                                                                   \
-  hipLaunchKernelGGL((layernorm_bwd_row_kernel<T, N>), dim3(nbr), dim3(64 * LNR_WAVES), 0, s, (const T*)dn, (const T*)add,        \
+  // A wavefront per row where that can be: 3000 rows of 1536 34.0 us in the looping kernel, now 14.2.  (3264 rows of
+  // 1024 11.5 us before the LDS stages took turns and the added gradient came with the row, now 10.2.)
+  const int waves = lnr_waves(rows, d);
+  if (waves) {
+    const int nbr = (rows + waves - 1) / waves;
+#define LN_BWD_ROW(N, W)                                                                                                \
+  hipLaunchKernelGGL((layernorm_bwd_row_kernel<T, N, W>), dim3(nbr), dim3(64 * W), 0, s, (const T*)dn, (const T*)add,   \
                      (const T*)sres, mean, rstd, (const T*)gamma, (T*)ds, (T*)ds_drop, (float*)scratch, rows, d, key, thr, \
                      inv_keep, nk)
-    if (nch <= 1) LN_BWD_ROW(1); else if (nch == 2) LN_BWD_ROW(2); else LN_BWD_ROW(3);
+#define LN_BWD_WAVES(N) do { if (waves == 4) LN_BWD_ROW(N, 4); else if (waves == 8) LN_BWD_ROW(N, 8); else LN_BWD_ROW(N, 16); } while (0)
+    if (nch == 1) LN_BWD_WAVES(1); else if (nch == 2) LN_BWD_WAVES(2); else LN_BWD_WAVES(3);
+#undef LN_BWD_WAVES
 #undef LN_BWD_ROW
     if (defer) { *defer = LnReduceJob{(const float*)scratch, nbr, 1, dgamma, dbeta, dbias}; return; }
     hipLaunchKernelGGL((reduce_partials_kernel<T>), dim3((d + 31) / 32, 3), dim3(32 * RP_LANES), 0, s, (const float*)scratch, nbr, 3, d,

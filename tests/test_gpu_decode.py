@@ -503,6 +503,35 @@ def test_attention_over_several_chunks_of_positions(d, heads, beam, copies, prec
     ctx.close()
 
 
+@pytest.mark.parametrize("prec,tol", [("fp16", 3e-2), ("bf16", 2e-1)])
+@pytest.mark.parametrize("beam", [1, 5, 9])
+def test_attention_over_few_positions(prec, tol, beam):
+    """Histories of 1 to 50 positions, at every step, and sources around the ends of a tile of 16 positions, with re-ordered beams."""
+    import paper_1904_01038_amd as T
+    shape = ModelShape(1, 1, 128, 2, 256, 96)
+    p = {"fp16": T.FP16, "bf16": T.BF16}[prec]
+    params = peaked(shape, p, 9)
+    lens = np.array([1, 15, 16, 17, 47, 49], np.int32)
+    B, R, steps = len(lens), len(lens) * beam, 50
+    rng = np.random.default_rng(beam)
+    src = rng.integers(4, shape.vocab, (B, lens.max())).astype(np.int32)
+    src[np.arange(lens.max())[None, :] >= lens[:, None]] = shape.pad_id
+    ctx = T.Tfm(T.make_config(shape, precision=p, max_sentences=B, max_len=steps, max_tokens=(int(lens.sum()) + 63) // 64 * 64))
+    ctx.set_params(params)
+    dec, oracle = T.Decoder(ctx, R, steps, int(lens.sum()), 4), DecodingOracle(shape, params)
+    dec.begin(src, lens, beam)
+    mems = [oracle.encode(src[b, :lens[b]]) for b in range(B)]
+    base, hist = np.arange(R) // beam * beam, np.zeros((R, 0), np.int32)
+    for t in range(steps):
+        prev = np.full(R, shape.eos_id, np.int32) if t == 0 else rng.integers(4, shape.vocab, R).astype(np.int32)
+        parent = None if t == 0 else (base + rng.integers(0, beam, R)).astype(np.int32)
+        hist = np.concatenate([hist if parent is None else hist[parent], prev[:, None]], axis=1)
+        dec.step(prev, parent)
+        row = t % R                                        # (one row a step, each in turn)
+        assert np.max(np.abs(dec.logprobs()[row] - oracle.next_logprobs(mems[row // beam], hist[row]))) <= tol, t + 1
+    ctx.close()
+
+
 def _thirty_steps():
     """The candidates of 30 steps of a small fp16 model, as (values, ids); the tokens fed depend on the step before."""
     import paper_1904_01038_amd as T

@@ -70,6 +70,13 @@ def test_residual_layernorm_forward_and_backward(prec, shape, p):
     assert np.abs(_np(dbias) - drop_ref.sum(0)).max() <= ctol * max(1.0, np.abs(drop_ref.sum(0)).max() / np.sqrt(rows))
 
 
+# rows around the ends of a block of the backward kernel (4, 8 or 16 rows) and where one size of block follows another
+@pytest.mark.parametrize("prec", ["fp32", "fp16"])
+@pytest.mark.parametrize("shape", [(3, 512), (4, 1536), (5, 1024), (1023, 1536), (1024, 512), (1025, 1024), (2047, 1024), (2048, 512), (2049, 1536), (4096, 512), (4097, 512)])
+def test_layernorm_backward_blocks(prec, shape):
+    test_residual_layernorm_forward_and_backward(prec, shape, 0.2)
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("shape", [(5, 13), (33, 1000), (257, 32768), (3, 40000), (64, 4104)])
 @pytest.mark.parametrize("eps", [0.0, 0.1])
