@@ -687,9 +687,11 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 //   192x128      2 x 2       64     3        3000 x 1536 x 4608 NN 55.3, 3000 x 1536 x 8192 89.3 (288 tiles of 128x128 in two rounds: 76.1, 122)
 //   128x128      2 x 2       64     4        4096 x 1024 x 4096 NN 42.7 (44.3), 3264 x 1024 x 1024 11.2 (11.8)
 //    64x128      2 x 2       64     4        3520 x 512 x 1536 NN 11.0 (11.8)
-//    64x64       2 x 2       64     5        280 x 1024 x 3072 NN, K in 3 slices, 10.4 (24 tiles of 128x128: 22.0).  80 KB, so two blocks share a compute unit.
-//                                            Few rows find their weights in memory, and a fourth K-step in flight covers more of that trip: the eight
-//                                            products, LayerNorms and attentions of a decoder block for 268 rows 73.8 -> 71.4 us (6 slots 72.7, 8 74.9, 3 80.1)
+//    64x64       2 x 2       64     5, 4     280 x 1024 x 3072 NN, K in 3 slices, 10.4 (24 tiles of 128x128: 22.0).  5 slots where a compute unit has one tile:
+//                                            few rows find their weights in memory, and a fourth K-step in flight covers more of that trip.  Two tiles
+//                                            cover each other's.  5 / 4 slots: 290 x 3072 x 1024 (240 tiles) 7.1/7.2, 900 x 512 x 2048 9.3/9.6, 500 x 1024 x
+//                                            1024 6.3/6.6; 290 x 4096 x 1024 (320 tiles) 11.1/10.8, NN 10.0/9.5, 900 x 1536 x 512 7.0/6.7, 3300 x 512 x 512 7.3/7.0;
+//                                            the kernels of a decoder block for 268 rows 71.0 / 73.8 (6 slots 71.0, 7 71.6)
 //   128x128      2 x 2       32     3        A^T B alone, up to 512 tiles, two on a compute unit: 6144 x 1024 x 190 7.6 (one: 10.1), 3072 x 1536 x 2902
 //                                            41.2 (48.2)
 // Wavefronts of 64x64 or more read half of the LDS bytes per flop of 32x32 ones.  Measured and dropped: 256x256 on 4 wavefronts of 128x128 (one per
@@ -854,7 +856,10 @@ static void gemm_mfma_dispatch(hipStream_t s, const GemmArgs& a) {
     case T192x256: gemm_mfma_launch<T, 192, 256, 2, 4, 32, 4, 1>(s, a, q.slices); break;
     case T192x128: gemm_mfma_launch<T, 192, 128, 2, 2, 64, 3, 1>(s, a, q.slices); break;
     case T64x128: gemm_mfma_launch<T, 64, 128, 2, 2, 64, 4, 1>(s, a, q.slices); break;
-    case T64x64: gemm_mfma_launch<T, 64, 64, 2, 2, 64, 5, 2>(s, a, q.slices); break;
+    case T64x64:
+      if (tiles_of(T64x64, a.M, a.N) * q.slices <= 256) gemm_mfma_launch<T, 64, 64, 2, 2, 64, 5, 2>(s, a, q.slices);
+      else gemm_mfma_launch<T, 64, 64, 2, 2, 64, 4, 2>(s, a, q.slices);
+      break;
     case T128x128_PAIRS: gemm_mfma_launch<T, 128, 128, 2, 2, 32, 3, 1>(s, a, q.slices); break;
     default: gemm_mfma_launch<T, 128, 128, 2, 2, 64, 4, 1>(s, a, q.slices); break;
   }
