@@ -124,10 +124,10 @@ void launch_attention_bwd_mfma(hipStream_t s, const AttnArgs& a);
 void launch_attention_fwd_naive(hipStream_t s, const AttnArgs& a);
 void launch_attention_bwd_naive(hipStream_t s, const AttnArgs& a);
 
-// The same as launch_residual_layernorm_fwd with y = bias + sum over `splits` fp32 slices partial[s][rows][d] (in that order)
-// and no dropout: the reduction of a split-K product fused with the residual connection and LayerNorm that follow it.
-void launch_splitk_layernorm_fwd(hipStream_t s, int dt, const void* x, const float* partial, int splits, const void* bias,
-                                 const void* gamma, const void* beta, void* s_out, void* n_out, int rows, int d);
+// The same as launch_residual_layernorm_fwd with y = bias + sum over `splits` fp32 slices partial[s][rows][d] (in that order): the reduction of a
+// split-K product fused with the residual connection and LayerNorm that follow it.  mean, rstd: null if nobody reads them.
+struct SplitkNorm { const void* x; const float* partial; int splits; const void *bias, *gamma, *beta; void *s_out, *n_out; float *mean, *rstd; };
+void launch_splitk_layernorm_fwd(hipStream_t s, int dt, const SplitkNorm& q, int rows, int d, uint64_t key, float p);
 void launch_residual_layernorm_fwd(hipStream_t s, int dt, const void* x, const void* y, const void* gamma,
                                    const void* beta, void* s_out, void* n_out, float* mean, float* rstd, int rows,
                                    int d, uint64_t key, float p);
@@ -140,7 +140,11 @@ struct LnReduceJob { const float* partial; int np; int slots; void *dgamma, *dbe
 constexpr int LN_REDUCE_MAX = 64;        // jobs per launch (more are split over several)
 void launch_layernorm_bwd(hipStream_t s, int dt, const void* dn, const void* add, const void* sres, const float* mean,
                           const float* rstd, const void* gamma, void* ds, void* ds_drop, void* dgamma, void* dbeta,
-                          void* dbias, int rows, int d, uint64_t key, float p, void* scratch, LnReduceJob* defer = nullptr);
+                          void* dbias, int rows, int d, uint64_t key, float p, void* scratch, LnReduceJob* defer = nullptr,
+                          const float* slices = nullptr, int splits = 0);
+// Does it take the incoming gradient as dn (or null) + the sum of fp32 slices [splits][rows][d], in this order, splits <= DEFERRED_SPLITS_MAX: an input
+// gradient whose product was cut along K, before its residual is added?
+bool layernorm_bwd_takes_slices(int dt, int rows, int d);
 void launch_ln_reduce_batched(hipStream_t s, int dt, const LnReduceJob* jobs, int n, int d);
 size_t colsum_scratch_bytes(int rows, int n);
 void launch_colsum(hipStream_t s, int dt, const void* x, int ld, int rows, int n, void* out, void* scratch);

@@ -8,91 +8,40 @@ namespace tfm {
 
 constexpr int LN_VEC = 8;
 
-// s = x + drop(y); n = gamma * (s - mean) * rstd + beta.  NCH = chunks of 8 elements per lane (d <= NCH * 512).
-template <typename T, int NCH>
-__global__ __launch_bounds__(256) void residual_layernorm_fwd_kernel(
-    const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ gamma, const T* __restrict__ beta,
-    T* __restrict__ s_out, T* __restrict__ n_out, float* __restrict__ mean, float* __restrict__ rstd, int rows, int d,
-    uint64_t key, uint32_t thr, float inv_keep) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+// s = x + drop(y); n = gamma * (s - mean) * rstd + beta.  NCH = chunks of 8 elements per lane (d <= NCH * 512), WAVES rows per block.
+// Bound by memory, a few hundred rows by one trip to it: everything a row needs is asked for before the first of it is looked at.  (gamma and beta
+// only after the statistics, and a chunk at a time: 280 x 1024 3.4 us against 3.0, 1020 x 1024 5.0 and 4.2, 900 x 1536 6.2 and 5.0, 3000 x 1536 11.1 and
+// 10.6, 3264 x 1024 8.5 both.  1, 2 or 8 rows a block: 1020 x 1024 4.4, 4.7 and 4.6.)
+// y comes in the compute dtype (MAXS = 0; or null), or as bias + the sum of fp32 slices, at most MAXS of them (the last one is asked for again where
+// there are fewer: with a branch around every slice the second 512 columns waited for the first, 24 rows x 1024, 4 slices 4.8 us against 3.2).  mean,
+// rstd: null in a decoding step.
+template <typename T, int NCH, int MAXS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void layernorm_fwd_row_kernel(
+    const T* __restrict__ x, const T* __restrict__ y, const float* __restrict__ partial, int splits, const T* __restrict__ bias,
+    const T* __restrict__ gamma, const T* __restrict__ beta, T* __restrict__ s_out, T* __restrict__ n_out, float* __restrict__ mean,
+    float* __restrict__ rstd, int rows, int d, uint64_t key, uint32_t thr, float inv_keep) {
+  const int lane = threadIdx.x & 63, row = blockIdx.x * WAVES + (threadIdx.x >> 6);
   if (row >= rows) return;
-  const size_t base = (size_t)row * d;
-  float v[NCH][LN_VEC];
-  float sum = 0.f;
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (lane + 64 * c) * LN_VEC;
-    if (col < d) {
-      load_f<T, LN_VEC>(x + base + col, v[c]);
-      if (y) {
-        float t[LN_VEC];
-        load_f<T, LN_VEC>(y + base + col, t);
-        if (thr) drop_apply<LN_VEC>(t, key, base + col, thr, inv_keep);
-#pragma unroll
-        for (int i = 0; i < LN_VEC; ++i) v[c][i] += t[i];
-      }
-      if (s_out) {
-        store_f<T, LN_VEC>(s_out + base + col, v[c]);
-        // the backward pass reads the stored (rounded) sum, so normalise exactly that
-#pragma unroll
-        for (int i = 0; i < LN_VEC; ++i) v[c][i] = to_f<T>(from_f<T>(v[c][i]));
-      }
-#pragma unroll
-      for (int i = 0; i < LN_VEC; ++i) sum += v[c][i];
-    }
-  }
-  const float mu = wave_sum(sum) / (float)d;
-  float sq = 0.f;
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (lane + 64 * c) * LN_VEC;
-    if (col < d) {
-#pragma unroll
-      for (int i = 0; i < LN_VEC; ++i) { const float t = v[c][i] - mu; sq += t * t; }
-    }
-  }
-  const float rs = rsqrtf(wave_sum(sq) / (float)d + LN_EPS);
-  if (lane == 0) { mean[row] = mu; rstd[row] = rs; }
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (lane + 64 * c) * LN_VEC;
-    if (col < d) {
-      float g[LN_VEC], b[LN_VEC], o[LN_VEC];
-      load_f<T, LN_VEC>(gamma + col, g);
-      load_f<T, LN_VEC>(beta + col, b);
-#pragma unroll
-      for (int i = 0; i < LN_VEC; ++i) o[i] = g[i] * ((v[c][i] - mu) * rs) + b[i];
-      store_f<T, LN_VEC>(n_out + base + col, o);
-    }
-  }
-}
-
-// s = x + (bias + sum of the fp32 slices); n = gamma * (s - mean) * rstd + beta.  A block is one wavefront and one row.  Bound by one trip to
-// memory between two kernels of a decoding step, so everything the row needs is asked for before the first of it is looked at: MAXS slices
-// (the last one again where there are fewer) of all its columns.  With a branch around every slice the second 512 columns waited for the first: 24 rows x
-// 1024, 4 slices 4.8 us, now 3.2; 268 rows, 3 slices 4.4 and 3.4.
-template <typename T, int NCH, int MAXS>
-__global__ __launch_bounds__(64) void splitk_layernorm_fwd_kernel(
-    const T* __restrict__ x, const float* __restrict__ partial, int splits, const T* __restrict__ bias,
-    const T* __restrict__ gamma, const T* __restrict__ beta, T* __restrict__ s_out, T* __restrict__ n_out, int rows, int d) {
-  const int lane = threadIdx.x, row = blockIdx.x;
   const size_t base = (size_t)row * d, slice = (size_t)rows * d;
-  Pack<T, LN_VEC> xr[NCH], gr[NCH], br[NCH], hr[NCH];
-  float4 t[NCH][MAXS][2];
+  Pack<T, LN_VEC> xr[NCH], yr[NCH], gr[NCH], br[NCH], hr[NCH];
+  float4 t[NCH][MAXS > 0 ? MAXS : 1][2];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int col = min((lane + 64 * c) * LN_VEC, d - LN_VEC);
     xr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(x + base + col);
+    if constexpr (MAXS > 0) {
 #pragma unroll
-    for (int k = 0; k < MAXS; ++k) {
-      const float4* p = reinterpret_cast<const float4*>(partial + min(k, splits - 1) * slice + base + col);
-      t[c][k][0] = p[0];
-      t[c][k][1] = p[1];
+      for (int k = 0; k < MAXS; ++k) {
+        const float4* p = reinterpret_cast<const float4*>(partial + min(k, splits - 1) * slice + base + col);
+        t[c][k][0] = p[0];
+        t[c][k][1] = p[1];
+      }
+      hr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>((bias ? bias : gamma) + col);
+    } else {
+      yr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>((y ? y : x) + base + col);
     }
     gr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(gamma + col);
     br[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(beta + col);
-    hr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>((bias ? bias : gamma) + col);
   }
   __builtin_amdgcn_sched_barrier(0);
   float v[NCH][LN_VEC];
@@ -101,23 +50,31 @@ __global__ __launch_bounds__(64) void splitk_layernorm_fwd_kernel(
   for (int c = 0; c < NCH; ++c) {
     const int col = (lane + 64 * c) * LN_VEC;
     if (col < d) {
-      float y[LN_VEC] = {t[c][0][0].x, t[c][0][0].y, t[c][0][0].z, t[c][0][0].w, t[c][0][1].x, t[c][0][1].y, t[c][0][1].z, t[c][0][1].w};
+      float u[LN_VEC];
+      if constexpr (MAXS > 0) {
 #pragma unroll
-      for (int k = 1; k < MAXS; ++k)                      // in order
-        if (k < splits) {
-          y[0] += t[c][k][0].x; y[1] += t[c][k][0].y; y[2] += t[c][k][0].z; y[3] += t[c][k][0].w;
-          y[4] += t[c][k][1].x; y[5] += t[c][k][1].y; y[6] += t[c][k][1].z; y[7] += t[c][k][1].w;
+        for (int i = 0; i < LN_VEC; ++i) u[i] = (&t[c][0][i >> 2].x)[i & 3];
+#pragma unroll
+        for (int k = 1; k < MAXS; ++k)                    // in order
+          if (k < splits) {
+#pragma unroll
+            for (int i = 0; i < LN_VEC; ++i) u[i] += (&t[c][k][i >> 2].x)[i & 3];
+          }
+        if (bias) {
+#pragma unroll
+          for (int i = 0; i < LN_VEC; ++i) u[i] += to_f<T>(hr[c].v[i]);
         }
-      if (bias) {
+      } else {
 #pragma unroll
-        for (int i = 0; i < LN_VEC; ++i) y[i] += to_f<T>(hr[c].v[i]);
+        for (int i = 0; i < LN_VEC; ++i) u[i] = to_f<T>(yr[c].v[i]);
       }
+      if (thr) drop_apply<LN_VEC>(u, key, base + col, thr, inv_keep);
 #pragma unroll
-      for (int i = 0; i < LN_VEC; ++i) v[c][i] = to_f<T>(xr[c].v[i]) + y[i];
+      for (int i = 0; i < LN_VEC; ++i) v[c][i] = MAXS > 0 || y ? to_f<T>(xr[c].v[i]) + u[i] : to_f<T>(xr[c].v[i]);
       if (s_out) {
         store_f<T, LN_VEC>(s_out + base + col, v[c]);
 #pragma unroll
-        for (int i = 0; i < LN_VEC; ++i) v[c][i] = to_f<T>(from_f<T>(v[c][i]));     // normalise what was stored, as above
+        for (int i = 0; i < LN_VEC; ++i) v[c][i] = to_f<T>(from_f<T>(v[c][i]));     // the backward pass reads the stored sum: normalise exactly that
       }
 #pragma unroll
       for (int i = 0; i < LN_VEC; ++i) sum += v[c][i];
@@ -134,6 +91,7 @@ __global__ __launch_bounds__(64) void splitk_layernorm_fwd_kernel(
     }
   }
   const float rs = rsqrtf(wave_sum(sq) / (float)d + LN_EPS);
+  if (mean && lane == 0) { mean[row] = mu; rstd[row] = rs; }
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int col = (lane + 64 * c) * LN_VEC;
@@ -147,41 +105,41 @@ __global__ __launch_bounds__(64) void splitk_layernorm_fwd_kernel(
 }
 
 template <typename T, int MAXS>
-static void splitk_ln_dispatch(hipStream_t s, const void* x, const float* partial, int splits, const void* bias, const void* gamma,
-                               const void* beta, void* s_out, void* n_out, int rows, int d) {
+static void splitk_ln_dispatch(hipStream_t s, const SplitkNorm& q, int rows, int d, uint64_t key, float p) {
+  const uint32_t thr = p > 0.f ? drop_threshold(p) : 0u;
+  const float inv_keep = 1.f / (1.f - p);
   const int nch = (d + 511) / 512;
-#define SLN(N)                                                                                                                                  \
-  hipLaunchKernelGGL((splitk_layernorm_fwd_kernel<T, N, MAXS>), dim3(rows), dim3(64), 0, s, (const T*)x, partial, splits, (const T*)bias, \
-                     (const T*)gamma, (const T*)beta, (T*)s_out, (T*)n_out, rows, d)
+#define SLN(N)                                                                                                                             \
+  hipLaunchKernelGGL((layernorm_fwd_row_kernel<T, N, MAXS, 1>), dim3(rows), dim3(64), 0, s, (const T*)q.x, (const T*)nullptr, q.partial, q.splits, \
+                     (const T*)q.bias, (const T*)q.gamma, (const T*)q.beta, (T*)q.s_out, (T*)q.n_out, q.mean, q.rstd, rows, d, key, thr, inv_keep)
   if (nch <= 1) SLN(1); else if (nch == 2) SLN(2); else if (nch == 3) SLN(3); else SLN(4);
 #undef SLN
 }
 template <typename T>
-static void splitk_ln_splits(hipStream_t s, const void* x, const float* partial, int splits, const void* bias, const void* gamma,
-                             const void* beta, void* s_out, void* n_out, int rows, int d) {
+static void splitk_ln_splits(hipStream_t s, const SplitkNorm& q, int rows, int d, uint64_t key, float p) {
   static_assert(DEFERRED_SPLITS_MAX == 8, "the widest instance");
-  if (splits <= 2) splitk_ln_dispatch<T, 2>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
-  else if (splits <= 4) splitk_ln_dispatch<T, 4>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
-  else splitk_ln_dispatch<T, 8>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
+  if (q.splits <= 2) splitk_ln_dispatch<T, 2>(s, q, rows, d, key, p);
+  else if (q.splits <= 4) splitk_ln_dispatch<T, 4>(s, q, rows, d, key, p);
+  else splitk_ln_dispatch<T, 8>(s, q, rows, d, key, p);
 }
-void launch_splitk_layernorm_fwd(hipStream_t s, int dt, const void* x, const float* partial, int splits, const void* bias,
-                                 const void* gamma, const void* beta, void* s_out, void* n_out, int rows, int d) {
+void launch_splitk_layernorm_fwd(hipStream_t s, int dt, const SplitkNorm& q, int rows, int d, uint64_t key, float p) {
   if (rows <= 0) return;
-  if (dt == F16) splitk_ln_splits<half_t>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
-  else if (dt == BF16) splitk_ln_splits<bf16_t>(s, x, partial, splits, bias, gamma, beta, s_out, n_out, rows, d);
+  if (dt == F16) splitk_ln_splits<half_t>(s, q, rows, d, key, p);
+  else if (dt == BF16) splitk_ln_splits<bf16_t>(s, q, rows, d, key, p);
   // (split-K launches exist for the 2-byte types only)
 }
 
 template <typename T>
 static void ln_fwd_dispatch(hipStream_t s, const void* x, const void* y, const void* gamma, const void* beta, void* s_out,
                             void* n_out, float* mean, float* rstd, int rows, int d, uint64_t key, float p) {
+  constexpr int WAVES = 4;
   const uint32_t thr = (p > 0.f && y) ? drop_threshold(p) : 0u;
   const float inv_keep = 1.f / (1.f - p);
-  dim3 grid((rows + 3) / 4), block(256);
   const int nch = (d + 511) / 512;
-#define LN_FWD(N)                                                                                                        \
-  hipLaunchKernelGGL((residual_layernorm_fwd_kernel<T, N>), grid, block, 0, s, (const T*)x, (const T*)y, (const T*)gamma, \
-                     (const T*)beta, (T*)s_out, (T*)n_out, mean, rstd, rows, d, key, thr, inv_keep)
+#define LN_FWD(N)                                                                                                                              \
+  hipLaunchKernelGGL((layernorm_fwd_row_kernel<T, N, 0, WAVES>), dim3((rows + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, s, (const T*)x, (const T*)y, \
+                     (const float*)nullptr, 0, (const T*)nullptr, (const T*)gamma, (const T*)beta, (T*)s_out, (T*)n_out, mean, rstd, rows, d, key, \
+                     thr, inv_keep)
   if (nch <= 1) LN_FWD(1); else if (nch == 2) LN_FWD(2); else if (nch == 3) LN_FWD(3); else LN_FWD(4);
 #undef LN_FWD
 }
@@ -311,9 +269,10 @@ __host__ __device__ __forceinline__ int ln_slot_column(int p) { return ((p & 63)
 // accumulated across rows, so the three per-column
 // quantities go from the row's registers straight into the block's LDS reduction, the register footprint stays below
 // 128 and a row's two dependent passes are the whole critical path.  (d = 512 NCH: every lane has all its columns.)
-template <typename T, int NCH, int WAVES>
+// MAXS > 0: the incoming gradient is dn (or nothing, if null) + the sum of at most MAXS fp32 slices (launch_layernorm_bwd).
+template <typename T, int NCH, int WAVES, int MAXS>
 __global__ __launch_bounds__(64 * WAVES) void layernorm_bwd_row_kernel(
-    const T* __restrict__ dn, const T* __restrict__ add, const T* __restrict__ sres, const float* __restrict__ mean,
+    const T* __restrict__ dn, const float* __restrict__ slices, int splits, const T* __restrict__ add, const T* __restrict__ sres, const float* __restrict__ mean,
     const float* __restrict__ rstd, const T* __restrict__ gamma, T* __restrict__ ds, T* __restrict__ ds_drop,
     float* __restrict__ partial, int rows, int d, uint64_t key, uint32_t thr, float inv_keep, int nk) {
   __shared__ float lds[2][WAVES][512];
@@ -330,12 +289,19 @@ __global__ __launch_bounds__(64 * WAVES) void layernorm_bwd_row_kernel(
     // all of the row's operands in one trip to memory, also what is only added at the end
     const float mu = mean[row], rs = rstd[row];
     Pack<T, LN_VEC> ar[NCH], br[NCH], gr[NCH], tr[NCH];
+    float4 sl[NCH][MAXS > 0 ? MAXS : 1][2];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int col = (lane + 64 * c) * LN_VEC;
-      ar[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(dn + base + col);
+      ar[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>((MAXS == 0 || dn ? dn : sres) + base + col);
       br[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(sres + base + col);
-      tr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>((add ? add : dn) + base + col);
+      tr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>((add ? add : sres) + base + col);
+#pragma unroll
+      for (int k = 0; k < MAXS; ++k) {                    // (past the end: the last one again)
+        const float4* p = reinterpret_cast<const float4*>(slices + (size_t)min(k, splits - 1) * rows * d + base + col);
+        sl[c][k][0] = p[0];
+        sl[c][k][1] = p[1];
+      }
       gr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(gamma + col);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -344,7 +310,14 @@ __global__ __launch_bounds__(64 * WAVES) void layernorm_bwd_row_kernel(
     for (int c = 0; c < NCH; ++c) {
 #pragma unroll
       for (int i = 0; i < LN_VEC; ++i) {
-        a[c][i] = to_f<T>(ar[c].v[i]);
+        a[c][i] = MAXS == 0 || dn ? to_f<T>(ar[c].v[i]) : 0.f;
+        if constexpr (MAXS > 0) {
+          float sum = (&sl[c][0][i >> 2].x)[i & 3];
+#pragma unroll
+          for (int k = 1; k < MAXS; ++k)
+            if (k < splits) sum += (&sl[c][k][i >> 2].x)[i & 3];
+          a[c][i] += sum;
+        }
         xh[c][i] = (to_f<T>(br[c].v[i]) - mu) * rs;
         o[c][i] = a[c][i] * to_f<T>(gr[c].v[i]);         // dxhat, turned into ds below
         s1 += o[c][i];
@@ -469,7 +442,7 @@ size_t layernorm_bwd_scratch_bytes(int rows, int d) {
 template <typename T>
 static void ln_bwd_dispatch(hipStream_t s, const void* dn, const void* add, const void* sres, const float* mean,
                             const float* rstd, const void* gamma, void* ds, void* ds_drop, void* dgamma, void* dbeta,
-                            void* dbias, int rows, int d, uint64_t key, float p, void* scratch, LnReduceJob* defer) {
+                            void* dbias, int rows, int d, uint64_t key, float p, void* scratch, LnReduceJob* defer, const float* slices, int splits) {
   const int nk = dbias ? 3 : 2;
   const uint32_t thr = (p > 0.f && ds_drop) ? drop_threshold(p) : 0u;
   const float inv_keep = 1.f / (1.f - p);
@@ -479,12 +452,16 @@ static void ln_bwd_dispatch(hipStream_t s, const void* dn, const void* add, cons
   const int waves = lnr_waves(rows, d);
   if (waves) {
     const int nbr = (rows + waves - 1) / waves;
-#define LN_BWD_ROW(N, W)                                                                                                \
-  hipLaunchKernelGGL((layernorm_bwd_row_kernel<T, N, W>), dim3(nbr), dim3(64 * W), 0, s, (const T*)dn, (const T*)add,   \
+#define LN_BWD_ROW(N, W, S)                                                                                             \
+  hipLaunchKernelGGL((layernorm_bwd_row_kernel<T, N, W, S>), dim3(nbr), dim3(64 * W), 0, s, (const T*)dn, slices, splits, (const T*)add,  \
                      (const T*)sres, mean, rstd, (const T*)gamma, (T*)ds, (T*)ds_drop, (float*)scratch, rows, d, key, thr, \
                      inv_keep, nk)
-#define LN_BWD_WAVES(N) do { if (waves == 4) LN_BWD_ROW(N, 4); else if (waves == 8) LN_BWD_ROW(N, 8); else LN_BWD_ROW(N, 16); } while (0)
-    if (nch == 1) LN_BWD_WAVES(1); else if (nch == 2) LN_BWD_WAVES(2); else LN_BWD_WAVES(3);
+#define LN_BWD_SLICES(N) do { if (splits <= 2) LN_BWD_ROW(N, LNR_FEWEST, 2); else if (splits <= 4) LN_BWD_ROW(N, LNR_FEWEST, 4); else LN_BWD_ROW(N, LNR_FEWEST, 8); } while (0)
+#define LN_BWD_WAVES(N) do { if (waves == 4) LN_BWD_ROW(N, 4, 0); else if (waves == 8) LN_BWD_ROW(N, 8, 0); else LN_BWD_ROW(N, 16, 0); } while (0)
+    if (splits > 0) {
+      if constexpr (sizeof(T) == 2) { if (nch == 1) LN_BWD_SLICES(1); else if (nch == 2) LN_BWD_SLICES(2); else LN_BWD_SLICES(3); }
+    } else if (nch == 1) LN_BWD_WAVES(1); else if (nch == 2) LN_BWD_WAVES(2); else LN_BWD_WAVES(3);
+#undef LN_BWD_SLICES
 #undef LN_BWD_WAVES
 #undef LN_BWD_ROW
     if (defer) { *defer = LnReduceJob{(const float*)scratch, nbr, 1, dgamma, dbeta, dbias}; return; }
@@ -505,12 +482,13 @@ static void ln_bwd_dispatch(hipStream_t s, const void* dn, const void* add, cons
                      (T*)dgamma, (T*)dbeta, (T*)dbias, 0);
 }
 
+bool layernorm_bwd_takes_slices(int dt, int rows, int d) { return dt != F32 && lnr_waves(rows, d) == LNR_FEWEST; }
 void launch_layernorm_bwd(hipStream_t s, int dt, const void* dn, const void* add, const void* sres, const float* mean,
                           const float* rstd, const void* gamma, void* ds, void* ds_drop, void* dgamma, void* dbeta,
-                          void* dbias, int rows, int d, uint64_t key, float p, void* scratch, LnReduceJob* defer) {
-  if (dt == F32) ln_bwd_dispatch<float>(s, dn, add, sres, mean, rstd, gamma, ds, ds_drop, dgamma, dbeta, dbias, rows, d, key, p, scratch, defer);
-  else if (dt == F16) ln_bwd_dispatch<half_t>(s, dn, add, sres, mean, rstd, gamma, ds, ds_drop, dgamma, dbeta, dbias, rows, d, key, p, scratch, defer);
-  else ln_bwd_dispatch<bf16_t>(s, dn, add, sres, mean, rstd, gamma, ds, ds_drop, dgamma, dbeta, dbias, rows, d, key, p, scratch, defer);
+                          void* dbias, int rows, int d, uint64_t key, float p, void* scratch, LnReduceJob* defer, const float* slices, int splits) {
+#define LN_BWD_T(T) ln_bwd_dispatch<T>(s, dn, add, sres, mean, rstd, gamma, ds, ds_drop, dgamma, dbeta, dbias, rows, d, key, p, scratch, defer, slices, splits)
+  if (dt == F32) LN_BWD_T(float); else if (dt == F16) LN_BWD_T(half_t); else LN_BWD_T(bf16_t);
+#undef LN_BWD_T
 }
 
 void launch_ln_reduce_batched(hipStream_t s, int dt, const LnReduceJob* jobs, int n, int d) {

@@ -895,19 +895,22 @@ void attention(const StepCtx& s, bool bwd, const Stream& qs, const Stream& ks, c
   else run(c, TFM_PROF_ATTENTION, 2.0 * f, bytes, [&] { launch_attention_bwd(c->stream, a); });
 }
 
-// y = f_k(fin): the sub-layer without its residual wrapper
-void sublayer_fwd(const StepCtx& s, Stream& st, int k, const void* fin, void* y) {
+// y = f_k(fin): the sub-layer without its residual wrapper.  Of few rows its last product runs split along K: the fp32 slices are then left
+// in the split-K workspace, without the bias, for the LayerNorm that follows, and their count is returned (0: y is complete).
+int sublayer_fwd(const StepCtx& s, Stream& st, int k, const void* fin, void* y) {
   tfm_ctx* c = s.c;
   Block& b = st.blocks[k];
   const int d = c->cfg.d_model, F = c->cfg.d_ffn, T = st.rows;
   const std::vector<int>& len = st.id ? s.tlen : s.slen;
+  int splits = 0;
+  auto last = [&](int in, const void* x) { gemm(c, 0, T, d, in, x, in, wh(c, b.w_o), in, y, d, wh(c, b.b_o), 0, nullptr, nullptr, false, 0, 0.f, 1.f, &splits); };
   need(c, b.ln_b);                                 // the block's parameters are one Adam chunk
   if (b.kind == SELF) {
     gemm(c, 0, T, 3 * d, d, fin, d, wh(c, b.w_a), d, b.inter, 3 * d, wh(c, b.b_a));
     const char* qkv = (const char*)b.inter;
     attention(s, false, st, st, len, len, qkv, 3 * d, qkv + d * c->esz, 3 * d, qkv + 2 * d * c->esz, 3 * d, b.ctx, b.lse, st.id == 1,
               site_key(s, st.id, b.layer, 3));
-    gemm(c, 0, T, d, d, b.ctx, d, wh(c, b.w_o), d, y, d, wh(c, b.b_o));
+    last(d, b.ctx);
   } else if (b.kind == CROSS) {
     Stream& en = c->enc;
     const void* mem = en.norm[en.blocks.size()];
@@ -916,19 +919,27 @@ void sublayer_fwd(const StepCtx& s, Stream& st, int k, const void* fin, void* y)
     const char* kv = (const char*)b.kv;
     attention(s, false, st, en, s.tlen, s.slen, b.inter, d, kv, c->ld_kv, kv + d * c->esz, c->ld_kv, b.ctx, b.lse, false,
               site_key(s, st.id, b.layer, 4));
-    gemm(c, 0, T, d, d, b.ctx, d, wh(c, b.w_o), d, y, d, wh(c, b.b_o));
+    last(d, b.ctx);
   } else {
     // (dropout on the hidden activations, if configured, is applied by the same epilogue after the ReLU)
     gemm(c, 0, T, F, d, fin, d, wh(c, b.w_a), d, b.inter, F, wh(c, b.b_a), 1, nullptr, nullptr, false, site_key(s, st.id, b.layer, 5),
          c->cfg.relu_dropout);
-    gemm(c, 0, T, d, F, b.inter, F, wh(c, b.w_o), F, y, d, wh(c, b.b_o));
+    last(F, b.inter);
   }
+  return splits;
 }
 
+// splits > 0: y is bias + the slices that sublayer_fwd left
 void ln_fwd(tfm_ctx* c, const void* x, const void* y, int g, int b, void* s_out, void* n_out, float* mean, float* rstd,
-            int rows, uint64_t key) {
+            int rows, uint64_t key, int splits = 0, int bias = 0) {
   const int d = c->cfg.d_model;
   need(c, b);
+  if (splits > 0) {
+    const SplitkNorm q{x, (const float*)c->splitk_ws, splits, wh(c, bias), wh(c, g), wh(c, b), s_out, n_out, mean, rstd};
+    run(c, TFM_PROF_NORM, 0.0, (double)rows * d * (4.0 * splits + c->esz * 3.0),
+        [&] { launch_splitk_layernorm_fwd(c->stream, c->dt, q, rows, d, key, c->cfg.dropout); });
+    return;
+  }
   const double bytes = (double)c->esz * rows * d * (1.0 + (y ? 1.0 : 0.0) + (s_out ? 1.0 : 0.0) + 1.0);
   run(c, TFM_PROF_NORM, 0.0, bytes, [&] {
     launch_residual_layernorm_fwd(c->stream, c->dt, x, y, wh(c, g), wh(c, b), s_out, n_out, mean, rstd, rows, d, key, c->cfg.dropout);
@@ -956,21 +967,31 @@ void stream_fwd(const StepCtx& s, Stream& st) {
   });
   if (pre) ln_fwd(c, st.resid[0], nullptr, st.blocks[0].ln_g, st.blocks[0].ln_b, nullptr, st.norm[0], st.mean[0], st.rstd[0], T, 0);
   for (int k = 0; k < K; ++k) {
-    sublayer_fwd(s, st, k, st.norm[k], c->y);
+    const int splits = sublayer_fwd(s, st, k, st.norm[k], c->y);
     int g, b;
     if (pre) { g = k + 1 < K ? st.blocks[k + 1].ln_g : st.lnf_g; b = k + 1 < K ? st.blocks[k + 1].ln_b : st.lnf_b; }
     else { g = st.blocks[k].ln_g; b = st.blocks[k].ln_b; }
     ln_fwd(c, pre ? st.resid[k] : st.norm[k], c->y, g, b, st.resid[k + 1], st.norm[k + 1], st.mean[k + 1], st.rstd[k + 1], T,
-           block_key(s, st, k));
+           block_key(s, st, k), splits, st.blocks[k].b_o);
   }
 }
 
 // backward of sub-layer k given dy (which lives in the block's own b.dy); writes the gradient w.r.t. its input (plus
-// `residual` if given) to dout.  Weight and bias gradients are queued (see wgrad).
-void sublayer_bwd(const StepCtx& s, Stream& st, int k, const void* dy, const void* fin, const void* residual, void* dout) {
+// `residual` if given) to dout.  Weight and bias gradients are queued (see wgrad).  slices: a LayerNorm's backward kernel is the next to read the
+// result.  Of few rows the last product runs split along K, and its fp32 slices may then stay in the split-K workspace for that kernel, which adds
+// the residual too: their count is returned, and dout is not written.  (280 rows x 1024, 3 slices: a reduction of its own 4.5 us, in LayerNorm's
+// kernels 0.4 forward and 0.9 backward.)
+int sublayer_bwd(const StepCtx& s, Stream& st, int k, const void* dy, const void* fin, const void* residual, void* dout, bool slices) {
   tfm_ctx* c = s.c;
   Block& b = st.blocks[k];
   const int d = c->cfg.d_model, F = c->cfg.d_ffn, T = st.rows;
+  int splits = 0;
+  auto last = [&](int in, const void* x) {
+    GemmArgs a{c->dt, 1, T, d, in, x, in, wh(c, b.w_a), d, dout, d, nullptr, 0, nullptr, nullptr};
+    a.splitk_ws = c->splitk_ws; a.splitk_ws_bytes = c->splitk_bytes; a.deferred_splits = &splits;
+    slices = slices && layernorm_bwd_takes_slices(c->dt, T, d) && gemm_mfma_supported(a) && gemm_mfma_slices(a);
+    gemm(c, 1, T, d, in, x, in, wh(c, b.w_a), d, dout, d, nullptr, 0, nullptr, slices ? nullptr : residual, false, 0, 0.f, 1.f, slices ? &splits : nullptr);
+  };
   const std::vector<int>& len = st.id ? s.tlen : s.slen;
   if (b.kind == SELF) {
     wgrad(c, d, d, T, dy, d, b.ctx, d, gr(c, b.w_o), d, gr(c, b.b_o));
@@ -979,8 +1000,8 @@ void sublayer_bwd(const StepCtx& s, Stream& st, int k, const void* dy, const voi
     char* dqkv = (char*)b.dint;
     attention(s, true, st, st, len, len, qkv, 3 * d, qkv + d * c->esz, 3 * d, qkv + 2 * d * c->esz, 3 * d, b.ctx, b.lse, st.id == 1,
               site_key(s, st.id, b.layer, 3), c->dctx, dqkv, 3 * d, dqkv + d * c->esz, 3 * d, dqkv + 2 * d * c->esz, 3 * d);
-    gemm(c, 1, T, d, 3 * d, dqkv, 3 * d, wh(c, b.w_a), d, dout, d, nullptr, 0, nullptr, residual);
     wgrad(c, 3 * d, d, T, dqkv, 3 * d, fin, d, gr(c, b.w_a), d, gr(c, b.b_a));
+    last(3 * d, dqkv);
   } else if (b.kind == CROSS) {
     Stream& en = c->enc;
     wgrad(c, d, d, T, dy, d, b.ctx, d, gr(c, b.w_o), d, gr(c, b.b_o));
@@ -991,31 +1012,32 @@ void sublayer_bwd(const StepCtx& s, Stream& st, int k, const void* dy, const voi
     // stacked weights' are formed from all layers at once after the decoder's backward pass (see tfm_train_step)
     attention(s, true, st, en, s.tlen, s.slen, b.inter, d, kv, c->ld_kv, kv + d * c->esz, c->ld_kv, b.ctx, b.lse, false,
               site_key(s, st.id, b.layer, 4), c->dctx, b.dint, d, dkv, c->ld_kv, dkv + d * c->esz, c->ld_kv);
-    gemm(c, 1, T, d, d, b.dint, d, wh(c, b.w_a), d, dout, d, nullptr, 0, nullptr, residual);
     wgrad(c, d, d, T, b.dint, d, fin, d, gr(c, b.w_a), d, gr(c, b.b_a));
+    last(d, b.dint);
   } else {
     wgrad(c, d, F, T, dy, d, b.inter, F, gr(c, b.w_o), F, gr(c, b.b_o));
     // the saved hidden activations are positive exactly where the ReLU passed AND the unit was kept: the mask, times the
     // dropout scale
     gemm(c, 1, T, F, d, dy, d, wh(c, b.w_o), F, b.dint, F, nullptr, 0, b.inter, nullptr, false, 0, 0.f,
          1.f / (1.f - c->cfg.relu_dropout));
-    gemm(c, 1, T, d, F, b.dint, F, wh(c, b.w_a), d, dout, d, nullptr, 0, nullptr, residual);
     wgrad(c, F, d, T, b.dint, F, fin, d, gr(c, b.w_a), d, gr(c, b.b_a));
+    last(F, b.dint);
   }
+  return splits;
 }
 
 void ln_bwd(tfm_ctx* c, const void* dn, const void* add, const void* sres, const float* mean, const float* rstd, int g, int b,
-            void* ds, void* ds_drop, int bias_param, int rows, uint64_t key) {
+            void* ds, void* ds_drop, int rows, uint64_t key, int splits) {
   const int d = c->cfg.d_model;
   const bool drop = c->cfg.dropout > 0.f && ds_drop;
-  const double bytes = (double)c->esz * rows * d * (2.0 + (add ? 1.0 : 0.0) + 1.0 + (drop ? 1.0 : 0.0));
+  const double bytes = rows * (double)d * (c->esz * ((dn ? 2.0 : 1.0) + (add ? 1.0 : 0.0) + 1.0 + (drop ? 1.0 : 0.0)) + 4.0 * splits);
   // the partial sums wait in their own slice of the pool for the batched reduction of the next flush
   LnReduceJob job;
   const bool defer = c->ln_next < c->ln_slices;
   void* scratch = defer ? (void*)(c->ln_pool + (size_t)c->ln_next * c->ln_slice) : c->red_scratch;
   run(c, TFM_PROF_NORM, 0.0, bytes, [&] {
     launch_layernorm_bwd(c->stream, c->dt, dn, add, sres, mean, rstd, wh(c, g), ds, drop ? ds_drop : nullptr, gr(c, g), gr(c, b),
-                         bias_param >= 0 ? gr(c, bias_param) : nullptr, rows, d, key, c->cfg.dropout, scratch, defer ? &job : nullptr);
+                         nullptr, rows, d, key, c->cfg.dropout, scratch, defer ? &job : nullptr, (const float*)c->splitk_ws, splits);
   });
   if (defer) { c->lnq.push_back(job); c->ln_next += 1; }
 }
@@ -1030,33 +1052,35 @@ void* stream_bwd(const StepCtx& s, Stream& st, void* dn_in) {
   // Every gradient w.r.t. a block output is consumed by the LayerNorm-backward kernel before the sub-layer's last
   // GEMM writes the next one, so a single buffer (dcur) carries it down the stack.
   void* dn = dn_in;
+  void* pp = c->dsA;
+  void* pp_alt = c->dsB;
+  int splits = 0;                                  // of the last input gradient: slices in the workspace, with what is left to add to them as dn
   if (!pre) {
     for (int k = K - 1; k >= 0; --k) {
       Block& b = st.blocks[k];
-      // with dropout the kernel writes both the residual branch's gradient (dsA) and the sub-layer's (b.dy); without, they
-      // are the same tensor
-      void* ds = drop ? c->dsA : b.dy;
-      ln_bwd(c, dn, nullptr, st.resid[k + 1], st.mean[k + 1], st.rstd[k + 1], b.ln_g, b.ln_b, ds, b.dy, -1, T, block_key(s, st, k));
+      // with dropout the kernel writes both the residual branch's gradient (dsA or dsB: it may still read the one before) and the
+      // sub-layer's (b.dy); without, they are the same tensor
+      void* ds = drop ? pp : b.dy;
+      ln_bwd(c, dn, nullptr, st.resid[k + 1], st.mean[k + 1], st.rstd[k + 1], b.ln_g, b.ln_b, ds, b.dy, T, block_key(s, st, k), splits);
       void* out = k == 0 ? c->demb[st.id] : c->dcur;
-      sublayer_bwd(s, st, k, b.dy, st.norm[k], ds, out);
-      dn = out;
+      splits = sublayer_bwd(s, st, k, b.dy, st.norm[k], ds, out, k > 0);
+      dn = splits > 0 ? ds : out;
+      std::swap(pp, pp_alt);
     }
     return dn;
   }
   // pre-norm: the residual stream's gradient ping-pongs between dsA and dsB; without dropout it IS the gradient of the
   // sub-layer below and is written straight into that block's own buffer
   void* dR = nullptr;
-  void* pp = c->dsA;
-  void* pp_alt = c->dsB;
   for (int idx = K; idx >= 0; --idx) {
     const int g = idx < K ? st.blocks[idx].ln_g : st.lnf_g;
     const int b = idx < K ? st.blocks[idx].ln_b : st.lnf_b;
     void* bdy = idx >= 1 ? st.blocks[idx - 1].dy : nullptr;
     void* ds = idx == 0 ? c->demb[st.id] : (drop ? pp : bdy);
-    ln_bwd(c, dn, dR, st.resid[idx], st.mean[idx], st.rstd[idx], g, b, ds, bdy, -1, T, idx >= 1 ? block_key(s, st, idx - 1) : 0);
+    ln_bwd(c, dn, dR, st.resid[idx], st.mean[idx], st.rstd[idx], g, b, ds, bdy, T, idx >= 1 ? block_key(s, st, idx - 1) : 0, splits);
     if (idx == 0) return ds;
-    sublayer_bwd(s, st, idx - 1, bdy, st.norm[idx - 1], nullptr, c->dcur);
-    dn = c->dcur;
+    splits = sublayer_bwd(s, st, idx - 1, bdy, st.norm[idx - 1], nullptr, c->dcur, true);
+    dn = splits > 0 ? nullptr : c->dcur;
     dR = ds;
     std::swap(pp, pp_alt);
   }
@@ -1563,7 +1587,7 @@ void decode_norm(tfm_decoder* D, const ThinNorm& q) {
   const int d = c->cfg.d_model;
   if (q.splits > 0) {
     run(c, TFM_PROF_NORM, 0.0, (double)D->rows * d * (4.0 * q.splits + c->esz * (2.0 + (q.s_out ? 1.0 : 0.0))), [&] {
-      launch_splitk_layernorm_fwd(c->stream, c->dt, q.x, q.partial, q.splits, q.bias, q.gamma, q.beta, q.s_out, q.n_out, D->rows, d);
+      launch_splitk_layernorm_fwd(c->stream, c->dt, SplitkNorm{q.x, q.partial, q.splits, q.bias, q.gamma, q.beta, q.s_out, q.n_out, nullptr, nullptr}, D->rows, d, 0, 0.f);
     });
     return;
   }

@@ -128,6 +128,33 @@ def test_half_precision_models(precision, name):
         assert cosine(gg[k], v) >= HALF_COS, (k, cosine(gg[k], v))
 
 
+@pytest.mark.parametrize("precision", ["fp16", "bf16"])
+@pytest.mark.parametrize("name", ["post", "lm_pre"])
+@pytest.mark.parametrize("dropout", [0.0, 0.1])
+@pytest.mark.parametrize("tokens", [50, 200, 900])
+def test_few_rows_whose_products_run_in_slices(precision, name, dropout, tokens):
+    """Width 512 and an inner size of 4096: up to 8 slices of a product, which the LayerNorm kernels of either direction add up, of up to 64
+    rows (the few-row kernel), some hundred, and as many as still run in slices.  In bf16 a pre-activation is off by some 2^-8 of its spread, so that
+    share of the hidden units passes its ReLU on one side only, and with it of the energy of a gradient of 50 rows: a cosine of 1 - 2^-9."""
+    import paper_1904_01038_amd as T
+    shape = {"post": ModelShape(1, 2, 512, 8, 4096, 264), "lm_pre": ModelShape(0, 2, 512, 8, 4096, 264, pre_norm=1)}[name]
+    prec = T.FP16 if precision == "fp16" else T.BF16
+    gpu, oracle = make_pair(shape, prec, generic=True, init_loss_scale=128.0 if precision == "fp16" else 1.0, max_sentences=64, max_len=64,
+                            max_tokens=2048, dropout=dropout, seed=11)
+    if shape.enc_layers:
+        batch = make_batches("base", 1, shape=shape, max_tokens=tokens, lo=5, hi=40 if tokens > 50 else 6)[0]
+    else:
+        batch = make_batches("lm16", 1, shape=shape, hi=tokens // 5, max_sentences=5)[0] if tokens < 900 else make_batches("lm16", 1, shape=shape, hi=60, max_sentences=15)[0]
+    rg, ro = step_both(gpu, oracle, batch)
+    assert rg["overflow"] == 0 and ro["overflow"] == 0
+    assert abs(rg["loss_sum"] - ro["loss_sum"]) <= HALF_LOSS * abs(ro["loss_sum"])
+    gg = gpu.get_grads()
+    least = 1.0 - 2.0 ** -9 if precision == "bf16" and tokens == 50 else HALF_COS
+    for k, v in oracle.G.items():
+        assert cosine(gg[k], v) >= least, (k, cosine(gg[k], v))
+    gpu.close()
+
+
 def test_padding_invariance_and_determinism():
     import paper_1904_01038_amd as T
     shape = SMALL["post"]
