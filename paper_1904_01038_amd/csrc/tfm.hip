@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -71,6 +72,8 @@ struct Arena {
 };
 
 constexpr int STAGE_SLOTS = 4;
+// Pinned memory that kernels read and write in place, call after call: coherence is asked for, the default follows HIP_HOST_COHERENT.
+constexpr unsigned REPORT_MEMORY = hipHostMallocCoherent | hipHostMallocMapped;
 constexpr double BESIDE_MIN = 2.5e9;               // rows (of both sides) x width^2 from which a sub-batch uses the second stream, see tfm_ctx::beside
 
 // Adaptive input embeddings / adaptive softmax (language model).  Cluster 0 is the head, clusters 1..n the tails.
@@ -167,6 +170,7 @@ struct tfm_ctx {
   size_t int_block_ints;
   Adaptive ad;
   std::vector<std::pair<int, int>> ad_pairs;
+  uint64_t *h_state = nullptr, *d_state = nullptr;  // pinned: the device state as last read (read_state), and the device's address of it
   // host staging
   int* stage[STAGE_SLOTS];
   hipEvent_t stage_ev[STAGE_SLOTS];
@@ -491,6 +495,30 @@ hipEvent_t mark(tfm_ctx* c, hipStream_t on) {
 }
 // what has been enqueued on `from` so far happens before what is enqueued on `to` from now on
 inline void order(tfm_ctx* c, hipStream_t from, hipStream_t to) { hipStreamWaitEvent(to, mark(c, from), 0); }
+// Waits for the `n` words that a kernel of the stream's reports (see common.h).  They are there a microsecond or two after they are
+// stored; hipStreamSynchronize came back 20 to 60 us later, of some 300 that a decoding step of few rows takes.  What takes longer than
+// WATCH_MS is waited for by the runtime, which also brings up an error on the device.
+constexpr int WATCH_MS = 10;
+hipError_t await_report(hipStream_t s, const uint64_t* words, size_t n) {
+  const auto begin = std::chrono::steady_clock::now();
+  unsigned looks = 0;
+  for (size_t i = 0; i < n; ++i)
+    while (__atomic_load_n(words + i, __ATOMIC_ACQUIRE) == REPORT_EMPTY) {
+      if ((++looks & 1023) == 0 && std::chrono::steady_clock::now() - begin > std::chrono::milliseconds(WATCH_MS)) return hipStreamSynchronize(s);
+      __asm__ volatile("pause");
+    }
+  return hipSuccess;
+}
+// The device state after everything that is on the context's stream
+hipError_t read_state(tfm_ctx* c, DevState* h) {
+  std::fill_n(c->h_state, REPORT_WORDS, REPORT_EMPTY);
+  launch_report_state(c->stream, c->st, c->d_state);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = await_report(c->stream, c->h_state, REPORT_WORDS);
+  else hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) std::memcpy(h, c->h_state, sizeof(*h));
+  return e;
+}
 inline hipStream_t wstream(tfm_ctx* c) { return c->beside ? c->side : c->stream; }
 // main -> side: the operands of the weight-gradient work enqueued next are ready
 inline void side_begin(tfm_ctx* c) { if (c->beside) order(c, c->stream, c->side); }
@@ -688,6 +716,9 @@ int tfm_create(const tfm_config* cfg, void* ws, size_t bytes, void* hip_stream, 
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->stage_ev[i], hipEventDisableTiming);
     if (e != hipSuccess) { fail(nullptr, TFM_EHIP, "staging buffers: %s", hipGetErrorString(e)); return cleanup(TFM_EHIP); }
   }
+  e = hipHostMalloc((void**)&c->h_state, REPORT_WORDS * 8, REPORT_MEMORY);
+  if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&c->d_state, c->h_state, 0);
+  if (e != hipSuccess) { fail(nullptr, TFM_EHIP, "report buffer: %s", hipGetErrorString(e)); return cleanup(TFM_EHIP); }
   *out = c;
   return TFM_OK;
 }
@@ -698,6 +729,7 @@ void tfm_destroy(tfm_ctx* c) {
   if (c->side) { hipStreamSynchronize(c->side); hipStreamDestroy(c->side); }
   for (hipEvent_t e : c->sync_ev) hipEventDestroy(e);
   for (hipEvent_t e : c->adam_ev) hipEventDestroy(e);
+  if (c->h_state) hipHostFree(c->h_state);
   for (int i = 0; i < STAGE_SLOTS; ++i) {
     if (c->stage[i]) hipHostFree(c->stage[i]);
     if (c->stage_ev[i]) hipEventDestroy(c->stage_ev[i]);
@@ -1420,8 +1452,7 @@ int tfm_train_step(tfm_ctx* c, const int32_t* src, const int32_t* tgt, const int
   HIP_TRY(c, hipGetLastError());
   if (out) {
     DevState h;
-    HIP_TRY(c, hipMemcpyAsync(&h, c->st, sizeof(h), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, read_state(c, &h));
     out->loss_sum = h.loss_sum; out->nll_sum = h.nll_sum; out->ntokens = Tt; out->overflow = h.step_overflow;
     out->loss_scale = h.loss_scale;
     // an update enqueued without synchronisation may have taken the scale below the minimum: this is where it shows
@@ -1471,8 +1502,7 @@ int tfm_apply_update(tfm_ctx* c, float lr, tfm_update_out* out) {
   if (out) {
     adam_join(c);
     DevState h;
-    HIP_TRY(c, hipMemcpyAsync(&h, c->st, sizeof(h), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, read_state(c, &h));
     out->skipped = h.skipped; out->loss_scale_after = h.loss_scale; out->clean_steps = h.clean_steps;
     out->num_updates = h.num_updates; out->grad_norm = h.grad_norm; out->ntokens_total = ntok;
     if (h.scale_too_small) return fail(c, TFM_ESCALE, "loss scale %g fell below the minimum %g", h.loss_scale, cf.min_loss_scale);
@@ -1498,7 +1528,7 @@ struct tfm_decoder {
   // Pinned host memory that the step's kernels read and write in place, with the device's addresses of it
   int* h_src;                                      // tfm_decoder_begin: source ids / pos / offsets, copied to the device
   int *h_in, *d_in;                                // a step's token, parent, index into a tail cluster's table [3 * max_rows]
-  float *h_out, *d_out;                            // top_logp [rows * topk] followed by the ids
+  uint64_t *h_out, *d_out;                         // a step's candidates [rows * topk]: log-probability and id
   // state of the batch being decoded
   int B, beam, rows, t, cur, n_src_max, src_rows;
   uint64_t generation;                             // the context's when the batch began
@@ -1686,10 +1716,8 @@ int tfm_decoder_create(tfm_ctx* c, void* ws, size_t bytes, int32_t max_rows, int
   if (bytes < need) { delete D; return fail(c, TFM_ENOMEM, "decoder workspace has %zu bytes, %zu needed", bytes, need); }
   decoder_carve(D, (char*)ws);
   hipError_t e = hipHostMalloc((void**)&D->h_src, (2 * (size_t)c->cfg.max_tokens + c->cfg.max_sentences + 1) * 4, hipHostMallocDefault);
-  // Kernels read and write these two in place, step after step: coherence is asked for, the default follows HIP_HOST_COHERENT.
-  const unsigned in_place = hipHostMallocCoherent | hipHostMallocMapped;
-  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_in, 3 * (size_t)max_rows * 4, in_place);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_out, (size_t)max_rows * topk * 8, in_place);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_in, 3 * (size_t)max_rows * 4, REPORT_MEMORY);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_out, (size_t)max_rows * topk * 8, REPORT_MEMORY);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&D->d_in, D->h_in, 0);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&D->d_out, D->h_out, 0);
   if (e != hipSuccess) {
@@ -1785,7 +1813,7 @@ int tfm_decoder_step(tfm_decoder* D, const int32_t* prev, const int32_t* parent,
     if (parent && (parent[r] < 0 || parent[r] >= R || parent[r] / D->beam != r / D->beam))
       return fail(c, TFM_EINVAL, "parent[%d] = %d is not a row of the same sentence", r, parent[r]);
   }
-  // the previous step's call synchronised, so the staging buffer is free
+  // the previous step's call has waited for its candidates, so the kernels that read the staging buffer are done
   for (int r = 0; r < R; ++r) { D->h_in[r] = prev[r]; D->h_in[R + r] = parent ? parent[r] : r; }
   // Adaptive inputs: a row fed with a token of tail cluster k gets the id -1 - (its row in the compact list of projected vectors);
   // the lists are ordered by cluster, rows ascending
@@ -1845,13 +1873,19 @@ int tfm_decoder_step(tfm_decoder* D, const int32_t* prev, const int32_t* parent,
       gemm(c, 0, R, Vk, w, D->a_u, w, wh(c, ad.E[k]), w, const_cast<void*>(scores.z[k]), scores.ld[k]);          // z = E u
     }
   }
-  const size_t n = (size_t)R * D->topk;                // (the values and ids go straight to the host's memory)
+  const size_t n = (size_t)R * D->topk;                // (the candidates go straight to the host's memory)
+  std::fill_n(D->h_out, n, REPORT_EMPTY);
   run(c, TFM_PROF_LOSS, 0.0, (double)c->esz * R * V,
-      [&] { launch_row_topk(c->stream, c->dt, scores, R, D->topk, D->d_out, (int*)(D->d_out + n), D->lse, D->topk_ws); });
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  HIP_TRY(c, hipGetLastError());
-  std::memcpy(top_logp, D->h_out, n * 4);
-  std::memcpy(top_id, D->h_out + n, n * 4);
+      [&] { launch_row_topk(c->stream, c->dt, scores, R, D->topk, D->d_out, D->lse, D->topk_ws); });
+  const hipError_t enqueued = hipGetLastError();
+  if (enqueued != hipSuccess) hipStreamSynchronize(c->stream);         // (nothing of this step is to reach the next one's words)
+  HIP_TRY(c, enqueued);
+  HIP_TRY(c, await_report(c->stream, D->h_out, n));
+  for (size_t i = 0; i < n; ++i) {
+    const uint32_t lo = (uint32_t)D->h_out[i];
+    std::memcpy(top_logp + i, &lo, 4);
+    top_id[i] = (int32_t)(D->h_out[i] >> 32);
+  }
   D->t += 1;
   return TFM_OK;
 }
