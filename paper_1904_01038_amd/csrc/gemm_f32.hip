@@ -25,6 +25,7 @@ struct F32Params {
   const float* bias; int relu; const float* mask; const float* residual;
   uint64_t drop_key; uint32_t drop_thr; float inv_keep, mask_scale;
   float* colsum;                                         // [M] sums of A's columns over K (TN only), or null
+  int quads;                                             // whole aligned quadruples of columns: the epilogue's operands and results 16 bytes at a time
 };
 
 // Rows r0 .. r0 + 31 of an operand, 8 k at a time.  TR: the contraction is the slow index.  VEC: 16-byte loads (K, ld and base allow it).
@@ -87,6 +88,19 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Params& p, int tm, int tn
   };
   const int trips = (p.K + 8 * U * WK - 1) / (8 * U * WK);
   fetch(0, a, b);
+  // Where a thread finishes at most one quadruple (4 wavefronts or more share a tile), what the epilogue adds to it is on its way with the operands.
+  // In a trip of its own behind the sums, element by element, it was 0.5 us of a launch: X W^T with a bias 128 x 192 x 64 3.9 us, now 3.3, 128 x 64 x 256
+  // 5.3 and 4.6, 512^3 8.6 and 8.0; dY W with a residual 128 x 64 x 256 4.9 and 4.4 (out of a graph, over 24 sets of operands).
+  constexpr bool ONE = WK >= 4;
+  const int er = (wk * 64 + lane) >> 3, ec = ((wk * 64 + lane) & 7) * 4;
+  const bool early = ONE && p.quads && wk * 64 + lane < 256 && m0 + er < p.M && n0 + ec < p.N;
+  float4 bias4 = {0.f, 0.f, 0.f, 0.f}, mask4 = {1.f, 1.f, 1.f, 1.f}, res4 = {0.f, 0.f, 0.f, 0.f};
+  if (early) {
+    const size_t o = (size_t)(m0 + er) * p.ldc + n0 + ec;
+    if (p.bias) bias4 = *reinterpret_cast<const float4*>(p.bias + n0 + ec);
+    if (p.mask) mask4 = *reinterpret_cast<const float4*>(p.mask + o);
+    if (p.residual) res4 = *reinterpret_cast<const float4*>(p.residual + o);
+  }
   for (int t = 0; t < trips; t += 2) {                    // (turns beyond K multiply zeros)
     fetch(t + 1, a2, b2);
     multiply(a, b);
@@ -116,6 +130,26 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Params& p, int tm, int tn
     for (int w = 0; w < WK; ++w) {
       const float4 x = *reinterpret_cast<const float4*>(&box[wave - wk + w][r * PITCH + c]);
       v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+    }
+    if (early) {
+      const float bv[4] = {bias4.x, bias4.y, bias4.z, bias4.w}, mv[4] = {mask4.x, mask4.y, mask4.z, mask4.w}, rv[4] = {res4.x, res4.y, res4.z, res4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (p.bias) v[e] += bv[e];
+        if (p.relu) v[e] = fmaxf(v[e], 0.f);
+      }
+      if (p.drop_thr) {                                  // (a multiple of 4 columns: the four bits are of one word)
+        const uint64_t word = drop_word(p.drop_key, ((uint64_t)m * p.N + n) >> 2);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = drop_keep(word, e, p.drop_thr) ? v[e] * p.inv_keep : 0.f;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (p.mask) v[e] = mv[e] > 0.f ? v[e] * p.mask_scale : 0.f;
+        if (p.residual) v[e] += rv[e];
+      }
+      *reinterpret_cast<float4*>(p.C + (size_t)m * p.ldc + n) = float4{v[0], v[1], v[2], v[3]};
+      continue;
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -149,7 +183,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_f32_grouped_kernel(F32
   int i = 0;
   for (int j = 1; j < tab.n; ++j) i = (int)blockIdx.x >= tab.job[j].tile_begin ? j : i;
   const F32Job& g = tab.job[i];
-  F32Params p{g.M, g.N, g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, nullptr, 0, nullptr, nullptr, 0, 0, 1.f, 1.f, g.colsum};
+  const bool quads = g.N % 4 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0;
+  F32Params p{g.M, g.N, g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, nullptr, 0, nullptr, nullptr, 0, 0, 1.f, 1.f, g.colsum, quads};
   const int tile = blockIdx.x - g.tile_begin;
   gemm_f32_tile<true, true, false, WM, WN, WK>(p, tile / g.tiles_n, tile % g.tiles_n);
 }
@@ -160,9 +195,9 @@ static long tiles32(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 3
 // 4.3 / 38 and 4.8; 128 x 64 x 1000 224 and 9.7 / 194 and 10.5 / 206 and 9.9; 512^3 93 and 7.9 / 89 and 6.9 / 107 and 7.1; with 64x64 blocks here 4096 x
 // 1024 x 1024 247 and 161 (53 TFLOP/s) / 241 and 154 / 285 and 142; 2000 x 8192 x 512 365 and 323 / 377 and 269 / 368 and 282.  The error against 64 bits
 // is 0.4-0.6 of the former where wavefronts share K, equal elsewhere.  Up to 1024 tiles of 32 (4 a compute unit) the small blocks keep more of the chip
-// busy, small and large: 512^3 7.9 and 20.8 / 6.9 and 22.6 / 7.1 and 26.5, 1024 x 1024 x 512 25.0 and 21.0 / 22.4 and 22.8 / 22.5 and 26.8, 2000 x
+// busy, small and large (before the epilogue's operands came early): 512^3 7.9 and 20.8 / 6.9 and 22.6 / 7.1 and 26.5, 1024 x 1024 x 512 25.0 and 21.0 / 22.4 and 22.8 / 22.5 and 26.8, 2000 x
 // 1024 x 1024 (2016 tiles) 87 and 74 / 78 and 69 / 75 and 74; 8 wavefronts take K = 1000 in 4 trips to memory where 4 take 8, and
-// below K = 256 have no second turn to take.
+// below K = 256 have no second turn to take.  (16 wavefronts beyond K = 512 spill: 128 x 64 x 1000 dY W 10.6 and 14.8.)
 template <int FORM, bool VEC>
 static void gemm_f32_launch(hipStream_t s, const F32Params& p) {
   const dim3 small((p.N + 31) / 32, (p.M + 31) / 32), large((p.N + 63) / 64, (p.M + 63) / 64);
@@ -187,9 +222,11 @@ bool gemm_f32_pays(const GemmArgs& a) {
 
 void launch_gemm_f32(hipStream_t s, const GemmArgs& a) {
   if (a.M <= 0 || a.N <= 0) return;
+  const auto whole = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
+  const bool quads = a.N % 4 == 0 && a.ldc % 4 == 0 && whole(a.C) && whole(a.bias) && whole(a.mask) && whole(a.residual);
   const F32Params p{a.M, a.N, a.K, (const float*)a.A, a.lda, (const float*)a.B, a.ldb, (float*)a.C, a.ldc, (const float*)a.bias, a.relu,
                     (const float*)a.mask, (const float*)a.residual, a.drop_key, a.drop_p > 0.f ? drop_threshold(a.drop_p) : 0u, 1.f / (1.f - a.drop_p),
-                    a.mask_scale, nullptr};
+                    a.mask_scale, nullptr, quads};
   const bool vec = f32_vec(a);
   if (a.form == 0) { if (vec) gemm_f32_launch<0, true>(s, p); else gemm_f32_launch<0, false>(s, p); }
   else if (a.form == 1) { if (vec) gemm_f32_launch<1, true>(s, p); else gemm_f32_launch<1, false>(s, p); }
