@@ -160,8 +160,8 @@ static __device__ __forceinline__ f32x4 mfma16(bf16_t, uint4 a, uint4 b, f32x4 c
 
 constexpr int DEC_ATT_WAVES = 8;                         // rows per block at most
 
-template <typename T, int U, bool SELF>                  // chunks of 16 * U positions
-__global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(DecodeAttnArgs p) {
+template <typename T, int U, bool SELF>                  // chunks of 16 * U positions; SELF: in the caches, at rows from the ancestry table
+static __device__ __forceinline__ void decode_attention64(const DecodeAttnArgs& p) {
   __shared__ __attribute__((aligned(16))) T sq[DEC_ATT_WAVES][64];
   constexpr int dh = 64;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4, odd = (lane >> 3) & 1, f = lane & 7;
@@ -292,6 +292,11 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
   }
 }
 
+template <typename T, int U>                             // over the history
+__global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(DecodeAttnArgs p) { decode_attention64<T, U, true>(p); }
+template <typename T, int U>                             // over the source sentence: no table, positions one behind the other
+__global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_source_attention64_kernel(DecodeAttnArgs p) { decode_attention64<T, U, false>(p); }
+
 // (16-byte accesses: the host side lays q, the caches and the output out with head slices at multiples of 128 bytes)
 static bool decode_attention_fast(const DecodeAttnArgs& a) {
   return a.dh == 64 && a.dt != F32 && a.ldq % 8 == 0 && a.row_stride % 8 == 0 && a.ldo % 8 == 0 && (!a.k_new || a.ld_new % 8 == 0);
@@ -308,11 +313,10 @@ void launch_decode_attention(hipStream_t s, const DecodeAttnArgs& a) {
     block = dim3(64 * w);
     const int halves = (a.n_max + 31) / 32, waves = a.rows * a.H;              // (the line: see the table above)
     const bool all = halves == 2 ? waves <= 3072 : halves > 3 && waves < 2048;
-#define DA64(T, SELF)                                                                                                        \
-  do { if (all) hipLaunchKernelGGL((decode_attention64_kernel<T, 4, SELF>), grid, block, 0, s, a);                             \
-       else hipLaunchKernelGGL((decode_attention64_kernel<T, 2, SELF>), grid, block, 0, s, a); } while (0)
-    if (a.dt == F16) { if (a.anc) DA64(half_t, true); else DA64(half_t, false); }
-    else if (a.anc) DA64(bf16_t, true); else DA64(bf16_t, false);
+#define DA64(KERNEL, T)                                                                                                      \
+  do { if (all) hipLaunchKernelGGL((KERNEL<T, 4>), grid, block, 0, s, a); else hipLaunchKernelGGL((KERNEL<T, 2>), grid, block, 0, s, a); } while (0)
+    if (a.dt == F16) { if (a.anc) DA64(decode_attention64_kernel, half_t); else DA64(decode_source_attention64_kernel, half_t); }
+    else if (a.anc) DA64(decode_attention64_kernel, bf16_t); else DA64(decode_source_attention64_kernel, bf16_t);
 #undef DA64
     return;
   }
