@@ -496,7 +496,9 @@ hipEvent_t mark(tfm_ctx* c, hipStream_t on) {
 // what has been enqueued on `from` so far happens before what is enqueued on `to` from now on
 inline void order(tfm_ctx* c, hipStream_t from, hipStream_t to) { hipStreamWaitEvent(to, mark(c, from), 0); }
 // Waits for the `n` words that a kernel of the stream's reports (see common.h).  They are there a microsecond or two after they are
-// stored; hipStreamSynchronize came back 20 to 60 us later, of some 300 that a decoding step of few rows takes.  What takes longer than
+// stored; hipStreamSynchronize came back 20 to 60 us later.  (Not for decoding steps: 52 to 120 launches a step whose records the runtime
+then releases in stalls instead of at the wait; generation of 24 rows 29.4 -> 30.8 ms on some hosts, on none faster beyond the
+spread of its processes.)  What takes longer than
 // WATCH_MS is waited for by the runtime, which also brings up an error on the device.
 constexpr int WATCH_MS = 10;
 hipError_t await_report(hipStream_t s, const uint64_t* words, size_t n) {
@@ -1874,13 +1876,12 @@ int tfm_decoder_step(tfm_decoder* D, const int32_t* prev, const int32_t* parent,
     }
   }
   const size_t n = (size_t)R * D->topk;                // (the candidates go straight to the host's memory)
-  std::fill_n(D->h_out, n, REPORT_EMPTY);
   run(c, TFM_PROF_LOSS, 0.0, (double)c->esz * R * V,
       [&] { launch_row_topk(c->stream, c->dt, scores, R, D->topk, D->d_out, D->lse, D->topk_ws); });
   const hipError_t enqueued = hipGetLastError();
   if (enqueued != hipSuccess) hipStreamSynchronize(c->stream);         // (nothing of this step is to reach the next one's words)
   HIP_TRY(c, enqueued);
-  HIP_TRY(c, await_report(c->stream, D->h_out, n));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));         // (waited for, not watched: see await_report)
   for (size_t i = 0; i < n; ++i) {
     const uint32_t lo = (uint32_t)D->h_out[i];
     std::memcpy(top_logp + i, &lo, 4);
