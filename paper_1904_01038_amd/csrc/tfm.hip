@@ -497,8 +497,8 @@ hipEvent_t mark(tfm_ctx* c, hipStream_t on) {
 inline void order(tfm_ctx* c, hipStream_t from, hipStream_t to) { hipStreamWaitEvent(to, mark(c, from), 0); }
 // Waits for the `n` words that a kernel of the stream's reports (see common.h).  They are there a microsecond or two after they are
 // stored; hipStreamSynchronize came back 20 to 60 us later.  (Not for decoding steps: 52 to 120 launches a step whose records the runtime
-then releases in stalls instead of at the wait; generation of 24 rows 29.4 -> 30.8 ms on some hosts, on none faster beyond the
-spread of its processes.)  What takes longer than
+// then releases in stalls instead of at the wait; generation of 24 rows 29.4 -> 30.8 ms on some hosts, on none faster beyond the
+// spread of its processes.)  What takes longer than
 // WATCH_MS is waited for by the runtime, which also brings up an error on the device.
 constexpr int WATCH_MS = 10;
 hipError_t await_report(hipStream_t s, const uint64_t* words, size_t n) {
