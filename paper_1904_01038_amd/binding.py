@@ -1,13 +1,15 @@
 """ctypes binding of the C boundary declared in include/tfm.h.
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.  PyTorch supplies the
-device workspace and the stream.  There is no fallback: if libtfm.so is missing or does not load, importing
-the library handle raises.
+device workspace and the stream.  There is no fallback: if libtfm.so is missing, does not load or was built from other
+sources than those beside it, importing the library handle raises.
 """
 import ctypes as C
 import os
 
 import numpy as np
+
+from . import build as _build
 
 FP32, FP16, BF16 = 0, 1, 2
 PROF_CLASSES = ["gemm", "attention", "norm", "loss", "embed", "optim"]
@@ -52,8 +54,21 @@ class ProfEntry(C.Structure):
 _lib = None
 
 
+def _check_sources(L):
+    """A library that is left of other sources would run in the place of those that are there.  (Without sources: any library.)"""
+    if not all(os.path.exists(path) for path in [_build.CSRC] + _build.HEADERS):
+        return
+    try:
+        built_from = (C.c_char * 65).in_dll(L, "tfm_built_from").value.decode()
+    except ValueError:                        # (a library that carries no fingerprint)
+        built_from = ""
+    if built_from != _build.fingerprint():
+        raise RuntimeError(lib_path() + " was built from other sources than " + _build.CSRC +
+                           " holds: run `python -c 'import __graft_entry__ as g; g.build()'`")
+
+
 def lib():
-    """The loaded library; raises if it has not been built."""
+    """The loaded library; raises if it has not been built, or not from the sources that are there."""
     global _lib
     if _lib is None:
         path = lib_path()
@@ -63,6 +78,7 @@ def lib():
         # import it first, otherwise the loader would pull in a second copy of the runtime.
         import torch  # noqa: F401
         L = C.CDLL(path)
+        _check_sources(L)
         vp, i32, i64, f32, u64 = C.c_void_p, C.c_int32, C.c_int64, C.c_float, C.c_uint64
         L.tfm_workspace_bytes.argtypes = [C.POINTER(TfmConfig), C.POINTER(C.c_size_t)]
         L.tfm_create.argtypes = [C.POINTER(TfmConfig), vp, C.c_size_t, vp, C.POINTER(vp)]
