@@ -360,7 +360,7 @@ struct TopkList { float* v; int* id; float *m, *s; };    // per row: n * k candi
 // of the launch over several segments (a flag of both: over one segment the search for a block's cost a step of one sentence 1 %)
 template <typename T, int VEC, bool CLUSTERS>
 __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(TopkSegments sg, TopkList in, int n_in, int k, TopkList out,
-                                                      uint64_t* __restrict__ top, float* __restrict__ lse_out) {
+                                                      float* __restrict__ top_logp, int* __restrict__ top_id, float* __restrict__ lse_out) {
   constexpr int NT = TOPK_THREADS, PER = TOPK_PER, NW = NT / 64;
   static_assert(NT >= TOPK_LIST, "one survivor per thread");
   __shared__ float sh[16], sh_bound[NW];
@@ -512,7 +512,8 @@ __global__ __launch_bounds__(TOPK_THREADS) void row_topk_kernel(TopkSegments sg,
   auto emit = [&](int r, float v, int id) {
     id = id == 0x7fffffff ? id : id + base;
     if (last) {
-      report(top + (size_t)row * k + r, __float_as_uint(v - lse), (uint32_t)id);
+      top_logp[(size_t)row * k + r] = v - lse;
+      top_id[(size_t)row * k + r] = id;
     } else {
       out.v[((size_t)row * lists + blk) * k + r] = v;
       out.id[((size_t)row * lists + blk) * k + r] = id;
@@ -575,7 +576,7 @@ size_t row_topk_scratch_bytes(int rows, const TopkSegments& sg, int k) {
 }
 
 template <typename T>
-static void row_topk_typed(hipStream_t s, TopkSegments sg, int rows, int k, uint64_t* top, float* lse, void* scratch) {
+static void row_topk_typed(hipStream_t s, TopkSegments sg, int rows, int k, float* top_logp, int* top_id, float* lse, void* scratch) {
   auto list_at = [&](char* p, int n) {
     TopkList l;
     const size_t c = (size_t)rows * n * k, h = (size_t)rows * n;
@@ -593,7 +594,7 @@ static void row_topk_typed(hipStream_t s, TopkSegments sg, int rows, int k, uint
   TopkList out = list_at(bufs[0], n), in{};
   // (rows along x: y and z of a grid end at 65536)
 #define TK(VEC, CLUSTERS) \
-  hipLaunchKernelGGL((row_topk_kernel<T, VEC, CLUSTERS>), dim3(rows, n), dim3(TOPK_THREADS), 0, s, sg, in, n_in, k, out, top, lse)
+  hipLaunchKernelGGL((row_topk_kernel<T, VEC, CLUSTERS>), dim3(rows, n), dim3(TOPK_THREADS), 0, s, sg, in, n_in, k, out, top_logp, top_id, lse)
   const bool clusters = sg.n > 1;                        // (whose loads are always of 8 values)
   if (clusters) TK(8, true); else if (al % (8 * sizeof(T)) == 0) TK(8, false); else if (al % (2 * sizeof(T)) == 0) TK(2, false); else TK(1, false);
   for (int which = 1; n > 1; which ^= 1) {
@@ -607,11 +608,11 @@ static void row_topk_typed(hipStream_t s, TopkSegments sg, int rows, int k, uint
 #undef TK
 }
 
-void launch_row_topk(hipStream_t s, int dt, const TopkSegments& sg, int rows, int k, uint64_t* top, float* lse, void* scratch) {
+void launch_row_topk(hipStream_t s, int dt, const TopkSegments& sg, int rows, int k, float* top_logp, int* top_id, float* lse, void* scratch) {
   if (rows <= 0) return;
-  if (dt == F32) row_topk_typed<float>(s, sg, rows, k, top, lse, scratch);
-  else if (dt == F16) row_topk_typed<half_t>(s, sg, rows, k, top, lse, scratch);
-  else row_topk_typed<bf16_t>(s, sg, rows, k, top, lse, scratch);
+  if (dt == F32) row_topk_typed<float>(s, sg, rows, k, top_logp, top_id, lse, scratch);
+  else if (dt == F16) row_topk_typed<half_t>(s, sg, rows, k, top_logp, top_id, lse, scratch);
+  else row_topk_typed<bf16_t>(s, sg, rows, k, top_logp, top_id, lse, scratch);
 }
 
 // out[r][col0 + v] = z[r][v] + off[r] - lse[r] in fp32 (test access to the full distribution); off: of row r at r * TOPK_SEGMENTS, or null

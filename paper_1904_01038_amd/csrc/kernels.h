@@ -246,12 +246,11 @@ struct TopkSegments {
   float* off;
   int blk0[TOPK_SEGMENTS + 1];                           // (the launch's: first block of a segment)
 };
-// per row: log-sum-exp and the k (<= 16) largest logits as log-probabilities, best first, ties by ascending id, to top[rows][k] (coherent pinned
-// memory; the value's bits below, the id above: see report in common.h).  Every block of a segment offers
+// per row: log-sum-exp and the k (<= 16) largest logits as log-probabilities, best first, ties by ascending id.  Every block of a segment offers
 // the k largest of its own scores, and off is added to those: scores that differ, and are equal once it is added, are not ties to the block.
 // (scratch: row_topk_scratch_bytes)
 size_t row_topk_scratch_bytes(int rows, const TopkSegments& sg, int k);
-void launch_row_topk(hipStream_t s, int dt, const TopkSegments& sg, int rows, int k, uint64_t* top, float* lse, void* scratch);
+void launch_row_topk(hipStream_t s, int dt, const TopkSegments& sg, int rows, int k, float* top_logp, int* top_id, float* lse, void* scratch);
 void launch_logprob_rows(hipStream_t s, int dt, const TopkSegments& sg, const float* lse, float* out, int r0, int rows);
 
 uint64_t dropout_site_key(uint64_t seed, uint64_t step, int stream, int layer, int sub);

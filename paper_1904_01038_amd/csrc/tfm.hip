@@ -1530,7 +1530,7 @@ struct tfm_decoder {
   // Pinned host memory that the step's kernels read and write in place, with the device's addresses of it
   int* h_src;                                      // tfm_decoder_begin: source ids / pos / offsets, copied to the device
   int *h_in, *d_in;                                // a step's token, parent, index into a tail cluster's table [3 * max_rows]
-  uint64_t *h_out, *d_out;                         // a step's candidates [rows * topk]: log-probability and id
+  float *h_out, *d_out;                            // top_logp [rows * topk] followed by the ids
   // state of the batch being decoded
   int B, beam, rows, t, cur, n_src_max, src_rows;
   uint64_t generation;                             // the context's when the batch began
@@ -1815,7 +1815,7 @@ int tfm_decoder_step(tfm_decoder* D, const int32_t* prev, const int32_t* parent,
     if (parent && (parent[r] < 0 || parent[r] >= R || parent[r] / D->beam != r / D->beam))
       return fail(c, TFM_EINVAL, "parent[%d] = %d is not a row of the same sentence", r, parent[r]);
   }
-  // the previous step's call has waited for its candidates, so the kernels that read the staging buffer are done
+  // the previous step's call synchronised, so the staging buffer is free
   for (int r = 0; r < R; ++r) { D->h_in[r] = prev[r]; D->h_in[R + r] = parent ? parent[r] : r; }
   // Adaptive inputs: a row fed with a token of tail cluster k gets the id -1 - (its row in the compact list of projected vectors);
   // the lists are ordered by cluster, rows ascending
@@ -1875,18 +1875,13 @@ int tfm_decoder_step(tfm_decoder* D, const int32_t* prev, const int32_t* parent,
       gemm(c, 0, R, Vk, w, D->a_u, w, wh(c, ad.E[k]), w, const_cast<void*>(scores.z[k]), scores.ld[k]);          // z = E u
     }
   }
-  const size_t n = (size_t)R * D->topk;                // (the candidates go straight to the host's memory)
+  const size_t n = (size_t)R * D->topk;                // (the values and ids go straight to the host's memory)
   run(c, TFM_PROF_LOSS, 0.0, (double)c->esz * R * V,
-      [&] { launch_row_topk(c->stream, c->dt, scores, R, D->topk, D->d_out, D->lse, D->topk_ws); });
-  const hipError_t enqueued = hipGetLastError();
-  if (enqueued != hipSuccess) hipStreamSynchronize(c->stream);         // (nothing of this step is to reach the next one's words)
-  HIP_TRY(c, enqueued);
-  HIP_TRY(c, hipStreamSynchronize(c->stream));         // (waited for, not watched: see await_report)
-  for (size_t i = 0; i < n; ++i) {
-    const uint32_t lo = (uint32_t)D->h_out[i];
-    std::memcpy(top_logp + i, &lo, 4);
-    top_id[i] = (int32_t)(D->h_out[i] >> 32);
-  }
+      [&] { launch_row_topk(c->stream, c->dt, scores, R, D->topk, D->d_out, (int*)(D->d_out + n), D->lse, D->topk_ws); });
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  HIP_TRY(c, hipGetLastError());
+  std::memcpy(top_logp, D->h_out, n * 4);
+  std::memcpy(top_id, D->h_out + n, n * 4);
   D->t += 1;
   return TFM_OK;
 }
