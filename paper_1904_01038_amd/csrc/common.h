@@ -29,14 +29,6 @@ template <> __device__ __forceinline__ float from_f<float>(float v) { return v; 
 template <> __device__ __forceinline__ half_t from_f<half_t>(float v) { return (half_t)v; }
 template <> __device__ __forceinline__ bf16_t from_f<bf16_t>(float v) { bf16_t r; r.x = f_to_bf16_bits(v); return r; }
 
-// ---- results for the host ------------------------------------------------------------------------------------------------------
-// A kernel leaves them in coherent pinned memory, one 8-byte store each that is either there or not, so that a host that has filled
-// the words with REPORT_EMPTY beforehand sees when they have arrived (read_state in tfm.hip).  Every word is written once.
-constexpr uint64_t REPORT_EMPTY = ~0ull;
-__device__ __forceinline__ void report(uint64_t* to, uint32_t lo, uint32_t hi) {
-  __hip_atomic_store(to, (uint64_t)lo | (uint64_t)hi << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // ---- vectors of VEC elements moved with one memory instruction ------------------------------------------------------
 template <typename T, int VEC> struct alignas(sizeof(T) * VEC) Pack { T v[VEC]; };
 

@@ -30,9 +30,7 @@ struct DevState {
   float bc1, bc2;            // 1 - beta^t
 };
 
-static_assert(sizeof(DevState) % 8 == 0, "whole words");
-constexpr int REPORT_WORDS = sizeof(DevState) / 8;
-void launch_report_state(hipStream_t s, const DevState* st, uint64_t* to);           // to coherent pinned memory, when the stream has come this far
+void launch_store_state(hipStream_t s, const DevState* st, DevState* to);   // to: coherent pinned memory
 
 // Rows of a product that are LayerNorm(x + y): s = x + y (y in the compute dtype, or null; or, with splits > 0, bias + the sum of
 // `splits` fp32 slices partial[s][rows][d]), n = gamma * (s - mean) / sqrt(var + 1e-5) + beta; everything [rows, d], contiguous.

@@ -293,15 +293,14 @@ void launch_scaler_update(hipStream_t s, DevState* st, long long ntokens, float 
   hipLaunchKernelGGL(scaler_update_kernel, dim3(1), dim3(64), 0, s, st, ntokens, clip_norm, beta1, beta2, scale_window, min_scale, dynamic, accumulated);
 }
 
-// The whole state to the host, once everything before it on the stream is done (to: REPORT_WORDS words, see report in common.h)
-__global__ __launch_bounds__(64) void report_state_kernel(const DevState* __restrict__ st, uint64_t* __restrict__ to) {
-  static_assert(REPORT_WORDS <= 64, "a lane per word");
-  if (threadIdx.x >= REPORT_WORDS) return;
-  const uint2 w = reinterpret_cast<const uint2*>(st)[threadIdx.x];
-  report(to + threadIdx.x, w.x, w.y);
+// The whole state to the host's memory
+__global__ __launch_bounds__(64) void store_state_kernel(const DevState* __restrict__ st, DevState* __restrict__ to) {
+  constexpr int WORDS = sizeof(DevState) / 4;
+  static_assert(sizeof(DevState) % 4 == 0 && WORDS <= 64, "a lane per word");
+  if (threadIdx.x < WORDS) reinterpret_cast<uint32_t*>(to)[threadIdx.x] = reinterpret_cast<const uint32_t*>(st)[threadIdx.x];
 }
-void launch_report_state(hipStream_t s, const DevState* st, uint64_t* to) {
-  hipLaunchKernelGGL(report_state_kernel, dim3(1), dim3(64), 0, s, st, to);
+void launch_store_state(hipStream_t s, const DevState* st, DevState* to) {
+  hipLaunchKernelGGL(store_state_kernel, dim3(1), dim3(64), 0, s, st, to);
 }
 
 // ---- Adam -------------------------------------------------------------------------------------------------------------------

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -73,7 +72,7 @@ struct Arena {
 
 constexpr int STAGE_SLOTS = 4;
 // Pinned memory that kernels read and write in place, call after call: coherence is asked for, the default follows HIP_HOST_COHERENT.
-constexpr unsigned REPORT_MEMORY = hipHostMallocCoherent | hipHostMallocMapped;
+constexpr unsigned IN_PLACE_MEMORY = hipHostMallocCoherent | hipHostMallocMapped;
 constexpr double BESIDE_MIN = 2.5e9;               // rows (of both sides) x width^2 from which a sub-batch uses the second stream, see tfm_ctx::beside
 
 // Adaptive input embeddings / adaptive softmax (language model).  Cluster 0 is the head, clusters 1..n the tails.
@@ -170,7 +169,7 @@ struct tfm_ctx {
   size_t int_block_ints;
   Adaptive ad;
   std::vector<std::pair<int, int>> ad_pairs;
-  uint64_t *h_state = nullptr, *d_state = nullptr;  // pinned: the device state as last read (read_state), and the device's address of it
+  DevState *h_state = nullptr, *d_state = nullptr;  // pinned: the device state as last read (read_state), and the device's address of it
   // host staging
   int* stage[STAGE_SLOTS];
   hipEvent_t stage_ev[STAGE_SLOTS];
@@ -495,30 +494,15 @@ hipEvent_t mark(tfm_ctx* c, hipStream_t on) {
 }
 // what has been enqueued on `from` so far happens before what is enqueued on `to` from now on
 inline void order(tfm_ctx* c, hipStream_t from, hipStream_t to) { hipStreamWaitEvent(to, mark(c, from), 0); }
-// Waits for the `n` words that a kernel of the stream's reports (see common.h).  They are there a microsecond or two after they are
-// stored; hipStreamSynchronize came back 20 to 60 us later.  (Not for decoding steps: 52 to 120 launches a step whose records the runtime
-// then releases in stalls instead of at the wait; generation of 24 rows 29.4 -> 30.8 ms on some hosts, on none faster beyond the
-// spread of its processes.)  What takes longer than
-// WATCH_MS is waited for by the runtime, which also brings up an error on the device.
-constexpr int WATCH_MS = 10;
-hipError_t await_report(hipStream_t s, const uint64_t* words, size_t n) {
-  const auto begin = std::chrono::steady_clock::now();
-  unsigned looks = 0;
-  for (size_t i = 0; i < n; ++i)
-    while (__atomic_load_n(words + i, __ATOMIC_ACQUIRE) == REPORT_EMPTY) {
-      if ((++looks & 1023) == 0 && std::chrono::steady_clock::now() - begin > std::chrono::milliseconds(WATCH_MS)) return hipStreamSynchronize(s);
-      __asm__ volatile("pause");
-    }
-  return hipSuccess;
-}
-// The device state after everything that is on the context's stream
+// The device state after everything that is on the context's stream, which is idle afterwards: the caller may go on with the workspace from
+// any other stream.  (A kernel stores the state where the host reads it: with a copy to pageable memory, a transfer and a wait more, the tiny step took
+// 316 us instead of 288, one of 13 sentences 3.09 ms instead of 3.05.)
 hipError_t read_state(tfm_ctx* c, DevState* h) {
-  std::fill_n(c->h_state, REPORT_WORDS, REPORT_EMPTY);
-  launch_report_state(c->stream, c->st, c->d_state);
+  launch_store_state(c->stream, c->st, c->d_state);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = await_report(c->stream, c->h_state, REPORT_WORDS);
-  else hipStreamSynchronize(c->stream);
-  if (e == hipSuccess) std::memcpy(h, c->h_state, sizeof(*h));
+  const hipError_t waited = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) e = waited;
+  if (e == hipSuccess) *h = *c->h_state;
   return e;
 }
 inline hipStream_t wstream(tfm_ctx* c) { return c->beside ? c->side : c->stream; }
@@ -718,9 +702,9 @@ int tfm_create(const tfm_config* cfg, void* ws, size_t bytes, void* hip_stream, 
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->stage_ev[i], hipEventDisableTiming);
     if (e != hipSuccess) { fail(nullptr, TFM_EHIP, "staging buffers: %s", hipGetErrorString(e)); return cleanup(TFM_EHIP); }
   }
-  e = hipHostMalloc((void**)&c->h_state, REPORT_WORDS * 8, REPORT_MEMORY);
+  e = hipHostMalloc((void**)&c->h_state, sizeof(DevState), IN_PLACE_MEMORY);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&c->d_state, c->h_state, 0);
-  if (e != hipSuccess) { fail(nullptr, TFM_EHIP, "report buffer: %s", hipGetErrorString(e)); return cleanup(TFM_EHIP); }
+  if (e != hipSuccess) { fail(nullptr, TFM_EHIP, "state buffer: %s", hipGetErrorString(e)); return cleanup(TFM_EHIP); }
   *out = c;
   return TFM_OK;
 }
@@ -1718,8 +1702,8 @@ int tfm_decoder_create(tfm_ctx* c, void* ws, size_t bytes, int32_t max_rows, int
   if (bytes < need) { delete D; return fail(c, TFM_ENOMEM, "decoder workspace has %zu bytes, %zu needed", bytes, need); }
   decoder_carve(D, (char*)ws);
   hipError_t e = hipHostMalloc((void**)&D->h_src, (2 * (size_t)c->cfg.max_tokens + c->cfg.max_sentences + 1) * 4, hipHostMallocDefault);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_in, 3 * (size_t)max_rows * 4, REPORT_MEMORY);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_out, (size_t)max_rows * topk * 8, REPORT_MEMORY);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_in, 3 * (size_t)max_rows * 4, IN_PLACE_MEMORY);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&D->h_out, (size_t)max_rows * topk * 8, IN_PLACE_MEMORY);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&D->d_in, D->h_in, 0);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&D->d_out, D->h_out, 0);
   if (e != hipSuccess) {

@@ -2,7 +2,7 @@
 import numpy as np
 import pytest
 
-from synth import ModelShape, PRESETS, make_batches
+from synth import ModelShape, PRESETS, init_params, make_batches
 from tests.gpu_util import make_pair, max_rel, cosine, step_both, check_params_after_update
 from tests.test_oracle_model import small_batch
 
@@ -170,6 +170,37 @@ def test_padding_invariance_and_determinism():
     assert r1["loss_sum"] == r2["loss_sum"]
     for k in g1:
         assert np.array_equal(g1[k], g2[k]), k
+
+
+@pytest.mark.parametrize("d,sentences", [(64, 3), (1024, 40)])
+def test_calls_with_results_leave_the_stream_idle(d, sentences):
+    """A call that returns results has waited for its stream: the runtime knows that it is idle, and the parameters in the caller's
+    workspace can be read on any other stream.  Few rows, all on one stream, and as many as use the second one."""
+    import torch
+    import paper_1904_01038_amd as T
+    shape = ModelShape(1, 1, d, d // 64, 4 * d, 264)
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    ctx = T.Tfm(T.make_config(shape, precision=T.FP16, max_sentences=sentences, max_len=64, max_tokens=64 * sentences, init_loss_scale=1.0), stream=stream)
+    ctx.set_params(init_params(shape, 1))
+    # the fp32 parameters come first in the workspace, the embedding first of them
+    n = shape.vocab * d
+    begin = -ctx.workspace.data_ptr() % 256
+    embed = ctx.workspace[begin:begin + 4 * n].view(torch.float32)
+    rng = np.random.default_rng(0)
+    tokens, lens = rng.integers(4, shape.vocab, (sentences, 64)).astype(np.int32), np.full(sentences, 64, np.int32)
+    for window in range(3):
+        ctx.train_step(tokens, tokens, lens, lens)
+        assert stream.query()
+        ctx.train_step(tokens, tokens, lens, lens, sync=False)
+        ctx.train_step(tokens, tokens, lens, lens)
+        assert stream.query()
+        assert ctx.apply_update(1e-4)["skipped"] == 0
+        assert stream.query()
+        with torch.cuda.stream(other):
+            seen = embed.clone()
+        other.synchronize()
+        assert np.array_equal(seen.cpu().numpy().reshape(shape.vocab, d), ctx.get_params()["embed"])
+    ctx.close()
 
 
 def test_bad_arguments_are_rejected_without_side_effects():
