@@ -265,6 +265,17 @@ __global__ __launch_bounds__(64 * LNB_WAVES) void layernorm_bwd_kernel(
 // (storing a lane's 8 values side by side would be an 8-way conflict, 16 wavefronts deep).  d must be a multiple of 512.
 __host__ __device__ __forceinline__ int ln_slot_column(int p) { return ((p & 63) + 64 * (p >> 9)) * 8 + ((p >> 6) & 7); }
 
+// What is done with a value stays behind this place, and so do the loads of everything made opaque ahead of it.  (A barrier for the scheduler comes late: the
+// additions of bf16 rows, made of integer shifts, had moved up between the loads by then, see layernorm_bwd_row_kernel.)
+template <typename P> __device__ __forceinline__ void opaque(P& x) {
+  typedef uint32_t words __attribute__((ext_vector_type(4)));
+  words w[sizeof(P) / 16];
+  __builtin_memcpy(w, &x, sizeof(P));
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(P) / 16); ++i) asm volatile("" : "+v"(w[i]));
+  __builtin_memcpy(&x, w, sizeof(P));
+}
+
 // The same computation when every row can have a wavefront of its own: WAVES of them per block (see lnr_waves), one row each, no loop.  Nothing is
 // accumulated across rows, so the three per-column
 // quantities go from the row's registers straight into the block's LDS reduction, the register footprint stays below
@@ -286,7 +297,8 @@ __global__ __launch_bounds__(64 * WAVES) void layernorm_bwd_row_kernel(
 #pragma unroll
     for (int i = 0; i < LN_VEC; ++i) a[c][i] = xh[c][i] = o[c][i] = 0.f;
   if (live) {
-    // all of the row's operands in one trip to memory, also what is only added at the end
+    // The row's operands in one trip to memory.  (A part of `add`, or all of it, the compiler asks for behind the sums, in the branch that reads it, but in
+    // the instances with opaque operands.)
     const float mu = mean[row], rs = rstd[row];
     Pack<T, LN_VEC> ar[NCH], br[NCH], gr[NCH], tr[NCH];
     float4 sl[NCH][MAXS > 0 ? MAXS : 1][2];
@@ -305,6 +317,17 @@ __global__ __launch_bounds__(64 * WAVES) void layernorm_bwd_row_kernel(
       gr[c] = *reinterpret_cast<const Pack<T, LN_VEC>*>(gamma + col);
     }
     __builtin_amdgcn_sched_barrier(0);
+    // bf16 rows with slices otherwise come in up to 20 groups of loads, each waited for before the next.  us without / with, and with an `add` (128 x
+    // 1024, 8 slices 6.3/5.8 and 6.6/5.9; 256 x 1024, 4 slices 5.2/5.0 and 5.5/5.2; 290 x 1024, 3 slices 5.2/5.0 and 5.5/5.1; 512 columns equal).  At 1536
+    // columns the groups are the better order: 64 rows, 8 slices 7.3/7.7 and 7.7/7.9, 192 rows, 3 slices 6.2/6.4 and 6.6/6.6.
+    if constexpr (MAXS > 0 && NCH <= 2 && std::is_same<T, bf16_t>::value) {
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        opaque(ar[c]); opaque(br[c]); opaque(gr[c]); opaque(tr[c]);
+#pragma unroll
+        for (int k = 0; k < MAXS; ++k) { opaque(sl[c][k][0]); opaque(sl[c][k][1]); }
+      }
+    }
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {

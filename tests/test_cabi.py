@@ -126,3 +126,14 @@ def test_masks_of_a_product_are_fetched_together():
     for name, body in kernels:
         runs = [len(re.findall("global_load_dwordx4", part)) for part in body.split("global_store")]
         assert max(runs) >= 12, (name, max(runs))
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_layernorm_backward_fetches_a_row_with_its_slices_together():
+    """512 or 1024 columns in 2-byte types: the row's operands and slices (2 x 16 bytes each, `add` apart) are asked for ahead of the first wait.  (In bf16
+    they came in up to 20 groups of loads.)"""
+    kernels = re.findall(r"^\S*layernorm_bwd_row_kernelI(\S*?)Li([12])ELi4ELi([248])EEE\S*:(.*?)s_endpgm", assembly("norm.hip"), flags=re.S | re.M)
+    assert len(kernels) == 12
+    for dtype, chunks, slices, body in kernels:
+        ahead = body.split("s_waitcnt vmcnt", 1)[0]
+        assert len(re.findall("global_load_dwordx4", ahead)) >= int(chunks) * (3 + 2 * int(slices)), (dtype, chunks, slices)
