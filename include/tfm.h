@@ -244,6 +244,17 @@ int tfm_op_attention_bwd(int32_t dtype, const void* q, int32_t ldq, const void* 
                          int32_t max_lq, int32_t max_lk, int32_t total_q, int32_t total_k, int32_t causal,
                          uint64_t drop_key, float drop_p, const int32_t* groups, int32_t n_groups, void* stream);
 
+/* Attention of a decoding step: one query a row, head h at columns h*dh..(h+1)*dh of q and o [rows, ldq / ldo].  Keys and values
+ * are rows of `row_stride` elements of k and v.  Over the history (src_off NULL): row r attends to positions 0..t, position s
+ * being row anc[r * max_steps + s] * max_steps + s of k and v, which have rows * max_steps rows; anc: device int32
+ * [rows, max_steps].  Over the source (anc NULL; t and max_steps are not looked at): row r attends to rows
+ * src_off[r / beam]..src_off[r / beam + 1] of k and v, at least 1 and at most n_max of them; src_off: device int32
+ * [rows / beam + 1].  beam divides rows.  Pointers 16-byte aligned, dh and row strides multiples of 8, n_max (t + 1) at most 4096, and fewer than
+ * 2^31 elements in rows * max_steps (src_rows, for the source) rows of k, else TFM_EINVAL. */
+int tfm_op_decode_attention(int32_t dtype, const void* q, int32_t ldq, const void* k, const void* v, int32_t row_stride,
+                            const int32_t* anc, int32_t max_steps, int32_t t, const int32_t* src_off, int32_t src_rows,
+                            int32_t n_max, int32_t beam, int32_t rows, int32_t H, int32_t dh, void* o, int32_t ldo, void* stream);
+
 /* s = x + dropout(y) (y may be NULL: s = x), n = gamma * (s - mean)/sqrt(var + 1e-5) + beta.  [rows, d], contiguous.
  * s_out may be NULL.  mean, rstd: device fp32 [rows].  gamma/beta in `dtype`.  dropout: keep bits from (key, p). */
 int tfm_op_residual_layernorm_fwd(int32_t dtype, const void* x, const void* y, const void* gamma, const void* beta,

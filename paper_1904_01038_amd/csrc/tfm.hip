@@ -1962,6 +1962,24 @@ int tfm_op_attention_bwd(int32_t dtype, const void* q, int32_t ldq, const void* 
   return op_done();
 }
 
+int tfm_op_decode_attention(int32_t dtype, const void* q, int32_t ldq, const void* k, const void* v, int32_t row_stride, const int32_t* anc,
+                            int32_t max_steps, int32_t t, const int32_t* src_off, int32_t src_rows, int32_t n_max, int32_t beam, int32_t rows,
+                            int32_t H, int32_t dh, void* o, int32_t ldo, void* stream) {
+  if (dtype < 0 || dtype > 2 || !q || !k || !v || !o || (anc == nullptr) == (src_off == nullptr)) return TFM_EINVAL;
+  if (rows < 1 || beam < 1 || rows % beam || H < 1 || H > 65535 || dh < 8 || dh > 128 || dh % 8) return TFM_EINVAL;
+  if ((int64_t)H * dh > std::min(std::min(ldq, ldo), row_stride) || (ldq | ldo | row_stride) % 8) return TFM_EINVAL;
+  if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return TFM_EINVAL;
+  if (anc && (t < 0 || t >= max_steps)) return TFM_EINVAL;
+  const int positions = anc ? t + 1 : n_max;
+  if (positions < 1 || positions > 4096 || (!anc && src_rows < 1)) return TFM_EINVAL;
+  if ((double)(anc ? (double)rows * max_steps : (double)src_rows) * row_stride >= 2147483648.0) return TFM_EINVAL;
+  DecodeAttnArgs a{};
+  a.dt = dtype; a.q = q; a.ldq = ldq; a.k = k; a.v = v; a.row_stride = row_stride; a.o = o; a.ldo = ldo; a.anc = anc; a.src_off = src_off;
+  a.rows = rows; a.H = H; a.dh = dh; a.beam = beam; a.t = t; a.max_steps = max_steps; a.n_max = positions;
+  launch_decode_attention((hipStream_t)stream, a);
+  return op_done();
+}
+
 int tfm_op_residual_layernorm_fwd(int32_t dtype, const void* x, const void* y, const void* gamma, const void* beta, void* s_out,
                                   void* n_out, float* mean, float* rstd, int32_t rows, int32_t d, uint64_t drop_key, float p,
                                   void* stream) {

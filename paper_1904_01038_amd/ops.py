@@ -71,6 +71,13 @@ def attention_bwd(q, k, v, o, d_o, lse, dq, dk, dv, q_off, k_off, H, dh, max_lq,
            "tfm_op_attention_bwd")
 
 
+def decode_attention(q, k, v, o, H, dh, beam=1, anc=None, t=0, src_off=None, n_max=0):
+    """k, v: rows of equal stride, [rows * anc.shape[1], ...] caches with anc (history), or the packed source rows with src_off."""
+    _check(lib().tfm_op_decode_attention(_dt(q), _p(q), q.stride(0), _p(k), _p(v), k.stride(0), _p(anc), 0 if anc is None else anc.shape[1], t,
+                                         _p(src_off), k.shape[0], n_max, beam, q.shape[0], H, dh, _p(o), o.stride(0), _stream()),
+           "tfm_op_decode_attention")
+
+
 def residual_layernorm_fwd(x, y, gamma, beta, s_out, n_out, mean, rstd, key=0, p=0.0):
     rows, d = x.shape
     _check(lib().tfm_op_residual_layernorm_fwd(_dt(x), _p(x), _p(y), _p(gamma), _p(beta), _p(s_out), _p(n_out),
