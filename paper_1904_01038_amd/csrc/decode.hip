@@ -140,14 +140,20 @@ __global__ __launch_bounds__(64) void decode_attention_kernel(DecodeAttnArgs p) 
 // The beams of a sentence are the wavefronts of one block: they read the same source positions (and mostly the same history),
 // which then come into one L1 and one L2 once, where blocks of one row each were dealt out to different XCDs.
 //
-// Chunks of 64 positions hold 132 registers (3072 wavefronts on the chip at once), chunks of 32 hold 92 (5120): a trip less for
-// 33-64 and 97-128 positions, against half the work for the others.  us with chunks of 64 / of 32, fp16, 16 heads, 4 beams, for
-// histories of 16, 32, 48, 64, 80 and 112 positions, and sources of 38-45:
-//     64 wavefronts  2.9/2.5  3.0/2.7  3.2/3.4  3.4/3.6   4.5/ 4.3   4.8/ 5.2   3.0/3.0
-//   1024             3.0/2.7  3.2/2.8  3.7/4.1  4.0/4.4   5.5/ 5.4   5.9/ 6.6   3.1/3.1
-//   2048             3.8/3.3  4.5/3.9  4.8/5.1  5.2/5.5   7.3/ 6.4   8.0/ 7.6   4.4/4.3
-//   3072             5.0/4.0  5.4/4.6  5.8/6.4  6.4/6.6   9.3/ 8.2  10.7/10.9   5.4/5.4
-//   4096             6.2/4.5  7.0/5.2  7.8/7.2  9.3/8.0  14.4/10.6  16.8/14.0   6.2/6.5
+// Chunks of 64 positions hold 132 registers over the history (3072 wavefronts on the chip at once) and 116-123 over the source (4096), chunks of 32
+// 92 (5120) and 70-78 (6144): a trip less for 33-64 and 97-128 positions, against half the work for the others.  us with chunks of 64 / of 32, fp16, 16 heads, 4 beams, for
+// histories of 16, 32, 48, 64, 80 and 112 positions
+//     64 wavefronts  2.9/2.5  3.0/2.7  3.2/3.4  3.4/3.6   4.5/ 4.3   4.8/ 5.2
+//   1024             3.0/2.7  3.2/2.8  3.7/4.1  4.0/4.4   5.5/ 5.4   5.9/ 6.6
+//   2048             3.8/3.3  4.5/3.9  4.8/5.1  5.2/5.5   7.3/ 6.4   8.0/ 7.6
+//   3072             5.0/4.0  5.4/4.6  5.8/6.4  6.4/6.6   9.3/ 8.2  10.7/10.9
+//   4096             6.2/4.5  7.0/5.2  7.8/7.2  9.3/8.0  14.4/10.6  16.8/14.0
+// and for sources, whose operands change from launch to launch (at least 4.2 us a launch from this host), of up to 32, 40, 48, 64, 80 and 112 positions
+//   1024             4.2/4.1  4.2/4.0  4.1/4.2  4.2/4.2   4.8/ 4.7   5.1/ 5.3
+//   2048             4.4/4.2  4.6/4.7  4.7/4.8  5.2/5.1   6.5/ 5.8   7.1/ 6.9
+//   3072             5.1/4.5  5.4/5.5  5.7/5.7  6.2/6.2   8.1/ 7.3   9.7/ 9.3
+//   4096             5.9/5.0  6.3/6.5  6.6/6.8  7.2/7.4  10.4/ 9.6  13.1/12.9
+//   4288                      7.5/7.2  7.9/7.4  8.6/8.2
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -311,8 +317,9 @@ void launch_decode_attention(hipStream_t s, const DecodeAttnArgs& a) {
     const int w = a.beam <= DEC_ATT_WAVES ? a.beam : 1;  // (rows = sentences * beam)
     grid = dim3(a.rows / w, a.H);
     block = dim3(64 * w);
-    const int halves = (a.n_max + 31) / 32, waves = a.rows * a.H;              // (the line: see the table above)
-    const bool all = halves == 2 ? waves <= 3072 : halves > 3 && waves < 2048;
+    // (the lines: see the table above.  33-64 positions of the history are faster in one chunk up to 3072 wavefronts, of the source up to 4096)
+    const int halves = (a.n_max + 31) / 32, waves = a.rows * a.H;
+    const bool all = halves == 2 ? waves <= (a.anc ? 3072 : 4096) : halves > 3 && waves < 2048;
 #define DA64(KERNEL, T)                                                                                                      \
   do { if (all) hipLaunchKernelGGL((KERNEL<T, 4>), grid, block, 0, s, a); else hipLaunchKernelGGL((KERNEL<T, 2>), grid, block, 0, s, a); } while (0)
     if (a.dt == F16) { if (a.anc) DA64(decode_attention64_kernel, half_t); else DA64(decode_source_attention64_kernel, half_t); }

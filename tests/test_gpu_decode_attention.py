@@ -70,10 +70,10 @@ def test_scores_are_formed_in_32_bits(prec, over, scale):
     assert _check(*on_gpu, beam, places, range(rows), prec) > 1e-3
 
 
-# 64, 1020, 2048, 2052, 3072 and 4288 wavefronts: on either side of the lines from which chunks of 32 positions are taken instead of 64
+# 64, 1020, 2048, 2052, 3072, 4096 and 4288 wavefronts: on either side of the lines from which chunks of 32 positions are taken instead of 64
 @pytest.mark.parametrize("prec", ["fp16", "bf16"])
 @pytest.mark.parametrize("over", ["history", "source"])
-@pytest.mark.parametrize("rows,H,beam", [(16, 4, 4), (255, 4, 5), (512, 4, 1), (513, 4, 9), (192, 16, 4), (268, 16, 4)])
+@pytest.mark.parametrize("rows,H,beam", [(16, 4, 4), (255, 4, 5), (512, 4, 1), (513, 4, 9), (192, 16, 4), (256, 16, 4), (268, 16, 4)])
 def test_chunks_of_positions_for_all_numbers_of_wavefronts(prec, over, rows, H, beam):
     import torch
     rng, gen = np.random.default_rng(rows), torch.Generator(device="cuda").manual_seed(rows)
