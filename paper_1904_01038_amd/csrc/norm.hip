@@ -104,6 +104,66 @@ __global__ __launch_bounds__(64 * WAVES) void layernorm_fwd_row_kernel(
   }
 }
 
+// The same with y in the compute dtype, a chunk at a time and gamma and beta behind the statistics: faster for the rows of ln_fwd_by_chunks.
+template <typename T, int NCH>
+__global__ __launch_bounds__(256) void layernorm_fwd_chunks_kernel(
+    const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ gamma, const T* __restrict__ beta,
+    T* __restrict__ s_out, T* __restrict__ n_out, float* __restrict__ mean, float* __restrict__ rstd, int rows, int d,
+    uint64_t key, uint32_t thr, float inv_keep) {
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const size_t base = (size_t)row * d;
+  float v[NCH][LN_VEC];
+  float sum = 0.f;
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    const int col = (lane + 64 * c) * LN_VEC;
+    if (col < d) {
+      load_f<T, LN_VEC>(x + base + col, v[c]);
+      if (y) {
+        float t[LN_VEC];
+        load_f<T, LN_VEC>(y + base + col, t);
+        if (thr) drop_apply<LN_VEC>(t, key, base + col, thr, inv_keep);
+#pragma unroll
+        for (int i = 0; i < LN_VEC; ++i) v[c][i] += t[i];
+      }
+      if (s_out) {
+        store_f<T, LN_VEC>(s_out + base + col, v[c]);
+        // the backward pass reads the stored (rounded) sum, so normalise exactly that
+#pragma unroll
+        for (int i = 0; i < LN_VEC; ++i) v[c][i] = to_f<T>(from_f<T>(v[c][i]));
+      }
+#pragma unroll
+      for (int i = 0; i < LN_VEC; ++i) sum += v[c][i];
+    }
+  }
+  const float mu = wave_sum(sum) / (float)d;
+  float sq = 0.f;
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    const int col = (lane + 64 * c) * LN_VEC;
+    if (col < d) {
+#pragma unroll
+      for (int i = 0; i < LN_VEC; ++i) { const float t = v[c][i] - mu; sq += t * t; }
+    }
+  }
+  const float rs = rsqrtf(wave_sum(sq) / (float)d + LN_EPS);
+  if (mean && lane == 0) { mean[row] = mu; rstd[row] = rs; }
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    const int col = (lane + 64 * c) * LN_VEC;
+    if (col < d) {
+      float g[LN_VEC], b[LN_VEC], o[LN_VEC];
+      load_f<T, LN_VEC>(gamma + col, g);
+      load_f<T, LN_VEC>(beta + col, b);
+#pragma unroll
+      for (int i = 0; i < LN_VEC; ++i) o[i] = g[i] * ((v[c][i] - mu) * rs) + b[i];
+      store_f<T, LN_VEC>(n_out + base + col, o);
+    }
+  }
+}
+
 template <typename T, int MAXS>
 static void splitk_ln_dispatch(hipStream_t s, const SplitkNorm& q, int rows, int d, uint64_t key, float p) {
   const uint32_t thr = p > 0.f ? drop_threshold(p) : 0u;
@@ -129,8 +189,23 @@ void launch_splitk_layernorm_fwd(hipStream_t s, int dt, const SplitkNorm& q, int
   // (split-K launches exist for the 2-byte types only)
 }
 
+// Some 3 to 4 blocks of 4 rows a compute unit are all there at once, ask for everything at once and then store at once: reads and writes overlap less
+// than where a wavefront works chunk by chunk.  Fewer blocks are bound by the trips to memory, of more the later ones overlap the earlier.  us in one trip /
+// by chunks:
+//   fp16 3000 x 1024  8.4/ 8.5  3264  9.3/ 8.9  4224 10.4/10.3  6000 12.8/12.7  8000 15.0/15.0      bf16 4224 10.4/10.1  6000 12.9/12.7
+//        3000 x 1536 10.7/11.3  3264 12.2/12.0  4224 14.8/13.8  5000 15.2/15.2  6000 17.7/18.3
+//        3000 x 2048 12.9/13.9  3264 15.6/14.8  4224 17.7/17.3  5000 18.7/20.1          up to 768 columns one trip throughout
+//   fp32 2000 x 1024 10.1/10.3  2600 13.4/12.6  3600 16.2/15.6  4000 15.8/15.9  4224 18.1/19.8
+//        1020 x 1536  8.9/ 9.5  2000 13.9/13.7  2600 18.1/16.3  3600 22.9/22.2  4000 23.4/24.0          up to 512 columns equal
+//        1020 x 2048 11.1/12.1  1200 14.6/14.1  2600 23.0/20.9  3600 29.9/28.4  4000 29.2/30.3
+// and without y, where the one trip asks for x twice: 512 columns, 2000 / 4000 rows fp16 3.7/3.6 and 5.1/4.8, fp32 5.0/5.0 and 9.6/9.2; wider rows within 2 %.
+static bool ln_fwd_by_chunks(int dt, int rows, int d, bool y) {
+  if (!y && d <= 512) return true;
+  if (dt == F32) return d > 512 && rows > (d > 1024 ? 1024 : 2048) && rows <= 3840;
+  return d > 768 && rows > 3072 && rows <= (d <= 1024 ? 6144 : 4352);
+}
 template <typename T>
-static void ln_fwd_dispatch(hipStream_t s, const void* x, const void* y, const void* gamma, const void* beta, void* s_out,
+static void ln_fwd_dispatch(hipStream_t s, int dt, const void* x, const void* y, const void* gamma, const void* beta, void* s_out,
                             void* n_out, float* mean, float* rstd, int rows, int d, uint64_t key, float p) {
   constexpr int WAVES = 4;
   const uint32_t thr = (p > 0.f && y) ? drop_threshold(p) : 0u;
@@ -140,17 +215,22 @@ static void ln_fwd_dispatch(hipStream_t s, const void* x, const void* y, const v
   hipLaunchKernelGGL((layernorm_fwd_row_kernel<T, N, 0, WAVES>), dim3((rows + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, s, (const T*)x, (const T*)y, \
                      (const float*)nullptr, 0, (const T*)nullptr, (const T*)gamma, (const T*)beta, (T*)s_out, (T*)n_out, mean, rstd, rows, d, key, \
                      thr, inv_keep)
-  if (nch <= 1) LN_FWD(1); else if (nch == 2) LN_FWD(2); else if (nch == 3) LN_FWD(3); else LN_FWD(4);
+#define LN_FWD_CHUNKS(N)                                                                                                                        \
+  hipLaunchKernelGGL((layernorm_fwd_chunks_kernel<T, N>), dim3((rows + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, s, (const T*)x, (const T*)y, \
+                     (const T*)gamma, (const T*)beta, (T*)s_out, (T*)n_out, mean, rstd, rows, d, key, thr, inv_keep)
+  if (ln_fwd_by_chunks(dt, rows, d, y != nullptr)) { if (nch <= 1) LN_FWD_CHUNKS(1); else if (nch == 2) LN_FWD_CHUNKS(2); else if (nch == 3) LN_FWD_CHUNKS(3); else LN_FWD_CHUNKS(4); }
+  else if (nch <= 1) LN_FWD(1); else if (nch == 2) LN_FWD(2); else if (nch == 3) LN_FWD(3); else LN_FWD(4);
 #undef LN_FWD
+#undef LN_FWD_CHUNKS
 }
 
 void launch_residual_layernorm_fwd(hipStream_t s, int dt, const void* x, const void* y, const void* gamma,
                                    const void* beta, void* s_out, void* n_out, float* mean, float* rstd, int rows,
                                    int d, uint64_t key, float p) {
   if (rows <= 0) return;
-  if (dt == F32) ln_fwd_dispatch<float>(s, x, y, gamma, beta, s_out, n_out, mean, rstd, rows, d, key, p);
-  else if (dt == F16) ln_fwd_dispatch<half_t>(s, x, y, gamma, beta, s_out, n_out, mean, rstd, rows, d, key, p);
-  else ln_fwd_dispatch<bf16_t>(s, x, y, gamma, beta, s_out, n_out, mean, rstd, rows, d, key, p);
+  if (dt == F32) ln_fwd_dispatch<float>(s, dt, x, y, gamma, beta, s_out, n_out, mean, rstd, rows, d, key, p);
+  else if (dt == F16) ln_fwd_dispatch<half_t>(s, dt, x, y, gamma, beta, s_out, n_out, mean, rstd, rows, d, key, p);
+  else ln_fwd_dispatch<bf16_t>(s, dt, x, y, gamma, beta, s_out, n_out, mean, rstd, rows, d, key, p);
 }
 
 // ---- backward -----------------------------------------------------------------------------------------------------------

@@ -77,6 +77,29 @@ def test_layernorm_backward_blocks(prec, shape):
     test_residual_layernorm_forward_and_backward(prec, shape, 0.2)
 
 
+# where the forward kernel that takes a row in one trip and the one that takes it by chunks follow one another
+@pytest.mark.parametrize("prec,rows,d", [("fp16", 3072, 1024), ("fp16", 6144, 776), ("bf16", 3072, 1536), ("bf16", 6144, 1024), ("fp16", 4352, 1536), ("bf16", 4352, 2048),
+                                         ("fp32", 2048, 1024), ("fp32", 3840, 520), ("fp32", 3840, 2048), ("fp32", 1024, 1536)])
+@pytest.mark.parametrize("p", [None, 0.0, 0.2])
+def test_layernorm_forward_kernels_agree(prec, rows, d, p):
+    """A row's results do not depend on how many rows there are beside it, to the bit.  p None: no second operand."""
+    import torch
+    import paper_1904_01038_amd as T
+    dt, gen = {"fp32": torch.float32, "fp16": torch.float16, "bf16": torch.bfloat16}[prec], torch.Generator(device="cuda").manual_seed(d)
+    x, y = (torch.randn(rows + 1, d, device="cuda", generator=gen).to(dt) for _ in range(2))
+    gamma, beta = (torch.randn(d, device="cuda", generator=gen).to(dt) for _ in range(2))
+    results = []
+    for n in (rows, rows + 1):
+        s_out, n_out = (torch.zeros(n, d, dtype=dt, device="cuda") for _ in range(2))
+        mean, rstd = (torch.zeros(n, device="cuda") for _ in range(2))
+        T.ops.residual_layernorm_fwd(x[:n], None if p is None else y[:n], gamma, beta, s_out, n_out, mean, rstd, 7, p or 0.0)
+        results.append([r[:rows] for r in (s_out, n_out, mean, rstd)])
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+    s = results[0][0].double()
+    ref = (s - s.mean(1, keepdim=True)) / (s.var(1, unbiased=False, keepdim=True) + 1e-5).sqrt() * gamma.double() + beta.double()
+    assert float((results[0][1].double() - ref).abs().max()) <= 2 * TOL[prec] * float(ref.abs().max())
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("shape", [(5, 13), (33, 1000), (257, 32768), (3, 40000), (64, 4104)])
 @pytest.mark.parametrize("eps", [0.0, 0.1])
