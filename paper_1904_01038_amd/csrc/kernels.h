@@ -196,6 +196,7 @@ struct AdamArgs {
   float weight_decay;        // L2 form: weight_decay * w joins the unscaled gradient
   const DevState* st;        // if non-null: skip flag, grad_mult, bc1, bc2 come from the device state
   float grad_mult, bc1, bc2;
+  bool beside;               // a piece of an update that runs beside the kernels of a forward pass
 };
 void launch_adam(hipStream_t s, const AdamArgs& a);
 // One-thread kernel: the loss-scale state machine and the Adam step scalars.  accumulated: the window's gradient is the sum that

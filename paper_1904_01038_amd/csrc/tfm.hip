@@ -1472,6 +1472,7 @@ int tfm_apply_update(tfm_ctx* c, float lr, tfm_update_out* out) {
     for (size_t k = 0; k < c->chunks.size(); ++k) {
       const tfm_ctx::Chunk& ch = c->chunks[k];
       AdamArgs b = a;
+      b.beside = true;
       b.w = c->W + ch.off; b.m = c->M + ch.off; b.v = c->V + ch.off; b.n = ch.n;
       b.g = (const char*)a.g + ch.off * gsz;
       b.half_copy = a.half_copy ? (char*)a.half_copy + ch.off * c->esz : nullptr;
