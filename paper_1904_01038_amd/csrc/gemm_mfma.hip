@@ -687,11 +687,13 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 //   192x128      2 x 2       64     3        3000 x 1536 x 4608 NN 55.3, 3000 x 1536 x 8192 89.3 (288 tiles of 128x128 in two rounds: 76.1, 122)
 //   128x128      2 x 2       64     4        4096 x 1024 x 4096 NN 42.7 (44.3), 3264 x 1024 x 1024 11.2 (11.8)
 //    64x128      2 x 2       64     4        3520 x 512 x 1536 NN 11.0 (11.8)
-//    64x64       2 x 2       64     5, 4     280 x 1024 x 3072 NN, K in 3 slices, 10.4 (24 tiles of 128x128: 22.0).  5 slots where a compute unit has one tile:
+//    64x64       2 x 2       64     5, 4     280 x 1024 x 3072 NN, K in 3 slices, 10.4 (24 tiles of 128x128: 22.0).  5 slots for X W^T where a compute unit has one tile:
 //                                            few rows find their weights in memory, and a fourth K-step in flight covers more of that trip.  Two tiles
 //                                            cover each other's.  5 / 4 slots: 290 x 3072 x 1024 (240 tiles) 7.1/7.2, 900 x 512 x 2048 9.3/9.6, 500 x 1024 x
 //                                            1024 6.3/6.6; 290 x 4096 x 1024 (320 tiles) 11.1/10.8, NN 10.0/9.5, 900 x 1536 x 512 7.0/6.7, 3300 x 512 x 512 7.3/7.0;
-//                                            the kernels of a decoder block for 268 rows 71.0 / 73.8 (6 slots 71.0, 7 71.6)
+//                                            the kernels of a decoder block for 268 rows 71.0 / 73.8 (6 slots 71.0, 7 71.6).  Of 119 such products with K = 512-8192
+//                                            4.1 % on average, at most 1.2 % slower; of 101 dY W, which read the weights along their rows, 0.2 % slower, up to
+//                                            2.5: those keep 4
 //   128x128      2 x 2       32     3        A^T B alone, up to 512 tiles, two on a compute unit: 6144 x 1024 x 190 7.6 (one: 10.1), 3072 x 1536 x 2902
 //                                            41.2 (48.2)
 // Wavefronts of 64x64 or more read half of the LDS bytes per flop of 32x32 ones.  Measured and dropped: 256x256 on 4 wavefronts of 128x128 (one per
@@ -784,13 +786,15 @@ static void gemm_mfma_launch(hipStream_t s, const GemmArgs& a, int splits) {
   p.ksteps_per_split = (nk + splits - 1) / splits;
   p.partial = splits > 1 ? (float*)a.splitk_ws : nullptr;
   dim3 grid(p.tiles_total, splits), block(64 * WM * WN);
-  constexpr bool TN_ONLY = BK == 32 && BM == 128;
+  constexpr bool TN_ONLY = BK == 32 && BM == 128, NT_ONLY = STAGES == 5;
   if constexpr (TN_ONLY) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, true, true>), grid, block, 0, s, p);
   else if (a.form == 0) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, false>), grid, block, 0, s, p);
   else if constexpr (BN == BM && BM >= 128) {
     if (a.form == 1) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, true>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, true, true>), grid, block, 0, s, p);
-  } else if (a.form == 1) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, true>), grid, block, 0, s, p);
+  } else if constexpr (!NT_ONLY) {
+    if (a.form == 1) hipLaunchKernelGGL((gemm_mfma_kernel<T, BM, BN, WM, WN, BK, STAGES, AHEAD, false, true>), grid, block, 0, s, p);
+  }
   if (a.deferred_splits) *a.deferred_splits = splits > 1 ? splits : 0;
   if (splits > 1 && !a.deferred_splits) launch_splitk_reduce(s, a.dt, (const float*)a.splitk_ws, splits, a.M, a.N, a.C, a.ldc, a.bias, a.relu, a.residual);
 }
@@ -857,7 +861,7 @@ static void gemm_mfma_dispatch(hipStream_t s, const GemmArgs& a) {
     case T192x128: gemm_mfma_launch<T, 192, 128, 2, 2, 64, 3, 1>(s, a, q.slices); break;
     case T64x128: gemm_mfma_launch<T, 64, 128, 2, 2, 64, 4, 1>(s, a, q.slices); break;
     case T64x64:
-      if (tiles_of(T64x64, a.M, a.N) * q.slices <= 256) gemm_mfma_launch<T, 64, 64, 2, 2, 64, 5, 2>(s, a, q.slices);
+      if (a.form == 0 && tiles_of(T64x64, a.M, a.N) * q.slices <= 256) gemm_mfma_launch<T, 64, 64, 2, 2, 64, 5, 2>(s, a, q.slices);
       else gemm_mfma_launch<T, 64, 64, 2, 2, 64, 4, 2>(s, a, q.slices);
       break;
     case T128x128_PAIRS: gemm_mfma_launch<T, 128, 128, 2, 2, 32, 3, 1>(s, a, q.slices); break;
