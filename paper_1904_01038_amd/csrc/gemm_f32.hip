@@ -25,7 +25,6 @@ struct F32Params {
   const float* bias; int relu; const float* mask; const float* residual;
   uint64_t drop_key; uint32_t drop_thr; float inv_keep, mask_scale;
   float* colsum;                                         // [M] sums of A's columns over K (TN only), or null
-  int quads;                                             // whole aligned quadruples of columns: the epilogue's operands and results 16 bytes at a time
 };
 
 // Rows r0 .. r0 + 31 of an operand, 8 k at a time.  TR: the contraction is the slow index.  VEC: 16-byte loads (K, ld and base allow it).
@@ -53,7 +52,7 @@ struct F32Operand {
 };
 
 // Tile (tm, tn) of 32 WM x 32 WN outputs; WK wavefronts share the contraction of each 32x32 part.
-template <bool ATR, bool BTR, bool VEC, int WM, int WN, int WK>
+template <bool ATR, bool BTR, bool VEC, int WM, int WN, int WK, bool QUADS>
 __device__ __forceinline__ void gemm_f32_tile(const F32Params& p, int tm, int tn) {
   constexpr int NW = WM * WN * WK, U = 4, PITCH = 36;     // (16-byte rows of the box, no bank conflicts in either pass)
   __shared__ __attribute__((aligned(16))) float box[NW][32 * PITCH];
@@ -88,14 +87,14 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Params& p, int tm, int tn
   };
   const int trips = (p.K + 8 * U * WK - 1) / (8 * U * WK);
   fetch(0, a, b);
-  // Where a thread finishes at most one quadruple (4 wavefronts or more share a tile), what the epilogue adds to it is on its way with the operands.
-  // In a trip of its own behind the sums, element by element, it was 0.5 us of a launch: X W^T with a bias 128 x 192 x 64 3.9 us, now 3.3, 128 x 64 x 256
-  // 5.3 and 4.6, 512^3 8.6 and 8.0; dY W with a residual 128 x 64 x 256 4.9 and 4.4 (out of a graph, over 24 sets of operands).
-  constexpr bool ONE = WK >= 4;
+  // QUADS (4 wavefronts or more share a tile, whole aligned quadruples of columns): a thread finishes at most one, and what the epilogue adds to it is on its
+  // way with the operands.  In a trip of its own behind the sums, element by element, it was 0.5 us of a launch: X W^T with a bias 128 x 192 x 64 3.9 us, now
+  // 3.3, 128 x 64 x 256 5.3 and 4.6, 512^3 8.6 and 8.0; dY W with a residual 128 x 64 x 256 4.9 and 4.4 (out of a graph, over 24 sets of operands).
+  // An instance of its own: with the other epilogue in it as well, which lanes beyond N went through, 82 x 132 x 64 3.6, now 3.4.
   const int er = (wk * 64 + lane) >> 3, ec = ((wk * 64 + lane) & 7) * 4;
-  const bool early = ONE && p.quads && wk * 64 + lane < 256 && m0 + er < p.M && n0 + ec < p.N;
   float4 bias4 = {0.f, 0.f, 0.f, 0.f}, mask4 = {1.f, 1.f, 1.f, 1.f}, res4 = {0.f, 0.f, 0.f, 0.f};
-  if (early) {
+  const bool mine = wk * 64 + lane < 256 && m0 + er < p.M && n0 + ec < p.N;
+  if (QUADS && mine) {
     const size_t o = (size_t)(m0 + er) * p.ldc + n0 + ec;
     if (p.bias) bias4 = *reinterpret_cast<const float4*>(p.bias + n0 + ec);
     if (p.mask) mask4 = *reinterpret_cast<const float4*>(p.mask + o);
@@ -122,6 +121,34 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Params& p, int tm, int tn
     p.colsum[m0 + lane] = t;
   }
   // 4 consecutive columns a lane
+  if constexpr (QUADS) {
+    if (!mine) return;
+    const int m = m0 + er, n = n0 + ec;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < WK; ++w) {
+      const float4 x = *reinterpret_cast<const float4*>(&box[wave - wk + w][er * PITCH + ec]);
+      v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+    }
+    const float bv[4] = {bias4.x, bias4.y, bias4.z, bias4.w}, mv[4] = {mask4.x, mask4.y, mask4.z, mask4.w}, rv[4] = {res4.x, res4.y, res4.z, res4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (p.bias) v[e] += bv[e];
+      if (p.relu) v[e] = fmaxf(v[e], 0.f);
+    }
+    if (p.drop_thr) {                                    // (a multiple of 4 columns: the four bits are of one word)
+      const uint64_t word = drop_word(p.drop_key, ((uint64_t)m * p.N + n) >> 2);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = drop_keep(word, e, p.drop_thr) ? v[e] * p.inv_keep : 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (p.mask) v[e] = mv[e] > 0.f ? v[e] * p.mask_scale : 0.f;
+      if (p.residual) v[e] += rv[e];
+    }
+    *reinterpret_cast<float4*>(p.C + (size_t)m * p.ldc + n) = float4{v[0], v[1], v[2], v[3]};
+    return;
+  }
   for (int idx = wk * 64 + lane; idx < 256; idx += 64 * WK) {
     const int r = idx >> 3, c = (idx & 7) * 4, m = m0 + r, n = n0 + c;
     if (m >= p.M) continue;
@@ -130,26 +157,6 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Params& p, int tm, int tn
     for (int w = 0; w < WK; ++w) {
       const float4 x = *reinterpret_cast<const float4*>(&box[wave - wk + w][r * PITCH + c]);
       v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
-    }
-    if (early) {
-      const float bv[4] = {bias4.x, bias4.y, bias4.z, bias4.w}, mv[4] = {mask4.x, mask4.y, mask4.z, mask4.w}, rv[4] = {res4.x, res4.y, res4.z, res4.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (p.bias) v[e] += bv[e];
-        if (p.relu) v[e] = fmaxf(v[e], 0.f);
-      }
-      if (p.drop_thr) {                                  // (a multiple of 4 columns: the four bits are of one word)
-        const uint64_t word = drop_word(p.drop_key, ((uint64_t)m * p.N + n) >> 2);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = drop_keep(word, e, p.drop_thr) ? v[e] * p.inv_keep : 0.f;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (p.mask) v[e] = mv[e] > 0.f ? v[e] * p.mask_scale : 0.f;
-        if (p.residual) v[e] += rv[e];
-      }
-      *reinterpret_cast<float4*>(p.C + (size_t)m * p.ldc + n) = float4{v[0], v[1], v[2], v[3]};
-      continue;
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -168,9 +175,11 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Params& p, int tm, int tn
   }
 }
 
-template <int FORM, bool VEC, int WM, int WN, int WK>
-__global__ __launch_bounds__(64 * WM * WN * WK) void gemm_f32_kernel(F32Params p) {
-  gemm_f32_tile<FORM == 2, FORM != 0, VEC, WM, WN, WK>(p, blockIdx.y, blockIdx.x);
+// (QUADS takes 12 registers.  X W^T with 4 wavefronts is held to the 128 with which 4 blocks share a compute unit: with 132 there were 3, 2000 x 512 x 64 with
+// a bias 8.3 us, now 6.6.  dY W with 8 has 142 and would spill with 128: 1000 x 512 x 300 14.6 us, now 10.2.)
+template <int FORM, bool VEC, int WM, int WN, int WK, bool QUADS>
+__global__ __launch_bounds__(64 * WM * WN * WK, QUADS && FORM == 0 && WK == 4 ? 4 : 1) void gemm_f32_kernel(F32Params p) {
+  gemm_f32_tile<FORM == 2, FORM != 0, VEC, WM, WN, WK, QUADS>(p, blockIdx.y, blockIdx.x);
 }
 
 // Weight gradients C_i = A_i^T B_i with the column sums of A_i, the tiles of many products end to end (see launch_wgrad_grouped)
@@ -178,15 +187,14 @@ struct F32Job { const float *A, *B; float *C, *colsum; int M, N, K, lda, ldb, ld
 struct F32Table { int n; F32Job job[WGRAD_GROUP_MAX]; };
 static_assert(sizeof(F32Table) <= 4096, "kernel argument space");
 
-template <int WM, int WN, int WK>
+template <int WM, int WN, int WK, bool QUADS>
 __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_f32_grouped_kernel(F32Table tab) {
   int i = 0;
   for (int j = 1; j < tab.n; ++j) i = (int)blockIdx.x >= tab.job[j].tile_begin ? j : i;
   const F32Job& g = tab.job[i];
-  const bool quads = g.N % 4 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0;
-  F32Params p{g.M, g.N, g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, nullptr, 0, nullptr, nullptr, 0, 0, 1.f, 1.f, g.colsum, quads};
+  F32Params p{g.M, g.N, g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, nullptr, 0, nullptr, nullptr, 0, 0, 1.f, 1.f, g.colsum};
   const int tile = blockIdx.x - g.tile_begin;
-  gemm_f32_tile<true, true, false, WM, WN, WK>(p, tile / g.tiles_n, tile % g.tiles_n);
+  gemm_f32_tile<true, true, false, WM, WN, WK, QUADS>(p, tile / g.tiles_n, tile % g.tiles_n);
 }
 
 static long tiles32(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 32); }
@@ -199,11 +207,15 @@ static long tiles32(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 3
 // 1024 x 1024 (2016 tiles) 87 and 74 / 78 and 69 / 75 and 74; 8 wavefronts take K = 1000 in 4 trips to memory where 4 take 8, and
 // below K = 256 have no second turn to take.  (16 wavefronts beyond K = 512 spill: 128 x 64 x 1000 dY W 10.6 and 14.8.)
 template <int FORM, bool VEC>
-static void gemm_f32_launch(hipStream_t s, const F32Params& p) {
+static void gemm_f32_launch(hipStream_t s, const F32Params& p, bool quads) {
   const dim3 small((p.N + 31) / 32, (p.M + 31) / 32), large((p.N + 63) / 64, (p.M + 63) / 64);
-  if (tiles32(p.M, p.N) > 1024) hipLaunchKernelGGL((gemm_f32_kernel<FORM, VEC, 2, 2, 1>), large, dim3(256), 0, s, p);
-  else if (p.K > 256) hipLaunchKernelGGL((gemm_f32_kernel<FORM, VEC, 1, 1, 8>), small, dim3(512), 0, s, p);
-  else hipLaunchKernelGGL((gemm_f32_kernel<FORM, VEC, 1, 1, 4>), small, dim3(256), 0, s, p);
+#define F32_SMALL(WK) \
+  do { if (quads) hipLaunchKernelGGL((gemm_f32_kernel<FORM, VEC, 1, 1, WK, true>), small, dim3(64 * WK), 0, s, p); \
+       else hipLaunchKernelGGL((gemm_f32_kernel<FORM, VEC, 1, 1, WK, false>), small, dim3(64 * WK), 0, s, p); } while (0)
+  if (tiles32(p.M, p.N) > 1024) hipLaunchKernelGGL((gemm_f32_kernel<FORM, VEC, 2, 2, 1, false>), large, dim3(256), 0, s, p);
+  else if (p.K > 256) F32_SMALL(8);
+  else F32_SMALL(4);
+#undef F32_SMALL
 }
 
 static bool f32_vec(const GemmArgs& a) {
@@ -226,11 +238,11 @@ void launch_gemm_f32(hipStream_t s, const GemmArgs& a) {
   const bool quads = a.N % 4 == 0 && a.ldc % 4 == 0 && whole(a.C) && whole(a.bias) && whole(a.mask) && whole(a.residual);
   const F32Params p{a.M, a.N, a.K, (const float*)a.A, a.lda, (const float*)a.B, a.ldb, (float*)a.C, a.ldc, (const float*)a.bias, a.relu,
                     (const float*)a.mask, (const float*)a.residual, a.drop_key, a.drop_p > 0.f ? drop_threshold(a.drop_p) : 0u, 1.f / (1.f - a.drop_p),
-                    a.mask_scale, nullptr, quads};
+                    a.mask_scale, nullptr};
   const bool vec = f32_vec(a);
-  if (a.form == 0) { if (vec) gemm_f32_launch<0, true>(s, p); else gemm_f32_launch<0, false>(s, p); }
-  else if (a.form == 1) { if (vec) gemm_f32_launch<1, true>(s, p); else gemm_f32_launch<1, false>(s, p); }
-  else gemm_f32_launch<2, false>(s, p);
+  if (a.form == 0) { if (vec) gemm_f32_launch<0, true>(s, p, quads); else gemm_f32_launch<0, false>(s, p, quads); }
+  else if (a.form == 1) { if (vec) gemm_f32_launch<1, true>(s, p, quads); else gemm_f32_launch<1, false>(s, p, quads); }
+  else gemm_f32_launch<2, false>(s, p, quads);
 }
 
 void launch_wgrad_grouped_f32(hipStream_t s, const WgradJob* jobs, int n) {
@@ -244,15 +256,21 @@ void launch_wgrad_grouped_f32(hipStream_t s, const WgradJob* jobs, int n) {
   const bool large = t32 >= 2048;
   const int edge = large ? 64 : 32;
   int tiles = 0;
+  bool quads = true;
   for (int i = 0; i < n; ++i) {
     const WgradJob& j = jobs[i];
+    quads = quads && j.N % 4 == 0 && j.ldc % 4 == 0 && ((uintptr_t)j.C & 15) == 0;
     tab.job[i] = {(const float*)j.A, (const float*)j.B, (float*)j.C, (float*)j.colsum, j.M, j.N, j.K, j.lda, j.ldb, j.ldc, tiles, (j.N + edge - 1) / edge};
     tiles += tab.job[i].tiles_n * ((j.M + edge - 1) / edge);
   }
   tab.n = n;
-  if (large) hipLaunchKernelGGL((gemm_f32_grouped_kernel<2, 2, 1>), dim3(tiles), dim3(256), 0, s, tab);
-  else if (K > 256) hipLaunchKernelGGL((gemm_f32_grouped_kernel<1, 1, 8>), dim3(tiles), dim3(512), 0, s, tab);
-  else hipLaunchKernelGGL((gemm_f32_grouped_kernel<1, 1, 4>), dim3(tiles), dim3(256), 0, s, tab);
+#define F32_GROUPED(WK) \
+  do { if (quads) hipLaunchKernelGGL((gemm_f32_grouped_kernel<1, 1, WK, true>), dim3(tiles), dim3(64 * WK), 0, s, tab); \
+       else hipLaunchKernelGGL((gemm_f32_grouped_kernel<1, 1, WK, false>), dim3(tiles), dim3(64 * WK), 0, s, tab); } while (0)
+  if (large) hipLaunchKernelGGL((gemm_f32_grouped_kernel<2, 2, 1, false>), dim3(tiles), dim3(256), 0, s, tab);
+  else if (K > 256) F32_GROUPED(8);
+  else F32_GROUPED(4);
+#undef F32_GROUPED
 }
 
 }  // namespace tfm
