@@ -303,6 +303,147 @@ __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_attention64_kernel(
 template <typename T, int U>                             // over the source sentence: no table, positions one behind the other
 __global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_source_attention64_kernel(DecodeAttnArgs p) { decode_attention64<T, U, false>(p); }
 
+// 8 elements of a key against 8 of the query, in 32-bit FMAs.  (v_dot2_f32_f16 truncates what lies far below the larger term and
+// below a fixed floor: 1.6e-5 of the result with subnormal keys, where FMAs are off by 6e-8.)
+template <typename T> __device__ __forceinline__ float dot8_acc(const float (&q)[8], uint4 k, float c) {
+  Pack<T, 8> x;
+  __builtin_memcpy(&x, &k, 16);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) c = fmaf(q[i], to_f<T>(x.v[i]), c);
+  return c;
+}
+// op over the lanes that differ in bits 0, 1 and 2 of their number (a group of 8), and in bits 3, 4 and 5 (across the groups)
+template <typename Op> __device__ __forceinline__ float over_lanes(float v, Op op) {
+  v = op(v, __int_as_float(dpp_move<0xB1, 0xf>(0, __float_as_int(v))));        // quad_perm 1,0,3,2
+  v = op(v, __int_as_float(dpp_move<0x4E, 0xf>(0, __float_as_int(v))));        // quad_perm 2,3,0,1
+  return op(v, __int_as_float(dpp_move<0x141, 0xf>(0, __float_as_int(v))));    // row_half_mirror
+}
+template <typename Op> __device__ __forceinline__ float over_groups(float v, Op op) {
+  auto bits = [&](uint32_t a, uint32_t b) { return __float_as_uint(op(__uint_as_float(a), __uint_as_float(b))); };
+  return __uint_as_float(with_lane_32(with_lane_16(with_lane_8(__float_as_uint(v), bits), bits), bits));
+}
+
+// The same for many wavefronts and many positions, which are bound by keys and values on their way from L2 where the beams of a sentence share them: a
+// load fetches 8 whole rows of 128 bytes, of the keys too, where the kernels above touch the halves of 16.  Lane = (group g = lane / 8, 16-byte piece
+// f = lane % 8): a score is 8 FMAs and 3 lane exchanges.  Chunks of 32 positions, 81 registers.  us above / here, histories of 66, 96 and 128 positions:
+//   104 x 16 heads, 4 beams  6.6/ 6.6   6.9/ 6.8   9.0/ 8.2      110 x 24, 5 beams  9.6/ 9.2  10.7/ 9.5  13.6/11.6
+//   136                      8.3/ 8.0   9.2/ 8.2  11.3/10.1      300 x 24          20.1/19.0  22.4/19.9  27.1/24.1
+//   268                     12.1/11.8  14.1/12.9  17.8/16.0      one beam: 130 x 16 10.6/11.3  12.2/12.9  15.3/15.8
+// and sources of up to 66, 80, 96 and 128:  200 x 16, 4 beams 8.2/7.9  9.2/8.6  10.0/8.8  13.3/11.8;  170 x 24, 5 beams 9.3/9.7  10.5/10.8  11.3/10.8  15.0/14.7.
+// The line is at two chunks and not at 44 positions, where the times cross (200 x 16, history of 40 7.5/7.5, of 64 8.6/7.8): the kernels add in another order, and
+// up to there a sentence has one of them.
+template <typename T>
+__global__ __launch_bounds__(64 * DEC_ATT_WAVES) void decode_long_attention_kernel(DecodeAttnArgs p) {
+  constexpr int U = 4;                                   // chunks of 8 * U positions
+  __shared__ __attribute__((aligned(16))) T sq[DEC_ATT_WAVES][64];
+  constexpr int dh = 64;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 3, f = lane & 7;
+  const int r = blockIdx.x * (blockDim.x >> 6) + wave, h = blockIdx.y;
+  T* qs = sq[wave];
+  int n, base = 0;
+  if (p.anc) n = p.t + 1;
+  else { const int s = r / p.beam; base = p.src_off[s]; n = p.src_off[s + 1] - base; }
+  const T* K = reinterpret_cast<const T*>(p.k) + h * dh;
+  const T* V = reinterpret_cast<const T*>(p.v) + h * dh;
+  // position t of a self-attention step may still be outside the caches: it is read from the new rows, and 16 lanes copy
+  // this head's 128 + 128 bytes into the row's own cache lines for the steps to come (nobody reads them during this launch)
+  const T* knew = nullptr;
+  const T* vnew = nullptr;
+  if (p.anc && p.k_new) {
+    knew = reinterpret_cast<const T*>(p.k_new) + (size_t)r * p.ld_new + h * dh;
+    vnew = reinterpret_cast<const T*>(p.v_new) + (size_t)r * p.ld_new + h * dh;
+  }
+  // Position s is row first[u] * per + s of the caches, s = g, g + 8, ... of the chunk (past the end: the last one, with weight 0).
+  // The choice between the two tables is made once for all U of them: made for each, it put a wait behind every single load.
+  const int per = p.anc ? p.max_steps : 1;
+  int first[U];
+  auto look_up = [&](int s0) {
+    if (p.anc) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) first[u] = p.anc[(size_t)r * p.max_steps + min(s0 + 8 * u + g, n - 1)];
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) first[u] = base;
+    }
+  };
+  look_up(0);
+  uint4 qh;                                              // this lane's piece of the query
+  if (p.q_partial) {                                     // the query arrives as the slices of a split-K product (at most 8)
+    const size_t at = (size_t)r * p.H * dh + h * dh + lane, slice = (size_t)p.rows * p.H * dh;
+    float part[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) part[k] = k < p.q_splits ? p.q_partial[k * slice + at] : 0.f;
+    float qv = part[0];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) qv += part[k];
+    if (p.q_bias) qv += to_f<T>(reinterpret_cast<const T*>(p.q_bias)[h * dh + lane]);
+    qs[lane] = from_f<T>(qv);                            // rounded as the stored projection would be
+    __syncthreads();                                     // (every row of the launch comes this way, or none does)
+    qh = reinterpret_cast<const uint4*>(qs)[f];
+  } else {
+    qh = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(p.q) + (size_t)r * p.ldq + h * dh)[f];
+  }
+  auto add = [](float x, float y) { return x + y; };
+  auto larger = [](float x, float y) { return fmaxf(x, y); };
+  float m = -INFINITY, l = 0.f, acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+  for (int s0 = 0; s0 < n; s0 += 8 * U) {
+    uint4 kv[U], vv[U];
+    int off[U];                                          // (the host checks that they fit)
+#pragma unroll
+    for (int u = 0; u < U; ++u) off[u] = (first[u] * per + min(s0 + 8 * u + g, n - 1)) * p.row_stride;
+#pragma unroll
+    for (int u = 0; u < U; ++u) kv[u] = *reinterpret_cast<const uint4*>(((knew && s0 + 8 * u + g >= p.t) ? knew : K + off[u]) + f * 8);
+#pragma unroll
+    for (int u = 0; u < U; ++u) vv[u] = *reinterpret_cast<const uint4*>(((vnew && s0 + 8 * u + g >= p.t) ? vnew : V + off[u]) + f * 8);
+    if (s0 + 8 * U < n) look_up(s0 + 8 * U);             // the next chunk's rows
+    // The query is looked at only now, when the chunk's loads are on their way (its conversion ahead of the loop would wait for it
+    // first: 0.35 us of 4.7), and its values are opaque: seen as halves, the FMAs would be paired into v_dot2_f32_f16.
+    asm volatile("" : "+v"(qh.x), "+v"(qh.y), "+v"(qh.z), "+v"(qh.w));
+    float q[8], sc[U], mn = m;
+    {
+      Pack<T, 8> x;
+      __builtin_memcpy(&x, &qh, 16);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        q[i] = to_f<T>(x.v[i]);
+        asm("" : "+v"(q[i]));
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sc[u] = over_lanes(dot8_acc<T>(q, kv[u], 0.f), add);
+      sc[u] = s0 + 8 * u + g < n ? sc[u] * 0.125f : -INFINITY;
+      mn = fmaxf(mn, sc[u]);
+    }
+    mn = over_groups(mn, larger);
+    const float top = mn > -INFINITY ? mn : 0.f;         // scores of -infinity alone, so far: weight 0, as beside others
+    const float keep = __expf(m - top);
+    m = mn;
+    l *= keep;                                           // (l: this group's share; the groups are added up at the end)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] *= keep;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float w = __expf(sc[u] - top);
+      l += w;
+      Pack<T, 8> x;
+      __builtin_memcpy(&x, &vv[u], 16);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] += w * to_f<T>(x.v[i]);
+    }
+  }
+  const float inv = 1.f / over_groups(l, add);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = over_groups(acc[i], add) * inv;
+  if (g == 0) store_f<T, 8>(reinterpret_cast<T*>(p.o) + (size_t)r * p.ldo + h * dh + f * 8, acc);
+  if (knew && g < 2) {
+    T* cache = const_cast<T*>(g == 0 ? K : V) + ((size_t)r * p.max_steps + p.t) * p.row_stride + f * 8;
+    *reinterpret_cast<uint4*>(cache) = *reinterpret_cast<const uint4*>((g == 0 ? knew : vnew) + f * 8);
+  }
+}
+
 // (16-byte accesses: the host side lays q, the caches and the output out with head slices at multiples of 128 bytes)
 static bool decode_attention_fast(const DecodeAttnArgs& a) {
   return a.dh == 64 && a.dt != F32 && a.ldq % 8 == 0 && a.row_stride % 8 == 0 && a.ldo % 8 == 0 && (!a.k_new || a.ld_new % 8 == 0);
@@ -320,6 +461,11 @@ void launch_decode_attention(hipStream_t s, const DecodeAttnArgs& a) {
     // (the lines: see the table above.  33-64 positions of the history are faster in one chunk up to 3072 wavefronts, of the source up to 4096)
     const int halves = (a.n_max + 31) / 32, waves = a.rows * a.H;
     const bool all = halves == 2 ? waves <= (a.anc ? 3072 : 4096) : halves > 3 && waves < 2048;
+    if (w > 1 && waves >= 2048 && a.n_max > (a.anc ? 64 : 80)) {               // (the lines: see decode_long_attention_kernel)
+      if (a.dt == F16) hipLaunchKernelGGL((decode_long_attention_kernel<half_t>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((decode_long_attention_kernel<bf16_t>), grid, block, 0, s, a);
+      return;
+    }
 #define DA64(KERNEL, T)                                                                                                      \
   do { if (all) hipLaunchKernelGGL((KERNEL<T, 4>), grid, block, 0, s, a); else hipLaunchKernelGGL((KERNEL<T, 2>), grid, block, 0, s, a); } while (0)
     if (a.dt == F16) { if (a.anc) DA64(decode_attention64_kernel, half_t); else DA64(decode_source_attention64_kernel, half_t); }
