@@ -11,17 +11,18 @@ constexpr int LN_VEC = 8;
 // s = x + drop(y); n = gamma * (s - mean) * rstd + beta.  NCH = chunks of 8 elements per lane (d <= NCH * 512), WAVES rows per block.
 // Bound by memory, a few hundred rows by one trip to it: everything a row needs is asked for before the first of it is looked at.  (gamma and beta
 // only after the statistics, and a chunk at a time: 280 x 1024 3.4 us against 3.0, 1020 x 1024 5.0 and 4.2, 900 x 1536 6.2 and 5.0, 3000 x 1536 11.1 and
-// 10.6, 3264 x 1024 8.5 both.  1, 2 or 8 rows a block: 1020 x 1024 4.4, 4.7 and 4.6.)
+// 10.6; more rows: see ln_fwd_by_chunks.  1, 2 or 8 rows a block: 1020 x 1024 4.4, 4.7 and 4.6.)
 // y comes in the compute dtype (MAXS = 0; or null), or as bias + the sum of fp32 slices, at most MAXS of them (the last one is asked for again where
 // there are fewer: with a branch around every slice the second 512 columns waited for the first, 24 rows x 1024, 4 slices 4.8 us against 3.2).  mean,
-// rstd: null in a decoding step.
-template <typename T, int NCH, int MAXS, int WAVES>
+// rstd: null in a decoding step, which has an instance without them and without dropout (TRAIN = false), and a wavefront a block, whose row is then in
+// scalar registers and needs no test: 5-12 % together, 268 rows x 1024, 3 slices 3.9 us, now 3.5.
+template <typename T, int NCH, int MAXS, int WAVES, bool TRAIN>
 __global__ __launch_bounds__(64 * WAVES) void layernorm_fwd_row_kernel(
     const T* __restrict__ x, const T* __restrict__ y, const float* __restrict__ partial, int splits, const T* __restrict__ bias,
     const T* __restrict__ gamma, const T* __restrict__ beta, T* __restrict__ s_out, T* __restrict__ n_out, float* __restrict__ mean,
     float* __restrict__ rstd, int rows, int d, uint64_t key, uint32_t thr, float inv_keep) {
-  const int lane = threadIdx.x & 63, row = blockIdx.x * WAVES + (threadIdx.x >> 6);
-  if (row >= rows) return;
+  const int lane = threadIdx.x & 63, row = WAVES == 1 ? (int)blockIdx.x : (int)(blockIdx.x * WAVES + (threadIdx.x >> 6));
+  if (WAVES > 1 && row >= rows) return;
   const size_t base = (size_t)row * d, slice = (size_t)rows * d;
   Pack<T, LN_VEC> xr[NCH], yr[NCH], gr[NCH], br[NCH], hr[NCH];
   float4 t[NCH][MAXS > 0 ? MAXS : 1][2];
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(64 * WAVES) void layernorm_fwd_row_kernel(
 #pragma unroll
         for (int i = 0; i < LN_VEC; ++i) u[i] = to_f<T>(yr[c].v[i]);
       }
-      if (thr) drop_apply<LN_VEC>(u, key, base + col, thr, inv_keep);
+      if (TRAIN && thr) drop_apply<LN_VEC>(u, key, base + col, thr, inv_keep);
 #pragma unroll
       for (int i = 0; i < LN_VEC; ++i) v[c][i] = MAXS > 0 || y ? to_f<T>(xr[c].v[i]) + u[i] : to_f<T>(xr[c].v[i]);
       if (s_out) {
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(64 * WAVES) void layernorm_fwd_row_kernel(
     }
   }
   const float rs = rsqrtf(wave_sum(sq) / (float)d + LN_EPS);
-  if (mean && lane == 0) { mean[row] = mu; rstd[row] = rs; }
+  if (TRAIN && mean && lane == 0) { mean[row] = mu; rstd[row] = rs; }
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int col = (lane + 64 * c) * LN_VEC;
@@ -169,10 +170,12 @@ static void splitk_ln_dispatch(hipStream_t s, const SplitkNorm& q, int rows, int
   const uint32_t thr = p > 0.f ? drop_threshold(p) : 0u;
   const float inv_keep = 1.f / (1.f - p);
   const int nch = (d + 511) / 512;
-#define SLN(N)                                                                                                                             \
-  hipLaunchKernelGGL((layernorm_fwd_row_kernel<T, N, MAXS, 1>), dim3(rows), dim3(64), 0, s, (const T*)q.x, (const T*)nullptr, q.partial, q.splits, \
+#define SLN_EITHER(N, TRAIN)                                                                                                                \
+  hipLaunchKernelGGL((layernorm_fwd_row_kernel<T, N, MAXS, 1, TRAIN>), dim3(rows), dim3(64), 0, s, (const T*)q.x, (const T*)nullptr, q.partial, q.splits, \
                      (const T*)q.bias, (const T*)q.gamma, (const T*)q.beta, (T*)q.s_out, (T*)q.n_out, q.mean, q.rstd, rows, d, key, thr, inv_keep)
+#define SLN(N) do { if (q.mean || thr) SLN_EITHER(N, true); else SLN_EITHER(N, false); } while (0)
   if (nch <= 1) SLN(1); else if (nch == 2) SLN(2); else if (nch == 3) SLN(3); else SLN(4);
+#undef SLN_EITHER
 #undef SLN
 }
 template <typename T>
@@ -212,7 +215,7 @@ static void ln_fwd_dispatch(hipStream_t s, int dt, const void* x, const void* y,
   const float inv_keep = 1.f / (1.f - p);
   const int nch = (d + 511) / 512;
 #define LN_FWD(N)                                                                                                                              \
-  hipLaunchKernelGGL((layernorm_fwd_row_kernel<T, N, 0, WAVES>), dim3((rows + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, s, (const T*)x, (const T*)y, \
+  hipLaunchKernelGGL((layernorm_fwd_row_kernel<T, N, 0, WAVES, true>), dim3((rows + WAVES - 1) / WAVES), dim3(64 * WAVES), 0, s, (const T*)x, (const T*)y, \
                      (const float*)nullptr, 0, (const T*)nullptr, (const T*)gamma, (const T*)beta, (T*)s_out, (T*)n_out, mean, rstd, rows, d, key, \
                      thr, inv_keep)
 #define LN_FWD_CHUNKS(N)                                                                                                                        \
@@ -359,7 +362,7 @@ template <typename P> __device__ __forceinline__ void opaque(P& x) {
 // The same computation when every row can have a wavefront of its own: WAVES of them per block (see lnr_waves), one row each, no loop.  Nothing is
 // accumulated across rows, so the three per-column
 // quantities go from the row's registers straight into the block's LDS reduction, the register footprint stays below
-// 128 and a row's two dependent passes are the whole critical path.  (d = 512 NCH: every lane has all its columns.)
+// 128 (without slices) and a row's two dependent passes are the whole critical path.  (d = 512 NCH: every lane has all its columns.)
 // MAXS > 0: the incoming gradient is dn (or nothing, if null) + the sum of at most MAXS fp32 slices (launch_layernorm_bwd).
 template <typename T, int NCH, int WAVES, int MAXS>
 __global__ __launch_bounds__(64 * WAVES) void layernorm_bwd_row_kernel(
