@@ -155,6 +155,22 @@ def test_few_rows_whose_products_run_in_slices(precision, name, dropout, tokens)
     gpu.close()
 
 
+@pytest.mark.parametrize("name", ["post", "lm_pre"])
+@pytest.mark.parametrize("dropout", [0.0, 0.1])
+def test_fifty_rows_in_bf16_but_for_what_a_relu_masks(name, dropout):
+    """The smallest of the batches above: gradients that are not formed from the masked hidden units themselves are held to what whole batches are held to."""
+    import paper_1904_01038_amd as T
+    shape = {"post": ModelShape(1, 2, 512, 8, 4096, 264), "lm_pre": ModelShape(0, 2, 512, 8, 4096, 264, pre_norm=1)}[name]
+    gpu, oracle = make_pair(shape, T.BF16, generic=True, max_sentences=64, max_len=64, max_tokens=2048, dropout=dropout, seed=11)
+    batch = make_batches("base", 1, shape=shape, max_tokens=50, lo=5, hi=6)[0] if shape.enc_layers else make_batches("lm16", 1, shape=shape, hi=10, max_sentences=5)[0]
+    step_both(gpu, oracle, batch)
+    gg = gpu.get_grads()
+    for k, v in oracle.G.items():
+        if not k.endswith((".ffn.w1", ".ffn.b1")):
+            assert cosine(gg[k], v) >= HALF_COS, (k, cosine(gg[k], v))
+    gpu.close()
+
+
 def test_padding_invariance_and_determinism():
     import paper_1904_01038_amd as T
     shape = SMALL["post"]
