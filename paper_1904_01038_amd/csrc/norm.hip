@@ -496,7 +496,18 @@ __device__ __forceinline__ void reduce_partials_body(const float* __restrict__ p
 #pragma unroll
       for (int u = 0; u < 8; ++u) acc += v[u];
     }
-    for (; p < np; p += RP_LANES) acc += partial[((size_t)p * nk + k) * n + j];
+    // The last ones too, where they are more than 3 (past the end: the last one again).  One after the other they made blocks of 4 rows lose what they gain:
+    // LayerNorm backward with its reduction, 1000 x 512 fp16, 250 partials 8.6 us against 7.9 with 63 of them, now 7.0; 1000 x 1024 10.3 and 10.4, now 8.8.
+    // (32 partials 5.2 us, in this form 5.6.)
+    if (np - (p - py) > 3 * RP_LANES) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = partial[((size_t)min(p + RP_LANES * u, np - 1) * nk + k) * n + j];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc = p + RP_LANES * u < np ? acc + v[u] : acc;
+    } else {
+      for (; p < np; p += RP_LANES) acc += partial[((size_t)p * nk + k) * n + j];
+    }
   }
   sh[py][cx] = acc;
   __syncthreads();
@@ -530,7 +541,7 @@ static int lnb_blocks(int rows) {
 }
 // Wavefronts per block of the row kernel, 0: the looping one.  A column sum takes a block through LDS row by row, so small blocks are done
 // sooner, and on more compute units, as long as there are not more than LNB_MAX_BLOCKS partials for the reduction behind it (whose share is
-// counted here).  us with 4 / 8 / 16 wavefronts: 280 x 1024 3.8/4.4/6.0, 1020 x 1024 5.9/5.9/7.2, 1500 x 1024 6.9/6.6/7.7, 2000 x 1024 7.9/7.4/8.2, 900 x
+// counted here, as it was before the last partials came in one trip).  us with 4 / 8 / 16 wavefronts: 280 x 1024 3.8/4.4/6.0, 1020 x 1024 5.9/5.9/7.2, 1500 x 1024 6.9/6.6/7.7, 2000 x 1024 7.9/7.4/8.2, 900 x
 // 512 3.4/3.5/4.4, 1800 x 512 5.0/4.6/5.3, 900 x 1536 7.1/7.5/9.5, 1800 x 1536 10.2/9.8/11.7; 3264 x 1024 -/11.4/11.2, 3700 x 512 -/6.6/6.2.
 constexpr int LNR_FEWEST = 4;
 static int lnr_waves(int rows, int d) {
